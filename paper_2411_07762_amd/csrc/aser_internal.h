@@ -153,6 +153,7 @@ struct GemmArgs {
     int pair_cols;             // TILES_ALL, k_parts == 1, 256 x 128 tiles: a workgroup takes tile columns j and tn - 1 - j of its tile row
                                // (equal work per workgroup when K shrinks linearly with the column, K_GE_COL)
     double* sumsq;             // RESID only: device scalar that receives the sum of squares (accumulates)
+    int split;                 // Gram schedules only: K parts of a left-over tile (>= 1)
     const int* gate;           // plain schedules only (may be null): every workgroup returns at once when *gate == 0
 };
 int aser_gemm_tn(aser_ctx* ctx, const GemmArgs& g);

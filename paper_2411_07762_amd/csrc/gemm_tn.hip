@@ -629,7 +629,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
     if (kx1 > g.K) kx1 = g.K;
     if (kx0 >= kx1) return;
     const int64_t full = T / W, rem = T % W;
-    const int64_t split = rem > 0 ? W / rem : 1;                      // K split of the left-over tiles
+    const int64_t split = g.split;                                    // K split of the left-over tiles
     const int64_t rounds = full + ((rem > 0 && widx < rem * split) ? 1 : 0);
     for (int64_t round = 0; round < rounds; ++round) {
         int64_t t = round * W + widx, k0 = kx0, k1 = kx1;
@@ -873,7 +873,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
     if (kx1 > g.K) kx1 = g.K;
     if (kx0 >= kx1) return;
     const int64_t full = T / W, rem = T % W;
-    const int64_t split = rem > 0 ? W / rem : 1;
+    const int64_t split = g.split;
     const int64_t rounds = full + ((rem > 0 && widx < rem * split) ? 1 : 0);
     for (int64_t round = 0; round < rounds; ++round) {
         int64_t t = round * W + widx, k0 = kx0, k1 = kx1;
@@ -908,6 +908,34 @@ int launch_gram_persistent(aser_ctx* ctx, const GemmArgs& g) {
     return launch_gram_persistent2<IN, false>(ctx, g);
 }
 
+// K chunks and left-over split of the LDS-direct schedule for T tiles and `steps` 32-token steps, from a cost in
+// microseconds fitted to a sweep of n = 256 .. 8192 and 256 .. 16384 tokens: 0.87 per step of the busiest
+// workgroup, 5 per tile visit (pipeline fill), 0.2 per tile flush of the whole launch (256 KB of fp32 atomics that
+// share the memory side).  A part of a left-over tile keeps at least four steps, so that the ring is filled once.
+struct GramSplit { int chunks, split; };
+GramSplit gram_dma_split(int64_t T, int64_t steps) {
+    GramSplit best{1, 1};
+    double best_cost = -1.0;
+    for (int c = 1; c <= 8; c *= 2) {
+        const int64_t W = 256 / c, full = T / W, rem = T % W, steps_c = ceil_div64(steps, c);
+        const int64_t most = rem ? W / rem : 1;
+        for (int64_t sp = 1; sp <= most; ++sp) {
+            const int64_t last = rem ? ceil_div64(steps_c, sp) : 0;
+            if (sp > 1 && last < 4) break;
+            const double flushes = (double)c * (double)(full * W + rem * sp);
+            const double cost = 0.87 * (double)(full * steps_c + last) + 5.0 * (double)(full + (rem ? 1 : 0)) + 0.2 * flushes;
+            if (best_cost < 0.0 || cost < best_cost) { best_cost = cost; best = GramSplit{c, (int)sp}; }
+        }
+    }
+    return best;
+}
+
+// Where the LDS-direct schedule beats the plain grid of register-staged tiles.  Measured (us, plain -> LDS-direct):
+// n = 1024: 24 -> 40 at 4096 tokens, 76 -> 75 at 16384; n = 1536: 23 -> 17 at 256, 56 -> 51 at 4096, 141 -> 86 at 16384;
+// n = 4096: 46 -> 43 at 256, 229 -> 131 at 4096, 330 -> 171 at 7503, 392 -> 279 at 16384; n = 8192: 148 -> 160 at 256,
+// 177 -> 169 at 512, 526 -> 348 at 4096.  Up to 1024 channels the plain grid's 128 x 128 tiles split K further.
+bool gram_dma_pays(int64_t n, int64_t rows) { return n > 1024 && rows >= (n > 5120 ? 512 : 256); }
+
 }  // namespace
 
 int aser_gemm_tn(aser_ctx* ctx, const GemmArgs& g) {
@@ -927,8 +955,9 @@ int aser_gemm_tn(aser_ctx* ctx, const GemmArgs& g) {
     ASER_FAIL(ctx, ASER_ERR_DTYPE, "gemm_tn: unknown input type");
 }
 
-// Gram update: lower-triangle tiles of G += X^T X.  Large problems use the persistent schedule
-// above; small ones split K over a plain grid.  Partial tiles are added with fp32 atomics.
+// Gram update: lower-triangle tiles of G += X^T X.  Aligned bf16 activations take the LDS-direct persistent schedule
+// wherever it is faster; fp32 or unaligned ones the register-staged persistent schedule from 8192 tokens (bf16; 4096
+// fp32) on; the rest splits K over a plain grid.  Partial tiles are added with fp32 atomics.
 int aser_syrk_gram(aser_ctx* ctx, const void* X, int x_dtype, int64_t rows, int64_t n, int64_t ldx,
                    float* G, int64_t ldg) {
     GemmArgs g{};
@@ -942,6 +971,11 @@ int aser_syrk_gram(aser_ctx* ctx, const void* X, int x_dtype, int64_t rows, int6
     const int64_t ksteps = ceil_div64(rows, bk);
     const int64_t t256 = ceil_div64(n, 256);
     const int64_t T256 = t256 * (t256 + 1) / 2;
+    if (g.in_type == GEMM_IN_BF16 && operands_fast<GEMM_IN_BF16>(g) && gram_dma_pays(n, rows)) {
+        const GramSplit sp = gram_dma_split(T256, ceil_div64(rows, kDmaBK));
+        g.bm = g.bn = 256; g.k_parts = sp.chunks; g.split = sp.split;
+        return launch_gram_dma(ctx, g);
+    }
     if (T256 >= 32 && ksteps >= 8 * 16 && !six) {
         // Number of K chunks: fewest steps on the busiest workgroup, each tile visit charged with
         // the cost of flushing a tile through atomics (about a dozen K steps).
@@ -954,8 +988,8 @@ int aser_syrk_gram(aser_ctx* ctx, const void* X, int x_dtype, int64_t rows, int6
             const int64_t cost = full * (steps_c + 12) + (rem ? ceil_div64(steps_c, split) + 12 : 0);
             if (best_cost < 0 || cost < best_cost) { best_cost = cost; best_c = c; }
         }
-        g.bm = g.bn = 256; g.k_parts = best_c;
-        if (g.in_type == GEMM_IN_BF16 && operands_fast<GEMM_IN_BF16>(g)) return launch_gram_dma(ctx, g);
+        const int64_t W = 256 / best_c, rem = T256 % W;
+        g.bm = g.bn = 256; g.k_parts = best_c; g.split = rem ? (int)(W / rem) : 1;
         return (g.in_type == GEMM_IN_BF16) ? launch_gram_persistent<GEMM_IN_BF16>(ctx, g)
                                            : launch_gram_persistent<GEMM_IN_F32X3>(ctx, g);
     }
