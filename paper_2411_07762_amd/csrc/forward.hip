@@ -829,6 +829,12 @@ extern "C" int aser_compensated_forward(aser_ctx* ctx, const int8_t* x_codes, co
     if (rows == 0) return ASER_OK;
     ASER_TRY(aser_prepare_device(ctx));
     const bool split = lowrank_split != 0;
+    const bool w4 = layout == ASER_CODES_INT4_PACKED;
+    // a few tokens: the kernels that split the contraction; their ceil(n / 2048) partial P (rows x r_pad floats at most) fit the
+    // plan's room for P (one of them) and for the bf16 planes behind it (4 r_pad (m + n) bytes; rows <= 2048)
+    if (aser_forward_few_pays(rows, m))
+        return aser_forward_few(ctx, x_codes, x_scales, (int)rows, n, w_codes, w4, w_scales, m, L_A, L_B, r, split,
+                                r > 0 ? (float*)((char*)ctx->ws + pl.off_p) : nullptr, Y, ldy);
     FwdArgs g{};
     g.xq = x_codes; g.xs = x_scales; g.rows = rows; g.n = n;
     g.wq = w_codes; g.ws = w_scales; g.m = m;
@@ -859,7 +865,6 @@ extern "C" int aser_compensated_forward(aser_ctx* ctx, const int8_t* x_codes, co
 #undef ASER_DOWN
         g.p_hi = p_hi; g.p_lo = p_lo; g.la_hi = lah; g.la_lo = lal; g.r_pad = rp;
     }
-    const bool w4 = layout == ASER_CODES_INT4_PACKED;
     if (rows >= kDmaTM && m >= kDmaTN) {                 // the 256 x 256 tiles without a register stage
         if (w4) return split ? launch_dma<true, true>(ctx, g) : launch_dma<true, false>(ctx, g);
         return split ? launch_dma<false, true>(ctx, g) : launch_dma<false, false>(ctx, g);

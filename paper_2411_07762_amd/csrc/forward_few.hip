@@ -1,0 +1,307 @@
+// The compensated layer at inference for a few tokens (decoding: one token, a batch of them, a short prompt):
+//     Y[t][o] = s_t c_o sum_i xq[t][i] wq[o][i]  +  sum_k P[t][k] L_A[o][k],   P[t][k] = s_t sum_i xq[t][i] L_B[k][i].
+//
+// What bounds it: reading the weight codes once (4096 x 14336 int4: 29 MB, 5.7 us at the rate of a large copy) and
+// the launches.  The tiles of the prefill kernels give such a call m / 256 workgroups that walk the whole
+// contraction one after the other, so here a workgroup owns 16 or 32 outputs and all tokens, and its wavefronts split
+// the contraction: every wavefront streams its own part of the code rows from global memory straight into
+// MFMA operands (a lane's 16 bytes are 16 int8 or 32 int4 channels of its row; the order of the channels inside a
+// step is free as long as both operands agree), nothing goes through LDS on the way.  The int32 partial sums are exact and meet
+// in LDS by integer atomics, so the result does not depend on their order.  The rank-r branch is a kernel in front
+// (few_down_kernel: P summed over up to 2048 channels per workgroup) and r / 4 further steps per output tile in the epilogue;
+// both run on the fp32 MFMA instruction, operands straight from global memory.  In the mode that rounds the factors
+// to bf16 the same three roundings are made (L_B, P, L_A) as in the prefill kernels.
+#include "aser_internal.h"
+
+namespace {
+
+typedef int v4i_t __attribute__((ext_vector_type(4)));
+
+typedef float f4v __attribute__((ext_vector_type(4)));
+
+constexpr int kDownChunk = 2048;      // channels per partial P: eight wavefronts of 256
+
+__device__ __forceinline__ float round_bf16(float x) {
+    const uint32_t u = __float_as_uint(x);
+    return __uint_as_float((u + 0x7FFFu + ((u >> 16) & 1u)) & 0xFFFF0000u);
+}
+
+// part[chunk][t][k] = sum over 2048 channels of xq[t][i] L_B[k][i] (without s_t), k up to rp (r rounded up to 16; zeros
+// behind r).  A workgroup takes 16 rows of L_B and 16 tokens, a wavefront 256 channels of them; lane (l % 16, g = l / 16)
+// feeds channels 16 s + 4 g + e of its row and of its token to the e-th of four v_mfma_f32_16x16x4_f32 (codes and products
+// exact, fp32 sums).  All loads of a wavefront are in flight at once: they are unconditional (addresses clamped into the
+// operands, the values dropped afterwards), because a load behind a branch is waited for where the branches meet.
+template <bool VEC>
+__global__ __launch_bounds__(512) void few_down_kernel(const int8_t* __restrict__ xq, int rows, int64_t n, const float* __restrict__ L_B,
+                                                       int r, int rp, int split, float* __restrict__ part) {
+    __shared__ float red[8][16][17];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int li = lane & 15, lg = lane >> 4;
+    const int64_t c0 = (int64_t)blockIdx.x * kDownChunk + wave * 256 + 4 * lg;
+    const int k = blockIdx.y * 16 + li, t = blockIdx.z * 16 + li;
+    const bool kok = k < r, tok = t < rows;
+    const float* bp = L_B + (int64_t)(kok ? k : 0) * n;
+    const int8_t* xp = xq + (int64_t)(tok ? t : 0) * n;
+    f4v acc = {0.f, 0.f, 0.f, 0.f};
+    if ((int64_t)blockIdx.x * kDownChunk + wave * 256 < n) {
+        float4 b[16];
+        uint32_t x[16];
+#pragma unroll
+        for (int s = 0; s < 16; ++s) {
+            const int64_t c = (c0 + 16 * s < n) ? c0 + 16 * s : 0;         // n % 32 == 0: a lane's four channels are whole or absent
+            if (VEC) b[s] = *(const float4*)(bp + c);
+            else b[s] = make_float4(bp[c], bp[c + 1], bp[c + 2], bp[c + 3]);
+            x[s] = *(const uint32_t*)(xp + c);
+        }
+#pragma unroll
+        for (int s = 0; s < 16; ++s) {
+            const bool in = c0 + 16 * s < n;
+            const uint32_t xs = (in && tok) ? x[s] : 0u;
+            const float bb[4] = {b[s].x, b[s].y, b[s].z, b[s].w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float v = (in && kok) ? bb[e] : 0.f;
+                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(split ? v : round_bf16(v), (float)((int)(xs << (24 - 8 * e)) >> 24), acc, 0, 0, 0);
+            }
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) red[wave][li][4 * lg + e] = acc[e];      // (token li, row 4 lg + e)
+    __syncthreads();
+    if (tid < 256) {
+        const int tt = tid >> 4, kk = tid & 15;
+        float s = 0.f;
+#pragma unroll
+        for (int w = 0; w < 8; ++w) s += red[w][tt][kk];
+        if (blockIdx.z * 16 + tt < rows) part[((int64_t)blockIdx.x * rows + blockIdx.z * 16 + tt) * rp + blockIdx.y * 16 + kk] = s;
+    }
+}
+
+struct FewArgs {
+    const int8_t* xq; const float* xs; int rows; int64_t n;
+    const void* wq; const float* ws; int64_t m;
+    const float* part; int chunks; const float* L_A; int r, rp, split, vec_a;
+    float* Y; int64_t ldy;
+};
+
+// OT: 16-output tiles per workgroup, TG: 16-token tiles, NW: wavefronts that split the contraction.
+// v_mfma_i32_16x16x64_i8: a lane feeds 16 bytes of row (output, token) lane % 16, and holds the sums of outputs
+// 4 (lane / 16) .. + 3 for token lane % 16.
+template <bool W4, int OT, int TG, int NW>
+__global__ __launch_bounds__(64 * NW) void few_main_kernel(FewArgs g) {
+    constexpr int OUT = 16 * OT, TOK = 16 * TG, NT = 64 * NW;
+    constexpr int STEP = W4 ? 128 : 64;                     // channels per step: 16 bytes of codes per lane
+    constexpr int U = (TG >= 4) ? 2 : 4;                    // steps in flight
+    constexpr int OP = OUT + 4;
+    __shared__ int red[TOK * OP];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int li = lane & 15, lg = lane >> 4;
+    const int64_t O0 = (int64_t)blockIdx.x * OUT;
+    const int T0 = blockIdx.y * TOK;
+    const int64_t steps = (g.n + STEP - 1) / STEP, per = (steps + NW - 1) / NW;
+    const int64_t s0 = wave * per, s1 = (s0 + per < steps) ? s0 + per : steps;
+
+    const char* wp[OT];
+#pragma unroll
+    for (int i = 0; i < OT; ++i) {
+        int64_t o = O0 + 16 * i + li;
+        if (o >= g.m) o = g.m - 1;                          // rows past the end repeat the last one; their sums are not stored
+        wp[i] = (const char*)g.wq + o * (W4 ? g.n / 2 : g.n) + 16 * lg;
+    }
+    const char* xp[TG];
+    bool xok[TG];
+#pragma unroll
+    for (int j = 0; j < TG; ++j) {
+        const int t = T0 + 16 * j + li;
+        xok[j] = t < g.rows;
+        xp[j] = (const char*)g.xq + (int64_t)(xok[j] ? t : 0) * g.n + (W4 ? 32 : 16) * lg;
+    }
+    v4i_t acc[OT][TG];
+#pragma unroll
+    for (int i = 0; i < OT; ++i)
+#pragma unroll
+        for (int j = 0; j < TG; ++j) acc[i][j] = v4i_t{0, 0, 0, 0};
+
+    v4i_t wv[U][OT], xv[U][TG][W4 ? 2 : 1];
+    auto load = [&](int64_t s, int u) {
+        const int64_t k = s * STEP;
+        const bool in = s < s1 && k + (W4 ? 32 : 16) * lg < g.n;      // n % 32 == 0: a lane's chunk is whole or absent
+#pragma unroll
+        for (int i = 0; i < OT; ++i) {
+            wv[u][i] = v4i_t{0, 0, 0, 0};
+            if (in) wv[u][i] = __builtin_nontemporal_load((const v4i_t*)(wp[i] + (W4 ? k / 2 : k)));
+        }
+#pragma unroll
+        for (int j = 0; j < TG; ++j) {
+#pragma unroll
+            for (int h = 0; h < (W4 ? 2 : 1); ++h) {
+                xv[u][j][h] = v4i_t{0, 0, 0, 0};
+                if (in && xok[j]) xv[u][j][h] = *(const v4i_t*)(xp[j] + k + 16 * h);
+            }
+        }
+    };
+    auto multiply = [&](int u) {
+        if (W4) {
+            // a lane's 32 channels as (even ones, odd ones); the codes become 16 q as signed bytes, and the factor 16
+            // goes into the scale
+            v4i_t xe[TG], xo[TG];
+#pragma unroll
+            for (int j = 0; j < TG; ++j) {
+                const v4i_t a = xv[u][j][0], b = xv[u][j][W4 ? 1 : 0];
+                xe[j] = v4i_t{(int)__builtin_amdgcn_perm((uint32_t)a.y, (uint32_t)a.x, 0x06040200u), (int)__builtin_amdgcn_perm((uint32_t)a.w, (uint32_t)a.z, 0x06040200u),
+                              (int)__builtin_amdgcn_perm((uint32_t)b.y, (uint32_t)b.x, 0x06040200u), (int)__builtin_amdgcn_perm((uint32_t)b.w, (uint32_t)b.z, 0x06040200u)};
+                xo[j] = v4i_t{(int)__builtin_amdgcn_perm((uint32_t)a.y, (uint32_t)a.x, 0x07050301u), (int)__builtin_amdgcn_perm((uint32_t)a.w, (uint32_t)a.z, 0x07050301u),
+                              (int)__builtin_amdgcn_perm((uint32_t)b.y, (uint32_t)b.x, 0x07050301u), (int)__builtin_amdgcn_perm((uint32_t)b.w, (uint32_t)b.z, 0x07050301u)};
+            }
+#pragma unroll
+            for (int i = 0; i < OT; ++i) {
+                const v4i_t w = wv[u][i];
+                const v4i_t we = {(int)(((uint32_t)w.x << 4) & 0xF0F0F0F0u), (int)(((uint32_t)w.y << 4) & 0xF0F0F0F0u),
+                                  (int)(((uint32_t)w.z << 4) & 0xF0F0F0F0u), (int)(((uint32_t)w.w << 4) & 0xF0F0F0F0u)};
+                const v4i_t wo = {(int)((uint32_t)w.x & 0xF0F0F0F0u), (int)((uint32_t)w.y & 0xF0F0F0F0u),
+                                  (int)((uint32_t)w.z & 0xF0F0F0F0u), (int)((uint32_t)w.w & 0xF0F0F0F0u)};
+#pragma unroll
+                for (int j = 0; j < TG; ++j) {
+                    acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(we, xe[j], acc[i][j], 0, 0, 0);
+                    acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wo, xo[j], acc[i][j], 0, 0, 0);
+                }
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < OT; ++i)
+#pragma unroll
+                for (int j = 0; j < TG; ++j) acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wv[u][i], xv[u][j][0], acc[i][j], 0, 0, 0);
+        }
+    };
+#pragma unroll
+    for (int u = 0; u < U; ++u) load(s0 + u, u);
+
+    for (int q = tid; q < TOK * OP; q += NT) red[q] = 0;
+    __syncthreads();
+    for (int64_t s = s0; s < s1; s += U) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            multiply(u);                                    // steps past s1 were loaded as zeros
+            load(s + U + u, u);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < OT; ++i)
+#pragma unroll
+        for (int j = 0; j < TG; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) atomicAdd(red + (16 * j + li) * OP + 16 * i + 4 * lg + e, acc[i][j][e]);
+    __syncthreads();
+
+    // a wavefront takes 16 x 16 tiles in turn: the scaled integer sums, then L_A P^T on top of them in the same layout
+    const float wfix = W4 ? (1.0f / 16.0f) : 1.0f;
+    for (int tile = wave; tile < OT * TG; tile += NW) {
+        const int i = tile % OT, j = tile / OT;
+        const int t = T0 + 16 * j + li;
+        if (T0 + 16 * j >= g.rows) continue;
+        const bool tok = t < g.rows;
+        const float sx = tok ? g.xs[t] : 0.f;
+        const int64_t o4 = O0 + 16 * i + 4 * lg;             // this lane's four outputs
+        f4v y;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) y[e] = (float)red[(16 * j + li) * OP + 16 * i + 4 * lg + e] * (sx * (o4 + e < g.m ? g.ws[o4 + e] * wfix : 0.f));
+        const int64_t orow = O0 + 16 * i + li;               // the row of L_A that this lane feeds
+        const float* ap = g.L_A + (orow < g.m ? orow : 0) * g.r;
+        const float* pp = g.part + (int64_t)(tok ? t : 0) * g.rp;
+        for (int k0 = 0; k0 < g.rp; k0 += 64) {              // four steps of 16 at a time: their loads are in flight together
+            float av[4][4];
+            float4 pv[4];
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const int k = k0 + 16 * s + 4 * lg;
+                pv[s] = *(const float4*)(pp + (k < g.rp ? k : 0));
+                if (g.vec_a) {
+                    const float4 v = *(const float4*)(ap + (k < g.r ? k : 0));
+                    av[s][0] = v.x; av[s][1] = v.y; av[s][2] = v.z; av[s][3] = v.w;
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) av[s][e] = ap[k + e < g.r ? k + e : 0];
+                }
+            }
+#pragma unroll 2
+            for (int c = 1; c < g.chunks; ++c) {
+                const float* pc = pp + (int64_t)c * g.rows * g.rp;
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {
+                    const int k = k0 + 16 * s + 4 * lg;
+                    const float4 v = *(const float4*)(pc + (k < g.rp ? k : 0));
+                    pv[s].x += v.x; pv[s].y += v.y; pv[s].z += v.z; pv[s].w += v.w;
+                }
+            }
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const float p4[4] = {pv[s].x * sx, pv[s].y * sx, pv[s].z * sx, pv[s].w * sx};     // sx is 0 past the last token
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int k = k0 + 16 * s + 4 * lg + e;
+                    const float a = (k < g.r && orow < g.m) ? av[s][e] : 0.f, p = k < g.r ? p4[e] : 0.f;
+                    y = __builtin_amdgcn_mfma_f32_16x16x4f32(g.split ? a : round_bf16(a), g.split ? p : round_bf16(p), y, 0, 0, 0);
+                }
+            }
+        }
+        if (!tok) continue;
+        float* yr = g.Y + (int64_t)t * g.ldy + o4;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (o4 + e < g.m) yr[e] = y[e];
+    }
+}
+
+template <bool W4, int OT, int TG, int NW>
+int launch_few(aser_ctx* ctx, const FewArgs& g) {
+    dim3 grid((unsigned)ceil_div64(g.m, 16 * OT), (unsigned)ceil_div64(g.rows, 16 * TG));
+    hipLaunchKernelGGL((few_main_kernel<W4, OT, TG, NW>), grid, dim3(64 * NW), 0, ctx->stream, g);
+    return aser_check_launch(ctx, "compensated_forward_few");
+}
+
+// Outputs per workgroup: the fewest with which the launch still is one workgroup per compute unit (two for up to 16
+// tokens, where the code stream is all there is).  Fewer outputs mean more wavefronts on the code stream, more outputs
+// mean fewer passes over the tokens.  Measured without factors (us for 16 / 32 / 64 outputs per workgroup):
+// 4096 x 4096 int4, 64 tokens 12.3 / 13.8 / 20.3, 256 tokens 38.8 / 23.5 / 33.4, 512 tokens 74.5 / 45.4 / 34.9;
+// 14336 x 4096 int4, 1 token 10.2 / 9.8 / 11.8, 32 tokens 23.6 / 16.3 / 15.5; 4096 x 11008 int8, 1 token 13.1 / 19.0 / 37.2.
+template <bool W4, int TG>
+int pick_outputs(aser_ctx* ctx, const FewArgs& g) {
+    const int64_t groups = ceil_div64(g.rows, 16 * TG), most = TG == 1 ? 512 : 256;
+    if (ceil_div64(g.m, 16) * groups <= most) return launch_few<W4, 1, TG, 8>(ctx, g);
+    if (ceil_div64(g.m, 32) * groups <= most)
+        return TG == 1 ? launch_few<W4, 2, TG, 4>(ctx, g) : launch_few<W4, 2, TG, 8>(ctx, g);
+    return launch_few<W4, 4, TG, 4>(ctx, g);
+}
+
+template <bool W4>
+int dispatch_few(aser_ctx* ctx, const FewArgs& g) {
+    const int tg = (g.rows + 15) / 16;
+    if (tg <= 1) return pick_outputs<W4, 1>(ctx, g);
+    if (tg <= 2) return pick_outputs<W4, 2>(ctx, g);
+    if (tg <= 4) return pick_outputs<W4, 4>(ctx, g);
+    return pick_outputs<W4, 8>(ctx, g);
+}
+
+}  // namespace
+
+// scratch: room for ceil(n / 2048) * rows * (r rounded up to 16) floats when r > 0.
+int aser_forward_few(aser_ctx* ctx, const int8_t* xq, const float* xs, int rows, int64_t n, const void* wq, bool w4, const float* ws,
+                     int64_t m, const float* L_A, const float* L_B, int r, bool split, float* scratch, float* Y, int64_t ldy) {
+    FewArgs g{};
+    g.xq = xq; g.xs = xs; g.rows = rows; g.n = n; g.wq = wq; g.ws = ws; g.m = m;
+    g.L_A = L_A; g.r = r; g.split = split ? 1 : 0; g.Y = Y; g.ldy = ldy;
+    if (r > 0) {
+        g.rp = (r + 15) / 16 * 16;
+        g.part = scratch;
+        g.chunks = (int)ceil_div64(n, kDownChunk);
+        g.vec_a = (((uintptr_t)L_A & 15) == 0 && (r & 3) == 0) ? 1 : 0;
+        dim3 grid((unsigned)g.chunks, (unsigned)(g.rp / 16), (unsigned)ceil_div64(rows, 16));
+        if (((uintptr_t)L_B & 15) == 0)
+            hipLaunchKernelGGL(few_down_kernel<true>, grid, dim3(512), 0, ctx->stream, xq, rows, n, L_B, r, g.rp, split ? 1 : 0, scratch);
+        else
+            hipLaunchKernelGGL(few_down_kernel<false>, grid, dim3(512), 0, ctx->stream, xq, rows, n, L_B, r, g.rp, split ? 1 : 0, scratch);
+        ASER_TRY(aser_check_launch(ctx, "compensated_forward_few_down"));
+    }
+    return w4 ? dispatch_few<true>(ctx, g) : dispatch_few<false>(ctx, g);
+}

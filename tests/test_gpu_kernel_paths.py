@@ -23,3 +23,41 @@ def test_gram_chunks_at_the_borders_of_the_schedules(n, rows):
     assert np.max(np.abs(lower(G.cpu().numpy()) - np.tril(ref)) / np.outer(d, d)) <= 2e-5
     assert np.max(np.abs(abs_sum.cpu().numpy() - ref_abs) / ref_abs) <= 1e-12
     assert int(count.item()) == 2 * rows
+
+
+@pytest.mark.parametrize("rows,n,m,r,packed", [
+    (1, 32, 17, 1, True), (1, 4096, 8208, 64, True), (15, 96, 500, 40, False), (16, 1056, 8200, 128, True), (17, 2080, 333, 0, False),
+    (33, 1024, 64, 8, True), (64, 3104, 8195, 64, False), (65, 11008, 130, 64, True), (128, 160, 8192, 128, False), (128, 4128, 700, 128, True),
+    (129, 1056, 260, 64, True), (500, 2080, 96, 72, False), (257, 4096, 8193, 16, True)])
+def test_forward_of_a_few_tokens(rows, n, m, r, packed):
+    """Integer sums are exact, so without factors only the fp32 scaling remains (two roundings: 1.2e-7, bar 1e-6); the split branch
+    carries fp32 sums of n and r terms (bar 2e-5, as for the prefill kernels), the other one bf16 factors (bar 4e-3)."""
+    rng = np.random.default_rng([77, rows, n, m, r])
+    xq = rng.integers(-127, 128, (rows, n)).astype(np.int8)
+    xs = rng.uniform(0.01, 0.05, rows).astype(np.float32)
+    q = rng.integers(-7, 8, (m, n)).astype(np.int8) if packed else rng.integers(-127, 128, (m, n)).astype(np.int8)
+    ws = rng.uniform(0.001, 0.003, m).astype(np.float32)
+    L_A = rng.standard_normal((m, max(r, 1))).astype(np.float32)
+    L_B = rng.standard_normal((max(r, 1), n)).astype(np.float32) * 0.01
+    X = xq.astype(np.float64) * xs.astype(np.float64)[:, None]
+    low = X @ L_B.astype(np.float64).T @ L_A.astype(np.float64).T
+    base = X @ (q.astype(np.float64) * ws.astype(np.float64)[:, None]).T
+    ctx = new_ctx()
+    ctx.ensure_workspace(aser.aser_forward_workspace_bytes(rows, n, m, r))
+    wq = torch.from_numpy(orc.pack_int4(q) if packed else q).to(DEV)
+    layout = aser.ASER_CODES_INT4_PACKED if packed else aser.ASER_CODES_INT8
+    lb = torch.zeros(L_B.size + 1, dtype=torch.float32, device=DEV)
+    lb[1:] = torch.from_numpy(L_B.reshape(-1)).to(DEV)
+    lbs = (lb[1:].view(L_B.shape), torch.from_numpy(L_B).to(DEV))            # 4-byte aligned, 16-byte aligned
+    for comp, split, bar in ((False, False, 1e-6), (True, True, 2e-5), (True, False, 4e-3)):
+        if comp and r == 0:
+            continue
+        want = base + low if comp else base
+        for lbd in lbs if rows > 1 else lbs[:1]:
+            Y = torch.full((rows, m + 3), 7.0, dtype=torch.float32, device=DEV)
+            ctx.check(aser.aser_compensated_forward(ctx, torch.from_numpy(xq).to(DEV), torch.from_numpy(xs).to(DEV), wq, layout,
+                                                    torch.from_numpy(ws).to(DEV), torch.from_numpy(L_A).to(DEV) if comp else None,
+                                                    lbd if comp else None, r if comp else 0, split, Y[:, :m]))
+            got = Y.cpu().numpy()
+            assert np.all(got[:, m:] == 7.0)
+            assert np.linalg.norm(got[:, :m] - want) <= bar * np.linalg.norm(want)
