@@ -6,7 +6,7 @@
 // path computes every one of them, in fp64 behind the product T S:
 //   B = Z Z^T  (k x k, k = min(m, n), Z = T S or its transpose)   fp64 accumulation of exact fp32 products
 //   B -> tridiagonal (d, e) by Householder reflections            two launches per column, see below
-//   eigenvalues of (d, e) by bisection on Sturm counts            one thread per eigenvalue
+//   eigenvalues of (d, e) by multisection on Sturm counts         16 to 64 lanes per eigenvalue
 //   sigma_i = sqrt(lambda_i), descending.
 // The singular values of T S and of (T S)^T agree, so B is formed on the shorter side.
 //
@@ -218,118 +218,146 @@ __global__ __launch_bounds__(256) void tridiag_pass_kernel(int64_t c0, int64_t k
     if (tid < nrows) p[r0 + tid] = red[0][tid] + red[1][tid] + red[2][tid] + red[3][tid];
 }
 
-// Eigenvalue number i (ascending) of the symmetric tridiagonal matrix (d, e) by bisection: the Sturm
-// count of x (number of eigenvalues below x) is the number of negative terms of the sequence
-// q_0 = d_0 - x, q_l = d_l - x - e_{l-1}^2 / q_{l-1}.  One thread per eigenvalue; the lanes of a
-// wavefront read the same (d_l, e_l) at the same time.  sigma[k - 1 - i] = sqrt(max(lambda_i, 0)).
-__global__ __launch_bounds__(64) void tridiag_bisect_kernel(int64_t k, const double* __restrict__ d,
-                                                            const double* __restrict__ e, double* __restrict__ sigma,
-                                                            double* __restrict__ lam_desc) {
-    const int64_t i = (int64_t)blockIdx.x * 64 + threadIdx.x;
-    // Gershgorin interval and the smallest pivot magnitude (every lane computes the same values)
-    double lo = 1e300, hi = -1e300, emax2 = 0.0;
-    for (int64_t l = 0; l < k; ++l) {
-        const double el = (l + 1 < k) ? fabs(e[l]) : 0.0, ep = (l > 0) ? fabs(e[l - 1]) : 0.0;
-        lo = fmin(lo, d[l] - el - ep);
-        hi = fmax(hi, d[l] + el + ep);
-        emax2 = fmax(emax2, el * el);
-    }
-    const double span = fmax(hi - lo, 1e-300);
-    lo -= 1e-12 * span;
-    hi += 1e-12 * span;
-    const double pivmin = fmax(emax2 * 2.2e-308 * 4.0, 1e-300);
-    if (i >= k) return;
-    double a = lo, b = hi;
-    for (int it = 0; it < 60; ++it) {
-        const double x = 0.5 * (a + b);
-        double q = d[0] - x;
-        if (fabs(q) < pivmin) q = -pivmin;
-        int64_t cnt = q < 0.0 ? 1 : 0;
-        for (int64_t l = 1; l < k; ++l) {
-            const double el = e[l - 1];
-            q = d[l] - x - el * el / q;
-            if (fabs(q) < pivmin) q = -pivmin;
-            cnt += q < 0.0 ? 1 : 0;
-        }
-        if (cnt <= i) a = x; else b = x;
-    }
-    const double lam = 0.5 * (a + b);
-    sigma[k - 1 - i] = lam > 0.0 ? sqrt(lam) : 0.0;
-    if (lam_desc) lam_desc[k - 1 - i] = lam;
+__device__ __forceinline__ double rcp_f64(double q) {          // full precision: hardware estimate and two Newton steps
+    double r = __builtin_amdgcn_rcp(q);
+    r = fma(fma(-q, r, 1.0), r, r);
+    return fma(fma(-q, r, 1.0), r, r);
 }
 
-// The same eigenvalue by multisection, one wavefront per eigenvalue: the 64 lanes take the Sturm counts of 64
-// points that cut the current interval into 65 parts, and the interval shrinks to the part where the count
-// passes i: 11 rounds for the 60 halvings of the bisection, on k wavefronts instead of k / 64 (k = 4096: the
-// sequential recurrence of 60 x k dependent divisions per thread was 25 ms on 64 compute units).
-__global__ __launch_bounds__(64) void tridiag_multisect_kernel(int64_t k, const double* __restrict__ d,
-                                                               const double* __restrict__ e, double* __restrict__ sigma,
-                                                               double* __restrict__ lam_desc) {
-    const int64_t i = blockIdx.x;
-    const int lane = threadIdx.x;
+// Every eigenvalue of the symmetric tridiagonal matrix (d, e) by multisection on Sturm counts: the count of x (number of
+// eigenvalues below x) is the number of negative terms of q_0 = d_0 - x, q_l = d_l - x - e_{l-1}^2 / q_{l-1}.
+// L lanes share an eigenvalue: they take the counts of L points that cut its interval into L + 1 parts, and
+// the interval shrinks to the part where the count passes i; `rounds` rounds for 60 halvings.  (d_l, e_{l-1}^2) lie in LDS and are
+// read by all lanes at once (in pieces of kSturmLds when k is larger), so a step is the recurrence alone: one
+// reciprocal and six fp64 operations, a chain of about 100 cycles.  More lanes per eigenvalue mean fewer rounds but more
+// wavefronts per SIMD; past one or two of them the chain is no longer what bounds it.  sigma[k - 1 - i] = sqrt(max(lambda_i, 0)).
+constexpr int kSturmLds = 4096;
+
+template <int L>
+__global__ __launch_bounds__(256) void tridiag_eigenvalues_kernel(int64_t k, const double* __restrict__ d, const double* __restrict__ e,
+                                                                  int rounds, double* __restrict__ sigma, double* __restrict__ lam_desc) {
+    extern __shared__ __align__(16) double2 de[];               // (d_l, e_{l-1}^2), padded to a multiple of 8
+    __shared__ double red[3][4];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t i = (int64_t)blockIdx.x * (256 / L) + tid / L;
+    const int sub = tid % L;
+    // Gershgorin interval and the smallest pivot magnitude
     double lo = 1e300, hi = -1e300, emax2 = 0.0;
-    for (int64_t l = 0; l < k; ++l) {
-        const double el = (l + 1 < k) ? fabs(e[l]) : 0.0, ep = (l > 0) ? fabs(e[l - 1]) : 0.0;
-        lo = fmin(lo, d[l] - el - ep);
-        hi = fmax(hi, d[l] + el + ep);
+    for (int64_t l = tid; l < k; l += 256) {
+        const double dl = d[l], el = (l + 1 < k) ? fabs(e[l]) : 0.0, ep = (l > 0) ? fabs(e[l - 1]) : 0.0;
+        lo = fmin(lo, dl - el - ep);
+        hi = fmax(hi, dl + el + ep);
         emax2 = fmax(emax2, el * el);
     }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        lo = fmin(lo, __shfl_xor(lo, o, 64));
+        hi = fmax(hi, __shfl_xor(hi, o, 64));
+        emax2 = fmax(emax2, __shfl_xor(emax2, o, 64));
+    }
+    if (lane == 0) { red[0][wave] = lo; red[1][wave] = hi; red[2][wave] = emax2; }
+    __syncthreads();
+    lo = fmin(fmin(red[0][0], red[0][1]), fmin(red[0][2], red[0][3]));
+    hi = fmax(fmax(red[1][0], red[1][1]), fmax(red[1][2], red[1][3]));
+    emax2 = fmax(fmax(red[2][0], red[2][1]), fmax(red[2][2], red[2][3]));
     const double span = fmax(hi - lo, 1e-300);
-    lo -= 1e-12 * span;
-    hi += 1e-12 * span;
     const double pivmin = fmax(emax2 * 2.2e-308 * 4.0, 1e-300);
-    double a = lo, b = hi;
-    for (int it = 0; it < 11; ++it) {
-        const double step = (b - a) * (1.0 / 65.0);
-        const double x = a + step * (double)(lane + 1);
-        double q = d[0] - x;
-        if (fabs(q) < pivmin) q = -pivmin;
-        int64_t cnt = q < 0.0 ? 1 : 0;
-        for (int64_t l = 1; l < k; ++l) {
-            const double el = e[l - 1];
-            q = d[l] - x - el * el / q;
-            if (fabs(q) < pivmin) q = -pivmin;
-            cnt += q < 0.0 ? 1 : 0;
+    double a = lo - 1e-12 * span, b = hi + 1e-12 * span;
+    const bool once = k <= kSturmLds;
+    for (int it = 0; it < rounds; ++it) {
+        const double x = a + (b - a) * ((double)(sub + 1) * (1.0 / (L + 1)));
+        double q = 1.0;
+        int cnt = 0;
+        for (int64_t l0 = 0; l0 < k; l0 += kSturmLds) {
+            const int len = (int)((k - l0 < kSturmLds) ? k - l0 : kSturmLds), padded = (len + 7) & ~7;
+            if (!once || it == 0) {
+                __syncthreads();                                // the previous piece has been read
+                for (int t = tid; t < padded; t += 256) {
+                    const int64_t l = l0 + t;
+                    const double el = (l > 0 && l < k) ? e[l - 1] : 0.0;
+                    de[t] = make_double2(l < k ? d[l] : 1e305, el * el);    // past the end: a positive term
+                }
+                __syncthreads();
+            }
+            for (int t = 0; t < padded; t += 8) {
+                double2 v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) v[u] = de[t + u];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    q = fma(-v[u].y, rcp_f64(q), v[u].x - x);
+                    if (fabs(q) < pivmin) q = -pivmin;
+                    cnt += (int)((uint32_t)__double2hiint(q) >> 31);
+                }
+            }
         }
-        // the count grows with x: the points with cnt <= i are the first p of them
-        const int p = __popcll(__builtin_amdgcn_ballot_w64(cnt <= i));
-        const double xa = __shfl(x, p > 0 ? p - 1 : 0, 64), xb = __shfl(x, p < 64 ? p : 63, 64);
-        const double na = p > 0 ? xa : a, nb = p < 64 ? xb : b;
+        // the count grows with x: the points with cnt <= i are the first p of the group
+        const uint64_t below = __builtin_amdgcn_ballot_w64((int64_t)cnt <= i) >> (lane / L * L);
+        const int p = __popcll(L == 64 ? below : (below & ((1ull << (L & 63)) - 1)));
+        const int first = lane / L * L;
+        const double xa = __shfl(x, first + (p > 0 ? p - 1 : 0), 64), xb = __shfl(x, first + (p < L ? p : L - 1), 64);
+        const double na = p > 0 ? xa : a, nb = p < L ? xb : b;
         a = na;
         b = nb;
     }
-    if (lane == 0) {
+    if (sub == 0 && i < k) {
         const double lam = 0.5 * (a + b);
         sigma[k - 1 - i] = lam > 0.0 ? sqrt(lam) : 0.0;
         if (lam_desc) lam_desc[k - 1 - i] = lam;
     }
 }
 
-// Every eigenvalue of the tridiagonal matrix: bisection with a thread each for small matrices, multisection with a
-// wavefront each from 1024 on.
 int tridiag_eigenvalues(aser_ctx* ctx, int64_t k, const double* d, const double* e, double* sigma, double* lam_desc) {
-    if (k >= 1024)
-        hipLaunchKernelGGL(tridiag_multisect_kernel, dim3((unsigned)k), dim3(64), 0, ctx->stream, k, d, e, sigma, lam_desc);
+    const size_t lds = (size_t)((k < kSturmLds ? (k + 7) / 8 * 8 : kSturmLds)) * sizeof(double2);
+    static bool attr_set[16] = {false};
+    if (ctx->device >= 0 && ctx->device < 16 && !attr_set[ctx->device]) {
+        const int most = (int)(kSturmLds * sizeof(double2));
+        ASER_HIP(ctx, hipFuncSetAttribute((const void*)tridiag_eigenvalues_kernel<64>, hipFuncAttributeMaxDynamicSharedMemorySize, most));
+        ASER_HIP(ctx, hipFuncSetAttribute((const void*)tridiag_eigenvalues_kernel<32>, hipFuncAttributeMaxDynamicSharedMemorySize, most));
+        ASER_HIP(ctx, hipFuncSetAttribute((const void*)tridiag_eigenvalues_kernel<16>, hipFuncAttributeMaxDynamicSharedMemorySize, most));
+        attr_set[ctx->device] = true;
+    }
+    // 65^10, 33^12 and 17^15 are all above 2^60
+    if (k <= 1024)
+        hipLaunchKernelGGL(tridiag_eigenvalues_kernel<64>, dim3((unsigned)ceil_div64(k, 4)), dim3(256), lds, ctx->stream, k, d, e, 10, sigma, lam_desc);
+    else if (k <= 2048)
+        hipLaunchKernelGGL(tridiag_eigenvalues_kernel<32>, dim3((unsigned)ceil_div64(k, 8)), dim3(256), lds, ctx->stream, k, d, e, 12, sigma, lam_desc);
     else
-        hipLaunchKernelGGL(tridiag_bisect_kernel, dim3((unsigned)ceil_div64(k, 64)), dim3(64), 0, ctx->stream, k, d, e, sigma, lam_desc);
+        hipLaunchKernelGGL(tridiag_eigenvalues_kernel<16>, dim3((unsigned)ceil_div64(k, 16)), dim3(256), lds, ctx->stream, k, d, e, 15, sigma, lam_desc);
     return aser_check_launch(ctx, "tridiag_eigenvalues");
 }
 
 // Eq. 9 on a descending spectrum: running sums in index order; r = number of leading indices whose
 // cumulative share stays below alpha, at least 1.  out: r, then sum, share(r), share(r + 1) as doubles.
-__global__ void select_rank_kernel(const double* __restrict__ sigma, int64_t k, double alpha, int32_t* __restrict__ r_out,
-                                   double* __restrict__ stats) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
+// One wavefront: 64 values are loaded at a time and added one after the other (every lane carries the same sums), so the
+// order and the rounding are those of a running sum; the shares are divided out only until the threshold is passed.
+__global__ __launch_bounds__(64) void select_rank_kernel(const double* __restrict__ sigma, int64_t k, double alpha, int32_t* __restrict__ r_out,
+                                                         double* __restrict__ stats) {
+    const int lane = threadIdx.x;
+    auto at = [&](double v, int l) {
+        return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l), __builtin_amdgcn_readlane(__double2loint(v), l));
+    };
     double total = 0.0;
-    for (int64_t i = 0; i < k; ++i) total += sigma[i];
+    double nv = lane < k ? sigma[lane] : 0.0;
+    for (int64_t i0 = 0; i0 < k; i0 += 64) {
+        const double v = nv;
+        nv = i0 + 64 + lane < k ? sigma[i0 + 64 + lane] : 0.0;
+#pragma unroll
+        for (int l = 0; l < 64; ++l) total += at(v, l);      // past the end: + 0, which changes nothing
+    }
     double cum = 0.0, at_r = 0.0, next = 0.0;
     int64_t r = 0;
     bool open = true;
-    for (int64_t i = 0; i < k && open; ++i) {
-        cum += sigma[i];
-        if (cum / total < alpha) { r = i + 1; at_r = cum / total; }
-        else { next = cum / total; open = false; }
+    for (int64_t i0 = 0; i0 < k && open; i0 += 64) {
+        const double v = i0 + lane < k ? sigma[i0 + lane] : 0.0;
+        for (int l = 0; l < 64 && i0 + l < k && open; ++l) {
+            cum += at(v, l);
+            const double share = cum / total;
+            if (share < alpha) { r = i0 + l + 1; at_r = share; }
+            else { next = share; open = false; }
+        }
     }
+    if (lane != 0) return;
     if (open) next = 1.0;
     if (r < 1) {                                          // the threshold lies below the first share: rank one
         r = 1;
