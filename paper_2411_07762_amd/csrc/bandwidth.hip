@@ -389,7 +389,7 @@ __global__ __launch_bounds__(256) void base_quantizer_kernel(const float* __rest
 }
 
 // ------------------------------------------------------------------------------------ activation RTN
-// One workgroup per token (256 to 1024 threads).  X' = X / m with an IEEE fp32 division, per-token
+// One workgroup per token (64 to 1024 threads).  X' = X / m with an IEEE fp32 division, per-token
 // absmax scale.  A thread owns groups of 8 consecutive channels: one 16-byte load of bf16 (two of
 // fp32), one 8-byte store of codes; the token stays in registers between the absmax reduction
 // and the rounding.
@@ -497,7 +497,7 @@ __global__ __launch_bounds__(NT) void act_rtn_kernel(const void* __restrict__ X,
     }
 }
 
-// Tokens of at most 4096 channels (16-byte aligned rows, n % 16 == 0): one wavefront per token, 4 groups
+// Many tokens of 2049 to 4096 channels (16-byte aligned rows, n % 16 == 0): one wavefront per token, 4 groups
 // of 16 channels per lane (32 bytes of bf16 in, 16 bytes of codes out), all loads of a token in
 // flight at once, absmax by lane shuffles: no LDS and no barrier.  The arithmetic, not the memory
 // system, bounds this kernel, so everything that depends on M alone is done once per wavefront,
@@ -793,7 +793,9 @@ extern "C" int aser_quantize_act_rtn(aser_ctx* ctx, const void* X, int x_dtype, 
     // at most four groups per thread (more cost registers and occupancy), then the fewest threads that cover the token
 #define ASER_ACT_PICK(B)                                          \
     do {                                                          \
-        if (groups <= 256 * 2) ASER_ACT_LAUNCH(B, 2, 256);        \
+        if (groups <= 64 * 2) ASER_ACT_LAUNCH(B, 2, 64);          \
+        else if (groups <= 128 * 2) ASER_ACT_LAUNCH(B, 2, 128);   \
+        else if (groups <= 256 * 2) ASER_ACT_LAUNCH(B, 2, 256);   \
         else if (groups <= 256 * 3) ASER_ACT_LAUNCH(B, 3, 256);   \
         else if (groups <= 256 * 4) ASER_ACT_LAUNCH(B, 4, 256);   \
         else if (groups <= 512 * 3) ASER_ACT_LAUNCH(B, 3, 512);   \
@@ -804,10 +806,11 @@ extern "C" int aser_quantize_act_rtn(aser_ctx* ctx, const void* X, int x_dtype, 
     const int esz = (x_dtype == ASER_DTYPE_BF16) ? 2 : 4;
     const bool wave_ok = n <= 4096 && (n & 15) == 0 && ((uintptr_t)X & 15) == 0 && ((ldx * esz) & 15) == 0 &&
                          ((uintptr_t)codes & 15) == 0 && (!mdiag || ((uintptr_t)mdiag & 15) == 0);
-    if (wave_ok) {
-        // several tokens per wavefront once there are enough tokens for four workgroups per compute unit
-        int tpw = (int)(rows / 4096);
-        tpw = tpw < 1 ? 1 : (tpw > 4 ? 4 : tpw);                 // 2 to 8 measure alike, 16 is slower
+    // The wavefront-per-token kernel pays for the set-up of its M table only on many wide tokens.  Measured (us, wavefront ->
+    // workgroup per token): 1 x 4096 bf16 10.0 -> 4.9, 2048 x 4096 14.4 -> 8.9, 16384 x 4096 51 -> 48, 16384 x 3072 42 -> 43,
+    // 65536 x 4096 164 -> 176, 131072 x 2048 217 -> 208; fp32: 65536 x 4096 268 -> 257, 131072 x 3072 374 -> 384
+    if (wave_ok && n > 2048 && rows > (x_dtype == ASER_DTYPE_BF16 ? 16384 : 65536)) {
+        const int tpw = 4;                                       // tokens per wavefront: 2 to 8 measure alike, 16 is slower
         dim3 wgrid((unsigned)ceil_div64(rows, 4 * (int64_t)tpw));
         if (x_dtype == ASER_DTYPE_BF16)
             hipLaunchKernelGGL(act_rtn_wave_kernel<true>, wgrid, dim3(256), 0, ctx->stream, X, rows, n, ldx, mdiag, qmax, codes, scales, tpw);

@@ -61,3 +61,42 @@ def test_forward_of_a_few_tokens(rows, n, m, r, packed):
             got = Y.cpu().numpy()
             assert np.all(got[:, m:] == 7.0)
             assert np.linalg.norm(got[:, :m] - want) <= bar * np.linalg.norm(want)
+
+
+@pytest.mark.parametrize("rows,n,dtype", [(16385, 2064, "bf16"), (16387, 4096, "bf16"), (65537, 2064, "f32"), (16384, 2064, "bf16"),
+                                          (3, 1016, "bf16"), (5, 1032, "f32"), (9, 2048, "bf16"), (7, 2056, "bf16")])
+def test_activation_quantizer_at_the_borders_of_its_kernels(rows, n, dtype):
+    """Bit-exact.  Tokens are independent, so a sample of them stands for all: the first and last 64 and 300 in between."""
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(rows + n)
+    X = torch.randn((rows, n), generator=gen, device=DEV).to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    md = torch.ones(n, device=DEV)
+    md[torch.randperm(n, generator=gen, device=DEV)[:32]] = 1.0 + 2.0 * torch.rand(32, generator=gen, device=DEV)
+    codes = torch.empty((rows, n), dtype=torch.int8, device=DEV)
+    scales = torch.empty(rows, dtype=torch.float32, device=DEV)
+    ctx = new_ctx()
+    ctx.check(aser.aser_quantize_act_rtn(ctx, X, md, 8, codes, scales))
+    pick = np.unique(np.concatenate([np.arange(min(64, rows)), np.arange(max(0, rows - 64), rows), np.random.default_rng(1).integers(0, rows, 300)]))
+    at = torch.from_numpy(pick).to(DEV)
+    q, s = orc.quantize_act_rtn(X[at].float().cpu().numpy(), md.cpu().numpy(), 8)
+    assert np.array_equal(codes[at].cpu().numpy(), q)
+    assert np.array_equal(scales[at].cpu().numpy(), s)
+
+
+@pytest.mark.parametrize("k", [2, 7, 8, 64, 1023, 1025, 2049, 4100])
+def test_eigenvalues_at_the_borders_of_the_multisection(k):
+    """T = a diagonal matrix (S = none): its singular values are the entries, and the path behind the Gram matrix is fp64, so they
+    come back to 60 halvings of the squared range: sigma to 1e-9 of the largest (sqrt of 2^-60)."""
+    rng = np.random.default_rng(k)
+    sg = np.sort(rng.uniform(0.5, 2.0, k).astype(np.float32))[::-1]
+    T = torch.zeros((k, k), dtype=torch.float32, device=DEV)
+    T.diagonal().copy_(torch.from_numpy(sg.copy()).to(DEV))
+    out = torch.empty(k, dtype=torch.float64, device=DEV)
+    ctx = new_ctx()
+    ctx.ensure_workspace(aser.aser_spectrum_workspace_bytes(k, k, False))
+    ctx.check(aser.aser_singular_values(ctx, T, None, out))
+    assert np.max(np.abs(out.cpu().numpy() - sg.astype(np.float64))) <= 1e-9 * 2.0
+    for alpha in (0.01, 0.4, 0.9999):
+        st, r, _ = aser.aser_select_rank(ctx, out, alpha)
+        ctx.check(st)
+        assert r == orc.rank_from_alpha(out.cpu().numpy(), alpha)
