@@ -282,10 +282,19 @@ __device__ __forceinline__ void tile_body(const GemmArgs& g, int64_t I0, int64_t
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm0 = (wave >> 1) * (BM / 2), wn0 = (wave & 1) * (BN / 2);
 
+    // 128 x 128 tiles: an operand's block of a step is 128 threads' work, so threads 0 .. 127 stage A and the others B
+    // (with both on the first two wavefronts, their conversion work set the time of a step: 0.75 -> 0.5 us)
+    constexpr bool SHARED = BM == 128 && BN == 128;
+    const bool second = __builtin_amdgcn_readfirstlane(tid >> 7) != 0;
     Fetch<IN, BM, FAST> fa;
     Fetch<IN, BN, FAST> fb;
-    fa.init(g.A, g.lda, I0, g.M, kBeg, kEnd, tid);
-    fb.init(g.B, g.ldb, J0, g.N, kBeg, kEnd, tid);
+    if (SHARED) {
+        fa.init(second ? g.B : g.A, second ? g.ldb : g.lda, second ? J0 : I0, second ? g.N : g.M, kBeg, kEnd, tid & 127);
+    } else {
+        fa.init(g.A, g.lda, I0, g.M, kBeg, kEnd, tid);
+        fb.init(g.B, g.ldb, J0, g.N, kBeg, kEnd, tid);
+    }
+    const int fa_off = (SHARED && second) ? Cfg::A_CHUNKS : 0;
 
     f32x16_t acc[TM][TN];
 #pragma unroll
@@ -309,15 +318,18 @@ __device__ __forceinline__ void tile_body(const GemmArgs& g, int64_t I0, int64_t
     constexpr int NSETS = (BM == 256 && BN == 256) ? 1 : 2;
     constexpr bool TWO_SETS = NSETS > 1;
     if (TWO_SETS) {
-        Staged ra[NSETS], rb[NSETS];                    // set u holds steps u + 1, u + 1 + NSETS, ...
+        Staged ra[NSETS], rb[SHARED ? 1 : NSETS];       // set u holds steps u + 1, u + 1 + NSETS, ...
         if (steps > 0) {
             fa.load(ra[0], kEnd);
-            fb.load(rb[0], kEnd);
-            fa.store(ra[0], smem);
-            fb.store(rb[0], smem + Cfg::A_CHUNKS);
+            if (!SHARED) fb.load(rb[0], kEnd);
+            fa.store(ra[0], smem + fa_off);
+            if (!SHARED) fb.store(rb[0], smem + Cfg::A_CHUNKS);
 #pragma unroll
             for (int u = 0; u < NSETS; ++u)
-                if (steps > u + 1) { fa.load(ra[u], kEnd); fb.load(rb[u], kEnd); }
+                if (steps > u + 1) {
+                    fa.load(ra[u], kEnd);
+                    if (!SHARED) fb.load(rb[SHARED ? 0 : u], kEnd);
+                }
         }
         __syncthreads();
         for (int64_t s0 = 0; s0 < steps; s0 += NSETS) {
@@ -330,9 +342,12 @@ __device__ __forceinline__ void tile_body(const GemmArgs& g, int64_t I0, int64_t
                     uint4* da = smem + ((u + 1) & 1) * Cfg::STAGE_CHUNKS;
                     mfma_step<IN, BM, BN>(acc, sa, sa + Cfg::A_CHUNKS, offa, offb);
                     if (s + 1 < steps) {
-                        fa.store(ra[u], da);
-                        fb.store(rb[u], da + Cfg::A_CHUNKS);
-                        if (s + 1 + NSETS < steps) { fa.load(ra[u], kEnd); fb.load(rb[u], kEnd); }
+                        fa.store(ra[u], da + fa_off);
+                        if (!SHARED) fb.store(rb[SHARED ? 0 : u], da + Cfg::A_CHUNKS);
+                        if (s + 1 + NSETS < steps) {
+                            fa.load(ra[u], kEnd);
+                            if (!SHARED) fb.load(rb[SHARED ? 0 : u], kEnd);
+                        }
                     }
                     __syncthreads();
                 }
