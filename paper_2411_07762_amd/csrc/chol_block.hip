@@ -4,13 +4,14 @@
 // One workgroup of 16 wavefronts, the block in LDS, blocked again into 32-wide sub-blocks k = 0..3.
 // All arithmetic is fp32: the products run on the fp32 MFMA instructions.
 //
-//   1. one wavefront factors the 32 x 32 diagonal sub-block A_kk with the sub-block and an identity
-//      next to it held in two 32 x 32 MFMA accumulators.  Pivot j: reciprocal square root of the
-//      diagonal entry, row j scaled (that is row j of R_kk and, in the second accumulator, row j of
-//      L_kk^-1 with R_kk = L_kk^T), then one rank-1 MFMA update per accumulator (the next row is
-//      updated by plain FMAs on a copy, so the pivot chain does not wait for the MFMAs).  An accumulator
-//      register holds row j in one half of the lanes and row j +- 4 in the other; the MFMA's second
-//      k-slot takes a zero multiplier for that half, so no lane exchange is needed.
+//   1. one wavefront factors the 32 x 32 diagonal sub-block A_kk in registers, 16 rows at a time: a register is a
+//      row, a lane a column of the block or of an identity that goes through the same row operations and so becomes
+//      L_kk^-1 (R_kk = L_kk^T).  A pivot is the reciprocal square root of its diagonal entry, the scaling of its row, and one
+//      fused multiply-add per later row with that row's multiplier broadcast from its lane; between the two halves
+//      rows 16 .. 31 take the first half's contribution in eight 16 x 16 x 4 MFMAs.  A wavefront alone on its SIMD issues an
+//      instruction every 7 to 8 cycles, so the instruction count is what bounds this part: 32 rows in one go took 9.5 k
+//      cycles per sub-block, rank-1 MFMA updates 10.3 k (their 64 cycles each do not overlap with the VALU work of the
+//      same wavefront).  Whole kernel at b = 128: 29.5 us with rank-1 MFMA updates, 28.0 with 32 rows in one go, 24.5 like this.
 //   2. everyone, 16 x 16 MFMA tiles: row panel R[k, right] = L_kk^-1 A[k, right] and, for the
 //      inverse, Y = R[above, k] X_kk with X_kk = R_kk^-1.
 //   3. everyone: trailing update A[right, right] -= R[k, right]^T R[k, right] over the upper
@@ -22,12 +23,12 @@
 
 namespace {
 
-typedef float f16v __attribute__((ext_vector_type(16)));
 typedef float f4v __attribute__((ext_vector_type(4)));
 
 constexpr int kN = 128;       // largest block
 constexpr int kP = 133;       // odd LDS pitch: a wavefront reads along a row or a column without bank conflicts
 constexpr int kPY = 33;
+constexpr int kPE = 33;
 constexpr int kSub = 32;
 constexpr int kThreads = 1024;
 constexpr int kWaves = kThreads / 64;
@@ -60,6 +61,37 @@ __device__ __forceinline__ void trailing_tile(float* As, int o, int ti, int tc, 
     for (int e = 0; e < 4; ++e) out[e * kP] = c[e];
 }
 
+// Sixteen pivots on rows held in registers (a[i] = row i, a lane per column; lanes 0 .. 15 are the columns of the pivots): row j
+// is scaled by the reciprocal square root of its pivot and subtracted from the later rows.  Row j goes to `out`, which
+// advances by `step` per row.  *bad: smallest column (counted from `first`) whose pivot was not positive.  The multipliers are
+// all broadcast before the first of them is used: a scalar written by a lane read may not be used by the next two instructions,
+// and scalars of their own fill that gap.
+__device__ __forceinline__ void pivots16(float (&a)[16], float* out, int step, int first, int* bad) {
+    float piv = lane_bcast(a[0], 0);
+    bool ok = piv > 0.f;
+    float rs = __builtin_amdgcn_rsqf(ok ? piv : 1.f);                 // 1 ulp: as good as the fp32 data it scales
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+        *bad = ok ? *bad : (*bad < first + j ? *bad : first + j);
+        const float rv = a[j] * rs;
+        *out = rv;
+        out += step;
+        float m[16];
+#pragma unroll
+        for (int i = j + 1; i < 16; ++i) m[i] = lane_bcast(rv, i);
+        __builtin_amdgcn_sched_barrier(0);
+        if (j + 1 < 16) {                                            // the next pivot's chain runs under the other rows
+            a[j + 1] = fmaf(-m[j + 1], rv, a[j + 1]);
+            if (j + 2 < 16) a[j + 2] = fmaf(-m[j + 2], rv, a[j + 2]);
+            piv = lane_bcast(a[j + 1], j + 1);
+            ok = piv > 0.f;
+            rs = __builtin_amdgcn_rsqf(ok ? piv : 1.f);
+        }
+#pragma unroll
+        for (int i = j + 3; i < 16; ++i) a[i] = fmaf(-m[i], rv, a[i]);
+    }
+}
+
 __global__ __launch_bounds__(kThreads) void chol_block_kernel(float* D, int64_t ld, int b, float* Rinv, int32_t* info,
                                                               int32_t pivot_base, int clear_d, const float* Lmul,
                                                               float* Cmul, float* beta_out, const int* gate) {
@@ -67,7 +99,9 @@ __global__ __launch_bounds__(kThreads) void chol_block_kernel(float* D, int64_t 
     if (gate && *gate == 0) return;
     float* As = sm;                      // working matrix, upper triangle -> R
     float* Xs = As + kN * kP;            // R^-1 (upper), zero elsewhere
-    float* Ys = Xs + kN * kP;            // 96 x 32 scratch, then 64 words that take masked-off stores
+    float* Ys = Xs + kN * kP;            // 96 x 32 scratch
+    float* Es = Ys + 96 * kPY;           // 16 x 32 scratch of the pivot wavefront, then 64 words that take masked-off stores
+    float* const dummy = Es + 16 * kPE + (threadIdx.x & 63);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int nsub = (b + kSub - 1) / kSub;
     const int nb = nsub * kSub;          // padded with the identity up to here
@@ -123,65 +157,43 @@ __global__ __launch_bounds__(kThreads) void chol_block_kernel(float* D, int64_t 
         const int o = kb * kSub;
         const int ncb = nsub - 1 - kb;             // 32-column blocks to the right
 
-        // ---- 1. diagonal sub-block: accumulator register e of lane l holds row 8 (e / 4) + 4 (l / 32) + e % 4, column l % 32
+        // ---- 1. diagonal sub-block, in two halves of 16 pivots
         if (wave == 0 && kb < nsub) {
-            const int h = lane >> 5, col = lane & 31;
-            f16v a1, a2;
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const int row = 8 * (e / 4) + 4 * h + e % 4;
-                a1[e] = As[(o + row) * kP + o + col];
-                a2[e] = (row == col) ? 1.f : 0.f;
-            }
+            const int grp = lane >> 4;                           // columns: 0, 1 of the matrix (see below), 2 of the inverse, 3 none
             int bad = kSub;
-            // LDS targets of this lane's row / column stores; the half of the lanes that holds another
-            // row in the same register writes to a scratch word instead (no exec-mask changes in the chain)
-            float* const dummy = Ys + 96 * kPY + lane;
-            // One row of look-ahead keeps the MFMA latency out of the pivot chain: update j leaves row
-            // j + 1 to two plain FMAs on a copy taken from the accumulators before the MFMAs of step j
-            // are issued (their multiplier for that row is zero), so pivot j + 1 depends on pivot j
-            // through a handful of VALU operations only, and the MFMAs run behind.
-            float x1 = a1[0], x2 = a2[0];             // row j of both accumulators, all updates applied
+            float a[16];
 #pragma unroll
-            for (int j = 0; j < kSub; ++j) {
-                const int hj = (j / 4) & 1;
-                const int en = 4 * ((j + 1) / 8) + (j + 1) % 4;                    // register of row j + 1
-                float y1 = 0.f, y2 = 0.f;
-                if (j + 1 < kSub) {                                               // updates < j applied
-                    // explicit early copies: read lazily, these elements would keep the old accumulator
-                    // tuples alive and every VALU access to them would wait for the MFMA in flight
-                    asm volatile("v_mov_b32 %0, %1" : "=v"(y1) : "v"(a1[en]));
-                    asm volatile("v_mov_b32 %0, %1" : "=v"(y2) : "v"(a2[en]));
-                }
-                const float piv = lane_bcast(x1, 32 * hj + j);
-                const bool ok = piv > 0.f;
-                bad = ok ? bad : (bad < j ? bad : j);
-                const float rs = __builtin_amdgcn_rsqf(ok ? piv : 1.f);   // 1 ulp: as good as the fp32 data it scales
-                // Instruction order matters (one wave, in-order issue): the wave stalls at an MFMA
-                // until the pipe accepts it, so the scalar work of the chain is placed behind the first
-                // MFMA of the step and the work on the second accumulator behind the second.
-                const float rv = x1 * rs;
-                const float mult = (h == hj && col != j + 1) ? -rv : 0.f;
-                if (j + 2 < kSub) a1 = __builtin_amdgcn_mfma_f32_32x32x2f32(mult, rv, a1, 0, 0, 0);
-                __builtin_amdgcn_sched_barrier(0);
-                float m = 0.f;
-                if (j + 1 < kSub) {
-                    m = lane_bcast(rv, 32 * hj + j + 1);                           // r_j[j + 1]
-                    // row j + 1 sits in the other half of the lanes when j + 1 starts a new group of four
-                    const float rvn = (j % 4 == 3) ? __shfl_xor(rv, 32, 64) : rv;
-                    x1 = fmaf(-m, rvn, y1);
-                }
-                *((h == hj) ? As + (o + j) * kP + o + col : dummy) = rv;   // row j of R_kk (left of the diagonal: dead)
-                const float lv = x2 * rs;
-                __builtin_amdgcn_sched_barrier(0);
-                if (j + 2 < kSub) a2 = __builtin_amdgcn_mfma_f32_32x32x2f32(mult, lv, a2, 0, 0, 0);
-                __builtin_amdgcn_sched_barrier(0);
-                if (j + 1 < kSub) {
-                    const float lvn = (j % 4 == 3) ? __shfl_xor(lv, 32, 64) : lv;
-                    x2 = fmaf(-m, lvn, y2);
-                }
-                *((h == hj) ? Xs + (o + col) * kP + o + j : dummy) = lv;   // X_kk = (L_kk^-1)^T
+            for (int i = 0; i < 16; ++i) {
+                const float v = As[(o + i) * kP + o + (lane & 31)];
+                a[i] = grp < 2 ? v : ((i == t_i) ? 1.f : 0.f);
             }
+            // rows 0 .. 15: lanes 0 .. 31 hold columns 0 .. 31 of the block, so the panel R12 comes along
+            pivots16(a, grp < 2 ? As + o * kP + o + lane : (grp == 2 ? Xs + (o + t_i) * kP + o : dummy), grp < 2 ? kP : (grp == 2 ? 1 : 0), 0, &bad);
+            // rows 16 .. 31 of block and inverse: [A22 | 0] - R12^T [R12 | L11^-1]
+            {
+                f4v c22, e21 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) c22[e] = As[(o + 16 + 4 * t_q + e) * kP + o + 16 + t_i];
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {
+                    const float r12 = As[(o + 4 * s + t_q) * kP + o + 16 + t_i], l11 = Xs[(o + t_i) * kP + o + 4 * s + t_q];
+                    c22 = __builtin_amdgcn_mfma_f32_16x16x4f32(-r12, r12, c22, 0, 0, 0);
+                    e21 = __builtin_amdgcn_mfma_f32_16x16x4f32(-r12, l11, e21, 0, 0, 0);
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    Es[(4 * t_q + e) * kPE + t_i] = c22[e];
+                    Es[(4 * t_q + e) * kPE + 16 + t_i] = e21[e];
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const float v = Es[i * kPE + (lane & 31)];
+                a[i] = grp < 2 ? v : ((i == t_i) ? 1.f : 0.f);
+            }
+            // lanes 0 .. 15: columns 16 .. 31 of the block; 16 .. 31: columns 0 .. 15 of the inverse
+            pivots16(a, grp == 0 ? As + (o + 16) * kP + o + 16 + t_i : (grp == 3 ? dummy : Xs + (o + (grp == 2 ? 16 : 0) + t_i) * kP + o + 16),
+                     grp == 0 ? kP : (grp == 3 ? 0 : 1), 16, &bad);
             if (bad < kSub && lane == 0 && o + bad < b && info) atomicMin(info, pivot_base + o + bad + 1);
         }
         if (kb > 0 && (wave > 0 || kb == nsub)) {
@@ -349,7 +361,7 @@ int aser_chol_block(aser_ctx* ctx, float* D, int64_t ld, int b, float* Rinv, int
                     const float* Lmul, float* Cmul, float* beta_out, const int* gate) {
     if (b <= 0 || b > kN) ASER_FAIL(ctx, ASER_ERR_SHAPE, "chol_block: block size out of range");
     static bool attr_set[16] = {false};
-    const size_t lds = (size_t)(2 * kN * kP + 96 * kPY + 64) * sizeof(float);
+    const size_t lds = (size_t)(2 * kN * kP + 96 * kPY + 16 * kPE + 64) * sizeof(float);
     if (ctx->device >= 0 && ctx->device < 16 && !attr_set[ctx->device]) {
         ASER_HIP(ctx, hipFuncSetAttribute((const void*)chol_block_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
         attr_set[ctx->device] = true;
