@@ -5,109 +5,385 @@
 // paper's error figure plots per layer (Sec. 5.3: ||W X - W_q X_q||_F for RTN, the same norm after
 // reconstruction for the other methods), in this library's tokens x channels orientation.
 //
-// Both outputs are contractions over the channel dimension, which is the contiguous dimension of
-// every operand here (X rows, W rows, code rows).  The MFMA kernel of this library wants operands that
-// are contiguous along the OTHER dimension (K-major), so each operand goes through one transposing
-// pass that also does its element-wise work: dequantisation of the weight codes, widening of bf16,
-// the division by M, dequantisation of the activation codes.  Then
-//     W~^T += L_B^T L_A^T          (K = r)
-//     Y     = (X^T)^T W^T          (K = n), ||Y||_F^2
-//     err^2 = ||Y - (X'_q^T)^T W~^T||_F^2   formed tile by tile in the product's epilogue.
-// All products are fp32-class (three bf16 MFMA products per fp32 product).
+// Both outputs are contractions over the channel dimension, which is the contiguous one of every operand (X rows,
+// W rows, code rows), and that is how the bf16 MFMA wants its operands.  The factors that are not bf16 already
+// become pairs of bf16 planes, x = hi + lo (about 2^-17 relative): W and W~ (one pass that also
+// dequantizes and adds L_A L_B), fp32 activations.  bf16 activations and activation codes (at most 127 in magnitude)
+// are exact as they are, so a product of either with W or W~ is two plane products instead of the three of a general
+// fp32 product.  ONE kernel then forms both outputs of a tile: it accumulates Y = X W^T over the plane
+// pairs, takes ||Y||^2 from the accumulators, multiplies row t by -1 / s_t, goes on accumulating the codes times W~^T on top, and
+// takes ||s_t (...)||^2: neither output is ever stored.  Without activation quantization M^-1 goes into W~ and the
+// factor is -1.
+// Bound: bf16 MFMA; 2048 tokens of the 4096 x 4096 layer are 2.7e11 operations in four plane products.
 #include <math.h>
 
 #include "aser_internal.h"
 
 namespace {
 
-// Wc[j][o] = code[o][j] * scale[o]: codes m x n (int8, or int4 pairs with the even column in the low
-// nibble), output n x m.  64 x 64 tiles through LDS, both sides coalesced.
-__global__ __launch_bounds__(256) void dequant_transpose_kernel(const uint8_t* __restrict__ codes, int layout,
-                                                                const float* __restrict__ scales, int64_t m, int64_t n,
-                                                                float* __restrict__ Wc) {
-    __shared__ float tile[64][65];
-    const int64_t o0 = (int64_t)blockIdx.y * 64, j0 = (int64_t)blockIdx.x * 64;
-    const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef float f32x16_t __attribute__((ext_vector_type(16)));
+typedef float f32x2_t __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ uint32_t pack2(float a, float b) {
+    const f32x2_t v = {a, b};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
+}
+
+// eight values as hi = bf16(x) and lo = bf16(x - hi)
+__device__ __forceinline__ void split8(const float (&v)[8], uint4& hi, uint4& lo) {
+    uint32_t h[4], l[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        h[q] = pack2(v[2 * q], v[2 * q + 1]);
+        l[q] = pack2(v[2 * q] - __uint_as_float(h[q] << 16), v[2 * q + 1] - __uint_as_float(h[q] & 0xFFFF0000u));
+    }
+    hi = make_uint4(h[0], h[1], h[2], h[3]);
+    lo = make_uint4(l[0], l[1], l[2], l[3]);
+}
+
+// Planes of W and of W~ = codes * scale + L_A L_B (divided by mdiag per column when it is given), np columns with zeros
+// from n on.  A workgroup takes 64 x 64 entries; the rank-r part runs on the fp32 MFMA (16 x 16 x 4), a wavefront 16 rows of it.
+__global__ __launch_bounds__(256) void weight_planes_kernel(const float* __restrict__ W, int64_t m, int64_t n, int64_t ldw, int64_t np,
+                                                            const uint8_t* __restrict__ codes, int layout, const float* __restrict__ scales,
+                                                            const float* __restrict__ L_A, const float* __restrict__ L_B, int r,
+                                                            const float* __restrict__ mdiag, int w_vec, int c_vec,
+                                                            uint16_t* __restrict__ w_hi, uint16_t* __restrict__ w_lo,
+                                                            uint16_t* __restrict__ v_hi, uint16_t* __restrict__ v_lo) {
+    __shared__ __align__(16) float low[64 * 68];                    // L_A L_B, transposed: [column][row]
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, li = lane & 15, lg = lane >> 4;
+    const int64_t o0 = (int64_t)blockIdx.y * 64, i0 = (int64_t)blockIdx.x * 64;
+    if (r > 0) {
+        f32x4_t acc[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        const int64_t o = o0 + 16 * wave + li;
+        const float* ap = L_A + (o < m ? o : m - 1) * r;             // rows and columns past the end: clamped here, dropped below
+        const float* bp[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) bp[j] = L_B + (i0 + 16 * j + li < n ? i0 + 16 * j + li : n - 1);
+        for (int k0 = 0; k0 < r; k0 += 16) {                         // four steps at a time: their loads are in flight together
+            float av[4], bv[4][4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int k = k0 + 4 * u + lg, kc = k < r ? k : r - 1;
+                av[u] = ap[kc];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) bv[u][j] = bp[j][(int64_t)kc * n];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const bool ok = k0 + 4 * u + lg < r;
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(ok ? av[u] : 0.f, ok ? bv[u][j] : 0.f, acc[j], 0, 0, 0);
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) *(f32x4_t*)(low + (16 * j + li) * 68 + 16 * wave + 4 * lg) = acc[j];
+    }
+    __syncthreads();
+    const int64_t o = o0 + (tid >> 2);
+    if (o >= m) return;
     const int64_t pitch = (layout == ASER_CODES_INT8) ? n : n / 2;
-    for (int i = ty; i < 64; i += 4) {
-        const int64_t o = o0 + i, j = j0 + tx;
-        float v = 0.f;
-        if (o < m && j < n) {
-            int q;
-            if (layout == ASER_CODES_INT8) {
-                q = (int)(int8_t)codes[o * pitch + j];
-            } else {
-                const uint8_t b = codes[o * pitch + (j >> 1)];
-                const int nib = (j & 1) ? (b >> 4) : (b & 0xF);
-                q = (nib ^ 8) - 8;                       // two's-complement nibble
-            }
-            v = (float)q * scales[o];
+    const float sc = scales[o];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int cl = 16 * (tid & 3) + 8 * h;
+        const int64_t c = i0 + cl;
+        if (c >= np) continue;                                      // np is a multiple of 32, so groups of 8 are whole
+        float w[8], v[8];
+        int q[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) { w[e] = 0.f; q[e] = 0; }
+        if (w_vec && c + 8 <= n) {
+            const float4 x = *(const float4*)(W + o * ldw + c), y = *(const float4*)(W + o * ldw + c + 4);
+            w[0] = x.x; w[1] = x.y; w[2] = x.z; w[3] = x.w; w[4] = y.x; w[5] = y.y; w[6] = y.z; w[7] = y.w;
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                if (c + e < n) w[e] = W[o * ldw + c + e];
         }
-        tile[i][tx] = v;
-    }
-    __syncthreads();
-    for (int i = ty; i < 64; i += 4) {
-        const int64_t j = j0 + i, o = o0 + tx;
-        if (j < n && o < m) Wc[j * m + o] = tile[tx][i];
+        if (layout == ASER_CODES_INT8) {
+            if (c_vec && c + 8 <= n) {
+                const uint2 x = *(const uint2*)(codes + o * pitch + c);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) q[e] = (int)((e < 4 ? x.x : x.y) << (24 - 8 * (e & 3))) >> 24;
+            } else {
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    if (c + e < n) q[e] = (int)(int8_t)codes[o * pitch + c + e];
+            }
+        } else {                                                    // two's-complement nibbles, even column in the low one
+            if (c_vec && c + 8 <= n) {
+                const uint32_t x = *(const uint32_t*)(codes + o * pitch + c / 2);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) q[e] = (int)(x << (28 - 4 * e)) >> 28;
+            } else {
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    if (c + e < n) q[e] = (int)((uint32_t)codes[o * pitch + (c + e) / 2] << (28 - 4 * (e & 1))) >> 28;
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            v[e] = (float)q[e] * sc;
+            if (r > 0) v[e] += low[(cl + e) * 68 + (tid >> 2)];
+            if (mdiag && c + e < n) v[e] /= mdiag[c + e];
+            if (c + e >= n) v[e] = 0.f;
+        }
+        uint4 hi, lo;
+        split8(w, hi, lo);
+        *(uint4*)(w_hi + o * np + c) = hi;
+        *(uint4*)(w_lo + o * np + c) = lo;
+        split8(v, hi, lo);
+        *(uint4*)(v_hi + o * np + c) = hi;
+        *(uint4*)(v_lo + o * np + c) = lo;
     }
 }
 
-// out[i][t] = f(X[t][i]) as fp32, X: rows x n (bf16 or fp32), out: n x rows.
-//   MODE 0: the value itself           MODE 1: X[t][i] / mdiag[i] (IEEE division; x / 1 = x)
-//   MODE 2: codes[t][i] * scales[t]    (X unused)
-template <bool BF16, int MODE>
-__global__ __launch_bounds__(256) void x_transpose_kernel(const void* __restrict__ X, int64_t rows, int64_t n, int64_t ldx,
-                                                          const float* __restrict__ mdiag, const int8_t* __restrict__ codes,
-                                                          const float* __restrict__ scales, float* __restrict__ out) {
-    __shared__ float tile[64][65];
-    const int64_t t0 = (int64_t)blockIdx.y * 64, i0 = (int64_t)blockIdx.x * 64;
-    const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-    for (int a = ty; a < 64; a += 4) {
-        const int64_t t = t0 + a, i = i0 + tx;
-        float v = 0.f;
-        if (t < rows && i < n) {
-            if (MODE == 2) {
-                v = (float)codes[t * n + i] * scales[t];
-            } else {
-                v = BF16 ? __uint_as_float((uint32_t)((const uint16_t*)X)[t * ldx + i] << 16) : ((const float*)X)[t * ldx + i];
-                if (MODE == 1 && mdiag) v = v / mdiag[i];
+// Activations as bf16 planes of np columns (zeros from n on): KIND 0 bf16 X copied, 1 fp32 X as hi and lo, 2 int8 codes.
+template <int KIND>
+__global__ __launch_bounds__(256) void act_planes_kernel(const void* __restrict__ X, int64_t rows, int64_t n, int64_t ldx, int64_t np,
+                                                         uint16_t* __restrict__ hi, uint16_t* __restrict__ lo) {
+    const int64_t total = rows * (np / 8);
+    for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < total; t += (int64_t)gridDim.x * 256) {
+        const int64_t row = t / (np / 8), c = (t % (np / 8)) * 8;
+        float v[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            v[e] = 0.f;
+            if (c + e < n) {
+                if (KIND == 0) v[e] = __uint_as_float((uint32_t)((const uint16_t*)X)[row * ldx + c + e] << 16);
+                if (KIND == 1) v[e] = ((const float*)X)[row * ldx + c + e];
+                if (KIND == 2) v[e] = (float)((const int8_t*)X)[row * ldx + c + e];
             }
         }
-        tile[a][tx] = v;
-    }
-    __syncthreads();
-    for (int a = ty; a < 64; a += 4) {
-        const int64_t i = i0 + a, t = t0 + tx;
-        if (i < n && t < rows) out[i * rows + t] = tile[tx][a];
+        uint4 h, l;
+        split8(v, h, l);
+        *(uint4*)(hi + row * np + c) = h;
+        if (KIND == 1) *(uint4*)(lo + row * np + c) = l;
     }
 }
 
-__global__ __launch_bounds__(256) void sumsq_f32_kernel(const float* __restrict__ p, int64_t total, double* __restrict__ out) {
-    __shared__ double red[4];
-    double acc = 0.0;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (int64_t)gridDim.x * 256) {
-        const double v = (double)p[i];
-        acc += v * v;
+struct EvalArgs {
+    const char* a[6]; int64_t pa[6];          // activation planes: address and row pitch in bytes
+    const char* b[6];                         // weight planes, row pitch 2 np
+    int segs1, segs;                          // plane products of Y, and of both outputs
+    int64_t np, rows, m;
+    const float* xs;                          // per-token scales, or null (1)
+    double* out;                              // [0] += ||Y||^2, [1] += ||difference||^2
+};
+
+// byte offset of 16-byte chunk c (0..3) of row r inside a [rows][64 bytes] LDS tile
+__device__ __forceinline__ int eval_off(int r, int c) { return r * 64 + ((c ^ ((r >> 2) & 3)) << 4); }
+
+// 64 TI tokens x 64 TJ outputs per workgroup (4 wavefronts 2 x 2), 32 channels of one plane product per step.  The
+// ring of four stages, the LDS-direct loads in inline assembly, the XOR swizzle and the XCD-aware numbering of the tiles are those of
+// the inference kernel's 256 x 256 tiles; operand fragments of the next 16 channels are read under the MFMAs of the
+// current ones.  Rows past the end repeat the last one and are left out of the sums.
+template <int TI, int TJ>
+__global__ __launch_bounds__(256) void eval_kernel(EvalArgs g, int tiles_n, int64_t tiles_total) {
+    extern __shared__ __align__(16) char smem[];
+    __shared__ float sx[64 * TI];
+    constexpr int A_BYTES = 64 * TI * 64, STAGE = A_BYTES + 64 * TJ * 64, NL = TI + TJ;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm0 = (wave >> 1) * 32 * TI, wn0 = (wave & 1) * 32 * TJ;
+    const int64_t per_xcd = (tiles_total + 7) / 8;
+    const int64_t tile = (int64_t)(blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    if (tile >= tiles_total) return;
+    const int64_t T0 = (tile / tiles_n) * 64 * TI, O0 = (tile % tiles_n) * 64 * TJ;
+    for (int t = tid; t < 64 * TI; t += 256) sx[t] = (T0 + t < g.rows) ? (g.xs ? g.xs[T0 + t] : 1.f) : 0.f;
+
+    // ---- fetch roles: instruction t of this wave is tile rows 16 (NT wave + t) + lane / 4, chunk slot lane % 4
+    const int chunk = 16 * ((lane & 3) ^ ((lane >> 4) & 3));
+    int arow[TI];
+    uint32_t aoff[TI], boff[TJ];
+#pragma unroll
+    for (int t = 0; t < TI; ++t) {
+        const int row = 16 * (TI * wave + t) + (lane >> 2);
+        arow[t] = (T0 + row < g.rows) ? row : (int)(g.rows - 1 - T0);
     }
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
+    for (int t = 0; t < TJ; ++t) {
+        const int row = 16 * (TJ * wave + t) + (lane >> 2);
+        boff[t] = (uint32_t)((O0 + row < g.m ? row : (int)(g.m - 1 - O0)) * 2 * (int)g.np + chunk);
+    }
+    const int64_t segsteps = g.np / 32, nsteps = segsteps * g.segs, steps1 = segsteps * g.segs1;
+    const uint32_t ring = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
+    int iseg = 0;
+    int64_t ikk = 0;                                      // plane product and step inside it of the stage to be fetched
+    const char *abase = nullptr, *bbase = nullptr;
+    auto seg_start = [&]() {
+        const int64_t pa = g.pa[iseg];
+        abase = g.a[iseg] + T0 * pa;
+        bbase = g.b[iseg] + O0 * 2 * g.np;
+#pragma unroll
+        for (int t = 0; t < TI; ++t) aoff[t] = (uint32_t)(arow[t] * (int)pa + chunk);
+    };
+    auto issue_one = [&](int64_t step, int q) {           // q: 0 .. TI - 1 activations, TI .. NL - 1 weights
+        const uint32_t dst = ring + (uint32_t)(step & 3) * STAGE + (q < TI ? (TI * wave + q) * 1024 : A_BYTES + (TJ * wave + q - TI) * 1024);
+        const char* base = q < TI ? abase : bbase;
+        const uint32_t off = q < TI ? aoff[q < TI ? q : 0] : boff[q < TI ? 0 : q - TI];
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(dst), "v"(off), "s"(base) : "memory", "m0");
+    };
+    auto stage_done = [&]() {                             // all loads of a stage are issued: on to the next one
+        abase += 64;
+        bbase += 64;
+        if (++ikk == segsteps) {
+            ikk = 0;
+            if (++iseg < g.segs) seg_start();
+        }
+    };
+    constexpr int W2 = 0x0F70 | (2 * NL & 15) | ((2 * NL >> 4) << 14), W1 = 0x0F70 | (NL & 15);
+
+    int offa[TI], offb[TJ];
+#pragma unroll
+    for (int i = 0; i < TI; ++i) offa[i] = eval_off(wm0 + 32 * i + (lane & 31), lane >> 5);
+#pragma unroll
+    for (int j = 0; j < TJ; ++j) offb[j] = A_BYTES + eval_off(wn0 + 32 * j + (lane & 31), lane >> 5);
+    auto read = [&](const char* st, int sl, int off) { return *(const bf16x8_t*)(st + (off ^ (sl ? 32 : 0))); };
+
+    f32x16_t acc[TI][TJ];
+#pragma unroll
+    for (int i = 0; i < TI; ++i)
+#pragma unroll
+        for (int j = 0; j < TJ; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+
+    seg_start();
+    for (int64_t s = 0; s < 3 && s < nsteps; ++s) {
+#pragma unroll
+        for (int q = 0; q < NL; ++q) issue_one(s, q);
+        stage_done();
+    }
+    if (nsteps >= 3) __builtin_amdgcn_s_waitcnt(W2);      // stage 0 has landed
+    else if (nsteps == 2) __builtin_amdgcn_s_waitcnt(W1);
+    else __builtin_amdgcn_s_waitcnt(0x0F70);
     __syncthreads();
-    if (threadIdx.x == 0) atomicAdd(out, red[0] + red[1] + red[2] + red[3]);
+    bf16x8_t a0[TI], b0[TJ], a1[TI], b1[TJ];
+#pragma unroll
+    for (int i = 0; i < TI; ++i) a0[i] = read(smem, 0, offa[i]);
+#pragma unroll
+    for (int j = 0; j < TJ; ++j) b0[j] = read(smem, 0, offb[j]);
+
+    // the sum of squares of the accumulators times a factor per row, over the rows and columns that exist
+    auto norm2 = [&](bool scaled) {
+        double sum = 0.0;
+#pragma unroll
+        for (int i = 0; i < TI; ++i)
+#pragma unroll
+            for (int j = 0; j < TJ; ++j) {
+                const bool in = O0 + wn0 + 32 * j + (lane & 31) < g.m;
+                float part = 0.f;                         // 16 squares of comparable size in fp32, then fp64
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const float s = sx[wm0 + 32 * i + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3)];
+                    const float v = s != 0.f ? acc[i][j][e] * (scaled ? s : 1.f) : 0.f;
+                    part = fmaf(v, v, part);
+                }
+                if (in) sum += (double)part;
+            }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+        return sum;
+    };
+    for (int64_t s = 0; s < nsteps; ++s) {
+        const char* st = smem + (int)(s & 3) * STAGE;
+        const char* sn = smem + (int)((s + 1) & 3) * STAGE;
+        const bool more = s + 1 < nsteps, fetch = s + 3 < nsteps;
+        if (s == steps1) {
+            const double y2 = norm2(false);
+            if (lane == 0) atomicAdd(g.out, y2);
+#pragma unroll
+            for (int i = 0; i < TI; ++i)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const float sc = sx[wm0 + 32 * i + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3)];
+                    const float f = sc > 1e-30f ? -1.f / sc : 0.f;      // below that both outputs' squares vanish in fp32
+#pragma unroll
+                    for (int j = 0; j < TJ; ++j) acc[i][j][e] *= f;
+                }
+        }
+        // slice 0 (16 channels): the operands of slice 1 are read under its MFMAs
+#pragma unroll
+        for (int i = 0; i < TI; ++i)
+#pragma unroll
+            for (int j = 0; j < TJ; ++j) {
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0[i], b0[j], acc[i][j], 0, 0, 0);
+                const int q = i * TJ + j;
+                if (q < TI) a1[q < TI ? q : 0] = read(st, 1, offa[q < TI ? q : 0]);
+#pragma unroll
+                for (int u = q; u < TJ; u += TI * TJ) b1[u] = read(st, 1, offb[u]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        // slice 1: behind its first MFMA the wait for the next stage and the barrier, then the loads of stage s + 3 and the
+        // reads of the next step's slice 0
+#pragma unroll
+        for (int i = 0; i < TI; ++i)
+#pragma unroll
+            for (int j = 0; j < TJ; ++j) {
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1[i], b1[j], acc[i][j], 0, 0, 0);
+                const int q = i * TJ + j;
+                if (q == 0 && more) {
+                    if (s + 2 < nsteps) __builtin_amdgcn_s_waitcnt(W1);
+                    else __builtin_amdgcn_s_waitcnt(0x0F70);
+                    __syncthreads();                      // everyone's share landed; stage s - 1 is free
+                }
+                if (q == 0) {
+                    if (more) {
+#pragma unroll
+                        for (int u = 0; u < TI; ++u) a0[u] = read(sn, 0, offa[u]);
+#pragma unroll
+                        for (int u = 0; u < TJ; ++u) b0[u] = read(sn, 0, offb[u]);
+                    }
+                    if (fetch) {
+#pragma unroll
+                        for (int u = 0; u < NL; ++u) issue_one(s + 3, u);
+                        stage_done();
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+    }
+    const double e2 = norm2(true);
+    if (lane == 0) atomicAdd(g.out + 1, e2);
+}
+
+template <int TI, int TJ>
+int launch_eval(aser_ctx* ctx, const EvalArgs& g) {
+    static bool done[16] = {false};
+    constexpr int lds = 4 * 64 * (64 * TI + 64 * TJ);
+    auto kern = eval_kernel<TI, TJ>;
+    if (ctx->device >= 0 && ctx->device < 16 && !done[ctx->device]) {
+        ASER_HIP(ctx, hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+        done[ctx->device] = true;
+    }
+    const int64_t tn = ceil_div64(g.m, 64 * TJ), total = tn * ceil_div64(g.rows, 64 * TI);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(8 * ceil_div64(total, 8))), dim3(256), lds, ctx->stream, g, (int)tn, total);
+    return aser_check_launch(ctx, "layer_output_error");
 }
 
 struct EvalPlan {
-    size_t off_wt, off_wc, off_xt, off_xq, off_y, off_lat, off_codes, off_scales, off_scal, total;
+    int64_t np;
+    size_t off_whi, off_wlo, off_vhi, off_vlo, off_xhi, off_xlo, off_cq, off_codes, off_scales, off_scal, total;
 };
 
-void eval_plan(int64_t m, int64_t n, int64_t rows, int r, EvalPlan* p) {
+void eval_plan(int64_t m, int64_t n, int64_t rows, EvalPlan* p) {
+    p->np = (n + 31) / 32 * 32;
     size_t off = 0;
-    p->off_wt = off; off += align_up((size_t)m * n * 4, 256);
-    p->off_wc = off; off += align_up((size_t)m * n * 4, 256);
-    p->off_xt = off; off += align_up((size_t)rows * n * 4, 256);
-    p->off_xq = off; off += align_up((size_t)rows * n * 4, 256);
-    p->off_y = off; off += align_up((size_t)rows * m * 4, 256);
-    p->off_lat = off; off += align_up((size_t)(r > 0 ? r : 1) * m * 4, 256);
+    const size_t wp = align_up((size_t)m * p->np * 2, 256), xp = align_up((size_t)rows * p->np * 2, 256);
+    p->off_whi = off; off += wp;
+    p->off_wlo = off; off += wp;
+    p->off_vhi = off; off += wp;
+    p->off_vlo = off; off += wp;
+    p->off_xhi = off; off += xp;
+    p->off_xlo = off; off += xp;
+    p->off_cq = off; off += xp;
     p->off_codes = off; off += align_up((size_t)rows * n, 256);
     p->off_scales = off; off += align_up((size_t)rows * 4, 256);
     p->off_scal = off; off += 256;
@@ -119,7 +395,7 @@ void eval_plan(int64_t m, int64_t n, int64_t rows, int r, EvalPlan* p) {
 extern "C" size_t aser_output_error_workspace_bytes(int64_t m, int64_t n, int64_t rows, int32_t r) {
     if (m <= 0 || n <= 0 || rows <= 0 || r < 0) return 0;
     EvalPlan p;
-    eval_plan(m, n, rows, r, &p);
+    eval_plan(m, n, rows, &p);
     return p.total + kAserWsTail;
 }
 
@@ -141,86 +417,67 @@ extern "C" int aser_layer_output_error(aser_ctx* ctx, const float* W, int64_t m,
     if (((uintptr_t)W & 3) || ((uintptr_t)scales & 3) || ((uintptr_t)X & (x_dtype == ASER_DTYPE_BF16 ? 1 : 3)))
         ASER_FAIL(ctx, ASER_ERR_INVALID_ARG, "layer_output_error: misaligned pointer");
     EvalPlan pl;
-    eval_plan(m, n, rows, r, &pl);
+    eval_plan(m, n, rows, &pl);
     if (!ctx->ws || ctx->ws_bytes < pl.total + kAserWsTail)
         ASER_FAIL(ctx, ASER_ERR_WORKSPACE, "layer_output_error: workspace too small (%zu needed)", pl.total + kAserWsTail);
     ASER_TRY(aser_prepare_device(ctx));
     char* ws = (char*)ctx->ws;
-    float* Wt = (float*)(ws + pl.off_wt);
-    float* Wc = (float*)(ws + pl.off_wc);
-    float* Xt = (float*)(ws + pl.off_xt);
-    float* Xq = (float*)(ws + pl.off_xq);
-    float* Y = (float*)(ws + pl.off_y);
-    float* LAt = (float*)(ws + pl.off_lat);
+    uint16_t* w_hi = (uint16_t*)(ws + pl.off_whi);
+    uint16_t* w_lo = (uint16_t*)(ws + pl.off_wlo);
+    uint16_t* v_hi = (uint16_t*)(ws + pl.off_vhi);
+    uint16_t* v_lo = (uint16_t*)(ws + pl.off_vlo);
+    uint16_t* x_hi = (uint16_t*)(ws + pl.off_xhi);
+    uint16_t* x_lo = (uint16_t*)(ws + pl.off_xlo);
+    uint16_t* c_q = (uint16_t*)(ws + pl.off_cq);
     int8_t* acodes = (int8_t*)(ws + pl.off_codes);
     float* ascales = (float*)(ws + pl.off_scales);
     double* scal = (double*)(ws + pl.off_scal);           // [0] = ||Y||^2, [1] = err^2
     const bool bf16 = x_dtype == ASER_DTYPE_BF16;
+    const int64_t np = pl.np;
 
     ASER_TRY(aser_fill_bytes(ctx, scal, 256));
-    // weights: W^T and W~^T = deq(codes)^T + L_B^T L_A^T
-    ASER_TRY(aser_transpose_f32(ctx, W, m, n, ldw, Wt, m));
     {
-        dim3 grid((unsigned)ceil_div64(n, 64), (unsigned)ceil_div64(m, 64));
-        hipLaunchKernelGGL(dequant_transpose_kernel, grid, dim3(256), 0, ctx->stream, (const uint8_t*)codes, (int)layout, scales,
-                           m, n, Wc);
-        ASER_TRY(aser_check_launch(ctx, "dequant_transpose"));
+        dim3 grid((unsigned)ceil_div64(np, 64), (unsigned)ceil_div64(m, 64));
+        const int w_vec = (((uintptr_t)W & 15) == 0 && (ldw & 3) == 0) ? 1 : 0;
+        const int c_vec = layout == ASER_CODES_INT8 ? (((uintptr_t)codes & 7) == 0 && (n & 7) == 0) : (((uintptr_t)codes & 3) == 0 && (n & 7) == 0);
+        hipLaunchKernelGGL(weight_planes_kernel, grid, dim3(256), 0, ctx->stream, W, m, n, ldw, np, (const uint8_t*)codes, (int)layout, scales,
+                           L_A, L_B, (int)r, act_bits == 0 ? mdiag : (const float*)nullptr, w_vec, c_vec, w_hi, w_lo, v_hi, v_lo);
+        ASER_TRY(aser_check_launch(ctx, "weight_planes"));
     }
-    if (r > 0) {
-        ASER_TRY(aser_transpose_f32(ctx, L_A, m, r, r, LAt, m));
-        GemmArgs g{};
-        g.A = L_B; g.lda = n; g.B = LAt; g.ldb = m; g.C = Wc; g.ldc = m;
-        g.M = n; g.N = m; g.K = r; g.alpha = 1.f;
-        g.in_type = GEMM_IN_F32X3; g.epi = GEMM_EPI_RMW; g.tiles = GEMM_TILES_ALL; g.krange = GEMM_K_FULL;
-        g.k_parts = 1; g.bm = 128; g.bn = 128;
-        ASER_TRY(aser_gemm_tn(ctx, g));
+    const int64_t groups = rows * (np / 8);
+    const dim3 xgrid((unsigned)(ceil_div64(groups, 256) < 4096 ? ceil_div64(groups, 256) : 4096));
+    // bf16 activations whose rows can be fetched 16 bytes at a time are read where they are
+    const bool direct = bf16 && ((uintptr_t)X & 15) == 0 && (ldx & 7) == 0 && ldx <= (1 << 22) && np == n;   // 128 rows within 32-bit offsets
+    if (!direct) {
+        if (bf16) hipLaunchKernelGGL(act_planes_kernel<0>, xgrid, dim3(256), 0, ctx->stream, X, rows, n, ldx, np, x_hi, x_lo);
+        else hipLaunchKernelGGL(act_planes_kernel<1>, xgrid, dim3(256), 0, ctx->stream, X, rows, n, ldx, np, x_hi, x_lo);
+        ASER_TRY(aser_check_launch(ctx, "act_planes"));
     }
-    // activations: X^T and the (quantized, dequantized) smoothed activations transposed
-    dim3 xgrid((unsigned)ceil_div64(n, 64), (unsigned)ceil_div64(rows, 64));
-    if (bf16)
-        hipLaunchKernelGGL((x_transpose_kernel<true, 0>), xgrid, dim3(256), 0, ctx->stream, X, rows, n, ldx, mdiag,
-                           (const int8_t*)nullptr, (const float*)nullptr, Xt);
-    else
-        hipLaunchKernelGGL((x_transpose_kernel<false, 0>), xgrid, dim3(256), 0, ctx->stream, X, rows, n, ldx, mdiag,
-                           (const int8_t*)nullptr, (const float*)nullptr, Xt);
-    ASER_TRY(aser_check_launch(ctx, "x_transpose"));
+    EvalArgs g{};
+    g.np = np; g.rows = rows; g.m = m; g.out = scal;
+    auto add = [&](const void* a, int64_t pa, const void* b) { g.a[g.segs] = (const char*)a; g.pa[g.segs] = pa; g.b[g.segs] = (const char*)b; ++g.segs; };
+    const void* xa = direct ? X : (const void*)x_hi;
+    const int64_t xpitch = direct ? ldx * 2 : np * 2;
+    add(xa, xpitch, w_hi);
+    add(xa, xpitch, w_lo);
+    if (!bf16) add(x_lo, np * 2, w_hi);
+    g.segs1 = g.segs;
     if (act_bits == 0) {
-        if (bf16)
-            hipLaunchKernelGGL((x_transpose_kernel<true, 1>), xgrid, dim3(256), 0, ctx->stream, X, rows, n, ldx, mdiag,
-                               (const int8_t*)nullptr, (const float*)nullptr, Xq);
-        else
-            hipLaunchKernelGGL((x_transpose_kernel<false, 1>), xgrid, dim3(256), 0, ctx->stream, X, rows, n, ldx, mdiag,
-                               (const int8_t*)nullptr, (const float*)nullptr, Xq);
+        add(xa, xpitch, v_hi);
+        add(xa, xpitch, v_lo);
+        if (!bf16) add(x_lo, np * 2, v_hi);
     } else {
         ASER_TRY(aser_quantize_act_rtn(ctx, X, x_dtype, rows, n, ldx, mdiag, act_bits, acodes, ascales));
-        hipLaunchKernelGGL((x_transpose_kernel<false, 2>), xgrid, dim3(256), 0, ctx->stream, (const void*)nullptr, rows, n, ldx,
-                           mdiag, (const int8_t*)acodes, (const float*)ascales, Xq);
+        hipLaunchKernelGGL(act_planes_kernel<2>, xgrid, dim3(256), 0, ctx->stream, (const void*)acodes, rows, n, n, np, c_q, c_q);
+        ASER_TRY(aser_check_launch(ctx, "code_planes"));
+        add(c_q, np * 2, v_hi);
+        add(c_q, np * 2, v_lo);
+        g.xs = ascales;
     }
-    ASER_TRY(aser_check_launch(ctx, "x_transpose_q"));
-    // Y = X W^T, its norm, and the residual against the compensated output
-    {
-        GemmArgs g{};
-        g.A = Xt; g.lda = rows; g.B = Wt; g.ldb = m; g.C = Y; g.ldc = m;
-        g.M = rows; g.N = m; g.K = n; g.alpha = 1.f;
-        g.in_type = GEMM_IN_F32X3; g.epi = GEMM_EPI_STORE; g.tiles = GEMM_TILES_ALL; g.krange = GEMM_K_FULL;
-        g.k_parts = 1;
-        g.bm = g.bn = (rows >= 2048 && m >= 2048) ? 256 : 128;
-        ASER_TRY(aser_gemm_tn(ctx, g));
-    }
-    {
-        const int64_t total = rows * m;
-        const int blocks = (int)(ceil_div64(total, 256 * 8) < 2048 ? ceil_div64(total, 256 * 8) : 2048);
-        hipLaunchKernelGGL(sumsq_f32_kernel, dim3(blocks > 0 ? blocks : 1), dim3(256), 0, ctx->stream, (const float*)Y, total, scal);
-        ASER_TRY(aser_check_launch(ctx, "sumsq"));
-    }
-    {
-        GemmArgs g{};
-        g.A = Xq; g.lda = rows; g.B = Wc; g.ldb = m; g.C = Y; g.ldc = m;
-        g.M = rows; g.N = m; g.K = n; g.alpha = -1.f; g.sumsq = scal + 1;
-        g.in_type = GEMM_IN_F32X3; g.epi = GEMM_EPI_RESID; g.tiles = GEMM_TILES_ALL; g.krange = GEMM_K_FULL;
-        g.k_parts = 1; g.bm = 128; g.bn = 128;
-        ASER_TRY(aser_gemm_tn(ctx, g));
-    }
+    // The largest tile with which the launch still fills the device
+    if (ceil_div64(rows, 128) * ceil_div64(m, 256) >= 200) ASER_TRY((launch_eval<2, 4>(ctx, g)));
+    else if (ceil_div64(rows, 128) * ceil_div64(m, 128) >= 200) ASER_TRY((launch_eval<2, 2>(ctx, g)));
+    else ASER_TRY((launch_eval<1, 1>(ctx, g)));
     double h[2] = {0.0, 0.0};
     ASER_HIP(ctx, hipMemcpyAsync(h, scal, sizeof(h), hipMemcpyDeviceToHost, ctx->stream));
     ASER_HIP(ctx, hipStreamSynchronize(ctx->stream));

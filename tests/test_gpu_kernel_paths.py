@@ -100,3 +100,36 @@ def test_eigenvalues_at_the_borders_of_the_multisection(k):
         st, r, _ = aser.aser_select_rank(ctx, out, alpha)
         ctx.check(st)
         assert r == orc.rank_from_alpha(out.cpu().numpy(), alpha)
+
+
+@pytest.mark.parametrize("rows,n,m,r,bits,x_dtype,act_bits,pad", [
+    (1, 32, 1, 1, 4, "bf16", 8, 0), (65, 100, 70, 9, 4, "bf16", 8, 0), (130, 96, 260, 0, 8, "bf16", 0, 8), (300, 1000, 65, 64, 8, "f32", 6, 0),
+    (64, 1026, 200, 33, 4, "f32", 0, 2), (257, 320, 129, 16, 8, "bf16", 8, 1), (1700, 224, 1800, 8, 4, "bf16", 8, 0),
+    (2049, 232, 4100, 16, 8, "bf16", 8, 0), (1990, 96, 4096, 0, 4, "f32", 8, 0)])
+def test_output_error_at_the_edges_of_its_tiles(rows, n, m, r, bits, x_dtype, act_bits, pad):
+    """The bar of the suite's other output-error tests: 2e-4 of the error plus 1e-5 of the output's norm."""
+    rng = np.random.default_rng([5, rows, n, m, r])
+    W = rng.standard_normal((m, n)).astype(np.float32) * 0.05
+    X = rng.standard_normal((rows, n)).astype(np.float32)
+    X[:, rng.integers(0, n, 2)] *= 20.0
+    if x_dtype == "bf16":
+        X = synth.bf16_to_f32(synth.f32_to_bf16_bits(X))
+    md = np.ones(n, np.float32)
+    md[rng.integers(0, n, 3)] = rng.uniform(1.0, 3.0, 3).astype(np.float32)
+    q = orc.quantize_rtn(W * md[None, :], np.zeros(0, np.int32), np.ones(n, np.float32), bits)
+    L_A = rng.standard_normal((m, max(r, 1))).astype(np.float32) * 0.01
+    L_B = rng.standard_normal((max(r, 1), n)).astype(np.float32) * 0.05
+    comp = r > 0
+    want, ynorm = orc.layer_output_error(W, X, md, q.codes, q.scales, L_A if comp else None, L_B if comp else None, act_bits or None)
+    ctx = new_ctx()
+    ctx.ensure_workspace(aser.aser_output_error_workspace_bytes(m, n, rows, r))
+    Xd = torch.zeros((rows, n + pad), dtype=torch.bfloat16 if x_dtype == "bf16" else torch.float32, device=DEV)
+    Xd[:, :n] = torch.from_numpy(X).to(DEV)
+    packed = bits == 4 and n % 2 == 0
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(DEV)
+    st, err, ref = aser.aser_layer_output_error(ctx, dev(W), Xd[:, :n], dev(md), dev(orc.pack_int4(q.codes) if packed else q.codes),
+                                                aser.ASER_CODES_INT4_PACKED if packed else aser.ASER_CODES_INT8, dev(q.scales),
+                                                dev(L_A) if comp else None, dev(L_B) if comp else None, r, act_bits)
+    ctx.check(st)
+    assert abs(ref - ynorm) <= 1e-5 * ynorm
+    assert abs(err - want) <= 2e-4 * want + 1e-5 * ynorm
