@@ -5,18 +5,17 @@
 // A truncated solver does not produce the sum over ALL singular values that Eq. 9 divides by, so this
 // path computes every one of them, in fp64 behind the product T S:
 //   B = Z Z^T  (k x k, k = min(m, n), Z = T S or its transpose)   fp64 accumulation of exact fp32 products
-//   B -> tridiagonal (d, e) by Householder reflections            two launches per column, see below
+//   B -> tridiagonal (d, e) by Householder reflections            one launch per column, see below
 //   eigenvalues of (d, e) by multisection on Sturm counts         16 to 64 lanes per eigenvalue
 //   sigma_i = sqrt(lambda_i), descending.
 // The singular values of T S and of (T S)^T agree, so B is formed on the shorter side.
 //
 // Tridiagonalisation.  Step j turns column j into (d_j, e_j, 0, ...) with H = I - tau v v^T and needs
-// p = tau B22 v and the rank-2 update B22 -= v w^T + w v^T with w = p - (tau / 2)(v^T p) v.  Both are
-// passes over the trailing matrix, and they are fused across steps: the pass of step j applies the
-// update of step j and, on the values it has just written, forms B22' v' for the NEXT reflector v'
-// (which only needs row j + 1 of the updated matrix, computed ahead by a one-workgroup kernel).  So a
-// step is one small kernel plus one pass that reads and writes the trailing matrix once: 16 (k - j)^2
-// bytes, 16 k^3 / 3 in total; the path is bound by HBM (or by the last-level cache when B fits).
+// p = tau B22 v and the rank-2 update B22 -= v w^T + w v^T with w = p - (tau / 2)(v^T p) v.  A step is one launch:
+// a pass over the trailing matrix that forms B22 v with the updates of the last (up to four) steps applied on the fly, of
+// which every fourth also writes the updated matrix, and in the workgroup that finishes last the reflector of the next
+// step.  So 10 bytes per entry and step on average instead of the 16 of an update in every step; bound by HBM or the
+// last-level cache when B fits.
 // B is kept as a full symmetric matrix so that every pass walks rows with unit stride.
 #include <math.h>
 
@@ -106,116 +105,186 @@ __device__ __forceinline__ double block_sum(double v, double* red) {   // blockD
     return r;
 }
 
-// One workgroup between two passes.  With j >= 0: finishes step j (w from the pass's p = B22 v), then
-// looks one row ahead: row j + 1 of the updated matrix gives d_{j+1} and the next reflector.  j = -1
-// starts the chain from row 0 of B.  Vectors are indexed by absolute row; v_cur / v_next alternate.
-//   tau[0]: tau of step j (read), tau[1]: tau of step j + 1 (written)
-__global__ __launch_bounds__(1024) void tridiag_head_kernel(int64_t j, int64_t k, const double* __restrict__ B,
-                                                            const double* __restrict__ v_cur, double* __restrict__ v_next,
-                                                            double* __restrict__ w, const double* __restrict__ p,
-                                                            double* __restrict__ d, double* __restrict__ e,
-                                                            const double* __restrict__ tau_cur, double* __restrict__ tau_next,
-                                                            double* __restrict__ vstore, double* __restrict__ taustore) {
+// Values that another workgroup of the same launch reads or wrote: agent-scope accesses, which do not stop in a cache that the
+// other compute units do not share.
+__device__ __forceinline__ void publish(double* p, double v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ double published(const double* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+constexpr int kTriThreads = 512, kTriRows = 8, kTriPairs = 4;
+
+struct TridiagStep {
+    int64_t c0, k;
+    double* B;
+    const double* v[kTriPairs];           // pending pairs: B still lacks - v w^T - w v^T for each of them
+    const double* w[kTriPairs];
+    const double* vn;                     // the reflector of this step
+    double *wn, *vnext;                   // out: its w, and the next reflector
+    double *p, *eff, *corner;             // B vn, row c0 and entry (k-1, k-1) of the up-to-date matrix
+    double *d, *e;
+    const double* tau_cur; double* tau_next;
+    int* counter;                         // workgroups that have finished (0 between launches)
+    double *vstore, *taustore;            // reflectors kept for a back-transformation, or null
+};
+
+// The start of the chain: d_0 and the first reflector from row 0 of B (or the whole of a matrix of one or two rows).
+__global__ __launch_bounds__(kTriThreads) void tridiag_first_kernel(TridiagStep a) {
     __shared__ double red[16];
     const int tid = threadIdx.x;
-    const int64_t row = j + 1;
-    double v_row = 0.0, w_row = 0.0;
-    if (j >= 0) {
-        const double tau = *tau_cur;
-        double dot = 0.0;
-        for (int64_t i = row + tid; i < k; i += 1024) dot += v_cur[i] * p[i];
-        dot = block_sum(dot, red);
-        const double kk = 0.5 * tau * tau * dot;
-        for (int64_t i = row + tid; i < k; i += 1024) w[i] = tau * p[i] - kk * v_cur[i];
-        __syncthreads();
-        v_row = v_cur[row];
-        w_row = w[row];
-    }
-    // row `row` of the updated matrix, from the diagonal on
-    const double* brow = B + row * k;
-    auto c_at = [&](int64_t i) -> double {
-        double c = brow[i];
-        if (j >= 0) c -= v_row * w[i] + w_row * v_cur[i];
-        return c;
-    };
-    if (tid == 0) d[row] = c_at(row);
-    if (row + 2 < k) {                                    // at least two entries below the diagonal: a reflector
+    const int64_t k = a.k;
+    if (tid == 0) a.d[0] = a.B[0];
+    if (k > 2) {
         double n2 = 0.0;
-        for (int64_t i = row + 1 + tid; i < k; i += 1024) {
-            const double c = c_at(i);
-            v_next[i] = c;
+        for (int64_t i = 1 + tid; i < k; i += kTriThreads) {
+            const double c = a.B[i];
+            a.vnext[i] = c;
+            if (a.vstore) a.vstore[i] = c;
             n2 += c * c;
         }
         n2 = block_sum(n2, red);
         __syncthreads();
         if (tid == 0) {
-            const double x0 = v_next[row + 1];
+            const double x0 = a.B[1];
             const double alpha = (x0 > 0.0) ? -sqrt(n2) : sqrt(n2);
-            const double v0 = x0 - alpha;
-            const double vn2 = n2 - x0 * x0 + v0 * v0;
-            v_next[row + 1] = v0;
-            const double tnew = vn2 > 0.0 ? 2.0 / vn2 : 0.0;
-            *tau_next = tnew;
-            e[row] = alpha;
-            if (taustore) taustore[row] = tnew;
+            const double v0 = x0 - alpha, vn2 = n2 - x0 * x0 + v0 * v0, tnew = vn2 > 0.0 ? 2.0 / vn2 : 0.0;
+            a.vnext[1] = v0;
+            *a.tau_next = tnew;
+            a.e[0] = alpha;
+            if (a.vstore) { a.vstore[1] = v0; a.taustore[0] = tnew; }
         }
-        if (vstore) {                                     // keep the reflector for the back-transformation of eigenvectors
-            __syncthreads();
-            for (int64_t i = row + 1 + tid; i < k; i += 1024) vstore[row * k + i] = v_next[i];
-        }
-    } else if (row + 2 == k) {                            // the last 2 x 2 block: no reflector
-        if (tid == 0) {
-            e[row] = c_at(row + 1);
-            double dl = B[(k - 1) * k + (k - 1)];
-            if (j >= 0) dl -= 2.0 * v_cur[k - 1] * w[k - 1];
-            d[k - 1] = dl;
-        }
+    } else if (k == 2 && tid == 0) {
+        a.e[0] = a.B[1];
+        a.d[1] = a.B[3];
     }
 }
 
-// Pass of step j over rows and columns >= c0 = j + 2: B -= v w^T + w v^T (skipped when !update), then
-// p_i = sum_l B_il vn_l on the new values.  A workgroup owns 8 rows; a thread walks columns with unit
-// stride across the workgroup and keeps its share of the 8 dot products in registers.
-__global__ __launch_bounds__(256) void tridiag_pass_kernel(int64_t c0, int64_t k, double* __restrict__ B,
-                                                           const double* __restrict__ v, const double* __restrict__ w,
-                                                           const double* __restrict__ vn, double* __restrict__ p,
-                                                           int update) {
-    __shared__ double red[4][8];
+// One step of the chain in one launch.  Every workgroup takes 8 rows of the trailing matrix (rows and columns >= c0): it
+// forms p_i = sum_l B_il vn_l on the up-to-date values, which are B minus the NP pending rank-2 updates; with
+// WRITE they also go back to memory and nothing is pending any more, otherwise the pass only reads.  The workgroup
+// that finishes last then has all of p: w = tau p - (tau^2 / 2)(vn^T p) vn, and from row c0 of the matrix after this
+// step's own update the next diagonal entry, the next off-diagonal one and the next reflector.
+// What bounds it: 8 (k - j)^2 bytes per read-only pass and twice that per writing one (every fourth), from the last-level
+// cache when B fits, and the tail of the last workgroup; a launch per column and role (pass, reflector) and a read and a
+// write of B in every pass were 26.7 us per column at k = 4096, this is 19.7.
+template <int NP, bool WRITE>
+__global__ __launch_bounds__(kTriThreads) void tridiag_step_kernel(TridiagStep a) {
+    __shared__ double red[kTriThreads / 64][kTriRows];
+    __shared__ int last;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int64_t r0 = c0 + (int64_t)blockIdx.x * 8;
-    double vi[8], wi[8], acc[8];
-    double* rowp[8];
+    const int64_t c0 = a.c0, k = a.k, r0 = c0 + (int64_t)blockIdx.x * kTriRows;
+    const int nrows = (int)((k - r0 < kTriRows) ? k - r0 : kTriRows);
+    {
+        constexpr int NQ = NP > 0 ? NP : 1;
+        double vi[NQ][kTriRows], wi[NQ][kTriRows], acc[kTriRows];
+        double* rowp[kTriRows];
 #pragma unroll
-    for (int r = 0; r < 8; ++r) {
-        const int64_t i = (r0 + r < k) ? r0 + r : k - 1;  // rows past the end repeat the last row; their results are dropped
-        vi[r] = update ? v[i] : 0.0;
-        wi[r] = update ? w[i] : 0.0;
-        rowp[r] = B + i * k;
-        acc[r] = 0.0;
-    }
-    const int nrows = (int)((k - r0 < 8) ? k - r0 : 8);
-    for (int64_t l = c0 + tid; l < k; l += 256) {
-        const double vl = update ? v[l] : 0.0, wl = update ? w[l] : 0.0, vnl = vn[l];
-        double b[8];
+        for (int r = 0; r < kTriRows; ++r) {
+            const int64_t i = (r0 + r < k) ? r0 + r : k - 1;       // rows past the end repeat the last row; their results are dropped
 #pragma unroll
-        for (int r = 0; r < 8; ++r) b[r] = rowp[r][l];
+            for (int q = 0; q < NP; ++q) { vi[q][r] = a.v[q][i]; wi[q][r] = a.w[q][i]; }
+            rowp[r] = a.B + i * k;
+            acc[r] = 0.0;
+        }
+        for (int64_t l = c0 + tid; l < k; l += kTriThreads) {
+            double vl[NQ], wl[NQ], b[kTriRows];
+            const double vnl = a.vn[l];
 #pragma unroll
-        for (int r = 0; r < 8; ++r) {
-            if (update) {
-                b[r] -= vi[r] * wl + wi[r] * vl;
-                if (r < nrows) rowp[r][l] = b[r];
+            for (int r = 0; r < kTriRows; ++r) b[r] = rowp[r][l];
+#pragma unroll
+            for (int q = 0; q < NP; ++q) { vl[q] = a.v[q][l]; wl[q] = a.w[q][l]; }
+#pragma unroll
+            for (int r = 0; r < kTriRows; ++r) {
+#pragma unroll
+                for (int q = 0; q < NP; ++q) b[r] -= vi[q][r] * wl[q] + wi[q][r] * vl[q];
+                if (WRITE && r < nrows) rowp[r][l] = b[r];
+                acc[r] = fma(b[r], vnl, acc[r]);
             }
-            acc[r] = fma(b[r], vnl, acc[r]);
+            if (blockIdx.x == 0) {
+                publish(a.eff + l, b[0]);
+                if (l == k - 1 && k - c0 == 2) publish(a.corner, b[1]);
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < kTriRows; ++r) {
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) acc[r] += __shfl_xor(acc[r], o, 64);
+            if (lane == 0) red[wave][r] = acc[r];
         }
     }
-#pragma unroll
-    for (int r = 0; r < 8; ++r) {
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) acc[r] += __shfl_xor(acc[r], o, 64);
-        if (lane == 0) red[wave][r] = acc[r];
-    }
     __syncthreads();
-    if (tid < nrows) p[r0 + tid] = red[0][tid] + red[1][tid] + red[2][tid] + red[3][tid];
+    if (tid < nrows) {
+        double s = 0.0;
+#pragma unroll
+        for (int u = 0; u < kTriThreads / 64; ++u) s += red[u][tid];
+        publish(a.p + r0 + tid, s);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                // what this wavefront published has arrived
+    __syncthreads();
+    if (tid == 0) last = (__hip_atomic_fetch_add(a.counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1) ? 1 : 0;
+    __syncthreads();
+    if (!last) return;
+
+    // ---- the last workgroup: w of this step, and the next reflector from row c0
+    double* flat = &red[0][0];
+    if (tid == 0) *a.counter = 0;
+    const int64_t row = c0;
+    const double tau = *a.tau_cur;
+    // The first 2048 entries of p, of the row and of the reflector are asked for together and kept; the rest of a longer
+    // vector is read when it is needed.
+    const double v_row = a.vn[row], p_row = published(a.p + row);
+    double pv[4], vv[4], ev[4];
+    auto fetch = [&](int64_t i0, bool with_row) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int64_t i = i0 + u * kTriThreads;
+            pv[u] = i < k ? published(a.p + i) : 0.0;
+            if (with_row) ev[u] = i < k ? published(a.eff + i) : 0.0;
+            vv[u] = i < k ? a.vn[i] : 0.0;
+        }
+    };
+    double dot = 0.0;
+    for (int64_t i0 = row + tid + 4 * kTriThreads; i0 < k; i0 += 4 * kTriThreads) {
+        fetch(i0, false);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) dot += vv[u] * pv[u];
+    }
+    fetch(row + tid, true);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) dot += vv[u] * pv[u];
+    dot = block_sum(dot, flat);
+    const double kk = 0.5 * tau * tau * dot, w_row = tau * p_row - kk * v_row;
+    const bool reflect = row + 2 < k;                               // at least two entries below the diagonal
+    double n2 = 0.0;
+    for (int64_t i0 = row + tid; i0 < k; i0 += 4 * kTriThreads) {
+        if (i0 != row + tid) fetch(i0, true);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int64_t i = i0 + u * kTriThreads;
+            if (i >= k) continue;
+            const double w = tau * pv[u] - kk * vv[u], c = ev[u] - (v_row * w + w_row * vv[u]);
+            a.wn[i] = w;
+            if (i == row) a.d[row] = c;
+            else if (reflect) {
+                a.vnext[i] = c;
+                if (a.vstore) a.vstore[row * k + i] = c;
+                n2 += c * c;
+                if (i == row + 1) red[kTriThreads / 64 - 1][kTriRows - 1] = c;      // behind what block_sum uses
+            } else {
+                a.e[row] = c;                                       // the last 2 x 2 block: no reflector
+                a.d[k - 1] = published(a.corner) - 2.0 * vv[u] * w;
+            }
+        }
+    }
+    if (!reflect) return;
+    n2 = block_sum(n2, flat);
+    if (tid == 0) {
+        const double x0 = red[kTriThreads / 64 - 1][kTriRows - 1];
+        const double alpha = (x0 > 0.0) ? -sqrt(n2) : sqrt(n2);
+        const double v0 = x0 - alpha, vn2 = n2 - x0 * x0 + v0 * v0, tnew = vn2 > 0.0 ? 2.0 / vn2 : 0.0;
+        a.vnext[row + 1] = v0;
+        *a.tau_next = tnew;
+        a.e[row] = alpha;
+        if (a.vstore) { a.vstore[row * k + row + 1] = v0; a.taustore[row] = tnew; }
+    }
 }
 
 __device__ __forceinline__ double rcp_f64(double q) {          // full precision: hardware estimate and two Newton steps
@@ -400,28 +469,51 @@ int gram_f64(aser_ctx* ctx, const TIN* P, int64_t K, int64_t k, int64_t ldp, dou
     return aser_check_launch(ctx, "gram_f64");
 }
 
-// Householder chain on B (overwritten): head(-1), pass(-1), then head(j), pass(j) for j = 0 .. k - 3.
-// vec: eight zeroed arrays of k doubles (v twice, w, p, d, e, tau, spare); d = vec[4], e = vec[5] on return.
+template <bool WRITE>
+void launch_tridiag_step(aser_ctx* ctx, int pairs, const TridiagStep& a) {
+    const dim3 grid((unsigned)ceil_div64(a.k - a.c0, kTriRows)), block(kTriThreads);
+    switch (pairs) {
+        case 0: hipLaunchKernelGGL((tridiag_step_kernel<0, WRITE>), grid, block, 0, ctx->stream, a); break;
+        case 1: hipLaunchKernelGGL((tridiag_step_kernel<1, WRITE>), grid, block, 0, ctx->stream, a); break;
+        case 2: hipLaunchKernelGGL((tridiag_step_kernel<2, WRITE>), grid, block, 0, ctx->stream, a); break;
+        case 3: hipLaunchKernelGGL((tridiag_step_kernel<3, WRITE>), grid, block, 0, ctx->stream, a); break;
+        default: hipLaunchKernelGGL((tridiag_step_kernel<4, WRITE>), grid, block, 0, ctx->stream, a); break;
+    }
+}
+
+// Householder chain on B (overwritten), one launch per column.
+// vec: eight zeroed arrays of k doubles; d = vec[4], e = vec[5] on return, vec[7] and the first ten rows of B are scratch.
 // vstore (k x k) / taustore (k), both zeroed by the caller, receive the reflectors when not null.
 int tridiagonalize(aser_ctx* ctx, double* B, int64_t k, double* const* vec, double* vstore, double* taustore) {
-    double *v0 = vec[0], *v1 = vec[1], *w = vec[2], *p = vec[3], *d = vec[4], *e = vec[5], *tau = vec[6];
-    double *vc = v0, *vn = v1;
-    hipLaunchKernelGGL(tridiag_head_kernel, dim3(1), dim3(1024), 0, ctx->stream, (int64_t)-1, k, (const double*)B,
-                       (const double*)vc, vn, w, (const double*)p, d, e, (const double*)tau, tau + 1, vstore, taustore);
-    ASER_TRY(aser_check_launch(ctx, "tridiag_head"));
-    int tsel = 1;                                          // tau[tsel] holds the tau of the reflector in vn
-    for (int64_t j = -1; j + 3 < k; ++j) {
-        // pass of step j: update with (vc, w) when j >= 0, then p = B22 vn
-        const int64_t c0 = j + 2;
-        hipLaunchKernelGGL(tridiag_pass_kernel, dim3((unsigned)ceil_div64(k - c0, 8)), dim3(256), 0, ctx->stream, c0, k, B,
-                           (const double*)vc, (const double*)w, (const double*)vn, p, j >= 0 ? 1 : 0);
-        ASER_TRY(aser_check_launch(ctx, "tridiag_pass"));
-        { double* t = vc; vc = vn; vn = t; }
-        hipLaunchKernelGGL(tridiag_head_kernel, dim3(1), dim3(1024), 0, ctx->stream, j + 1, k, (const double*)B,
-                           (const double*)vc, vn, w, (const double*)p, d, e, (const double*)(tau + tsel), tau + (tsel ^ 1),
-                           vstore, taustore);
-        ASER_TRY(aser_check_launch(ctx, "tridiag_head"));
-        tsel ^= 1;
+    // The pairs (v, w) of the last steps: five slots in rows of B that the chain has left behind, and until those exist
+    // (kFirst steps) two v and one w in vec, with every pass writing.
+    constexpr int64_t kSlots = kTriPairs + 1, kFirst = 2 * kSlots + 2;
+    auto v_of = [&](int64_t s) { return s < kFirst ? vec[s & 1] : B + (2 * (s % kSlots)) * k; };
+    auto w_of = [&](int64_t s) { return s < kFirst ? vec[2] : B + (2 * (s % kSlots) + 1) * k; };
+    double* tau = vec[6];
+    TridiagStep a{};
+    a.k = k; a.B = B; a.p = vec[3]; a.eff = vec[7]; a.corner = tau + 2; a.counter = (int*)(tau + 3);
+    a.d = vec[4]; a.e = vec[5]; a.vstore = vstore; a.taustore = taustore;
+    a.vnext = v_of(0); a.tau_next = tau;
+    hipLaunchKernelGGL(tridiag_first_kernel, dim3(1), dim3(kTriThreads), 0, ctx->stream, a);
+    ASER_TRY(aser_check_launch(ctx, "tridiag_first"));
+    int64_t pending = 0;                                   // steps s - pending .. s - 1 have not been applied to B
+    for (int64_t s = 0; s + 2 < k; ++s) {                  // reflector s acts on rows and columns s + 1 ..
+        a.c0 = s + 1;
+        for (int64_t q = 0; q < pending; ++q) { a.v[q] = v_of(s - pending + q); a.w[q] = w_of(s - pending + q); }
+        a.vn = v_of(s); a.wn = w_of(s); a.vnext = v_of(s + 1);
+        a.tau_cur = tau + (s & 1); a.tau_next = tau + ((s + 1) & 1);
+        // deferring the update pays where the traffic is what a pass costs.  Whole spectra in ms with 1 / 2 / 4 pairs pending at
+        // most: k = 256 2.13 / 2.19 / 2.35, 1024 10.60 / 10.63 / 11.31, 2048 27.3 / 26.2 / 27.2, 4096 101 / 90 / 88
+        const int64_t rest = k - a.c0, most = rest >= 2048 ? kTriPairs : (rest >= 1024 ? 2 : 1);
+        if (pending > 0 && (pending >= most || s < kFirst + 1)) {
+            launch_tridiag_step<true>(ctx, (int)pending, a);
+            pending = 0;
+        } else {
+            launch_tridiag_step<false>(ctx, (int)pending, a);
+        }
+        ASER_TRY(aser_check_launch(ctx, "tridiag_step"));
+        ++pending;
     }
     return ASER_OK;
 }
@@ -442,7 +534,10 @@ __global__ __launch_bounds__(256) void ts_f64_kernel(const float* __restrict__ T
     if (i >= m || j >= n) return;
     const float* trow = T + i * ldt;
     double acc = 0.0;
-    for (int64_t l = j; l < n; ++l) acc = fma((double)trow[l], (double)S[l * lds + j], acc);
+    // from the first row that any column of this workgroup needs (the entries above the diagonal do not count), so that the
+    // loop is uniform and its loads run ahead
+#pragma unroll 8
+    for (int64_t l = (int64_t)blockIdx.x * 64; l < n; ++l) acc = fma((double)trow[l], l >= j ? (double)S[l * lds + j] : 0.0, acc);
     if (TRANSPOSED) out[j * m + i] = acc; else out[i * n + j] = acc;
 }
 
@@ -452,38 +547,60 @@ __device__ __forceinline__ uint32_t hash32(uint32_t x) {
 }
 
 // One step of inverse iteration on the symmetric tridiagonal matrix (d, e): x <- (T - shift I)^-1 x by Gaussian
-// elimination with row interchanges (a zero pivot becomes `tiny`), then scaled to unit maximum.  dd, du, du2: k
-// doubles each of scratch.
+// elimination with row interchanges (a zero pivot becomes `tiny`), then scaled to unit maximum.  dd (reciprocal pivots), du,
+// du2: k doubles each of scratch.  One thread: the recurrence is a chain, and what it reads (eight entries at a time) is asked for
+// before it is needed; 64-bit divisions and a load behind every store took three quarters of a microsecond per row.
 __device__ __forceinline__ void invit_solve_one(int64_t k, const double* __restrict__ d, const double* __restrict__ e,
                                                 double shift, double tiny, double* x, double* dd, double* du, double* du2) {
-    double a = d[0] - shift, b = (k > 1) ? e[0] : 0.0;       // current row: diagonal and super-diagonal
-    for (int64_t i = 0; i + 1 < k; ++i) {
-        const double sub = e[i], dn = d[i + 1] - shift, en = (i + 2 < k) ? e[i + 1] : 0.0;
-        if (fabs(a) >= fabs(sub)) {
-            if (fabs(a) < tiny) a = tiny;
-            const double mult = sub / a;
-            dd[i] = a; du[i] = b; du2[i] = 0.0;
-            x[i + 1] -= mult * x[i];
-            a = dn - mult * b;
-            b = en;
-        } else {
-            const double mult = a / sub;
-            dd[i] = sub; du[i] = dn; du2[i] = en;
-            const double xi = x[i];
-            x[i] = x[i + 1];
-            x[i + 1] = xi - mult * x[i];
-            a = b - mult * dn;
-            b = -mult * en;
+    double a = d[0] - shift, b = (k > 1) ? e[0] : 0.0, xi = x[0];      // current row: diagonal, super-diagonal, right-hand side
+    for (int64_t i0 = 0; i0 + 1 < k; i0 += 8) {
+        double sub[8], dn[8], en[8], xn[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int64_t i = (i0 + u + 1 < k) ? i0 + u : k - 2;
+            sub[u] = e[i];
+            dn[u] = d[i + 1] - shift;
+            en[u] = (i + 2 < k) ? e[i + 1] : 0.0;
+            xn[u] = x[i + 1];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int64_t i = i0 + u;
+            if (i + 1 < k) {
+                const bool keep = fabs(a) >= fabs(sub[u]);
+                if (keep && fabs(a) < tiny) a = tiny;
+                const double rp = rcp_f64(keep ? a : sub[u]), mult = (keep ? sub[u] : a) * rp;
+                const double top = keep ? b : dn[u], top2 = keep ? 0.0 : en[u], xt = keep ? xi : xn[u];
+                dd[i] = rp; du[i] = top; du2[i] = top2; x[i] = xt;
+                xi = (keep ? xn[u] : xi) - mult * xt;
+                a = (keep ? dn[u] : b) - mult * top;
+                b = (keep ? en[u] : 0.0) - mult * top2;
+            }
         }
     }
     if (fabs(a) < tiny) a = tiny;
-    dd[k - 1] = a;
-    x[k - 1] /= dd[k - 1];
-    if (k > 1) x[k - 2] = (x[k - 2] - du[k - 2] * x[k - 1]) / dd[k - 2];
-    for (int64_t i = k - 3; i >= 0; --i) x[i] = (x[i] - du[i] * x[i + 1] - du2[i] * x[i + 2]) / dd[i];
-    double mx = 0.0;
-    for (int64_t i = 0; i < k; ++i) mx = fmax(mx, fabs(x[i]));
+    double x1 = xi * rcp_f64(a), x2 = 0.0, mx = fabs(x1);               // x_{i+1}, x_{i+2}
+    x[k - 1] = x1;
+    for (int64_t i0 = k - 2; i0 >= 0; i0 -= 8) {
+        double rp[8], t1[8], t2[8], xv[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int64_t i = (i0 - u >= 0) ? i0 - u : 0;
+            rp[u] = dd[i]; t1[u] = du[i]; t2[u] = du2[i]; xv[u] = x[i];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            if (i0 - u >= 0) {
+                const double v = (xv[u] - t1[u] * x1 - t2[u] * x2) * rp[u];
+                x2 = x1;
+                x1 = v;
+                x[i0 - u] = v;
+                mx = fmax(mx, fabs(v));
+            }
+        }
+    }
     const double sc = mx > 0.0 ? 1.0 / mx : 1.0;
+#pragma unroll 8
     for (int64_t i = 0; i < k; ++i) x[i] *= sc;
 }
 
@@ -627,6 +744,41 @@ __global__ __launch_bounds__(256) void backtransform_kernel(int64_t k, const dou
     }
 }
 
+// The same for k <= 64 PER: one wavefront per vector with the vector in registers, the next reflector on its way while the current one is
+// applied (k = 256: 194 us with a workgroup per vector and two barriers per reflector).
+template <int PER>
+__global__ __launch_bounds__(64) void backtransform_wave_kernel(int64_t k, const double* __restrict__ vstore,
+                                                                const double* __restrict__ taustore, double* __restrict__ X) {
+    const int lane = threadIdx.x;
+    double* x = X + (int64_t)blockIdx.x * k;
+    double xv[PER], v[PER], vn[PER];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) xv[u] = lane + 64 * u < k ? x[lane + 64 * u] : 0.0;
+    auto load = [&](int64_t j, double (&t)[PER]) {                   // entries up to j are zero in the store
+#pragma unroll
+        for (int u = 0; u < PER; ++u) t[u] = lane + 64 * u < k ? vstore[j * k + lane + 64 * u] : 0.0;
+    };
+    if (k >= 3) load(k - 3, v);
+    double tau = k >= 3 ? taustore[k - 3] : 0.0;
+    for (int64_t j = k - 3; j >= 0; --j) {
+        const int64_t nx = j > 0 ? j - 1 : 0;
+        load(nx, vn);
+        const double taun = taustore[nx];
+        double s = 0.0;
+#pragma unroll
+        for (int u = 0; u < PER; ++u) s += v[u] * xv[u];
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+        s *= tau;
+#pragma unroll
+        for (int u = 0; u < PER; ++u) { xv[u] -= s * v[u]; v[u] = vn[u]; }
+        tau = taun;
+    }
+#pragma unroll
+    for (int u = 0; u < PER; ++u)
+        if (lane + 64 * u < k) x[lane + 64 * u] = xv[u];
+}
+
 // Factors from the eigenvectors (rows of X, r x k) and eigenvalues lam (descending) of the Gram matrix.
 //   k == m (left singular vectors u_c = X[c]):   L_A[i][c] = u_c[i] sigma_c,        L_B[c][j] = sum_i u_c[i] T[i][j] / sigma_c
 //   k == n (right singular vectors v_c = X[c]):  L_A[i][c] = sum_j A[i][j] v_c[j],  L_B[c][j] = sum_i L_A[i][c] T[i][j] / sigma_c^2
@@ -650,8 +802,10 @@ __global__ __launch_bounds__(256) void exact_factors_kernel(int phase, int left,
         } else {
             v = 0.0;
             if (A32) {
+#pragma unroll 8
                 for (int64_t j = 0; j < n; ++j) v = fma((double)A32[i * n + j], X[(int64_t)c * k + j], v);
             } else {
+#pragma unroll 8
                 for (int64_t j = 0; j < n; ++j) v = fma(A64[i * n + j], X[(int64_t)c * k + j], v);
             }
         }
@@ -669,6 +823,7 @@ __global__ __launch_bounds__(256) void exact_factors_kernel(int phase, int left,
     const int c = (int)(t / n);
     const int64_t j = t % n;
     double acc = 0.0;
+#pragma unroll 8
     for (int64_t i = 0; i < m; ++i) acc = fma(LA64[i * r + c], (double)T[i * ldt + j], acc);
     L_B[t] = lam[c] > 0.0 ? (float)(acc / lam[c]) : 0.f;     // L_A^T T / sigma^2 in both cases (L_A = u sigma)
 }
@@ -798,8 +953,13 @@ int aser_exact_reconstruct(aser_ctx* ctx, const float* T, int64_t m, int64_t n, 
                            (const double*)lam, X, scr);
         ASER_TRY(aser_check_launch(ctx, "tridiag_invit"));
     }
-    hipLaunchKernelGGL(backtransform_kernel, dim3((unsigned)r), dim3(256), 0, ctx->stream, k, (const double*)vstore,
-                       (const double*)taustore, X);
+    if (k <= 256)
+        hipLaunchKernelGGL(backtransform_wave_kernel<4>, dim3((unsigned)r), dim3(64), 0, ctx->stream, k, (const double*)vstore, (const double*)taustore, X);
+    else if (k <= 1024)
+        hipLaunchKernelGGL(backtransform_wave_kernel<16>, dim3((unsigned)r), dim3(64), 0, ctx->stream, k, (const double*)vstore, (const double*)taustore, X);
+    else
+        hipLaunchKernelGGL(backtransform_kernel, dim3((unsigned)r), dim3(256), 0, ctx->stream, k, (const double*)vstore,
+                           (const double*)taustore, X);
     ASER_TRY(aser_check_launch(ctx, "backtransform"));
     for (int phase = 0; phase < 2; ++phase) {
         const int64_t total = phase == 0 ? m * (int64_t)r : (int64_t)r * n;

@@ -133,3 +133,21 @@ def test_output_error_at_the_edges_of_its_tiles(rows, n, m, r, bits, x_dtype, ac
     ctx.check(st)
     assert abs(ref - ynorm) <= 1e-5 * ynorm
     assert abs(err - want) <= 2e-4 * want + 1e-5 * ynorm
+
+
+@pytest.mark.parametrize("n,f", [(1, 1), (255, 255), (513, 40), (1024, 1), (1537, 300), (32768, 64)])
+def test_outlier_selection_with_many_ties(n, f):
+    """Scores of few distinct values, exactly equal on both sides (powers of two): the order is that of the channel index, bit for bit."""
+    rng = np.random.default_rng(n)
+    W = np.full((4, n), 0.5, np.float32)
+    abs_sum = (2.0 ** rng.integers(0, 4, n)).astype(np.float64)
+    ref = orc.smooth_outliers(W, abs_sum, 8, f)
+    ctx = new_ctx()
+    ctx.ensure_workspace(aser.aser_workspace_bytes(4, n, 0))
+    idx = torch.full((f,), 7, dtype=torch.int32, device=DEV)
+    mdiag = torch.empty(n, dtype=torch.float32, device=DEV)
+    for call in (aser.aser_smooth_outliers, aser.aser_smooth_outliers_noalloc):
+        idx.fill_(7)
+        ctx.check(call(ctx, torch.from_numpy(W).to(DEV), torch.from_numpy(abs_sum).to(DEV), torch.tensor([8], dtype=torch.int64, device=DEV), f, idx, mdiag))
+        assert np.array_equal(idx.cpu().numpy(), ref.idx)
+        assert np.array_equal(mdiag.cpu().numpy(), ref.mdiag)
