@@ -148,10 +148,10 @@ struct GemmArgs {
     float alpha;
     int in_type, epi, tiles, krange;
     int k_parts;               // split of the K range over blockIdx.y
-    int bm, bn;                // tile: 256x256, 128x256, 256x128 or 128x128
+    int bm, bn;                // tile: 256x256 (not X6), 256x128 (fp32 forms) or 128x128
     int upper_only;            // ATOMIC only: skip entries with row > col (C is symmetric, its upper part is used)
-    int pair_cols;             // TILES_ALL, k_parts == 1, 256 x 128 tiles: a workgroup takes tile columns j and tn - 1 - j of its tile row
-                               // (equal work per workgroup when K shrinks linearly with the column, K_GE_COL)
+    int long_first;            // TILES_ALL: tiles are numbered column by column, so that with K_GE_COL (K shrinks with the column) the
+                               // longest start first and the short ones fill the gaps
     double* sumsq;             // RESID only: device scalar that receives the sum of squares (accumulates)
     int split;                 // Gram schedules only: K parts of a left-over tile (>= 1)
     const int* gate;           // plain schedules only (may be null): every workgroup returns at once when *gate == 0

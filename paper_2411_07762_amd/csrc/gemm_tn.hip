@@ -217,11 +217,11 @@ struct SchedPattern<R, MF, R> {
 // All MFMAs of one K step from LDS stage (sa, sb).  Operand fragments are double buffered: the
 // LDS reads of k-slice kk + 1 are in flight while the MFMAs of slice kk execute (one wave per
 // SIMD: nothing else hides the LDS latency), and the scheduling hints spread them evenly.
-template <int IN, int BM, int BN>
-__device__ __forceinline__ void mfma_step(f32x16_t (&acc)[BM / 64][BN / 64], const uint4* sa, const uint4* sb,
-                                          const int (&offa)[BM / 64], const int (&offb)[BN / 64]) {
+template <int IN, int BM, int BN, int TM, int TN>
+__device__ __forceinline__ void mfma_step(f32x16_t (&acc)[TM][TN], const uint4* sa, const uint4* sb,
+                                          const int (&offa)[TM], const int (&offb)[TN]) {
     using Cfg = TileCfg<IN, BM, BN>;
-    constexpr int NP = Cfg::NP, KB = Cfg::KB, TM = Cfg::TM, TN = Cfg::TN, KK = Cfg::BK / 16;
+    constexpr int NP = Cfg::NP, KB = Cfg::KB, KK = Cfg::BK / 16;
     constexpr int R = NP * (TM + TN);                   // LDS reads per k-slice
     constexpr int MF = TM * TN * (NP == 3 ? 6 : (NP == 2 ? 3 : 1));     // MFMAs per k-slice
     bf16x8_t a[2][NP][TM], b[2][NP][TN];
@@ -266,6 +266,120 @@ __device__ __forceinline__ void mfma_step(f32x16_t (&acc)[BM / 64][BN / 64], con
         if (kk + 1 < KK) SchedPattern<R, MF, 0>::emit();
         else __builtin_amdgcn_sched_group_barrier(0x008, MF, 0);
     }
+}
+
+// Epilogue of a wavefront's part at (I0, J0).  acc[i][j][e] is C(row, col) with row = 32 i + 8 (e / 4) + 4 (lane / 32) + e % 4,
+// col = 32 j + lane % 32.  RESID: the tile can form the residual norm (the large tiles have no registers to spare for it).
+template <int TM, int TN, bool RESID>
+__device__ __forceinline__ void tile_epilogue(const GemmArgs& g, f32x16_t (&acc)[TM][TN], int64_t I0, int64_t J0, int lane) {
+    const float alpha = g.alpha;
+    if (RESID && g.epi == GEMM_EPI_RESID) {
+        // squared Frobenius norm of C + alpha acc, nothing stored: the loads of one row of 32 x 32
+        // blocks are in flight together, squares are summed in fp64, one atomic per wavefront
+        double sum = 0.0;
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            const int64_t rbase = I0 + 32 * i + 4 * (lane >> 5);
+            float old[TN][16];
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                const int64_t col = J0 + 32 * j + (lane & 31);
+                const float* cbase = g.C + rbase * g.ldc + col;
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const int dr = 8 * (e >> 2) + (e & 3);
+                    const bool in = col < g.N && rbase + dr < g.M;
+                    old[j][e] = in ? cbase[(int64_t)dr * g.ldc] : 0.f;
+                    if (!in) acc[i][j][e] = 0.f;
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                float part = 0.f;                          // 16 squares of comparable size in fp32, then fp64
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const float d = old[j][e] + alpha * acc[i][j][e];
+                    part = fmaf(d, d, part);
+                }
+                sum += (double)part;
+            }
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+        if (lane == 0) atomicAdd(g.sumsq, sum);
+        return;
+    }
+    if (g.epi == GEMM_EPI_RMW) {
+        // read-modify-write: one row of 32 x 32 blocks (up to 64 values per lane) is loaded before
+        // anything is stored, so that the loads overlap instead of forming a chain
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            const int64_t rbase = I0 + 32 * i + 4 * (lane >> 5);
+            float old[TN][16];
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                const int64_t col = J0 + 32 * j + (lane & 31);
+                const float* cbase = g.C + rbase * g.ldc + col;
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const int dr = 8 * (e >> 2) + (e & 3);
+                    old[j][e] = (col < g.N && rbase + dr < g.M) ? cbase[(int64_t)dr * g.ldc] : 0.f;
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                const int64_t col = J0 + 32 * j + (lane & 31);
+                float* cbase = g.C + rbase * g.ldc + col;
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const int dr = 8 * (e >> 2) + (e & 3);
+                    if (col < g.N && rbase + dr < g.M) cbase[(int64_t)dr * g.ldc] = old[j][e] + alpha * acc[i][j][e];
+                }
+            }
+        }
+        return;
+    }
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            const int64_t col = J0 + 32 * j + (lane & 31);
+            const int64_t rbase = I0 + 32 * i + 4 * (lane >> 5);
+            if (col >= g.N) continue;
+            float* cbase = g.C + rbase * g.ldc + col;
+            if (g.epi == GEMM_EPI_ATOMIC) {
+                // upper_only: entries left of the diagonal are never read by the caller; leaving them
+                // out halves the atomic traffic of the small symmetric products
+                const int64_t rmax = g.upper_only ? (col + 1 < g.M ? col + 1 : g.M) : g.M;
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const int dr = 8 * (e >> 2) + (e & 3);
+                    if (rbase + dr < rmax) unsafeAtomicAdd(cbase + (int64_t)dr * g.ldc, alpha * acc[i][j][e]);
+                }
+            } else {
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const int dr = 8 * (e >> 2) + (e & 3);
+                    if (rbase + dr < g.M) cbase[(int64_t)dr * g.ldc] = alpha * acc[i][j][e];
+                }
+                if (g.Ct) {
+                    // transposed copy: the 4 consecutive rows of one accumulator group are contiguous in Ct
+                    float* tbase = g.Ct + col * g.ldct + rbase;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const int dr = 8 * q;
+                        if (rbase + dr + 3 < g.M && ((((uintptr_t)(tbase + dr)) & 15) == 0)) {
+                            *(float4*)(tbase + dr) = make_float4(alpha * acc[i][j][4 * q], alpha * acc[i][j][4 * q + 1],
+                                                                 alpha * acc[i][j][4 * q + 2], alpha * acc[i][j][4 * q + 3]);
+                        } else {
+#pragma unroll
+                            for (int u = 0; u < 4; ++u)
+                                if (rbase + dr + u < g.M) tbase[dr + u] = alpha * acc[i][j][4 * q + u];
+                        }
+                    }
+                }
+            }
+        }
 }
 
 // One tile of C over the K range [kBeg, kEnd).
@@ -340,7 +454,7 @@ __device__ __forceinline__ void tile_body(const GemmArgs& g, int64_t I0, int64_t
                     // NSETS is even, so the LDS stage of step s is u & 1
                     const uint4* sa = smem + (u & 1) * Cfg::STAGE_CHUNKS;
                     uint4* da = smem + ((u + 1) & 1) * Cfg::STAGE_CHUNKS;
-                    mfma_step<IN, BM, BN>(acc, sa, sa + Cfg::A_CHUNKS, offa, offb);
+                    mfma_step<IN, BM, BN, TM, TN>(acc, sa, sa + Cfg::A_CHUNKS, offa, offb);
                     if (s + 1 < steps) {
                         fa.store(ra[u], da + fa_off);
                         if (!SHARED) fb.store(rb[SHARED ? 0 : u], da + Cfg::A_CHUNKS);
@@ -366,7 +480,7 @@ __device__ __forceinline__ void tile_body(const GemmArgs& g, int64_t I0, int64_t
         for (int64_t s = 0; s < steps; ++s) {
             const uint4* sa = smem + (s & 1) * Cfg::STAGE_CHUNKS;
             uint4* da = smem + ((s + 1) & 1) * Cfg::STAGE_CHUNKS;
-            mfma_step<IN, BM, BN>(acc, sa, sa + Cfg::A_CHUNKS, offa, offb);
+            mfma_step<IN, BM, BN, TM, TN>(acc, sa, sa + Cfg::A_CHUNKS, offa, offb);
             if (s + 1 < steps) {
                 fa.store(a0, da);
                 fb.store(b0, da + Cfg::A_CHUNKS);
@@ -376,128 +490,177 @@ __device__ __forceinline__ void tile_body(const GemmArgs& g, int64_t I0, int64_t
         }
     }
 
-    // Epilogue.  acc[i][j][e] is C(row, col) with row = 32 i + 8 (e / 4) + 4 (lane / 32) + e % 4,
-    // col = 32 j + lane % 32 inside the wave's sub-tile.
-    const float alpha = g.alpha;
-    if (BM == 128 && BN == 128 && g.epi == GEMM_EPI_RESID) {   // (the large tiles have no registers to spare for it)
-        // squared Frobenius norm of C + alpha acc, nothing stored: the loads of one row of 32 x 32
-        // blocks are in flight together, squares are summed in fp64, one atomic per wavefront
-        double sum = 0.0;
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
-            const int64_t rbase = I0 + wm0 + 32 * i + 4 * (lane >> 5);
-            float old[TN][16];
-#pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                const int64_t col = J0 + wn0 + 32 * j + (lane & 31);
-                const float* cbase = g.C + rbase * g.ldc + col;
-#pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int dr = 8 * (e >> 2) + (e & 3);
-                    const bool in = col < g.N && rbase + dr < g.M;
-                    old[j][e] = in ? cbase[(int64_t)dr * g.ldc] : 0.f;
-                    if (!in) acc[i][j][e] = 0.f;
-                }
-            }
-#pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                float part = 0.f;                          // 16 squares of comparable size in fp32, then fp64
-#pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const float d = old[j][e] + alpha * acc[i][j][e];
-                    part = fmaf(d, d, part);
-                }
-                sum += (double)part;
-            }
-        }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
-        if (lane == 0) atomicAdd(g.sumsq, sum);
-        return;
+    tile_epilogue<TM, TN, BM == 128 && BN == 128>(g, acc, I0 + wm0, J0 + wn0, lane);
+}
+
+// ---------------------------------------------------------------------------------------------
+// The 256 x 128 tile of the fp32 forms on eight wavefronts (two per SIMD, 4 x 2, 64 x 64 each).  A K step is about as much
+// conversion (fp32 -> bf16 terms, about six instructions per element) as MFMA work, and with one wavefront per SIMD the two follow
+// one another; with two, one converts while the other multiplies.  A thread stages R rows (4 of A, 2 of B, of a k-block of
+// 8) x 4 columns of an operand, so a chunk of LDS is filled by 8 / R threads.  Measured on T S (us, four -> eight wavefronts):
+// 4096 x 4096 281 -> 223, 14336 x 4096 1101 -> 776, 4096 x 11008 2056 -> 1454.  The 128 x 128 tile keeps four wavefronts:
+// its launches are a few K steps long, and more wavefronts only lengthen their start (mean at 4096 channels 16.6 -> 18.8).
+template <int IN, int BMN, int R, bool FAST>
+struct FetchRows {
+    static constexpr int GROUPS = BMN / 4, UNITS = GROUPS * (32 / R), NP = InTraits<IN>::NP;
+    const char* p;      // address of (this thread's first row in the next step, first column)
+    const char* plast;  // same columns in the last valid row (FAST)
+    int64_t ld_bytes, k;
+    int cg, kr;         // column group, first row inside a step
+    int ncols;
+    bool vec_ok;
+
+    __device__ __forceinline__ void init(const void* base, int64_t ld, int64_t mn0, int64_t MN, int64_t k0, int64_t kEnd, int unit) {
+        // neighbouring threads fill one chunk, so that a wavefront's stores cover whole chunks of consecutive banks
+        constexpr int SUB = 8 / R;
+        cg = (unit / SUB) % GROUPS;
+        kr = (unit / (SUB * GROUPS)) * 8 + (unit % SUB) * R;
+        int64_t col = mn0 + (int64_t)cg * 4;
+        const int64_t rem = MN - col;
+        ncols = rem >= 4 ? 4 : (rem > 0 ? (int)rem : 0);
+        k = k0 + kr;
+        ld_bytes = ld * 4;
+        if (FAST && ncols != 4) col = 0;                  // never stored to C
+        p = (const char*)base + k * ld_bytes + col * 4;
+        plast = (const char*)base + (kEnd - 1) * ld_bytes + col * 4;
+        vec_ok = FAST || ((((uintptr_t)p & 15) == 0) && ((ld_bytes & 15) == 0) && ncols == 4);
     }
-    if (g.epi == GEMM_EPI_RMW) {
-        // read-modify-write: one row of 32 x 32 blocks (up to 64 values per lane) is loaded before
-        // anything is stored, so that the loads overlap instead of forming a chain
+
+    __device__ __forceinline__ void load(uint4 (&r)[R], int64_t kEnd) {
+        if (FAST) {
+            if (k + R <= kEnd) {
 #pragma unroll
-        for (int i = 0; i < TM; ++i) {
-            const int64_t rbase = I0 + wm0 + 32 * i + 4 * (lane >> 5);
-            float old[TN][16];
-#pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                const int64_t col = J0 + wn0 + 32 * j + (lane & 31);
-                const float* cbase = g.C + rbase * g.ldc + col;
-#pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int dr = 8 * (e >> 2) + (e & 3);
-                    old[j][e] = (col < g.N && rbase + dr < g.M) ? cbase[(int64_t)dr * g.ldc] : 0.f;
-                }
-            }
-#pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                const int64_t col = J0 + wn0 + 32 * j + (lane & 31);
-                float* cbase = g.C + rbase * g.ldc + col;
-#pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int dr = 8 * (e >> 2) + (e & 3);
-                    if (col < g.N && rbase + dr < g.M) cbase[(int64_t)dr * g.ldc] = old[j][e] + alpha * acc[i][j][e];
-                }
-            }
-        }
-        return;
-    }
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            const int64_t col = J0 + wn0 + 32 * j + (lane & 31);
-            const int64_t rbase = I0 + wm0 + 32 * i + 4 * (lane >> 5);
-            if (col >= g.N) continue;
-            float* cbase = g.C + rbase * g.ldc + col;
-            if (g.epi == GEMM_EPI_ATOMIC) {
-                // upper_only: entries left of the diagonal are never read by the caller; leaving them
-                // out halves the atomic traffic of the small symmetric products
-                const int64_t rmax = g.upper_only ? (col + 1 < g.M ? col + 1 : g.M) : g.M;
-#pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int dr = 8 * (e >> 2) + (e & 3);
-                    if (rbase + dr < rmax) unsafeAtomicAdd(cbase + (int64_t)dr * g.ldc, alpha * acc[i][j][e]);
-                }
+                for (int j = 0; j < R; ++j) r[j] = *(const uint4*)(p + j * ld_bytes);
             } else {
 #pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int dr = 8 * (e >> 2) + (e & 3);
-                    if (rbase + dr < g.M) cbase[(int64_t)dr * g.ldc] = alpha * acc[i][j][e];
+                for (int j = 0; j < R; ++j) {
+                    const bool ok = k + j < kEnd;
+                    const uint4 v = *(const uint4*)(ok ? p + j * ld_bytes : plast);
+                    r[j] = ok ? v : make_uint4(0u, 0u, 0u, 0u);
                 }
-                if (g.Ct) {
-                    // transposed copy: the 4 consecutive rows of one accumulator group are contiguous in Ct
-                    float* tbase = g.Ct + col * g.ldct + rbase;
+            }
+        } else {
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int dr = 8 * q;
-                        if (rbase + dr + 3 < g.M && ((((uintptr_t)(tbase + dr)) & 15) == 0)) {
-                            *(float4*)(tbase + dr) = make_float4(alpha * acc[i][j][4 * q], alpha * acc[i][j][4 * q + 1],
-                                                                 alpha * acc[i][j][4 * q + 2], alpha * acc[i][j][4 * q + 3]);
-                        } else {
-#pragma unroll
-                            for (int u = 0; u < 4; ++u)
-                                if (rbase + dr + u < g.M) tbase[dr + u] = alpha * acc[i][j][4 * q + u];
-                        }
+            for (int j = 0; j < R; ++j) {
+                r[j] = make_uint4(0u, 0u, 0u, 0u);
+                if (k + j < kEnd) {
+                    const char* q = p + j * ld_bytes;
+                    if (vec_ok) {
+                        r[j] = *(const uint4*)q;
+                    } else {
+                        uint32_t w[4] = {0u, 0u, 0u, 0u};
+                        for (int e = 0; e < ncols; ++e) w[e] = *(const uint32_t*)(q + 4 * e);
+                        r[j] = make_uint4(w[0], w[1], w[2], w[3]);
                     }
                 }
             }
         }
+        p += 32 * ld_bytes;
+        k += 32;
+    }
+
+    __device__ __forceinline__ void store(const uint4 (&r)[R], uint4* lds) const {
+        const float* x = (const float*)r;                 // x[4 j + c]: row j, column c
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            uint32_t t[NP][R / 2];
+#pragma unroll
+            for (int q = 0; q < R / 2; ++q) {
+                float u = x[4 * (2 * q) + c], v = x[4 * (2 * q + 1) + c];
+#pragma unroll
+                for (int n = 0; n < NP; ++n) {            // the next term is what the ones before it leave (exact differences)
+                    t[n][q] = pack_bf16x2(u, v);
+                    u -= __uint_as_float(t[n][q] << 16);
+                    v -= __uint_as_float(t[n][q] & 0xFFFF0000u);
+                }
+            }
+            char* pos = (char*)(lds + (kr >> 3) * BMN + swz(cg * 4 + c)) + (kr & 7) * 2;
+#pragma unroll
+            for (int n = 0; n < NP; ++n) {
+                char* q = pos + n * 4 * BMN * 16;
+                if (R == 4) *(uint2*)q = make_uint2(t[n][0], t[n][R / 2 - 1]);
+                else *(uint32_t*)q = t[n][0];
+            }
+        }
+    }
+};
+
+constexpr int kWideThreads = 512;
+
+template <int IN, bool FAST>
+__device__ __forceinline__ void tile_body_wide(const GemmArgs& g, int64_t I0, int64_t J0, int64_t kBeg, int64_t kEnd, uint4* smem) {
+    constexpr int BM = 256, BN = 128, TM = 2, TN = 2, RA = 4, RB = 2;
+    using Cfg = TileCfg<IN, BM, BN>;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wm0 = (wave >> 1) * 64, wn0 = (wave & 1) * 64;
+    FetchRows<IN, BM, RA, FAST> fa;
+    FetchRows<IN, BN, RB, FAST> fb;
+    fa.init(g.A, g.lda, I0, g.M, kBeg, kEnd, tid);
+    fb.init(g.B, g.ldb, J0, g.N, kBeg, kEnd, tid);
+
+    f32x16_t acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+    int offa[TM], offb[TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i) offa[i] = (lane >> 5) * BM + swz(wm0 + 32 * i + (lane & 31));
+#pragma unroll
+    for (int j = 0; j < TN; ++j) offb[j] = (lane >> 5) * BN + swz(wn0 + 32 * j + (lane & 31));
+
+    const int64_t steps = (kEnd - kBeg + Cfg::BK - 1) / Cfg::BK;
+    uint4 ra[2][RA], rb[2][RB];                           // set u holds steps u + 1, u + 3, ...
+    if (steps > 0) {
+        fa.load(ra[0], kEnd);
+        fb.load(rb[0], kEnd);
+        fa.store(ra[0], smem);
+        fb.store(rb[0], smem + Cfg::A_CHUNKS);
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+            if (steps > u + 1) { fa.load(ra[u], kEnd); fb.load(rb[u], kEnd); }
+    }
+    __syncthreads();
+    for (int64_t s0 = 0; s0 < steps; s0 += 2) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int64_t s = s0 + u;
+            if (s < steps) {
+                const uint4* sa = smem + u * Cfg::STAGE_CHUNKS;
+                uint4* da = smem + (u ^ 1) * Cfg::STAGE_CHUNKS;
+                auto convert = [&]() {
+                    if (s + 1 < steps) {
+                        fa.store(ra[u], da);
+                        fb.store(rb[u], da + Cfg::A_CHUNKS);
+                        if (s + 3 < steps) { fa.load(ra[u], kEnd); fb.load(rb[u], kEnd); }
+                    }
+                };
+                // the two wavefronts of a SIMD start a step with different halves of its work
+                const bool convert_first = (wave >> 2) != 0;
+                if (convert_first) convert();
+                mfma_step<IN, BM, BN, TM, TN>(acc, sa, sa + Cfg::A_CHUNKS, offa, offb);
+                if (!convert_first) convert();
+                __syncthreads();
+            }
+        }
+    }
+    tile_epilogue<TM, TN, false>(g, acc, I0 + wm0, J0 + wn0, lane);
 }
 
 // Tile and K-part of a workgroup for the plain schedules.
-template <int IN, int BM, int BN, bool FAST>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))) void gemm_tn_kernel(GemmArgs g) {
-    extern __shared__ uint4 smem[];
+template <int IN, int BM, int BN, bool FAST, bool WIDE>
+__device__ __forceinline__ void gemm_tn_workgroup(const GemmArgs& g, uint4* smem) {
     constexpr int BK = InTraits<IN>::BK;
     if (g.gate && *g.gate == 0) return;
     const int64_t tm = (g.M + BM - 1) / BM, tn = (g.N + BN - 1) / BN;
     int64_t ti, tj;
     const int64_t t = blockIdx.x;
-    if (g.tiles == GEMM_TILES_ALL) {
+    if (g.long_first) {                                   // column by column: with K_GE_COL the tiles with the longest K start first
+        ti = t % tm;
+        tj = t / tm;
+    } else if (g.tiles == GEMM_TILES_ALL) {
         ti = t / tn;
         tj = t % tn;
     } else {
@@ -508,7 +671,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
         const int64_t q = t - p * (p + 1) / 2;
         if (g.tiles == GEMM_TILES_LOWER) { ti = p; tj = q; } else { ti = q; tj = p; }
     }
-    (void)tm;
     const int64_t I0 = ti * BM, J0 = tj * BN;
     int64_t k0 = 0;
     if (g.krange == GEMM_K_GE_COL) k0 = (J0 / BK) * BK;
@@ -518,26 +680,20 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
     int64_t kEnd = kBeg + per * BK;
     if (kEnd > g.K) kEnd = g.K;
     if (kBeg >= kEnd && g.epi != GEMM_EPI_STORE) return;
-    tile_body<IN, BM, BN, FAST>(g, I0, J0, kBeg, kEnd, smem);
+    if constexpr (WIDE) tile_body_wide<IN, FAST>(g, I0, J0, kBeg, kEnd, smem);
+    else tile_body<IN, BM, BN, FAST>(g, I0, J0, kBeg, kEnd, smem);
 }
 
-// 256 x 128 tiles, tile columns j and tn - 1 - j of one tile row per workgroup, one after the other:
-// equal work per workgroup when the K range shrinks linearly with the column (B lower triangular).
-template <int IN, bool FAST>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))) void gemm_tn_pair_kernel(GemmArgs g) {
+template <int IN, int BM, int BN, bool FAST>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))) void gemm_tn_kernel(GemmArgs g) {
     extern __shared__ uint4 smem[];
-    constexpr int BK = InTraits<IN>::BK, BM = 256, BN = 128;
-    const int64_t tn = (g.N + BN - 1) / BN, half = (tn + 1) / 2;
-    const int64_t ti = blockIdx.x / half, j0 = blockIdx.x % half;
-#pragma nounroll
-    for (int rep = 0; rep < 2; ++rep) {
-        const int64_t tj = rep ? tn - 1 - j0 : j0;
-        if (rep && tj == j0) break;
-        const int64_t J0 = tj * BN;
-        const int64_t k0 = (g.krange == GEMM_K_GE_COL) ? (J0 / BK) * BK : 0;
-        if (rep) __syncthreads();                        // the first tile's readers are done with the LDS stages
-        tile_body<IN, BM, BN, FAST>(g, ti * BM, J0, k0, g.K, smem);
-    }
+    gemm_tn_workgroup<IN, BM, BN, FAST, false>(g, smem);
+}
+
+template <int IN, bool FAST>
+__global__ __launch_bounds__(kWideThreads) void gemm_tn_wide_kernel(GemmArgs g) {
+    extern __shared__ uint4 smem[];
+    gemm_tn_workgroup<IN, 256, 128, FAST, true>(g, smem);
 }
 
 // True when both operands allow the branch-free 16-byte fetch path.
@@ -552,7 +708,10 @@ template <int IN, int BM, int BN, bool FAST>
 int launch_plain(aser_ctx* ctx, const GemmArgs& g) {
     using Cfg = TileCfg<IN, BM, BN>;
     static bool attr_set[16] = {false};
-    auto kern = gemm_tn_kernel<IN, BM, BN, FAST>;
+    constexpr bool WIDE = BM == 256 && BN == 128;          // see tile_body_wide
+    void (*kern)(GemmArgs);
+    if constexpr (WIDE) kern = gemm_tn_wide_kernel<IN, FAST>;
+    else kern = gemm_tn_kernel<IN, BM, BN, FAST>;
     if (ctx->device >= 0 && ctx->device < 16 && !attr_set[ctx->device]) {
         ASER_HIP(ctx, hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)Cfg::LDS_BYTES));
         attr_set[ctx->device] = true;
@@ -560,27 +719,12 @@ int launch_plain(aser_ctx* ctx, const GemmArgs& g) {
     const int64_t tm = ceil_div64(g.M, BM), tn = ceil_div64(g.N, BN);
     int64_t tiles = (g.tiles == GEMM_TILES_ALL) ? tm * tn : tm * (tm + 1) / 2;
     dim3 grid((unsigned)tiles, (unsigned)g.k_parts, 1);
-    hipLaunchKernelGGL(kern, grid, dim3(kThreads), Cfg::LDS_BYTES, ctx->stream, g);
+    hipLaunchKernelGGL(kern, grid, dim3(WIDE ? kWideThreads : kThreads), Cfg::LDS_BYTES, ctx->stream, g);
     return aser_check_launch(ctx, "gemm_tn");
 }
 
 template <int IN, bool FAST>
-int launch_pair(aser_ctx* ctx, const GemmArgs& g) {
-    using Cfg = TileCfg<IN, 256, 128>;
-    static bool attr_set[16] = {false};
-    auto kern = gemm_tn_pair_kernel<IN, FAST>;
-    if (ctx->device >= 0 && ctx->device < 16 && !attr_set[ctx->device]) {
-        ASER_HIP(ctx, hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)Cfg::LDS_BYTES));
-        attr_set[ctx->device] = true;
-    }
-    const int64_t tm = ceil_div64(g.M, 256), tn = ceil_div64(g.N, 128);
-    hipLaunchKernelGGL(kern, dim3((unsigned)(tm * ((tn + 1) / 2))), dim3(kThreads), Cfg::LDS_BYTES, ctx->stream, g);
-    return aser_check_launch(ctx, "gemm_tn_pair");
-}
-
-template <int IN, bool FAST>
 int dispatch_tile2(aser_ctx* ctx, const GemmArgs& g) {
-    if (g.pair_cols) return launch_pair<IN, FAST>(ctx, g);
     if (g.bm == 256 && g.bn == 256) {
         if constexpr (IN == GEMM_IN_F32X6) {
             ASER_FAIL(ctx, ASER_ERR_INVALID_ARG, "gemm_tn: the six-product form has no 256 x 256 tile (LDS)");
@@ -588,8 +732,9 @@ int dispatch_tile2(aser_ctx* ctx, const GemmArgs& g) {
             return launch_plain<IN, 256, 256, FAST>(ctx, g);
         }
     }
-    if (g.bm == 128 && g.bn == 256) return launch_plain<IN, 128, 256, FAST>(ctx, g);
-    if (g.bm == 256 && g.bn == 128) return launch_plain<IN, 256, 128, FAST>(ctx, g);
+    if constexpr (IN != GEMM_IN_BF16) {
+        if (g.bm == 256 && g.bn == 128) return launch_plain<IN, 256, 128, FAST>(ctx, g);
+    }
     if (g.bm == 128 && g.bn == 128) return launch_plain<IN, 128, 128, FAST>(ctx, g);
     ASER_FAIL(ctx, ASER_ERR_INVALID_ARG, "gemm_tn: unsupported tile %dx%d", g.bm, g.bn);
 }
@@ -960,8 +1105,7 @@ int aser_gemm_tn(aser_ctx* ctx, const GemmArgs& g) {
     if (g.tiles != GEMM_TILES_ALL && (g.M != g.N || g.bm != g.bn))
         ASER_FAIL(ctx, ASER_ERR_INVALID_ARG, "gemm_tn: triangular tiling needs a square problem and tile");
     if (g.Ct && g.epi != GEMM_EPI_STORE) ASER_FAIL(ctx, ASER_ERR_INVALID_ARG, "gemm_tn: Ct needs the store epilogue");
-    if (g.pair_cols && (g.tiles != GEMM_TILES_ALL || g.k_parts != 1 || g.bm != 256 || g.bn != 128))
-        ASER_FAIL(ctx, ASER_ERR_INVALID_ARG, "gemm_tn: paired tile columns need all tiles, k_parts == 1 and 256 x 128 tiles");
+    if (g.long_first && g.tiles != GEMM_TILES_ALL) ASER_FAIL(ctx, ASER_ERR_INVALID_ARG, "gemm_tn: this tile order needs all tiles");
     if (g.epi == GEMM_EPI_RESID && (!g.sumsq || g.k_parts != 1 || g.bm != 128 || g.bn != 128))
         ASER_FAIL(ctx, ASER_ERR_INVALID_ARG, "gemm_tn: the residual epilogue needs sumsq, k_parts == 1 and 128 x 128 tiles");
     if (g.in_type == GEMM_IN_BF16) return dispatch_tile<GEMM_IN_BF16>(ctx, g);

@@ -278,10 +278,9 @@ extern "C" int aser_error_reconstruct_enqueue(aser_ctx* ctx, const float* T, int
         g.M = m; g.N = n; g.K = n; g.alpha = 1.f;
         g.in_type = form; g.epi = GEMM_EPI_STORE; g.tiles = GEMM_TILES_ALL; g.krange = GEMM_K_GE_COL;
         g.k_parts = 1;
-        // S is lower triangular, so the K range of a tile shrinks with its column: pairing column j with
-        // column tn - 1 - j gives every workgroup the same work
-        g.pair_cols = (m > 1024 && n > 1024) ? 1 : 0;
-        g.bm = g.pair_cols ? 256 : 128; g.bn = 128;
+        // S is lower triangular, so the K range of a tile shrinks with its column
+        g.long_first = 1;
+        g.bm = (m > 1024 && n > 1024) ? 256 : 128; g.bn = 128;
         ASER_TRY(aser_gemm_tn(ctx, g));
     }
     // two clearing passes for everything that must start at zero: the scalars (lambda .. cluster share
@@ -308,7 +307,10 @@ extern "C" int aser_error_reconstruct_enqueue(aser_ctx* ctx, const float* T, int
         }
     }
     ASER_TRY(chol_qr(ctx, form, Qacc, Qcur, m, 0, b, Mb, Rq_inv, info));                 // Q_0
-    const int bmA = 128, bnB = 128;
+    // the products with A: tiles of 256 rows on eight wavefronts from 8192 rows on (reconstruction of 4096 x 11008: 5.21 -> 5.04 ms;
+    // of 4096 x 4096 with 256 rows throughout: 2.19 -> 2.31)
+    auto bm = [](int64_t rows) { return rows >= 8192 ? 256 : 128; };
+    const int bnB = 128;
     int done = 0;                                        // subspace iterations so far
     auto iterate = [&](int count) -> int {
         for (int c = 0; c < count; ++c, ++done) {
@@ -318,14 +320,14 @@ extern "C" int aser_error_reconstruct_enqueue(aser_ctx* ctx, const float* T, int
             // with a wide spread the columns of Zt R~^-1 for a stale R~ drift apart faster than the next
             // Cholesky-QR tolerates), otherwise the previous iteration's factor serves and both kernels return at once
             const int* gate = (done < 3 || (done & 1) == 0) ? nullptr : gate_dev;
-            ASER_TRY(gemm_tn_atomic(ctx, form, A, n, Qcur, b, Zt, b, n, b, m, bmA, bnB, false));    // Zt = A^T Q_k
+            ASER_TRY(gemm_tn_atomic(ctx, form, A, n, Qcur, b, Zt, b, n, b, m, bm(n), bnB, false));  // Zt = A^T Q_k
             {
                 GemmArgs gz = atomic_args(ctx->share, form, Zt, b, Zt, b, Mb, b, b, b, n, 128, 128, /*upper_only=*/true);
                 gz.gate = gate;
                 ASER_TRY(aser_gemm_tn(ctx, gz));
                 ASER_TRY(aser_chol_block(ctx, Mb, b, b, Rz_inv, info, kPivotBase, /*clear_d=*/true, nullptr, nullptr, beta_dev, gate));
             }
-            ASER_TRY(gemm_tn_atomic(ctx, form, At, m, Zt, b, Qraw, b, m, b, n, bmA, bnB, false));   // A Zt
+            ASER_TRY(gemm_tn_atomic(ctx, form, At, m, Zt, b, Qraw, b, m, b, n, bm(m), bnB, false)); // A Zt
             // (A Zt + beta' Q_{k-1} P_k) R~^-1; Qraw and Zt are zero again afterwards
             ASER_TRY(aser_combine_f32(ctx, Qraw, Rz_inv, it ? Qold : nullptr, Pm, beta_dev, Qacc, m, b, Zt, n));
             // = Q_{k+1} R_q, into the old block; also P_{k+1} = R~^-1 R_q^-1
@@ -339,7 +341,7 @@ extern "C" int aser_error_reconstruct_enqueue(aser_ctx* ctx, const float* T, int
         ASER_TRY(chol_qr(ctx, form, Qcur, Qacc, m, 0, b, Mb, Rq_inv, info));                 // second pass: orthonormal to fp32
         float* Qp = Qacc;
         // Rayleigh-Ritz: Z = A^T Q, eigen-pairs of Z^T Z = Q^T A A^T Q
-        ASER_TRY(gemm_tn_atomic(ctx, form, A, n, Qp, b, Zt, b, n, b, m, bmA, bnB, false));
+        ASER_TRY(gemm_tn_atomic(ctx, form, A, n, Qp, b, Zt, b, n, b, m, bm(n), bnB, false));
         float* Zp = Zt;
         float* tp = Qraw;
         ASER_TRY(gemm_tn_atomic(ctx, form, Zp, b, Zp, b, Mb, b, b, b, n, 128, 128, false));
@@ -366,7 +368,7 @@ extern "C" int aser_error_reconstruct_enqueue(aser_ctx* ctx, const float* T, int
         // L_A = Q (Uhat_r Sigma_r)
         ASER_TRY(aser_gemm_small_f32(ctx, Qp, b, WA, r, L_A, r, m, b, r));
         // L_B^T = (T^T Q) (Uhat_r Sigma_r^-1)  ->  L_B
-        ASER_TRY(gemm_tn_atomic(ctx, form, T, ldt, Qp, b, Zp, b, n, b, m, bmA, bnB, true));  // C^T = T^T Q (n x b)
+        ASER_TRY(gemm_tn_atomic(ctx, form, T, ldt, Qp, b, Zp, b, n, b, m, bm(n), bnB, true));  // C^T = T^T Q (n x b)
         return aser_gemm_small_f32(ctx, Zp, b, WBt, r, L_B, n, n, b, r, 0, true);            // (n x r)^T = L_B
     };
     ASER_TRY(iterate(p.iters));

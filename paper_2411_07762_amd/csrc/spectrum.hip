@@ -909,8 +909,8 @@ int aser_exact_reconstruct(aser_ctx* ctx, const float* T, int64_t m, int64_t n, 
         g.M = m; g.N = n; g.K = n; g.alpha = 1.f;
         g.in_type = aser_f32_form(ctx, m * n); g.epi = GEMM_EPI_STORE; g.tiles = GEMM_TILES_ALL; g.krange = GEMM_K_GE_COL;
         g.k_parts = 1;
-        g.pair_cols = (m > 1024 && n > 1024) ? 1 : 0;
-        g.bm = g.pair_cols ? 256 : 128; g.bn = 128;
+        g.long_first = 1;
+        g.bm = (m > 1024 && n > 1024) ? 256 : 128; g.bn = 128;
         ASER_TRY(aser_gemm_tn(ctx, g));
         A32 = A;
         if (left) ASER_TRY(gram_f64<float>(ctx, At, n, k, m, B));
@@ -1012,8 +1012,8 @@ extern "C" int aser_singular_values(aser_ctx* ctx, const float* T, int64_t m, in
         g.M = m; g.N = n; g.K = n; g.alpha = 1.f;
         g.in_type = aser_f32_form(ctx, m * n); g.epi = GEMM_EPI_STORE; g.tiles = GEMM_TILES_ALL; g.krange = GEMM_K_GE_COL;
         g.k_parts = 1;
-        g.pair_cols = (m > 1024 && n > 1024) ? 1 : 0;
-        g.bm = g.pair_cols ? 256 : 128; g.bn = 128;
+        g.long_first = 1;
+        g.bm = (m > 1024 && n > 1024) ? 256 : 128; g.bn = 128;
         ASER_TRY(aser_gemm_tn(ctx, g));
         if (m <= n) { P = At; ldp = m; K = n; } else { P = A; ldp = n; K = m; }
     } else if (m <= n) {

@@ -131,7 +131,8 @@ extern "C" int aser_whiten(aser_ctx* ctx, const float* G, int64_t ldg, int64_t n
     // Wide matrices take the long-K update for two block rows at a time (256 x 256 tiles convert each
     // fp32 operand element once per 256 instead of 128 result columns or rows); the second block row of
     // a pair then still lacks the contribution of the first, a K = 128 update of its own.
-    const bool pairs = n >= 12288;   // measured: 11008 columns are still faster one block row at a time
+    // measured (ms, one block row at a time / in pairs): 11008 columns 6.3 / 7.2, 14336 9.7 / 10.4, 20480 21.1 / 19.6, 28672 47.7 / 40.1
+    const bool pairs = n >= 16384;
     const int form = aser_f32_form(ctx, n * n);   // three or six bf16 products per fp32 product
     const bool six = form == GEMM_IN_F32X6;
     auto update = [&](int64_t row0, int64_t rows, int64_t kfrom, int64_t klen, int bm, int bn) -> int {
@@ -156,7 +157,7 @@ extern "C" int aser_whiten(aser_ctx* ctx, const float* G, int64_t ldg, int64_t n
                 ASER_TRY(update(k0, b, k0 - kNb, kNb, 128, 128));   // K = 128 only, as the row panel: many small tiles
             }
         } else if (k0 > 0) {
-            ASER_TRY(update(k0, b, 0, k0, 128, (n - k0 >= 4096) ? 256 : 128));
+            ASER_TRY(update(k0, b, 0, k0, 128, 128));
         }
         ASER_TRY(aser_chol_block(ctx, D, lds, b, Rinv, info_dev, (int32_t)k0));
         const int64_t rem = n - k0 - b;

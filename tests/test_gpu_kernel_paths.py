@@ -151,3 +151,30 @@ def test_outlier_selection_with_many_ties(n, f):
         ctx.check(call(ctx, torch.from_numpy(W).to(DEV), torch.from_numpy(abs_sum).to(DEV), torch.tensor([8], dtype=torch.int64, device=DEV), f, idx, mdiag))
         assert np.array_equal(idx.cpu().numpy(), ref.idx)
         assert np.array_equal(mdiag.cpu().numpy(), ref.mdiag)
+
+
+@pytest.mark.parametrize("m,n", [(8200, 1100), (8193, 1027), (1025, 8201), (1100, 1028)])
+def test_reconstruction_at_the_borders_of_its_tiles(m, n):
+    """Sizes around the rules that pick the 256-row tiles (1024 and 8192 rows), with and without 16-byte rows: the bars of the
+    other reconstruction tests (error 1e-4, product 1e-3; the gap behind the planted directions is far above 1.05)."""
+    rng = np.random.default_rng([m, n])
+    r = f = 8
+    idx = np.sort(rng.choice(n, f, replace=False)).astype(np.int32)
+    T = (rng.random((m, n), dtype=np.float32) - 0.5) * 0.02
+    T[:, idx] = rng.standard_normal((m, f)).astype(np.float32) * 0.05
+    S = np.tril(rng.standard_normal((n, n)).astype(np.float32), -1) * 0.3
+    np.fill_diagonal(S, 20.0 + rng.random(n, dtype=np.float32))
+    ref = orc.error_reconstruct(T.astype(np.float64), S.astype(np.float64), r)
+    assert ref.gap > 1.05
+    ctx = new_ctx()
+    ctx.ensure_workspace(aser.aser_workspace_bytes(m, n, r))
+    L_A = torch.empty((m, r), dtype=torch.float32, device=DEV)
+    L_B = torch.empty((r, n), dtype=torch.float32, device=DEV)
+    sigma = torch.empty(r, dtype=torch.float32, device=DEV)
+    st, err, _ = aser.aser_error_reconstruct(ctx, torch.from_numpy(T).to(DEV), torch.from_numpy(S).to(DEV), r, L_A, L_B, sigma,
+                                             idx=torch.from_numpy(idx).to(DEV), f=f)
+    ctx.check(st)
+    assert abs(err - ref.err) <= 1e-4 * ref.err
+    want = ref.L_A @ ref.L_B
+    got = L_A.double().cpu().numpy() @ L_B.double().cpu().numpy()
+    assert np.linalg.norm(got - want) <= 1e-3 * np.linalg.norm(want)
