@@ -287,10 +287,223 @@ __global__ __launch_bounds__(kTriThreads) void tridiag_step_kernel(TridiagStep a
     }
 }
 
+// Sum over the wavefront by lane-shifted additions; every lane returns it.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double shifted(double v) {
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)u, CTRL, ROWS, 0xf, false);
+    const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(u >> 32), CTRL, ROWS, 0xf, false);
+    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+__device__ __forceinline__ double lane_value(double v, int lane) {       // lane: the same in the whole wavefront
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)u, lane), hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(u >> 32), lane);
+    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+__device__ __forceinline__ double wave_sum(double v) {
+    v += shifted<0x111, 0xf>(v);                          // within rows of 16 lanes: 1, 2, 4, 8 to the right
+    v += shifted<0x112, 0xf>(v);
+    v += shifted<0x114, 0xf>(v);
+    v += shifted<0x118, 0xf>(v);
+    v += shifted<0x142, 0xa>(v);                          // the last lane of rows 0 and 2 to rows 1 and 3
+    v += shifted<0x143, 0xc>(v);                          // the last lane of row 1 to rows 2 and 3
+    return lane_value(v, 63);
+}
+
 __device__ __forceinline__ double rcp_f64(double q) {          // full precision: hardware estimate and two Newton steps
     double r = __builtin_amdgcn_rcp(q);
     r = fma(fma(-q, r, 1.0), r, r);
     return fma(fma(-q, r, 1.0), r, r);
+}
+
+// The rest of the chain in one workgroup once at most 256 rows and columns are left, with at most one pair pending.  They are
+// numbered so that the last one is 255.  Wavefront w owns the rows w + 16 q and lane l the columns l + 64 t, so that an
+// element always belongs to the same thread, and nothing but the reflectors that the caller asked for leaves the
+// compute unit: everything behind row and column 63 is in registers, the first 64 rows in LDS (half of their corner in
+// registers too; their mirror image is not kept).  By symmetry p_j = sum_i B_ij vn_i: sums over a thread's
+// rows without lane exchange, where the entries of vn, v and w that go with a row are LDS broadcasts; of the rows in LDS
+// also their product with vn, for the columns of their mirror image.  The first wavefront alone forms w and the next
+// reflector, without a barrier inside; its 350 instructions, issued every 7 cycles or so, are most of the 1.8 us that a step
+// costs below 100 rows (2.3 at 192, 4.4 at 256).  A launch per column is 7.7 us: the chain of k = 256, 1960 us -> 715.
+// Kept in B instead of LDS, the first 64 rows and columns made it 970.
+constexpr int kTailRows = 256, kTailWaves = 16, kTailMem = 64;
+__device__ __forceinline__ void lds_barrier() {           // leaves stores to memory on their way
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+__device__ __forceinline__ double pick(double x0, double x1, double x2, double x3, int j) {       // entry j of a vector
+    const int t = j >> 6;
+    return lane_value(t == 0 ? x0 : (t == 1 ? x1 : (t == 2 ? x2 : x3)), j & 63);
+}
+__global__ __launch_bounds__(64 * kTailWaves) void tridiag_tail_kernel(TridiagStep a) {
+    constexpr int Q = kTailRows / kTailWaves, T = kTailRows / 64, Q0 = kTailMem / kTailWaves, T0 = kTailMem / 64;
+    constexpr int kLow = kTailRows - kTailMem;
+    static_assert(T == 4 && T0 == 1, "pick, the corner");
+    extern __shared__ double low[];                       // [kTailMem][kLow]
+    __shared__ double2 vw[kTailRows];
+    __shared__ double rowdot[kTailMem], nv[kTailRows], part[kTailWaves][kTailRows], rowbuf[kTailRows], diag[kTailRows], off[kTailRows],
+        taus[kTailRows], corner, tau_s;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t k = a.k;
+    const int first = kTailRows - (int)(k - a.c0);        // 0 .. kTailRows - 2; row i here is row i + base of the matrix
+    const int64_t base = a.c0 - first;
+    const double* const Bo = a.B + base * k + base;       // entries from `first` on only
+    double* const low0 = low + kTailMem * kLow + tid;     // [Q0 / 2][threads]
+    double corner0[Q0 / 2], m[Q - Q0][T - T0];
+#pragma unroll
+    for (int q = Q0; q < Q; ++q)
+#pragma unroll
+        for (int t = T0; t < T; ++t) {
+            const int i = wave + kTailWaves * q, j = lane + 64 * t;
+            m[q - Q0][t - T0] = (i >= first && j >= first) ? Bo[i * k + j] : 0.0;
+        }
+#pragma unroll
+    for (int q = 0; q < Q0; ++q) {
+        const int i = wave + kTailWaves * q;
+        const double x0 = (i >= first && lane >= first) ? Bo[i * k + lane] : 0.0;
+        if (q < Q0 / 2) corner0[q] = x0;
+        else low0[(q - Q0 / 2) * 64 * kTailWaves] = x0;
+        if (i >= first)
+#pragma unroll
+            for (int t = T0; t < T; ++t) low[i * kLow + lane + 64 * (t - T0)] = Bo[i * k + lane + 64 * t];
+    }
+    // the loads are over here: without this the compiler waits for all memory before every use of an element
+#pragma unroll
+    for (int q = 0; q < Q0 / 2; ++q) asm volatile("" : "+v"(corner0[q]));
+#pragma unroll
+    for (int q = 0; q < Q - Q0; ++q)
+#pragma unroll
+        for (int t = 0; t < T - T0; ++t) asm volatile("" : "+v"(m[q][t]));
+    if (tid < kTailRows) {
+        const bool in = tid >= first;
+        nv[tid] = in ? a.vn[base + tid] : 0.0;
+        vw[tid] = (in && a.v[0]) ? make_double2(a.v[0][base + tid], a.w[0][base + tid]) : make_double2(0.0, 0.0);
+        rowbuf[tid] = 0.0;
+    }
+    if (tid == 0) tau_s = *a.tau_cur;
+    __syncthreads();
+
+    for (int c = first;; ++c) {                           // row c: its reflector is nv
+        const bool reflect = c + 2 < kTailRows;
+        double acc[T - T0];
+#pragma unroll
+        for (int t = 0; t < T - T0; ++t) acc[t] = 0.0;
+        if (c < kTailMem) {
+            double acc0 = 0.0;
+#pragma unroll
+            for (int q = 0; q < Q0; ++q) {
+                const int i = wave + kTailWaves * q;
+                if (i < c) continue;
+                asm volatile("" ::: "memory");            // nothing of another row is read ahead: the registers are full
+                const double2 r = vw[i], u0 = vw[lane];
+                const double n = nv[i];
+                double& x0 = q < Q0 / 2 ? corner0[q] : low0[(q - Q0 / 2) * 64 * kTailWaves];
+                const double y0 = x0 - (r.x * u0.y + r.y * u0.x);
+                x0 = y0;
+                acc0 = fma(y0, n, acc0);
+                if (i == c) rowbuf[lane] = y0;
+                double dot = 0.0;
+#pragma unroll
+                for (int t = T0; t < T; ++t) {
+                    const int j = lane + 64 * t;
+                    double* const at = low + i * kLow + j - kTailMem;
+                    const double2 u = vw[j];
+                    const double x = *at - (r.x * u.y + r.y * u.x);
+                    *at = x;
+                    acc[t - T0] = fma(x, n, acc[t - T0]);
+                    dot = fma(x, nv[j], dot);
+                    if (i == c) rowbuf[j] = x;
+                }
+                dot = wave_sum(dot);
+                if (lane == 0) rowdot[i] = dot;
+            }
+            part[wave][lane] = acc0;
+            asm volatile("" ::: "memory");
+        }
+        double2 u[T - T0];
+#pragma unroll
+        for (int t = T0; t < T; ++t) u[t - T0] = vw[lane + 64 * t];
+#pragma unroll
+        for (int q = Q0; q < Q; ++q) {
+            const int i = wave + kTailWaves * q;
+            if (i < c) continue;
+            const double2 r = vw[i];
+            const double n = nv[i];
+#pragma unroll
+            for (int t = 0; t < T - T0; ++t)
+                if (64 * (t + T0) + 63 >= c) {
+                    double& x = m[q - Q0][t];
+                    x -= r.x * u[t].y + r.y * u[t].x;
+                    acc[t] = fma(x, n, acc[t]);
+                    if (i == c) rowbuf[lane + 64 * (t + T0)] = x;
+                }
+        }
+        if (!reflect && tid == 64 * kTailWaves - 1) corner = m[Q - Q0 - 1][T - T0 - 1];
+#pragma unroll
+        for (int t = T0; t < T; ++t) part[wave][lane + 64 * t] = acc[t - T0];
+        lds_barrier();
+        {
+            const int j = tid & (kTailRows - 1), g = 4 * (tid / kTailRows);
+            part[g][j] = (part[g][j] + part[g + 1][j]) + (part[g + 2][j] + part[g + 3][j]);
+        }
+        lds_barrier();
+        if (wave == 0) {
+            double p[T], vn[T], dot = 0.0, tau = tau_s;
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                const int j = lane + 64 * t;
+                vn[t] = nv[j];
+                p[t] = (part[0][j] + part[4][j]) + (part[8][j] + part[12][j]);
+                if (t == 0) p[t] += rowdot[j];
+                p[t] = j < c ? 0.0 : p[t];
+                dot = fma(p[t], vn[t], dot);
+            }
+            const double v_row = nv[c], p_row = pick(p[0], p[1], p[2], p[3], c);
+            dot = wave_sum(dot);
+            const double kk = 0.5 * tau * tau * dot, w_row = tau * p_row - kk * v_row;
+            double w[T], x[T], n2 = 0.0;
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                const int j = lane + 64 * t;
+                w[t] = tau * p[t] - kk * vn[t];
+                x[t] = rowbuf[j] - (v_row * w[t] + w_row * vn[t]);
+                if (j == c) diag[c] = x[t];
+                x[t] = j <= c ? 0.0 : x[t];
+                n2 = fma(x[t], x[t], n2);
+            }
+            if (!reflect) {                               // the last 2 x 2 block: no reflector
+                if (lane == 63) {
+                    off[c] = x[T - 1];
+                    diag[c + 1] = corner - 2.0 * vn[T - 1] * w[T - 1];
+                }
+            } else {
+                n2 = wave_sum(n2);
+                const double x0 = pick(x[0], x[1], x[2], x[3], c + 1), alpha = (x0 > 0.0) ? -sqrt(n2) : sqrt(n2);
+                const double v0 = x0 - alpha, vn2 = n2 - x0 * x0 + v0 * v0;
+                tau = vn2 > 0.0 ? 2.0 * rcp_f64(vn2) : 0.0;
+#pragma unroll
+                for (int t = 0; t < T; ++t) {
+                    const int j = lane + 64 * t;
+                    vw[j] = make_double2(vn[t], w[t]);
+                    vn[t] = j == c + 1 ? v0 : x[t];
+                    nv[j] = vn[t];
+                    if (a.vstore && j > c) a.vstore[(base + c) * k + base + j] = vn[t];
+                }
+                if (lane == 0) {
+                    off[c] = alpha;
+                    taus[c] = tau_s = tau;
+                }
+            }
+        }
+        lds_barrier();
+        if (!reflect) break;
+    }
+    if (tid >= first && tid < kTailRows) {
+        a.d[base + tid] = diag[tid];
+        if (tid + 1 < kTailRows) a.e[base + tid] = off[tid];
+        if (a.vstore && tid + 2 < kTailRows) a.taustore[base + tid] = taus[tid];
+    }
 }
 
 // Every eigenvalue of the symmetric tridiagonal matrix (d, e) by multisection on Sturm counts: the count of x (number of
@@ -481,7 +694,7 @@ void launch_tridiag_step(aser_ctx* ctx, int pairs, const TridiagStep& a) {
     }
 }
 
-// Householder chain on B (overwritten), one launch per column.
+// Householder chain on B (overwritten), one launch per column and one for the last 256.
 // vec: eight zeroed arrays of k doubles; d = vec[4], e = vec[5] on return, vec[7] and the first ten rows of B are scratch.
 // vstore (k x k) / taustore (k), both zeroed by the caller, receive the reflectors when not null.
 int tridiagonalize(aser_ctx* ctx, double* B, int64_t k, double* const* vec, double* vstore, double* taustore) {
@@ -503,8 +716,15 @@ int tridiagonalize(aser_ctx* ctx, double* B, int64_t k, double* const* vec, doub
         for (int64_t q = 0; q < pending; ++q) { a.v[q] = v_of(s - pending + q); a.w[q] = w_of(s - pending + q); }
         a.vn = v_of(s); a.wn = w_of(s); a.vnext = v_of(s + 1);
         a.tau_cur = tau + (s & 1); a.tau_next = tau + ((s + 1) & 1);
+        if (k - a.c0 <= kTailRows && pending <= 1) {       // what the registers and the LDS of one compute unit hold
+            if (pending == 0) a.v[0] = a.w[0] = nullptr;
+            constexpr int lds = (kTailMem * (kTailRows - kTailMem) + kTailMem * kTailMem / 2) * 8;
+            ASER_HIP(ctx, hipFuncSetAttribute((const void*)tridiag_tail_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+            hipLaunchKernelGGL(tridiag_tail_kernel, dim3(1), dim3(64 * kTailWaves), lds, ctx->stream, a);
+            return aser_check_launch(ctx, "tridiag_tail");
+        }
         // deferring the update pays where the traffic is what a pass costs.  Whole spectra in ms with 1 / 2 / 4 pairs pending at
-        // most: k = 256 2.13 / 2.19 / 2.35, 1024 10.60 / 10.63 / 11.31, 2048 27.3 / 26.2 / 27.2, 4096 101 / 90 / 88
+        // most: k = 1024 10.60 / 10.63 / 11.31, 2048 27.3 / 26.2 / 27.2, 4096 101 / 90 / 88
         const int64_t rest = k - a.c0, most = rest >= 2048 ? kTriPairs : (rest >= 1024 ? 2 : 1);
         if (pending > 0 && (pending >= most || s < kFirst + 1)) {
             launch_tridiag_step<true>(ctx, (int)pending, a);

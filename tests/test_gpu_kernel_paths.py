@@ -102,6 +102,20 @@ def test_eigenvalues_at_the_borders_of_the_multisection(k):
         assert r == orc.rank_from_alpha(out.cpu().numpy(), alpha)
 
 
+@pytest.mark.parametrize("k", [1, 2, 3, 4, 17, 63, 64, 65, 66, 128, 129, 193, 200, 255, 256, 257, 258, 259, 267, 268, 270, 330, 513])
+def test_eigenvalues_of_matrices_that_end_in_one_workgroup(k):
+    """Full matrices: the squares within the backward error of the Gram product and of the Householder chain, O(k) roundings of
+    the largest (factor 16), against numpy's SVD of the same values in fp64."""
+    rng = np.random.default_rng(k)
+    A = (rng.standard_normal((k + 5, k)) * np.exp(rng.uniform(-3, 3, k))[None, :]).astype(np.float32)
+    out = torch.empty(k, dtype=torch.float64, device=DEV)
+    ctx = new_ctx()
+    ctx.ensure_workspace(aser.aser_spectrum_workspace_bytes(k + 5, k, False))
+    ctx.check(aser.aser_singular_values(ctx, torch.from_numpy(A).to(DEV), None, out))
+    want = np.linalg.svd(A.astype(np.float64), compute_uv=False)
+    assert np.max(np.abs(out.cpu().numpy() ** 2 - want ** 2)) <= 16 * k * 2.0 ** -52 * want[0] ** 2
+
+
 @pytest.mark.parametrize("rows,n,m,r,bits,x_dtype,act_bits,pad", [
     (1, 32, 1, 1, 4, "bf16", 8, 0), (65, 100, 70, 9, 4, "bf16", 8, 0), (130, 96, 260, 0, 8, "bf16", 0, 8), (300, 1000, 65, 64, 8, "f32", 6, 0),
     (64, 1026, 200, 33, 4, "f32", 0, 2), (257, 320, 129, 16, 8, "bf16", 8, 1), (1700, 224, 1800, 8, 4, "bf16", 8, 0),
