@@ -373,7 +373,15 @@ struct EvalPlan {
     size_t off_whi, off_wlo, off_vhi, off_vlo, off_xhi, off_xlo, off_cq, off_codes, off_scales, off_scal, total;
 };
 
-void eval_plan(int64_t m, int64_t n, int64_t rows, EvalPlan* p) {
+// The size asked for stays what it was when the operands and one output were kept in fp32 (two m x n, two rows x n, a rows x m and
+// an r x m array), which is more than the planes take unless n is short of a multiple of 32 and rows are few: callers
+// that bind a workspace for it, and what is refused for want of one, do not change.
+size_t eval_fp32_bytes(int64_t m, int64_t n, int64_t rows, int r) {
+    return 2 * align_up((size_t)m * n * 4, 256) + 2 * align_up((size_t)rows * n * 4, 256) + align_up((size_t)rows * m * 4, 256) +
+           align_up((size_t)(r > 0 ? r : 1) * m * 4, 256) + align_up((size_t)rows * n, 256) + align_up((size_t)rows * 4, 256) + 256;
+}
+
+void eval_plan(int64_t m, int64_t n, int64_t rows, int r, EvalPlan* p) {
     p->np = (n + 31) / 32 * 32;
     size_t off = 0;
     const size_t wp = align_up((size_t)m * p->np * 2, 256), xp = align_up((size_t)rows * p->np * 2, 256);
@@ -387,7 +395,8 @@ void eval_plan(int64_t m, int64_t n, int64_t rows, EvalPlan* p) {
     p->off_codes = off; off += align_up((size_t)rows * n, 256);
     p->off_scales = off; off += align_up((size_t)rows * 4, 256);
     p->off_scal = off; off += 256;
-    p->total = off;
+    const size_t fp32_bytes = eval_fp32_bytes(m, n, rows, r);
+    p->total = off > fp32_bytes ? off : fp32_bytes;
 }
 
 }  // namespace
@@ -395,7 +404,7 @@ void eval_plan(int64_t m, int64_t n, int64_t rows, EvalPlan* p) {
 extern "C" size_t aser_output_error_workspace_bytes(int64_t m, int64_t n, int64_t rows, int32_t r) {
     if (m <= 0 || n <= 0 || rows <= 0 || r < 0) return 0;
     EvalPlan p;
-    eval_plan(m, n, rows, &p);
+    eval_plan(m, n, rows, r, &p);
     return p.total + kAserWsTail;
 }
 
@@ -417,7 +426,7 @@ extern "C" int aser_layer_output_error(aser_ctx* ctx, const float* W, int64_t m,
     if (((uintptr_t)W & 3) || ((uintptr_t)scales & 3) || ((uintptr_t)X & (x_dtype == ASER_DTYPE_BF16 ? 1 : 3)))
         ASER_FAIL(ctx, ASER_ERR_INVALID_ARG, "layer_output_error: misaligned pointer");
     EvalPlan pl;
-    eval_plan(m, n, rows, &pl);
+    eval_plan(m, n, rows, r, &pl);
     if (!ctx->ws || ctx->ws_bytes < pl.total + kAserWsTail)
         ASER_FAIL(ctx, ASER_ERR_WORKSPACE, "layer_output_error: workspace too small (%zu needed)", pl.total + kAserWsTail);
     ASER_TRY(aser_prepare_device(ctx));
