@@ -126,8 +126,7 @@ static inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; 
 enum GemmEpi {
     GEMM_EPI_STORE = 0,    // C = alpha * acc            (needs k_parts == 1)
     GEMM_EPI_ATOMIC = 1,   // atomicAdd(C, alpha * acc)  (any k_parts)
-    GEMM_EPI_RMW = 2,      // C += alpha * acc           (needs k_parts == 1, disjoint tiles)
-    GEMM_EPI_RESID = 3     // *sumsq += ||C + alpha * acc||_F^2, C only read (needs k_parts == 1)
+    GEMM_EPI_RESID = 2     // *sumsq += ||C + alpha * acc||_F^2, C only read (needs k_parts == 1)
 };
 enum GemmTiles {
     GEMM_TILES_ALL = 0,    // every BM x BN tile of C
