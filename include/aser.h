@@ -213,7 +213,7 @@ int aser_whiten(aser_ctx* ctx, const float* G, int64_t ldg, int64_t n, const flo
  * (the widest subspace block is 128: tens to hundreds of milliseconds on layers of thousands of channels,
  * against milliseconds for the iteration), take a dense fp64 solver:
  * every eigenvalue of the Gram matrix of the shorter side of T S (Householder tridiagonalisation,
- * bisection), the eigenvectors of the r largest (inverse iteration), *err from the tail of the spectrum;
+ * multisection on Sturm counts), the eigenvectors of the r largest (inverse iteration), *err from the tail of the spectrum;
  * idx, f and the block-width rule do not apply, *n_iter is 0.  Larger layers, and any call with
  * opts->max_iter or opts->block set, run the subspace iteration for a fixed number of iterations
  * (aser_svd_plan reports it) without a residual test: the excess of the whitened error over the optimum
@@ -317,7 +317,7 @@ int aser_svd_plan(int64_t m, int64_t n, int32_t r, const aser_svd_opts* opts, in
  * have the same singular values because S S^T = X X^T).
  * T: m x n fp32 (ldt); S: n x n fp32 lower triangular (lds) or NULL; sigma: DEVICE, min(m, n) doubles.
  * The product T S carries about 2^-16 relative error per term; behind it everything is fp64 (Gram matrix
- * of the shorter side, Householder tridiagonalisation, bisection), so a singular value is off by at most
+ * of the shorter side, Householder tridiagonalisation, multisection), so a singular value is off by at most
  * about 1e-5 of the mean singular value plus 1e-7 of the largest.  min(m, n) <= 16384.
  * Asynchronous.  Needs aser_spectrum_workspace_bytes(m, n, S != NULL) bytes of workspace. */
 size_t aser_spectrum_workspace_bytes(int64_t m, int64_t n, int32_t with_s);

@@ -322,9 +322,10 @@ __device__ __forceinline__ double rcp_f64(double q) {          // full precision
 // compute unit: everything behind row and column 63 is in registers, the first 64 rows in LDS (half of their corner in
 // registers too; their mirror image is not kept).  By symmetry p_j = sum_i B_ij vn_i: sums over a thread's
 // rows without lane exchange, where the entries of vn, v and w that go with a row are LDS broadcasts; of the rows in LDS
-// also their product with vn, for the columns of their mirror image.  The first wavefront alone forms w and the next
-// reflector, without a barrier inside; its 350 instructions, issued every 7 cycles or so, are most of the 1.8 us that a step
-// costs below 100 rows (2.3 at 192, 4.4 at 256).  A launch per column is 7.7 us: the chain of k = 256, 1960 us -> 715.
+// also their product with vn, for the columns of their mirror image.  The first four wavefronts form w and the next
+// reflector, a column per lane: a wavefront issues an instruction every 7 cycles or so, and 150 of them with two more
+// barriers are less than the 350 that one wavefront with four columns per lane needs (k = 256: 715 -> 665 us).  A step costs
+// 1.6 us below 100 rows, 2.1 at 192 and 4.2 at 256; a launch per column is 7.7 us, the chain of k = 256 was 1960 us.
 // Kept in B instead of LDS, the first 64 rows and columns made it 970.
 constexpr int kTailRows = 256, kTailWaves = 16, kTailMem = 64;
 __device__ __forceinline__ void lds_barrier() {           // leaves stores to memory on their way
@@ -332,18 +333,14 @@ __device__ __forceinline__ void lds_barrier() {           // leaves stores to me
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
 }
-__device__ __forceinline__ double pick(double x0, double x1, double x2, double x3, int j) {       // entry j of a vector
-    const int t = j >> 6;
-    return lane_value(t == 0 ? x0 : (t == 1 ? x1 : (t == 2 ? x2 : x3)), j & 63);
-}
 __global__ __launch_bounds__(64 * kTailWaves) void tridiag_tail_kernel(TridiagStep a) {
     constexpr int Q = kTailRows / kTailWaves, T = kTailRows / 64, Q0 = kTailMem / kTailWaves, T0 = kTailMem / 64;
     constexpr int kLow = kTailRows - kTailMem;
-    static_assert(T == 4 && T0 == 1, "pick, the corner");
+    static_assert(T == 4 && T0 == 1, "sums of four wavefronts, the corner");
     extern __shared__ double low[];                       // [kTailMem][kLow]
     __shared__ double2 vw[kTailRows];
     __shared__ double rowdot[kTailMem], nv[kTailRows], part[kTailWaves][kTailRows], rowbuf[kTailRows], diag[kTailRows], off[kTailRows],
-        taus[kTailRows], corner, tau_s;
+        taus[kTailRows], red[2 * T], entry[2], corner, tau_s;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t k = a.k;
     const int first = kTailRows - (int)(k - a.c0);        // 0 .. kTailRows - 2; row i here is row i + base of the matrix
@@ -443,62 +440,58 @@ __global__ __launch_bounds__(64 * kTailWaves) void tridiag_tail_kernel(TridiagSt
 #pragma unroll
         for (int t = T0; t < T; ++t) part[wave][lane + 64 * t] = acc[t - T0];
         lds_barrier();
-        {
-            const int j = tid & (kTailRows - 1), g = 4 * (tid / kTailRows);
-            part[g][j] = (part[g][j] + part[g + 1][j]) + (part[g + 2][j] + part[g + 3][j]);
+        // column j = tid on the first four wavefronts; the others only keep the barriers
+        const bool head = wave < T;
+        double vn = 0.0, p = 0.0, tau = 0.0, v_row = 0.0, w = 0.0, x = 0.0;
+        if (head) {
+            vn = nv[tid];
+            tau = tau_s;
+            v_row = nv[c];
+            double q[4];
+#pragma unroll
+            for (int g = 0; g < 4; ++g) q[g] = (part[4 * g][tid] + part[4 * g + 1][tid]) + (part[4 * g + 2][tid] + part[4 * g + 3][tid]);
+            p = (q[0] + q[1]) + (q[2] + q[3]);
+            if (wave == 0) p += rowdot[lane];
+            p = tid < c ? 0.0 : p;
+            const double dot = wave_sum(p * vn);
+            if (lane == 0) red[wave] = dot;
+            if (tid == c) entry[0] = p;
         }
         lds_barrier();
-        if (wave == 0) {
-            double p[T], vn[T], dot = 0.0, tau = tau_s;
-#pragma unroll
-            for (int t = 0; t < T; ++t) {
-                const int j = lane + 64 * t;
-                vn[t] = nv[j];
-                p[t] = (part[0][j] + part[4][j]) + (part[8][j] + part[12][j]);
-                if (t == 0) p[t] += rowdot[j];
-                p[t] = j < c ? 0.0 : p[t];
-                dot = fma(p[t], vn[t], dot);
+        if (head) {
+            const double dot = (red[0] + red[1]) + (red[2] + red[3]);
+            const double kk = 0.5 * tau * tau * dot, w_row = tau * entry[0] - kk * v_row;
+            w = tau * p - kk * vn;
+            x = rowbuf[tid] - (v_row * w + w_row * vn);
+            if (tid == c) diag[c] = x;
+            x = tid <= c ? 0.0 : x;
+            if (tid == c + 1) entry[1] = x;
+            const double n2 = wave_sum(x * x);
+            if (lane == 0) red[T + wave] = n2;
+        }
+        if (!reflect) {                                   // the last 2 x 2 block: no reflector
+            if (tid == kTailRows - 1) {
+                off[c] = x;
+                diag[c + 1] = corner - 2.0 * vn * w;
             }
-            const double v_row = nv[c], p_row = pick(p[0], p[1], p[2], p[3], c);
-            dot = wave_sum(dot);
-            const double kk = 0.5 * tau * tau * dot, w_row = tau * p_row - kk * v_row;
-            double w[T], x[T], n2 = 0.0;
-#pragma unroll
-            for (int t = 0; t < T; ++t) {
-                const int j = lane + 64 * t;
-                w[t] = tau * p[t] - kk * vn[t];
-                x[t] = rowbuf[j] - (v_row * w[t] + w_row * vn[t]);
-                if (j == c) diag[c] = x[t];
-                x[t] = j <= c ? 0.0 : x[t];
-                n2 = fma(x[t], x[t], n2);
-            }
-            if (!reflect) {                               // the last 2 x 2 block: no reflector
-                if (lane == 63) {
-                    off[c] = x[T - 1];
-                    diag[c + 1] = corner - 2.0 * vn[T - 1] * w[T - 1];
-                }
-            } else {
-                n2 = wave_sum(n2);
-                const double x0 = pick(x[0], x[1], x[2], x[3], c + 1), alpha = (x0 > 0.0) ? -sqrt(n2) : sqrt(n2);
-                const double v0 = x0 - alpha, vn2 = n2 - x0 * x0 + v0 * v0;
+            break;
+        }
+        lds_barrier();
+        if (head) {
+            const double n2 = (red[T] + red[T + 1]) + (red[T + 2] + red[T + 3]), x0 = entry[1], alpha = (x0 > 0.0) ? -sqrt(n2) : sqrt(n2);
+            const double v0 = x0 - alpha, vn2 = n2 - x0 * x0 + v0 * v0, next = tid == c + 1 ? v0 : x;
+            vw[tid] = make_double2(vn, w);
+            nv[tid] = next;
+            if (a.vstore && tid > c) a.vstore[(base + c) * k + base + tid] = next;
+            if (tid == 0) {
                 tau = vn2 > 0.0 ? 2.0 * rcp_f64(vn2) : 0.0;
-#pragma unroll
-                for (int t = 0; t < T; ++t) {
-                    const int j = lane + 64 * t;
-                    vw[j] = make_double2(vn[t], w[t]);
-                    vn[t] = j == c + 1 ? v0 : x[t];
-                    nv[j] = vn[t];
-                    if (a.vstore && j > c) a.vstore[(base + c) * k + base + j] = vn[t];
-                }
-                if (lane == 0) {
-                    off[c] = alpha;
-                    taus[c] = tau_s = tau;
-                }
+                off[c] = alpha;
+                taus[c] = tau_s = tau;
             }
         }
         lds_barrier();
-        if (!reflect) break;
     }
+    lds_barrier();
     if (tid >= first && tid < kTailRows) {
         a.d[base + tid] = diag[tid];
         if (tid + 1 < kTailRows) a.e[base + tid] = off[tid];
