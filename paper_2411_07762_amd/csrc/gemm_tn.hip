@@ -1039,33 +1039,35 @@ int launch_gram_persistent(aser_ctx* ctx, const GemmArgs& g) {
     return launch_gram_persistent2<IN, false>(ctx, g);
 }
 
-// K chunks and left-over split of the LDS-direct schedule for T tiles and `steps` 32-token steps, from a cost in
-// microseconds fitted to a sweep of n = 256 .. 8192 and 256 .. 16384 tokens: 0.87 per step of the busiest
-// workgroup, 5 per tile visit (pipeline fill), 0.2 per tile flush of the whole launch (256 KB of fp32 atomics that
-// share the memory side).  A part of a left-over tile keeps at least four steps, so that the ring is filled once.
+// The LDS-direct schedule for calls of fewer tokens than it needs to fill its rounds by itself: K chunks and split of the
+// left-over tiles, or chunks = 0 where the plain grid of `parts` K parts and `steps64` 64-token steps each is faster.
+// A tile is summed in as many parts as the plain grid's, or up to a third more: fewer make the fp32 chains longer (a
+// call of 7503 tokens of 4096 channels in two chunks instead of seven parts was 40 % further off the fp64 result), more round
+// G more often when a statistic comes in many calls.  Costs in microseconds from sweeps of n = 1536 .. 11008 and 1000 ..
+// 7500 tokens (model within 15 % of every figure).  LDS-direct: 0.87 per 32-token step of the busiest workgroup, 5 per tile
+// visit, 0.14 per 256 x 256 tile flush of the launch (fp32 atomics that share the memory side).  Plain: per round of 256 workgroups 1.9 a
+// step and 24, 0.1 per flush.  Measured, plain -> LDS-direct with this rule: n = 1536: 70 -> 56 at 4000 tokens; n = 4096: 75 -> 70 at 1024,
+// 147 -> 114 at 2000, 177 -> 127 at 3000, 344 -> 315 at 7503 (183 against 191 at 4000: plain); n = 5120: 252 -> 240 at 3750;
+// n = 8192: 434 -> 394 at 3000; n = 11008: 579 -> 484 at 2000.
 struct GramSplit { int chunks, split; };
-GramSplit gram_dma_split(int64_t T, int64_t steps) {
-    GramSplit best{1, 1};
-    double best_cost = -1.0;
+GramSplit gram_dma_split(int64_t T, int64_t steps, int64_t parts, int64_t steps64) {
+    GramSplit best{0, 1};
+    double best_cost = (double)ceil_div64(T * parts, 256) * (1.9 * (double)steps64 + 24.0) + 0.1 * (double)(T * parts);
     for (int c = 1; c <= 8; c *= 2) {
         const int64_t W = 256 / c, full = T / W, rem = T % W, steps_c = ceil_div64(steps, c);
         const int64_t most = rem ? W / rem : 1;
         for (int64_t sp = 1; sp <= most; ++sp) {
+            const int64_t p = full ? c : c * sp;            // parts of most tiles
+            if (p < parts || 3 * p > 4 * parts) continue;
             const int64_t last = rem ? ceil_div64(steps_c, sp) : 0;
-            if (sp > 1 && last < 4) break;
+            if (sp > 1 && last < 4) break;                  // the ring is filled once
             const double flushes = (double)c * (double)(full * W + rem * sp);
-            const double cost = 0.87 * (double)(full * steps_c + last) + 5.0 * (double)(full + (rem ? 1 : 0)) + 0.2 * flushes;
-            if (best_cost < 0.0 || cost < best_cost) { best_cost = cost; best = GramSplit{c, (int)sp}; }
+            const double cost = 0.87 * (double)(full * steps_c + last) + 5.0 * (double)(full + (rem ? 1 : 0)) + 0.14 * flushes;
+            if (cost < best_cost) { best_cost = cost; best = GramSplit{c, (int)sp}; }
         }
     }
     return best;
 }
-
-// Where the LDS-direct schedule beats the plain grid of register-staged tiles.  Measured (us, plain -> LDS-direct):
-// n = 1024: 24 -> 40 at 4096 tokens, 76 -> 75 at 16384; n = 1536: 23 -> 17 at 256, 56 -> 51 at 4096, 141 -> 86 at 16384;
-// n = 4096: 46 -> 43 at 256, 229 -> 131 at 4096, 330 -> 171 at 7503, 392 -> 279 at 16384; n = 8192: 148 -> 160 at 256,
-// 177 -> 169 at 512, 526 -> 348 at 4096.  Up to 1024 channels the plain grid's 128 x 128 tiles split K further.
-bool gram_dma_pays(int64_t n, int64_t rows) { return n > 1024 && rows >= (n > 5120 ? 512 : 256); }
 
 }  // namespace
 
@@ -1101,11 +1103,6 @@ int aser_syrk_gram(aser_ctx* ctx, const void* X, int x_dtype, int64_t rows, int6
     const int64_t ksteps = ceil_div64(rows, bk);
     const int64_t t256 = ceil_div64(n, 256);
     const int64_t T256 = t256 * (t256 + 1) / 2;
-    if (g.in_type == GEMM_IN_BF16 && operands_fast<GEMM_IN_BF16>(g) && gram_dma_pays(n, rows)) {
-        const GramSplit sp = gram_dma_split(T256, ceil_div64(rows, kDmaBK));
-        g.bm = g.bn = 256; g.k_parts = sp.chunks; g.split = sp.split;
-        return launch_gram_dma(ctx, g);
-    }
     if (T256 >= 32 && ksteps >= 8 * 16 && !six) {
         // Number of K chunks: fewest steps on the busiest workgroup, each tile visit charged with
         // the cost of flushing a tile through atomics (about a dozen K steps).
@@ -1120,6 +1117,7 @@ int aser_syrk_gram(aser_ctx* ctx, const void* X, int x_dtype, int64_t rows, int6
         }
         const int64_t W = 256 / best_c, rem = T256 % W;
         g.bm = g.bn = 256; g.k_parts = best_c; g.split = rem ? (int)(W / rem) : 1;
+        if (g.in_type == GEMM_IN_BF16 && operands_fast<GEMM_IN_BF16>(g)) return launch_gram_dma(ctx, g);
         return (g.in_type == GEMM_IN_BF16) ? launch_gram_persistent<GEMM_IN_BF16>(ctx, g)
                                            : launch_gram_persistent<GEMM_IN_F32X3>(ctx, g);
     }
@@ -1129,6 +1127,15 @@ int aser_syrk_gram(aser_ctx* ctx, const void* X, int x_dtype, int64_t rows, int6
     const int64_t max_parts = ksteps / 16 > 0 ? ksteps / 16 : 1;   // keep >= 16 steps per part
     if (parts > max_parts) parts = max_parts;
     if (parts < 1) parts = 1;
+    // up to 1024 channels the plain grid's 128 x 128 tiles split K further (4096 tokens: 24 us against 40), and a few tokens of
+    // wide channels are all flushes (256 of 8192: 148 us against 160)
+    if (n > 1024 && rows >= (n > 5120 ? 512 : 256) && g.in_type == GEMM_IN_BF16 && operands_fast<GEMM_IN_BF16>(g)) {
+        const GramSplit sp = gram_dma_split(T256, ceil_div64(rows, kDmaBK), parts, ceil_div64(ksteps, parts));
+        if (sp.chunks > 0) {
+            g.k_parts = sp.chunks; g.split = sp.split;
+            return launch_gram_dma(ctx, g);
+        }
+    }
     g.k_parts = (int)parts;
     return aser_gemm_tn(ctx, g);
 }
