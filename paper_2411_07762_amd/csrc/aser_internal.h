@@ -163,6 +163,8 @@ int aser_gemm_tn(aser_ctx* ctx, const GemmArgs& g);
 // step; every workgroup adds 0.06 u of atomic traffic that the others wait behind.  More parts shorten
 // the K loop but multiply the atomics, and one workgroup more than 256 doubles the rounds.
 // A part keeps at least min_steps K steps.
+// A step of the 128 x 128 tile has become shorter since the fit (0.5 us); slopes of 0.5 to 0.75 and 0.04 to 0.06 per workgroup give whitenings
+// of 1536 to 11008 columns and reconstructions of 1024 x 4096 to 14336 x 4096 within 1 % of each other, so the constants stand.
 // share > 1: that many layers are in flight on the device (aser_calibrate_layers).  What a launch costs the
 // other layers is the compute-unit time it holds, workgroups x their duration / 256, and every other layer
 // pays it; the cost then is the launch's own duration plus (share - 1) times that.
