@@ -187,7 +187,7 @@ __device__ __forceinline__ int eval_off(int r, int c) { return r * 64 + ((c ^ ((
 template <int TI, int TJ>
 __global__ __launch_bounds__(256) void eval_kernel(EvalArgs g, int tiles_n, int64_t tiles_total) {
     extern __shared__ __align__(16) char smem[];
-    __shared__ float sx[64 * TI];
+    __shared__ float sx[64 * TI], live[64 * TI];          // per row: its scale, 1; 0 past the last row
     constexpr int A_BYTES = 64 * TI * 64, STAGE = A_BYTES + 64 * TJ * 64, NL = TI + TJ;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -196,7 +196,11 @@ __global__ __launch_bounds__(256) void eval_kernel(EvalArgs g, int tiles_n, int6
     const int64_t tile = (int64_t)(blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
     if (tile >= tiles_total) return;
     const int64_t T0 = (tile / tiles_n) * 64 * TI, O0 = (tile % tiles_n) * 64 * TJ;
-    for (int t = tid; t < 64 * TI; t += 256) sx[t] = (T0 + t < g.rows) ? (g.xs ? g.xs[T0 + t] : 1.f) : 0.f;
+    for (int t = tid; t < 64 * TI; t += 256) {
+        const bool in = T0 + t < g.rows;
+        sx[t] = in ? (g.xs ? g.xs[T0 + t] : 1.f) : 0.f;
+        live[t] = in ? 1.f : 0.f;
+    }
 
     // ---- fetch roles: instruction t of this wave is tile rows 16 (NT wave + t) + lane / 4, chunk slot lane % 4
     const int chunk = 16 * ((lane & 3) ^ ((lane >> 4) & 3));
@@ -271,22 +275,20 @@ __global__ __launch_bounds__(256) void eval_kernel(EvalArgs g, int tiles_n, int6
 #pragma unroll
     for (int j = 0; j < TJ; ++j) b0[j] = read(smem, 0, offb[j]);
 
-    // the sum of squares of the accumulators times a factor per row, over the rows and columns that exist
-    auto norm2 = [&](bool scaled) {
+    // the sum of squares, in fp64, of the accumulators times a factor per row (0 past the last row, which those rows repeat)
+    auto norm2 = [&](const float* factor) {
         double sum = 0.0;
 #pragma unroll
         for (int i = 0; i < TI; ++i)
 #pragma unroll
             for (int j = 0; j < TJ; ++j) {
-                const bool in = O0 + wn0 + 32 * j + (lane & 31) < g.m;
-                float part = 0.f;                         // 16 squares of comparable size in fp32, then fp64
+                double part = 0.0;
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
-                    const float s = sx[wm0 + 32 * i + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3)];
-                    const float v = s != 0.f ? acc[i][j][e] * (scaled ? s : 1.f) : 0.f;
-                    part = fmaf(v, v, part);
+                    const double v = (double)acc[i][j][e] * (double)factor[wm0 + 32 * i + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3)];
+                    part = fma(v, v, part);
                 }
-                if (in) sum += (double)part;
+                if (O0 + wn0 + 32 * j + (lane & 31) < g.m) sum += part;
             }
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
@@ -297,14 +299,14 @@ __global__ __launch_bounds__(256) void eval_kernel(EvalArgs g, int tiles_n, int6
         const char* sn = smem + (int)((s + 1) & 3) * STAGE;
         const bool more = s + 1 < nsteps, fetch = s + 3 < nsteps;
         if (s == steps1) {
-            const double y2 = norm2(false);
+            const double y2 = norm2(live);
             if (lane == 0) atomicAdd(g.out, y2);
 #pragma unroll
             for (int i = 0; i < TI; ++i)
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
                     const float sc = sx[wm0 + 32 * i + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3)];
-                    const float f = sc > 1e-30f ? -1.f / sc : 0.f;      // below that both outputs' squares vanish in fp32
+                    const float f = sc >= 1.17549435e-38f ? -1.f / sc : 0.f;      // no reciprocal of a denormal scale (or past the last row)
 #pragma unroll
                     for (int j = 0; j < TJ; ++j) acc[i][j][e] *= f;
                 }
@@ -350,7 +352,7 @@ __global__ __launch_bounds__(256) void eval_kernel(EvalArgs g, int tiles_n, int6
                 __builtin_amdgcn_sched_barrier(0);
             }
     }
-    const double e2 = norm2(true);
+    const double e2 = norm2(sx);
     if (lane == 0) atomicAdd(g.out + 1, e2);
 }
 

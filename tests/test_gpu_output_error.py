@@ -121,3 +121,30 @@ def test_headline_layer_output_error_w4a8():
         assert abs(err - want) <= 2e-4 * want
         res[(act_bits, comp)] = err
     assert res[(8, True)] < res[(8, False)] and res[(6, True)] < res[(6, False)]
+
+
+@pytest.mark.parametrize("rows,m", [(70, 130), (1700, 1800), (2049, 4100)])
+@pytest.mark.parametrize("power,act_bits,x_dtype", [(-100, 8, "bf16"), (-80, 8, "f32"), (66, 8, "bf16"), (66, 0, "f32")])
+def test_norms_of_tiny_and_huge_outputs(rows, m, power, act_bits, x_dtype):
+    """Outputs of about 1e-30, 1e-24 and 1e20, whose squares leave the range of fp32: the sums of squares are fp64, so both norms
+    stay what they are for the same activations at unit scale, times the power of two.  Bars as above."""
+    rng = np.random.default_rng([9, rows, m])
+    n, r = 64, 8
+    W = rng.standard_normal((m, n)).astype(np.float32) * 0.5
+    X = synth.bf16_to_f32(synth.f32_to_bf16_bits(rng.standard_normal((rows, n)).astype(np.float32)))
+    md = np.ones(n, np.float32)
+    md[:3] = 2.5
+    q = orc.quantize_rtn(W * md[None, :], np.zeros(0, np.int32), np.ones(n, np.float32), 4)
+    L_A = rng.standard_normal((m, r)).astype(np.float32) * 0.01
+    L_B = rng.standard_normal((r, n)).astype(np.float32) * 0.05
+    want, ynorm = orc.layer_output_error(W, X, md, q.codes, q.scales, L_A, L_B, act_bits or None)
+    ctx = new_ctx()
+    ctx.ensure_workspace(aser.aser_output_error_workspace_bytes(m, n, rows, r))
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(DEV)
+    Xd = dev(X * np.float32(2.0 ** power)).to(torch.bfloat16 if x_dtype == "bf16" else torch.float32)
+    st, err, ref = aser.aser_layer_output_error(ctx, dev(W), Xd, dev(md), dev(q.codes), aser.ASER_CODES_INT8, dev(q.scales), dev(L_A), dev(L_B),
+                                                r, act_bits)
+    ctx.check(st)
+    err, ref = err * 2.0 ** -power, ref * 2.0 ** -power
+    assert abs(ref - ynorm) <= 1e-5 * ynorm
+    assert abs(err - want) <= 2e-4 * want + 1e-5 * ynorm
