@@ -492,7 +492,8 @@ extern "C" int aser_layer_output_error(aser_ctx* ctx, const float* W, int64_t m,
     double h[2] = {0.0, 0.0};
     ASER_HIP(ctx, hipMemcpyAsync(h, scal, sizeof(h), hipMemcpyDeviceToHost, ctx->stream));
     ASER_HIP(ctx, hipStreamSynchronize(ctx->stream));
-    if (!(h[0] >= 0.0) || !(h[1] >= 0.0)) ASER_FAIL(ctx, ASER_ERR_INVALID_ARG, "layer_output_error: non-finite values in the inputs");
+    // finite outputs give finite sums in fp64; an infinite activation may leave an infinite sum instead of a NaN
+    if (!isfinite(h[0]) || !isfinite(h[1])) ASER_FAIL(ctx, ASER_ERR_INVALID_ARG, "layer_output_error: non-finite values in the inputs");
     *err = sqrt(h[1]);
     if (ref_norm) *ref_norm = sqrt(h[0]);
     return ASER_OK;

@@ -148,3 +148,21 @@ def test_norms_of_tiny_and_huge_outputs(rows, m, power, act_bits, x_dtype):
     err, ref = err * 2.0 ** -power, ref * 2.0 ** -power
     assert abs(ref - ynorm) <= 1e-5 * ynorm
     assert abs(err - want) <= 2e-4 * want + 1e-5 * ynorm
+
+
+@pytest.mark.parametrize("x_dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("act_bits", [0, 8])
+@pytest.mark.parametrize("value", [np.inf, np.nan])
+def test_non_finite_activations_are_refused(value, act_bits, x_dtype):
+    """One infinite or NaN entry; weights and codes of opposite signs, so that an infinite activation moves both outputs of every
+    channel to the same side and no difference of infinities makes it a NaN."""
+    W = torch.full((4, 32), 1.001, device=DEV)
+    codes = torch.full((4, 32), -7, dtype=torch.int8, device=DEV)
+    scales = torch.full((4,), 0.1431, device=DEV)
+    X = torch.ones((3, 32), device=DEV)
+    X[1, 5] = float(value)
+    ctx = new_ctx()
+    ctx.ensure_workspace(aser.aser_output_error_workspace_bytes(4, 32, 3, 0))
+    st, _, _ = aser.aser_layer_output_error(ctx, W, X.to(torch.bfloat16) if x_dtype == "bf16" else X, None, codes, aser.ASER_CODES_INT8, scales, None, None,
+                                            0, act_bits)
+    assert st == aser.ASER_ERR_INVALID_ARG and "non-finite" in ctx.last_error()
