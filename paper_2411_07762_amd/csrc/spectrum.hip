@@ -566,6 +566,7 @@ __global__ __launch_bounds__(256) void tridiag_eigenvalues_kernel(int64_t k, con
                 }
             }
         }
+        if (q != q) cnt = 0;             // a NaN in d or e reaches the last term and would count by its sign; with zeros sigma is 0
         // the count grows with x: the points with cnt <= i are the first p of the group
         const uint64_t below = __builtin_amdgcn_ballot_w64((int64_t)cnt <= i) >> (lane / L * L);
         const int p = __popcll(L == 64 ? below : (below & ((1ull << (L & 63)) - 1)));

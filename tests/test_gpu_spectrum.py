@@ -153,3 +153,22 @@ def test_spectrum_of_known_matrices():
     assert abs(sig[0] - np.linalg.norm(u) * np.linalg.norm(v)) < 1e-5 * sig[0] and np.all(sig[1:] < 1e-5 * sig[0])
     st, er = aser.aser_effective_rank(ctx, torch.from_numpy(np.full(7, 2.5)).to(DEV), 0.0)
     assert st == aser.ASER_OK and abs(er - 7.0) < 1e-12
+
+
+@pytest.mark.parametrize("k", [40, 300, 1100, 2100])
+@pytest.mark.parametrize("value", [np.nan, -np.nan, np.inf])
+def test_rank_of_a_non_finite_spectrum_is_refused(k, value):
+    """A NaN or an infinity in T, or in S, must not come out as a positive spectrum: every count of a NaN recurrence is zero, the
+    singular values are zero, and the rank rule has nothing to divide by."""
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(k)
+    ctx = new_ctx()
+    ctx.ensure_workspace(aser.aser_spectrum_workspace_bytes(k, k, True))
+    for in_t in (True, False):
+        T = torch.randn((k, k), generator=gen, device=DEV)
+        S = torch.tril(torch.randn((k, k), generator=gen, device=DEV))
+        (T if in_t else S)[k // 2, k // 3] = float(value)
+        sig = torch.full((k,), -1.0, dtype=torch.float64, device=DEV)
+        ctx.check(aser.aser_singular_values(ctx, T, S, sig))
+        st, _, _ = aser.aser_select_rank(ctx, sig, 0.5)
+        assert st == aser.ASER_ERR_INVALID_ARG and "positive sum" in ctx.last_error()
