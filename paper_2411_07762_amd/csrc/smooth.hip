@@ -3,6 +3,7 @@
 // All statistics are fp64 so that the selected indices do not depend on summation order in
 // any realistic case; ties go to the lower channel index.
 #include "aser_internal.h"
+#include "rank_slot.h"
 
 namespace {
 
@@ -57,7 +58,7 @@ __global__ __launch_bounds__(1024) void select_kernel(const double* __restrict__
     for (int i = tid; i < n; i += 1024) {
         mdiag[i] = 1.0f;
         const int r = rank[2 * (int64_t)i];
-        if (r >= f) continue;
+        if (!rank_has_slot(r, f)) continue;
         // No candidate for this slot (fewer than f channels with a finite score): it gets -1, which every
         // consumer of idx skips, and the flag makes the next synchronising call fail with a status.
         const bool none = candidate(score[i]) < 0.0;
@@ -74,7 +75,7 @@ __global__ __launch_bounds__(1024) void select_kernel(const double* __restrict__
 #pragma unroll
     for (int w = 1; w < 16; ++w) xmin = fmin(xmin, red[w]);
     for (int i = tid; i < n; i += 1024)
-        if (rank[2 * (int64_t)i] < f && candidate(score[i]) >= 0.0) mdiag[i] = (float)((abs_sum[i] / cnt) / xmin);
+        if (rank_has_slot(rank[2 * (int64_t)i], f) && candidate(score[i]) >= 0.0) mdiag[i] = (float)((abs_sum[i] / cnt) / xmin);
 }
 
 __global__ __launch_bounds__(256) void gather_wo_kernel(const float* __restrict__ W, int64_t m, int64_t n, int64_t ldw,
