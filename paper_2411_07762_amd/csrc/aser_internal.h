@@ -229,13 +229,5 @@ int aser_gemm_small_f32(aser_ctx* ctx, float* A, int64_t lda, const float* B, in
 
 // The compensated layer for a few tokens (forward_few.hip); arguments as aser_compensated_forward has checked them.
 // scratch: ceil(n / 2048) * rows * (r rounded up to 16) floats when r > 0, 16-byte aligned.
-// Taken while its widest tiles (128 tokens x 64 outputs) are at most one workgroup per compute unit; from there on the
-// 256 x 256 tiles of the prefill kernels re-use more per load.  Measured without factors (us, 256 x 256 tiles -> here):
-// 4096 x 4096 int4: 256 tokens 44 -> 24, 512 tokens 45 -> 35; 14336 x 4096 int4: 128 tokens 61 -> 36, 192 tokens 60 -> 58,
-// 256 tokens 47 -> 68; 8192 x 8192 int8: 256 tokens 103 -> 67, 384 tokens 97 -> 130.  At most 2048 tokens, so that the
-// partial sums fit the workspace (see aser_compensated_forward).
-static inline bool aser_forward_few_pays(int64_t rows, int64_t m) {
-    return rows <= 2048 && ceil_div64(rows, 128) * ceil_div64(m, 64) <= 256;
-}
 int aser_forward_few(aser_ctx* ctx, const int8_t* xq, const float* xs, int rows, int64_t n, const void* wq, bool w4, const float* ws,
                      int64_t m, const float* L_A, const float* L_B, int r, bool split, float* scratch, float* Y, int64_t ldy);

@@ -28,6 +28,7 @@
 #include <type_traits>
 
 #include "aser_internal.h"
+#include "dispatch_rules.h"
 
 namespace {
 
@@ -832,7 +833,7 @@ extern "C" int aser_compensated_forward(aser_ctx* ctx, const int8_t* x_codes, co
     const bool w4 = layout == ASER_CODES_INT4_PACKED;
     // a few tokens: the kernels that split the contraction; their ceil(n / 2048) partial P (rows x r_pad floats at most) fit the
     // plan's room for P (one of them) and for the bf16 planes behind it (4 r_pad (m + n) bytes; rows <= 2048)
-    if (aser_forward_few_pays(rows, m))
+    if (aser_forward_few_pays(rows, n, m, r, split))
         return aser_forward_few(ctx, x_codes, x_scales, (int)rows, n, w_codes, w4, w_scales, m, L_A, L_B, r, split,
                                 r > 0 ? (float*)((char*)ctx->ws + pl.off_p) : nullptr, Y, ldy);
     FwdArgs g{};

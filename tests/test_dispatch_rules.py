@@ -1,0 +1,48 @@
+"""The rules on sizes that pick a kernel (csrc/dispatch_rules.h, compiled for the host) against measured times: wherever the
+two sides were measured to differ by more than 3 %, the rule must take the faster one."""
+import os
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2411_07762_amd", "csrc")
+
+
+@pytest.fixture(scope="module")
+def rule(tmp_path_factory):
+    d = tmp_path_factory.mktemp("rules")
+
+    def evaluate(name, expression, queries):
+        src, exe = d / (name + ".cpp"), d / name
+        src.write_text('#include "dispatch_rules.h"\n#include <stdio.h>\n#include <stdlib.h>\nint main(int c, char** v) {\n'
+                       '    int64_t a[8] = {0};\n    for (int i = 1; i < c; ++i) a[i - 1] = atoll(v[i]);\n    %s\n}\n' % expression)
+        subprocess.run(["g++", "-std=c++17", "-O1", "-I", CSRC, str(src), "-o", str(exe)], check=True, timeout=60)
+        return [[int(x) for x in subprocess.run([str(exe)] + [str(x) for x in q], capture_output=True, text=True, check=True, timeout=10).stdout.split()]
+                for q in queries]
+    return evaluate
+
+
+# tokens, channels, outputs, rank, split factors; us of the prefill kernels, us of the kernels for a few tokens (int4 codes)
+FORWARD = [
+    (1, 4096, 4096, 64, 0, 83.2, 13.9), (16, 1024, 14336, 64, 0, 36.5, 14.6), (64, 1024, 14336, 64, 0, 39.9, 27.0), (2048, 256, 768, 0, 0, 13.6, 15.9),
+    (512, 512, 3072, 0, 0, 15.8, 17.3), (384, 256, 4096, 0, 0, 20.9, 15.2), (300, 4096, 4096, 0, 0, 49.0, 32.2), (2048, 4096, 1024, 0, 0, 45.3, 35.1),
+    (512, 1024, 4096, 0, 0, 20.3, 19.5), (128, 512, 14336, 16, 0, 29.4, 38.8), (2048, 1024, 1024, 16, 0, 36.5, 43.0), (2048, 4096, 1024, 16, 0, 79.8, 70.4),
+    (2048, 1024, 512, 64, 0, 39.2, 32.0), (2048, 1024, 1024, 64, 0, 39.7, 48.4), (1024, 1024, 2048, 64, 0, 40.3, 44.8), (512, 1024, 4096, 64, 0, 40.5, 45.0),
+    (256, 1024, 8192, 64, 0, 40.4, 43.9), (256, 2048, 8192, 64, 0, 55.3, 52.2), (2048, 4096, 1024, 64, 0, 85.8, 94.2), (512, 4096, 4096, 64, 0, 86.4, 72.6),
+    (256, 4096, 8192, 64, 0, 86.0, 72.1), (2048, 1024, 1024, 64, 1, 46.8, 48.5), (512, 1024, 4096, 64, 1, 47.5, 44.8), (2048, 4096, 1024, 64, 1, 100.6, 93.4),
+    (1536, 512, 768, 64, 1, 37.8, 43.6), (256, 1024, 8192, 128, 1, 68.1, 61.2), (2048, 4096, 1024, 128, 1, 135.8, 148.6), (2048, 4096, 256, 128, 1, 137.1, 91.8),
+    (2048, 8192, 512, 128, 0, 168.3, 183.8), (2048, 8192, 256, 128, 0, 168.1, 165.6), (768, 4096, 2048, 128, 0, 102.1, 113.7), (128, 4096, 14336, 128, 0, 115.5, 98.4),
+]
+
+
+def test_kernels_for_a_few_tokens_are_taken_where_they_are_faster(rule):
+    got = rule("forward", 'printf("%d", (int)aser_forward_few_pays(a[0], a[1], a[2], (int)a[3], a[4] != 0));', [q[:5] for q in FORWARD])
+    wrong = [q for q, (few,) in zip(FORWARD, got) if (q[5] > 1.03 * q[6] and not few) or (q[6] > 1.03 * q[5] and few)]
+    assert not wrong
+
+
+def test_the_prefill_cases_reach_the_prefill_kernels(rule):
+    from test_gpu_kernel_paths import PREFILL
+    got = rule("prefill", 'printf("%d", (int)aser_forward_few_pays(a[0], a[1], a[2], (int)a[3], a[4] != 0));',
+               [(rows, n, m, r, split) for rows, n, m, r, _ in PREFILL for split in (0, 1)])
+    assert not any(few for (few,) in got)

@@ -63,6 +63,19 @@ def test_forward_of_a_few_tokens(rows, n, m, r, packed):
             assert np.linalg.norm(got[:, :m] - want) <= bar * np.linalg.norm(want)
 
 
+# Sizes that the kernels for a few tokens do not take (tests/test_dispatch_rules.py holds the rule to that): the 256 x 256 tiles with
+# fewer steps than their ring has stages and with half a step at the end, the 128 x 256 tiles (fewer than 256 tokens or outputs), and the
+# first product of the rank-r branch with one to four blocks of 32 columns; ragged tokens and outputs.
+PREFILL = [(2049, 32, 260, 40, False), (2049, 32, 300, 128, True), (2049, 96, 257, 72, True), (2305, 96, 513, 16, False), (2100, 352, 300, 128, False),
+           (300, 352, 16500, 40, True), (200, 352, 8250, 72, True), (200, 96, 8250, 16, False), (2100, 96, 200, 128, False), (2100, 32, 130, 24, True),
+           (129, 1056, 16400, 0, True), (1, 96, 16500, 128, False)]
+
+
+@pytest.mark.parametrize("rows,n,m,r,packed", PREFILL)
+def test_forward_of_the_prefill_kernels(rows, n, m, r, packed):
+    test_forward_of_a_few_tokens(rows, n, m, r, packed)
+
+
 @pytest.mark.parametrize("rows,n,dtype", [(16385, 2064, "bf16"), (16387, 4096, "bf16"), (65537, 2064, "f32"), (16384, 2064, "bf16"),
                                           (3, 1016, "bf16"), (5, 1032, "f32"), (9, 2048, "bf16"), (7, 2056, "bf16")])
 def test_activation_quantizer_at_the_borders_of_its_kernels(rows, n, dtype):
