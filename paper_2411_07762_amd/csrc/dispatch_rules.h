@@ -21,3 +21,10 @@ static inline bool aser_forward_few_pays(int64_t rows, int64_t n, int64_t m, int
     if (r == 0) return n >= 1024 || (rows > 256 && rows < 1024 && ((rows - 1) & 255) < 128);   // or the last 256 tokens' tile would be half empty
     return split ? n >= 1024 && rank_work <= 64 * n && rank_work <= 128 * 1536 : n >= 2048 && rank_work <= 9 * n;
 }
+
+// True where f rounds of an arg-max in one workgroup select the outlier channels faster than the comparison of all pairs of
+// channels: a round costs 1.6 to 3.3 us, the pairs n^2 / 5.4e6 us and one more launch, so the line is a constant plus n^2 (the rounds
+// take 1024 threads instead of 512 above 16384 channels).
+// Measured (us, rounds -> pairs): 4096 channels, f = 4: 17 -> 21, 8: 23 -> 22; 11008, 8: 33 -> 40; 14336, 16: 56 -> 59; 16384, 8: 36 -> 65, 16: 58 -> 66,
+// 32: 102 -> 68; 32768, 8: 43 -> 201, 32: 121 -> 203, 64: 225 -> 206.
+static inline bool aser_select_by_rounds(int64_t n, int f) { return f <= 4 + n * n / (n <= 16384 ? 17000000 : 20000000); }

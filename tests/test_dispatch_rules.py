@@ -46,3 +46,18 @@ def test_the_prefill_cases_reach_the_prefill_kernels(rule):
     got = rule("prefill", 'printf("%d", (int)aser_forward_few_pays(a[0], a[1], a[2], (int)a[3], a[4] != 0));',
                [(rows, n, m, r, split) for rows, n, m, r, _ in PREFILL for split in (0, 1)])
     assert not any(few for (few,) in got)
+
+
+# channels, f; us of f rounds of an arg-max, us of the comparison of all pairs
+SELECT = [
+    (256, 1, 12.0, 18.9), (256, 4, 14.1, 19.0), (1024, 4, 14.5, 18.9), (2048, 4, 15.5, 19.5), (4096, 0, 11.7, 13.4), (4096, 1, 12.4, 21.6), (4096, 4, 16.9, 21.4),
+    (4096, 8, 23.2, 21.5), (4096, 16, 35.4, 22.2), (4096, 64, 107.8, 23.8), (8192, 4, 21.9, 29.1), (11008, 8, 32.8, 40.2), (14336, 8, 34.9, 55.1), (14336, 16, 55.8, 58.7),
+    (16384, 8, 36.2, 65.3), (16384, 16, 58.2, 66.2), (16384, 32, 102.2, 67.6), (24576, 32, 111.8, 125.4), (32768, 1, 20.0, 199.5), (32768, 8, 43.4, 200.8),
+    (32768, 32, 121.3, 203.1), (32768, 64, 225.1, 206.1), (32768, 256, 846.8, 214.5),
+]
+
+
+def test_the_selection_takes_the_faster_of_rounds_and_pairs(rule):
+    got = rule("select", 'printf("%d", (int)aser_select_by_rounds(a[0], (int)a[1]));', [q[:2] for q in SELECT])
+    wrong = [q for q, (rounds,) in zip(SELECT, got) if (q[2] > 1.03 * q[3] and rounds) or (q[3] > 1.03 * q[2] and not rounds)]
+    assert not wrong

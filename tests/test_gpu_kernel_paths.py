@@ -180,6 +180,13 @@ def test_outlier_selection_with_many_ties(n, f):
         assert np.array_equal(mdiag.cpu().numpy(), ref.mdiag)
 
 
+@pytest.mark.parametrize("n,f", [(300, 4), (4096, 4), (4096, 5), (4097, 4), (16384, 19), (16384, 20), (16385, 6), (32768, 57), (32768, 58)])
+def test_outlier_selection_on_both_sides_of_its_rule(n, f):
+    """The last f that is selected by rounds of an arg-max and the first by the comparison of all pairs, at the widths where the
+    former changes its workgroup."""
+    test_outlier_selection_with_many_ties(n, f)
+
+
 @pytest.mark.parametrize("m,n", [(8200, 1100), (8193, 1027), (1025, 8201), (1100, 1028)])
 def test_reconstruction_at_the_borders_of_its_tiles(m, n):
     """Sizes around the rules that pick the 256-row tiles (1024 and 8192 rows), with and without 16-byte rows: the bars of the
