@@ -370,35 +370,31 @@ int launch_eval(aser_ctx* ctx, const EvalArgs& g) {
     return aser_check_launch(ctx, "layer_output_error");
 }
 
+// The workspace is what the operands, one output and L_A take in fp32 (two m x n, two rows x n, a rows x m and an r x m array), the
+// activation codes and scales, and a block of scalars.  The bf16 planes, four of the weights and three of the activations with rows
+// padded to np channels, lie in the room of the former.  They fit unless n is short of a multiple of 32 and rows (or n) are few; then the
+// outputs, or the tokens, are taken in blocks of m_blk, rows_blk.  One of each always fits: 14 np bytes, np <= n + 31, in
+// at least 16 n + 8 bytes of six arrays of 256 bytes or more.
 struct EvalPlan {
-    int64_t np;
-    size_t off_whi, off_wlo, off_vhi, off_vlo, off_xhi, off_xlo, off_cq, off_codes, off_scales, off_scal, total;
+    int64_t np, m_blk, rows_blk;
+    size_t planes, off_codes, off_scales, off_scal, total;
 };
-
-// The size asked for stays what it was when the operands and one output were kept in fp32 (two m x n, two rows x n, a rows x m and
-// an r x m array), which is more than the planes take unless n is short of a multiple of 32 and rows are few: callers
-// that bind a workspace for it, and what is refused for want of one, do not change.
-size_t eval_fp32_bytes(int64_t m, int64_t n, int64_t rows, int r) {
-    return 2 * align_up((size_t)m * n * 4, 256) + 2 * align_up((size_t)rows * n * 4, 256) + align_up((size_t)rows * m * 4, 256) +
-           align_up((size_t)(r > 0 ? r : 1) * m * 4, 256) + align_up((size_t)rows * n, 256) + align_up((size_t)rows * 4, 256) + 256;
-}
 
 void eval_plan(int64_t m, int64_t n, int64_t rows, int r, EvalPlan* p) {
     p->np = (n + 31) / 32 * 32;
-    size_t off = 0;
-    const size_t wp = align_up((size_t)m * p->np * 2, 256), xp = align_up((size_t)rows * p->np * 2, 256);
-    p->off_whi = off; off += wp;
-    p->off_wlo = off; off += wp;
-    p->off_vhi = off; off += wp;
-    p->off_vlo = off; off += wp;
-    p->off_xhi = off; off += xp;
-    p->off_xlo = off; off += xp;
-    p->off_cq = off; off += xp;
+    p->planes = 2 * align_up((size_t)m * n * 4, 256) + 2 * align_up((size_t)rows * n * 4, 256) + align_up((size_t)rows * m * 4, 256) +
+                align_up((size_t)(r > 0 ? r : 1) * m * 4, 256);
+    size_t off = p->planes;
     p->off_codes = off; off += align_up((size_t)rows * n, 256);
     p->off_scales = off; off += align_up((size_t)rows * 4, 256);
     p->off_scal = off; off += 256;
-    const size_t fp32_bytes = eval_fp32_bytes(m, n, rows, r);
-    p->total = off > fp32_bytes ? off : fp32_bytes;
+    p->total = off;
+    p->m_blk = m;
+    p->rows_blk = rows;
+    while ((size_t)(8 * p->m_blk + 6 * p->rows_blk) * p->np > p->planes && (p->m_blk > 1 || p->rows_blk > 1)) {
+        int64_t& larger = 8 * p->m_blk >= 6 * p->rows_blk && p->m_blk > 1 ? p->m_blk : (p->rows_blk > 1 ? p->rows_blk : p->m_blk);
+        larger = (larger + 1) / 2;
+    }
 }
 
 }  // namespace
@@ -433,62 +429,69 @@ extern "C" int aser_layer_output_error(aser_ctx* ctx, const float* W, int64_t m,
         ASER_FAIL(ctx, ASER_ERR_WORKSPACE, "layer_output_error: workspace too small (%zu needed)", pl.total + kAserWsTail);
     ASER_TRY(aser_prepare_device(ctx));
     char* ws = (char*)ctx->ws;
-    uint16_t* w_hi = (uint16_t*)(ws + pl.off_whi);
-    uint16_t* w_lo = (uint16_t*)(ws + pl.off_wlo);
-    uint16_t* v_hi = (uint16_t*)(ws + pl.off_vhi);
-    uint16_t* v_lo = (uint16_t*)(ws + pl.off_vlo);
-    uint16_t* x_hi = (uint16_t*)(ws + pl.off_xhi);
-    uint16_t* x_lo = (uint16_t*)(ws + pl.off_xlo);
-    uint16_t* c_q = (uint16_t*)(ws + pl.off_cq);
+    const int64_t np = pl.np, wn = pl.m_blk * np, xn = pl.rows_blk * np;
+    uint16_t* w_hi = (uint16_t*)ws;                       // planes: rows of np entries, 64 bytes or a multiple
+    uint16_t *w_lo = w_hi + wn, *v_hi = w_lo + wn, *v_lo = v_hi + wn, *x_hi = v_lo + wn, *x_lo = x_hi + xn, *c_q = x_lo + xn;
     int8_t* acodes = (int8_t*)(ws + pl.off_codes);
     float* ascales = (float*)(ws + pl.off_scales);
     double* scal = (double*)(ws + pl.off_scal);           // [0] = ||Y||^2, [1] = err^2
     const bool bf16 = x_dtype == ASER_DTYPE_BF16;
-    const int64_t np = pl.np;
-
-    ASER_TRY(aser_fill_bytes(ctx, scal, 256));
-    {
-        dim3 grid((unsigned)ceil_div64(np, 64), (unsigned)ceil_div64(m, 64));
-        const int w_vec = (((uintptr_t)W & 15) == 0 && (ldw & 3) == 0) ? 1 : 0;
-        const int c_vec = layout == ASER_CODES_INT8 ? (((uintptr_t)codes & 7) == 0 && (n & 7) == 0) : (((uintptr_t)codes & 3) == 0 && (n & 7) == 0);
-        hipLaunchKernelGGL(weight_planes_kernel, grid, dim3(256), 0, ctx->stream, W, m, n, ldw, np, (const uint8_t*)codes, (int)layout, scales,
-                           L_A, L_B, (int)r, act_bits == 0 ? mdiag : (const float*)nullptr, w_vec, c_vec, w_hi, w_lo, v_hi, v_lo);
-        ASER_TRY(aser_check_launch(ctx, "weight_planes"));
-    }
-    const int64_t groups = rows * (np / 8);
-    const dim3 xgrid((unsigned)(ceil_div64(groups, 256) < 4096 ? ceil_div64(groups, 256) : 4096));
+    const size_t xsz = bf16 ? 2 : 4;
+    const int64_t cpitch = layout == ASER_CODES_INT8 ? n : n / 2;
+    const int w_vec = (((uintptr_t)W & 15) == 0 && (ldw & 3) == 0) ? 1 : 0;
+    const int c_vec = ((uintptr_t)codes & (layout == ASER_CODES_INT8 ? 7 : 3)) == 0 && (n & 7) == 0;
     // bf16 activations whose rows can be fetched 16 bytes at a time are read where they are
     const bool direct = bf16 && ((uintptr_t)X & 15) == 0 && (ldx & 7) == 0 && ldx <= (1 << 22) && np == n;   // 128 rows within 32-bit offsets
-    if (!direct) {
-        if (bf16) hipLaunchKernelGGL(act_planes_kernel<0>, xgrid, dim3(256), 0, ctx->stream, X, rows, n, ldx, np, x_hi, x_lo);
-        else hipLaunchKernelGGL(act_planes_kernel<1>, xgrid, dim3(256), 0, ctx->stream, X, rows, n, ldx, np, x_hi, x_lo);
-        ASER_TRY(aser_check_launch(ctx, "act_planes"));
+
+    ASER_TRY(aser_fill_bytes(ctx, scal, 256));
+    if (act_bits != 0) ASER_TRY(aser_quantize_act_rtn(ctx, X, x_dtype, rows, n, ldx, mdiag, act_bits, acodes, ascales));
+    for (int64_t t0 = 0; t0 < rows; t0 += pl.rows_blk) {
+        const int64_t tr = rows - t0 < pl.rows_blk ? rows - t0 : pl.rows_blk;
+        const void* Xt = (const char*)X + (size_t)t0 * ldx * xsz;
+        const int64_t groups = tr * (np / 8);
+        const dim3 xgrid((unsigned)(ceil_div64(groups, 256) < 4096 ? ceil_div64(groups, 256) : 4096));
+        if (!direct) {
+            if (bf16) hipLaunchKernelGGL(act_planes_kernel<0>, xgrid, dim3(256), 0, ctx->stream, Xt, tr, n, ldx, np, x_hi, x_lo);
+            else hipLaunchKernelGGL(act_planes_kernel<1>, xgrid, dim3(256), 0, ctx->stream, Xt, tr, n, ldx, np, x_hi, x_lo);
+            ASER_TRY(aser_check_launch(ctx, "act_planes"));
+        }
+        if (act_bits != 0) {
+            hipLaunchKernelGGL(act_planes_kernel<2>, xgrid, dim3(256), 0, ctx->stream, (const void*)(acodes + t0 * n), tr, n, n, np, c_q, c_q);
+            ASER_TRY(aser_check_launch(ctx, "code_planes"));
+        }
+        for (int64_t o0 = 0; o0 < m; o0 += pl.m_blk) {
+            const int64_t om = m - o0 < pl.m_blk ? m - o0 : pl.m_blk;
+            if (t0 == 0 || pl.m_blk < m) {
+                const dim3 grid((unsigned)ceil_div64(np, 64), (unsigned)ceil_div64(om, 64));
+                hipLaunchKernelGGL(weight_planes_kernel, grid, dim3(256), 0, ctx->stream, W + o0 * ldw, om, n, ldw, np,
+                                   (const uint8_t*)codes + o0 * cpitch, (int)layout, scales + o0, L_A ? L_A + o0 * r : L_A, L_B, (int)r,
+                                   act_bits == 0 ? mdiag : (const float*)nullptr, w_vec, c_vec, w_hi, w_lo, v_hi, v_lo);
+                ASER_TRY(aser_check_launch(ctx, "weight_planes"));
+            }
+            EvalArgs g{};
+            g.np = np; g.rows = tr; g.m = om; g.out = scal;
+            auto add = [&](const void* a, int64_t pa, const void* b) { g.a[g.segs] = (const char*)a; g.pa[g.segs] = pa; g.b[g.segs] = (const char*)b; ++g.segs; };
+            const void* xa = direct ? Xt : (const void*)x_hi;
+            const int64_t xpitch = direct ? ldx * 2 : np * 2;
+            add(xa, xpitch, w_hi);
+            add(xa, xpitch, w_lo);
+            if (!bf16) add(x_lo, np * 2, w_hi);
+            g.segs1 = g.segs;
+            if (act_bits == 0) {
+                add(xa, xpitch, v_hi);
+                add(xa, xpitch, v_lo);
+                if (!bf16) add(x_lo, np * 2, v_hi);
+            } else {
+                add(c_q, np * 2, v_hi);
+                add(c_q, np * 2, v_lo);
+                g.xs = ascales + t0;
+            }
+            // The largest tile with which the launch still fills the device
+            if (ceil_div64(tr, 128) * ceil_div64(om, 256) >= 200) ASER_TRY((launch_eval<2, 4>(ctx, g)));
+            else if (ceil_div64(tr, 128) * ceil_div64(om, 128) >= 200) ASER_TRY((launch_eval<2, 2>(ctx, g)));
+            else ASER_TRY((launch_eval<1, 1>(ctx, g)));
+        }
     }
-    EvalArgs g{};
-    g.np = np; g.rows = rows; g.m = m; g.out = scal;
-    auto add = [&](const void* a, int64_t pa, const void* b) { g.a[g.segs] = (const char*)a; g.pa[g.segs] = pa; g.b[g.segs] = (const char*)b; ++g.segs; };
-    const void* xa = direct ? X : (const void*)x_hi;
-    const int64_t xpitch = direct ? ldx * 2 : np * 2;
-    add(xa, xpitch, w_hi);
-    add(xa, xpitch, w_lo);
-    if (!bf16) add(x_lo, np * 2, w_hi);
-    g.segs1 = g.segs;
-    if (act_bits == 0) {
-        add(xa, xpitch, v_hi);
-        add(xa, xpitch, v_lo);
-        if (!bf16) add(x_lo, np * 2, v_hi);
-    } else {
-        ASER_TRY(aser_quantize_act_rtn(ctx, X, x_dtype, rows, n, ldx, mdiag, act_bits, acodes, ascales));
-        hipLaunchKernelGGL(act_planes_kernel<2>, xgrid, dim3(256), 0, ctx->stream, (const void*)acodes, rows, n, n, np, c_q, c_q);
-        ASER_TRY(aser_check_launch(ctx, "code_planes"));
-        add(c_q, np * 2, v_hi);
-        add(c_q, np * 2, v_lo);
-        g.xs = ascales;
-    }
-    // The largest tile with which the launch still fills the device
-    if (ceil_div64(rows, 128) * ceil_div64(m, 256) >= 200) ASER_TRY((launch_eval<2, 4>(ctx, g)));
-    else if (ceil_div64(rows, 128) * ceil_div64(m, 128) >= 200) ASER_TRY((launch_eval<2, 2>(ctx, g)));
-    else ASER_TRY((launch_eval<1, 1>(ctx, g)));
     double h[2] = {0.0, 0.0};
     ASER_HIP(ctx, hipMemcpyAsync(h, scal, sizeof(h), hipMemcpyDeviceToHost, ctx->stream));
     ASER_HIP(ctx, hipStreamSynchronize(ctx->stream));

@@ -274,3 +274,16 @@ def test_product_path_does_not_import_the_oracle():
         for fn in files:
             if fn.endswith((".py", ".hip", ".h", ".cpp")):
                 assert "oracle" not in open(os.path.join(dirpath, fn)).read().lower().replace("no cpu fallback", ""), fn
+
+
+def test_output_error_workspace_is_the_documented_size():
+    """Two m x n, two rows x n, a rows x m and an r x m array in fp32, the codes and scales of the activations, a block of scalars and
+    the status block: callers bind a buffer of that size once, also where n is not a multiple of 32 and rows are few."""
+    import random
+    up = lambda x: -(-x // 256) * 256
+    rng = random.Random(3)
+    shapes = [(1, 1, 1, 0), (4096, 4097, 16, 64), (700, 33, 3, 0), (1, 1, 1000, 0), (5000, 1025, 40, 8), (64, 1000, 1, 64)]
+    shapes += [(rng.randint(1, 9000), rng.randint(1, 9000), int(2 ** rng.uniform(0, 12)), rng.choice([0, 1, 64])) for _ in range(300)]
+    for m, n, rows, r in shapes:
+        want = 2 * up(4 * m * n) + 2 * up(4 * rows * n) + up(4 * rows * m) + up(4 * max(r, 1) * m) + up(rows * n) + up(4 * rows) + 256
+        assert aser.aser_output_error_workspace_bytes(m, n, rows, r) == want + aser.aser_forward_workspace_bytes(1, 32, 1, 0), (m, n, rows, r)

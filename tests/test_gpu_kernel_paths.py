@@ -162,6 +162,14 @@ def test_output_error_at_the_edges_of_its_tiles(rows, n, m, r, bits, x_dtype, ac
     assert abs(err - want) <= 2e-4 * want + 1e-5 * ynorm
 
 
+@pytest.mark.parametrize("rows,n,m,r,bits,x_dtype,act_bits,pad", [
+    (3, 33, 700, 0, 8, "bf16", 8, 0), (3, 33, 701, 0, 8, "f32", 0, 0), (1000, 1, 1, 0, 8, "f32", 8, 0), (1000, 3, 2, 1, 8, "bf16", 0, 5),
+    (16, 1025, 4099, 4, 8, "bf16", 8, 0), (1, 65, 1, 0, 4, "f32", 8, 0), (300, 34, 9, 3, 4, "bf16", 6, 0), (2, 1, 300, 1, 8, "bf16", 8, 0)])
+def test_output_error_in_blocks(rows, n, m, r, bits, x_dtype, act_bits, pad):
+    """Sizes whose padded planes do not fit the workspace at once (n short of a multiple of 32, few tokens or few channels)."""
+    test_output_error_at_the_edges_of_its_tiles(rows, n, m, r, bits, x_dtype, act_bits, pad)
+
+
 @pytest.mark.parametrize("n,f", [(1, 1), (255, 255), (513, 40), (1024, 1), (1537, 300), (32768, 64)])
 def test_outlier_selection_with_many_ties(n, f):
     """Scores of few distinct values, exactly equal on both sides (powers of two): the order is that of the channel index, bit for bit."""
