@@ -28,3 +28,33 @@ static inline bool aser_forward_few_pays(int64_t rows, int64_t n, int64_t m, int
 // Measured (us, rounds -> pairs): 4096 channels, f = 4: 17 -> 21, 8: 23 -> 22; 11008, 8: 33 -> 40; 14336, 16: 56 -> 59; 16384, 8: 36 -> 65, 16: 58 -> 66,
 // 32: 102 -> 68; 32768, 8: 43 -> 201, 32: 121 -> 203, 64: 225 -> 206.
 static inline bool aser_select_by_rounds(int64_t n, int f) { return f <= 4 + n * n / (n <= 16384 ? 17000000 : 20000000); }
+
+// Gram update of a chunk of tokens that the LDS-direct schedule does not fill its rounds with by itself: the K chunks of that schedule
+// and the split of its left-over tiles, or chunks = 0 where the plain grid of `parts` K parts and `steps64` 64-token steps each
+// is faster.  T: 256 x 256 tiles of the lower triangle; steps: 32-token steps.
+// EVERY tile, of the full rounds and left over, is summed in as many parts as the plain grid's, or up to a third more: fewer make the
+// fp32 chains longer, more round G more often when a statistic comes in many calls.  Root mean square error of the diagonal against
+// fp64, in 1e-8 (plain grid, then as many parts, then the left-over tiles alone in twice to eight times as many): 4096 channels, eight calls
+// of 2000 tokens 9.05, 9.05, 9.01 to 9.54; four calls of 7503 10.2 (7 parts), 10.3 (8 parts), 10.4 to 10.6; one call of 7503 9.8, 9.1, 8.9 to 9.0.
+// Costs in microseconds, fitted to 1040 .. 14336 channels and 256 .. 7503 tokens (nine tenths of the figures within 12 % for the
+// LDS-direct schedule, 9 % for the plain grid, the medians within 2 %).  LDS-direct: 0.60 per step of the busiest workgroup and
+// 0.186 per 256 x 256 tile flush of the launch (fp32 atomics that share the memory side).  Plain: per round of 256 workgroups 1.97
+// a step and 4.3, 0.165 per flush.  Measured, plain -> LDS-direct: 1536 channels: 59 -> 42 us at 4000 tokens; 4096: 68 -> 61 at 1000, 137 -> 114 at
+// 2000, 165 -> 133 at 3000, 240 -> 197 at 5000, plain at 4000 (171) and 7503 (301); 8192: 409 -> 368 at 3000; 11008: 580 -> 467 at 2000.
+struct AserGramSplit { int chunks, split; };
+static inline AserGramSplit aser_gram_dma_split(int64_t T, int64_t steps, int64_t parts, int64_t steps64) {
+    AserGramSplit best = {0, 1};
+    double best_cost = (double)((T * parts + 255) / 256) * (1.97 * (double)steps64 + 4.3) + 0.165 * (double)(T * parts) + 4.1;
+    for (int c = 1; c <= 8; c *= 2) {
+        const int64_t W = 256 / c, full = T / W, rem = T % W, steps_c = (steps + c - 1) / c;
+        if (full > 0 && (c < parts || 3 * c > 4 * parts)) continue;
+        for (int64_t sp = 1; sp <= (rem ? W / rem : 1); ++sp) {
+            if (rem && (c * sp < parts || 3 * c * sp > 4 * parts)) continue;
+            const int64_t last = rem ? (steps_c + sp - 1) / sp : 0;
+            if (sp > 1 && last < 4) break;                  // the ring is filled once
+            const double cost = 0.60 * (double)(full * steps_c + last) + 0.186 * (double)(c * (full * W + rem * sp)) + 8.9;
+            if (cost <= best_cost) { best_cost = cost; best = AserGramSplit{c, (int)sp}; }     // equal: more chunks, fewer XCDs on one slab
+        }
+    }
+    return best;
+}

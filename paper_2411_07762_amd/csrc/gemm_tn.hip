@@ -20,6 +20,7 @@
 #include <type_traits>
 
 #include "aser_internal.h"
+#include "dispatch_rules.h"
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
@@ -1039,36 +1040,6 @@ int launch_gram_persistent(aser_ctx* ctx, const GemmArgs& g) {
     return launch_gram_persistent2<IN, false>(ctx, g);
 }
 
-// The LDS-direct schedule for calls of fewer tokens than it needs to fill its rounds by itself: K chunks and split of the
-// left-over tiles, or chunks = 0 where the plain grid of `parts` K parts and `steps64` 64-token steps each is faster.
-// A tile is summed in as many parts as the plain grid's, or up to a third more: fewer make the fp32 chains longer (a
-// call of 7503 tokens of 4096 channels in two chunks instead of seven parts was 40 % further off the fp64 result), more round
-// G more often when a statistic comes in many calls.  Costs in microseconds from sweeps of n = 1536 .. 11008 and 1000 ..
-// 7500 tokens (model within 15 % of every figure).  LDS-direct: 0.87 per 32-token step of the busiest workgroup, 5 per tile
-// visit, 0.14 per 256 x 256 tile flush of the launch (fp32 atomics that share the memory side).  Plain: per round of 256 workgroups 1.9 a
-// step and 24, 0.1 per flush.  Measured, plain -> LDS-direct with this rule: n = 1536: 70 -> 56 at 4000 tokens; n = 4096: 75 -> 70 at 1024,
-// 147 -> 114 at 2000, 177 -> 127 at 3000, 344 -> 315 at 7503 (183 against 191 at 4000: plain); n = 5120: 252 -> 240 at 3750;
-// n = 8192: 434 -> 394 at 3000; n = 11008: 579 -> 484 at 2000.
-struct GramSplit { int chunks, split; };
-GramSplit gram_dma_split(int64_t T, int64_t steps, int64_t parts, int64_t steps64) {
-    GramSplit best{0, 1};
-    double best_cost = (double)ceil_div64(T * parts, 256) * (1.9 * (double)steps64 + 24.0) + 0.1 * (double)(T * parts);
-    for (int c = 1; c <= 8; c *= 2) {
-        const int64_t W = 256 / c, full = T / W, rem = T % W, steps_c = ceil_div64(steps, c);
-        const int64_t most = rem ? W / rem : 1;
-        for (int64_t sp = 1; sp <= most; ++sp) {
-            const int64_t p = full ? c : c * sp;            // parts of most tiles
-            if (p < parts || 3 * p > 4 * parts) continue;
-            const int64_t last = rem ? ceil_div64(steps_c, sp) : 0;
-            if (sp > 1 && last < 4) break;                  // the ring is filled once
-            const double flushes = (double)c * (double)(full * W + rem * sp);
-            const double cost = 0.87 * (double)(full * steps_c + last) + 5.0 * (double)(full + (rem ? 1 : 0)) + 0.14 * flushes;
-            if (cost < best_cost) { best_cost = cost; best = GramSplit{c, (int)sp}; }
-        }
-    }
-    return best;
-}
-
 }  // namespace
 
 int aser_gemm_tn(aser_ctx* ctx, const GemmArgs& g) {
@@ -1128,9 +1099,9 @@ int aser_syrk_gram(aser_ctx* ctx, const void* X, int x_dtype, int64_t rows, int6
     if (parts > max_parts) parts = max_parts;
     if (parts < 1) parts = 1;
     // up to 1024 channels the plain grid's 128 x 128 tiles split K further (4096 tokens: 24 us against 40), and a few tokens of
-    // wide channels are all flushes (256 of 8192: 148 us against 160)
-    if (n > 1024 && rows >= (n > 5120 ? 512 : 256) && g.in_type == GEMM_IN_BF16 && operands_fast<GEMM_IN_BF16>(g)) {
-        const GramSplit sp = gram_dma_split(T256, ceil_div64(rows, kDmaBK), parts, ceil_div64(ksteps, parts));
+    // wide channels are all flushes (256 of 3584: 31.5 us against 32.2, of 8192: 148 against 160)
+    if (n > 1024 && rows >= (n > 5120 ? 512 : (n > 2560 ? 384 : 256)) && g.in_type == GEMM_IN_BF16 && operands_fast<GEMM_IN_BF16>(g)) {
+        const AserGramSplit sp = aser_gram_dma_split(T256, ceil_div64(rows, kDmaBK), parts, ceil_div64(ksteps, parts));
         if (sp.chunks > 0) {
             g.k_parts = sp.chunks; g.split = sp.split;
             return launch_gram_dma(ctx, g);

@@ -61,3 +61,45 @@ def test_the_selection_takes_the_faster_of_rounds_and_pairs(rule):
     got = rule("select", 'printf("%d", (int)aser_select_by_rounds(a[0], (int)a[1]));', [q[:2] for q in SELECT])
     wrong = [q for q, (rounds,) in zip(SELECT, got) if (q[2] > 1.03 * q[3] and rounds) or (q[3] > 1.03 * q[2] and not rounds)]
     assert not wrong
+
+
+# channels, tokens of a call; us of the plain grid, us of (K chunks, split of the left-over tiles) of the LDS-direct schedule
+GRAM = [
+    (1040, 4000, 57.5, {(4, 1): 33.5, (2, 2): 35.5, (1, 4): 35.7}), (1280, 2000, 46.2, {(2, 1): 33.6, (1, 2): 34.2}),
+    (1536, 256, 21.6, {(1, 1): 18.3}), (1536, 4000, 59.3, {(4, 1): 41.6, (2, 2): 42.3, (1, 4): 44.4}),
+    (2048, 1000, 43.4, {(1, 1): 33.4}), (2048, 3000, 66.4, {(2, 1): 50.3, (1, 2): 54.8}),
+    (2560, 5000, 88.6, {(2, 2): 75.5, (4, 1): 75.8, (1, 4): 76.8}), (2560, 6000, 139.3, {}),
+    (3072, 5000, 142.8, {(4, 1): 115.4}),
+    (3584, 3500, 137.1, {(4, 1): 122.0}),
+    (4096, 1000, 68.3, {(1, 1): 60.7}), (4096, 2000, 136.6, {(2, 1): 113.9}),
+    (4096, 3000, 165.2, {(2, 1): 133.4}), (4096, 4000, 171.3, {(4, 1): 180.3}),
+    (4096, 5000, 240.2, {(4, 1): 196.6}), (4096, 7503, 301.4, {(8, 1): 305.2}),
+    (5120, 1500, 92.5, {(1, 1): 78.9}), (5120, 5000, 313.1, {(4, 1): 248.9}),
+    (5120, 6000, 381.3, {}), (6144, 512, 96.4, {(1, 1): 88.3}),
+    (7168, 2000, 279.5, {(2, 1): 227.7}), (8192, 3000, 409.3, {(2, 1): 368.2}),
+    (11008, 2000, 579.5, {(2, 1): 467.0}), (14336, 5000, 1393.0, {(1, 1): 1046.0}),
+]
+
+
+def gram_query(n, rows):
+    """The arguments of the rule as the Gram update makes them: tiles, 32-token steps, K parts of the plain grid, 64-token steps of each."""
+    t = -(-n // 256)
+    tiles, k64 = t * (t + 1) // 2, -(-rows // 64)
+    parts = max(1, min(-(-1024 // tiles), max(1, k64 // 16)))
+    return tiles, -(-rows // 32), parts, -(-k64 // parts)
+
+
+def test_gram_chunks_take_the_faster_schedule_and_keep_their_number_of_parts(rule):
+    call = 'AserGramSplit s = aser_gram_dma_split(a[0], a[1], a[2], a[3]); printf("%d %d", s.chunks, s.split);'
+    got = rule("gram", call, [gram_query(n, rows) for n, rows, _, _ in GRAM])
+    for (n, rows, plain, dma), (c, split) in zip(GRAM, got):
+        taken = dma[(c, split)] if c else plain
+        assert taken <= 1.03 * plain and taken <= 1.1 * min([plain] + list(dma.values())), (n, rows, c, split)
+    # every tile, of the full rounds and left over, in as many parts as the plain grid's or up to a third more
+    sizes = [(n, rows) for n in range(1032, 14400, 488) for rows in (256, 700, 1500, 2200, 3333, 5000, 7503, 8191)]
+    for (n, rows), (c, split) in zip(sizes, rule("bound", call, [gram_query(n, rows) for n, rows in sizes])):
+        tiles, _, parts, _ = gram_query(n, rows)
+        if c:
+            per_round = 256 // c
+            counts = ([c] if tiles >= per_round else []) + ([c * split] if tiles % per_round else [])
+            assert all(parts <= k and 3 * k <= 4 * parts for k in counts), (n, rows, c, split, parts)
