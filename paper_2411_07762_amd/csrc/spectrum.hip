@@ -13,9 +13,10 @@
 // Tridiagonalisation.  Step j turns column j into (d_j, e_j, 0, ...) with H = I - tau v v^T and needs
 // p = tau B22 v and the rank-2 update B22 -= v w^T + w v^T with w = p - (tau / 2)(v^T p) v.  A step is one launch:
 // a pass over the trailing matrix that forms B22 v with the updates of the last (up to four) steps applied on the fly, of
-// which every fourth also writes the updated matrix, and in the workgroup that finishes last the reflector of the next
-// step.  So 10 bytes per entry and step on average instead of the 16 of an update in every step; bound by HBM or the
-// last-level cache when B fits.
+// which one in up to four also writes the updated matrix, and in the workgroup that finishes last the reflector of the next
+// step.  A step moves 8 bytes per entry of the trailing matrix, or 16 when it writes: 10 on average while at least 2048 columns
+// are left (one of four steps writes), 12 down to 1024 (one of two), 16 below, where the launch is what a step costs; the
+// last 256 columns do not leave one workgroup.  Bound by HBM or the last-level cache when B fits.
 // B is kept as a full symmetric matrix so that every pass walks rows with unit stride.
 #include <math.h>
 
@@ -119,7 +120,7 @@ struct TridiagStep {
     const double* w[kTriPairs];
     const double* vn;                     // the reflector of this step
     double *wn, *vnext;                   // out: its w, and the next reflector
-    double *p, *eff, *corner;             // B vn, row c0 and entry (k-1, k-1) of the up-to-date matrix
+    double *p, *eff;                      // B vn, and row c0 of the up-to-date matrix
     double *d, *e;
     const double* tau_cur; double* tau_next;
     int* counter;                         // workgroups that have finished (0 between launches)
@@ -157,12 +158,12 @@ __global__ __launch_bounds__(kTriThreads) void tridiag_first_kernel(TridiagStep 
     }
 }
 
-// One step of the chain in one launch.  Every workgroup takes 8 rows of the trailing matrix (rows and columns >= c0): it
+// One step of the chain in one launch, while more than kTailRows rows are left.  Every workgroup takes 8 rows of the trailing matrix (rows and columns >= c0): it
 // forms p_i = sum_l B_il vn_l on the up-to-date values, which are B minus the NP pending rank-2 updates; with
 // WRITE they also go back to memory and nothing is pending any more, otherwise the pass only reads.  The workgroup
 // that finishes last then has all of p: w = tau p - (tau^2 / 2)(vn^T p) vn, and from row c0 of the matrix after this
 // step's own update the next diagonal entry, the next off-diagonal one and the next reflector.
-// What bounds it: 8 (k - j)^2 bytes per read-only pass and twice that per writing one (every fourth), from the last-level
+// What bounds it: 8 (k - j)^2 bytes per read-only pass and twice that per writing one (one in up to four), from the last-level
 // cache when B fits, and the tail of the last workgroup; a launch per column and role (pass, reflector) and a read and a
 // write of B in every pass were 26.7 us per column at k = 4096, this is 19.7.
 template <int NP, bool WRITE>
@@ -198,10 +199,7 @@ __global__ __launch_bounds__(kTriThreads) void tridiag_step_kernel(TridiagStep a
                 if (WRITE && r < nrows) rowp[r][l] = b[r];
                 acc[r] = fma(b[r], vnl, acc[r]);
             }
-            if (blockIdx.x == 0) {
-                publish(a.eff + l, b[0]);
-                if (l == k - 1 && k - c0 == 2) publish(a.corner, b[1]);
-            }
+            if (blockIdx.x == 0) publish(a.eff + l, b[0]);
         }
 #pragma unroll
         for (int r = 0; r < kTriRows; ++r) {
@@ -252,7 +250,6 @@ __global__ __launch_bounds__(kTriThreads) void tridiag_step_kernel(TridiagStep a
     for (int u = 0; u < 4; ++u) dot += vv[u] * pv[u];
     dot = block_sum(dot, flat);
     const double kk = 0.5 * tau * tau * dot, w_row = tau * p_row - kk * v_row;
-    const bool reflect = row + 2 < k;                               // at least two entries below the diagonal
     double n2 = 0.0;
     for (int64_t i0 = row + tid; i0 < k; i0 += 4 * kTriThreads) {
         if (i0 != row + tid) fetch(i0, true);
@@ -263,18 +260,14 @@ __global__ __launch_bounds__(kTriThreads) void tridiag_step_kernel(TridiagStep a
             const double w = tau * pv[u] - kk * vv[u], c = ev[u] - (v_row * w + w_row * vv[u]);
             a.wn[i] = w;
             if (i == row) a.d[row] = c;
-            else if (reflect) {
+            else {
                 a.vnext[i] = c;
                 if (a.vstore) a.vstore[row * k + i] = c;
                 n2 += c * c;
                 if (i == row + 1) red[kTriThreads / 64 - 1][kTriRows - 1] = c;      // behind what block_sum uses
-            } else {
-                a.e[row] = c;                                       // the last 2 x 2 block: no reflector
-                a.d[k - 1] = published(a.corner) - 2.0 * vv[u] * w;
             }
         }
     }
-    if (!reflect) return;
     n2 = block_sum(n2, flat);
     if (tid == 0) {
         const double x0 = red[kTriThreads / 64 - 1][kTriRows - 1];
@@ -676,15 +669,18 @@ int gram_f64(aser_ctx* ctx, const TIN* P, int64_t K, int64_t k, int64_t ldp, dou
     return aser_check_launch(ctx, "gram_f64");
 }
 
-template <bool WRITE>
-void launch_tridiag_step(aser_ctx* ctx, int pairs, const TridiagStep& a) {
+// write: the pending pairs are applied (one to four of them); otherwise zero to three stay pending.
+void launch_tridiag_step(aser_ctx* ctx, bool write, int pairs, const TridiagStep& a) {
     const dim3 grid((unsigned)ceil_div64(a.k - a.c0, kTriRows)), block(kTriThreads);
-    switch (pairs) {
-        case 0: hipLaunchKernelGGL((tridiag_step_kernel<0, WRITE>), grid, block, 0, ctx->stream, a); break;
-        case 1: hipLaunchKernelGGL((tridiag_step_kernel<1, WRITE>), grid, block, 0, ctx->stream, a); break;
-        case 2: hipLaunchKernelGGL((tridiag_step_kernel<2, WRITE>), grid, block, 0, ctx->stream, a); break;
-        case 3: hipLaunchKernelGGL((tridiag_step_kernel<3, WRITE>), grid, block, 0, ctx->stream, a); break;
-        default: hipLaunchKernelGGL((tridiag_step_kernel<4, WRITE>), grid, block, 0, ctx->stream, a); break;
+    switch (write ? pairs : -pairs) {
+        case 1: hipLaunchKernelGGL((tridiag_step_kernel<1, true>), grid, block, 0, ctx->stream, a); break;
+        case 2: hipLaunchKernelGGL((tridiag_step_kernel<2, true>), grid, block, 0, ctx->stream, a); break;
+        case 3: hipLaunchKernelGGL((tridiag_step_kernel<3, true>), grid, block, 0, ctx->stream, a); break;
+        case 4: hipLaunchKernelGGL((tridiag_step_kernel<4, true>), grid, block, 0, ctx->stream, a); break;
+        case 0: hipLaunchKernelGGL((tridiag_step_kernel<0, false>), grid, block, 0, ctx->stream, a); break;
+        case -1: hipLaunchKernelGGL((tridiag_step_kernel<1, false>), grid, block, 0, ctx->stream, a); break;
+        case -2: hipLaunchKernelGGL((tridiag_step_kernel<2, false>), grid, block, 0, ctx->stream, a); break;
+        default: hipLaunchKernelGGL((tridiag_step_kernel<3, false>), grid, block, 0, ctx->stream, a); break;
     }
 }
 
@@ -699,7 +695,7 @@ int tridiagonalize(aser_ctx* ctx, double* B, int64_t k, double* const* vec, doub
     auto w_of = [&](int64_t s) { return s < kFirst ? vec[2] : B + (2 * (s % kSlots) + 1) * k; };
     double* tau = vec[6];
     TridiagStep a{};
-    a.k = k; a.B = B; a.p = vec[3]; a.eff = vec[7]; a.corner = tau + 2; a.counter = (int*)(tau + 3);
+    a.k = k; a.B = B; a.p = vec[3]; a.eff = vec[7]; a.counter = (int*)(tau + 3);
     a.d = vec[4]; a.e = vec[5]; a.vstore = vstore; a.taustore = taustore;
     a.vnext = v_of(0); a.tau_next = tau;
     hipLaunchKernelGGL(tridiag_first_kernel, dim3(1), dim3(kTriThreads), 0, ctx->stream, a);
@@ -720,12 +716,9 @@ int tridiagonalize(aser_ctx* ctx, double* B, int64_t k, double* const* vec, doub
         // deferring the update pays where the traffic is what a pass costs.  Whole spectra in ms with 1 / 2 / 4 pairs pending at
         // most: k = 1024 10.60 / 10.63 / 11.31, 2048 27.3 / 26.2 / 27.2, 4096 101 / 90 / 88
         const int64_t rest = k - a.c0, most = rest >= 2048 ? kTriPairs : (rest >= 1024 ? 2 : 1);
-        if (pending > 0 && (pending >= most || s < kFirst + 1)) {
-            launch_tridiag_step<true>(ctx, (int)pending, a);
-            pending = 0;
-        } else {
-            launch_tridiag_step<false>(ctx, (int)pending, a);
-        }
+        const bool write = pending > 0 && (pending >= most || s < kFirst + 1);
+        launch_tridiag_step(ctx, write, (int)pending, a);
+        if (write) pending = 0;
         ASER_TRY(aser_check_launch(ctx, "tridiag_step"));
         ++pending;
     }
