@@ -129,6 +129,55 @@ def test_eigenvalues_of_matrices_that_end_in_one_workgroup(k):
     assert np.max(np.abs(out.cpu().numpy() ** 2 - want ** 2)) <= 16 * k * 2.0 ** -52 * want[0] ** 2
 
 
+def known_matrix(m, n, sg, seed):
+    """H_1 D H_2 with D the diagonal matrix of sg and H = I - 2 u u^T: a full matrix with known singular values and vectors."""
+    rng = np.random.default_rng(seed)
+    u, v = rng.standard_normal(m), rng.standard_normal(n)
+    u, v = u / np.linalg.norm(u), v / np.linalg.norm(v)
+    A = np.zeros((m, n))
+    A[np.arange(sg.size), np.arange(sg.size)] = sg
+    A -= 2.0 * np.outer(u, u @ A)
+    return A - 2.0 * np.outer(A @ v, v)
+
+
+@pytest.mark.parametrize("k", [1040, 1500, 2300, 3100, 4100])
+def test_eigenvalues_of_wide_full_matrices(k):
+    """Deferred updates of two and four pairs, and above 4096 the Sturm counts in pieces, on full matrices.  The bar is the rounding
+    of the matrix to fp32 (Weyl: at most its Frobenius norm) and the backward error of the fp64 chain as below."""
+    sg = np.sort(np.random.default_rng(k).uniform(0.5, 2.0, k))[::-1]
+    A = known_matrix(k, k, sg, k).astype(np.float32)
+    out = torch.empty(k, dtype=torch.float64, device=DEV)
+    ctx = new_ctx()
+    ctx.ensure_workspace(aser.aser_spectrum_workspace_bytes(k, k, False))
+    ctx.check(aser.aser_singular_values(ctx, torch.from_numpy(A).to(DEV), None, out))
+    bar = 2.0 ** -24 * np.linalg.norm(sg) + 16 * k * 2.0 ** -52 * sg[0] ** 2 / (2 * sg[-1])
+    assert np.max(np.abs(out.cpu().numpy() - sg)) <= bar
+
+
+@pytest.mark.parametrize("m,n", [(1300, 1200), (2100, 2300), (1100, 3000)])
+def test_dense_solver_keeps_its_reflectors_over_deferred_updates(m, n):
+    """A rank above the subspace iteration's, S = I: T is a known matrix with a gap behind the r-th singular value, so the product of
+    the factors is its truncation.  The bars of the other reconstruction tests (error 1e-4, product 1e-3)."""
+    r = 130
+    rng = np.random.default_rng([m, n])
+    sg = np.concatenate([np.sort(rng.uniform(2.0, 3.0, r))[::-1], np.sort(rng.uniform(0.1, 1.0, min(m, n) - r))[::-1]])
+    T = known_matrix(m, n, sg, [m, n]).astype(np.float32)
+    top = sg.copy()
+    top[r:] = 0.0
+    want, tail = known_matrix(m, n, top, [m, n]), np.linalg.norm(sg[r:])
+    ctx = new_ctx()
+    ctx.ensure_workspace(aser.aser_workspace_bytes(m, n, r))
+    L_A = torch.empty((m, r), dtype=torch.float32, device=DEV)
+    L_B = torch.empty((r, n), dtype=torch.float32, device=DEV)
+    sigma = torch.empty(r, dtype=torch.float32, device=DEV)
+    st, err, _ = aser.aser_error_reconstruct(ctx, torch.from_numpy(T).to(DEV), torch.eye(n, device=DEV), r, L_A, L_B, sigma)
+    ctx.check(st)
+    assert abs(err - tail) <= 1e-4 * tail
+    assert np.max(np.abs(sigma.cpu().numpy() - sg[:r])) <= 1e-4
+    got = L_A.double().cpu().numpy() @ L_B.double().cpu().numpy()
+    assert np.linalg.norm(got - want) <= 1e-3 * np.linalg.norm(want)
+
+
 @pytest.mark.parametrize("rows,n,m,r,bits,x_dtype,act_bits,pad", [
     (1, 32, 1, 1, 4, "bf16", 8, 0), (65, 100, 70, 9, 4, "bf16", 8, 0), (130, 96, 260, 0, 8, "bf16", 0, 8), (300, 1000, 65, 64, 8, "f32", 6, 0),
     (64, 1026, 200, 33, 4, "f32", 0, 2), (257, 320, 129, 16, 8, "bf16", 8, 1), (1700, 224, 1800, 8, 4, "bf16", 8, 0),
