@@ -458,11 +458,13 @@ def extras(ctx, aser, torch, spec, buf, W, X, reps):
         ranks[str(alpha)] = r_sel
     st, erank = aser.aser_effective_rank(ctx, sig)
     ctx.check(st)
-    pass_bytes = 16.0 * k ** 3 / 3.0
+    # a step reads the trailing matrix of c rows and writes it back once in four, two or one steps (from 2048, 1024 rows on, below);
+    # the last 256 rows are read once
+    pass_bytes = 8.0 * sum(c * c * (1.25 if c >= 2048 else 1.5 if c >= 1024 else 2.0) for c in range(257, k)) + 8.0 * min(k, 256) ** 2
     res["spectrum"] = {"ms": ms, "k": k, "rank_from_alpha": ranks, "effective_rank_of_T_S": erank,
                        "tridiagonalisation_algorithmic_bytes": pass_bytes,
-                       "note": "bound by the passes over the fp64 trailing matrix (16 k^3 / 3 bytes, served by the "
-                               "last-level cache when the matrix fits) and by 2 (k - 2) launches"}
+                       "note": "bound by the passes over the fp64 trailing matrix (served by the last-level cache when the matrix "
+                               "fits) and by one launch per column up to the last 256"}
     # a rank beyond the widest subspace block of the iteration (the rule of Eq. 9 can ask for one): the dense fp64 solver
     r_big = 200
     if min(spec.m, spec.n) >= r_big and min(spec.m, spec.n) <= 16384 and spec.r <= 128:

@@ -40,7 +40,8 @@ static inline bool aser_select_by_rounds(int64_t n, int f) { return f <= 4 + n *
 // LDS-direct schedule, 9 % for the plain grid, the medians within 2 %).  LDS-direct: 0.60 per step of the busiest workgroup and
 // 0.186 per 256 x 256 tile flush of the launch (fp32 atomics that share the memory side).  Plain: per round of 256 workgroups 1.97
 // a step and 4.3, 0.165 per flush.  Measured, plain -> LDS-direct: 1536 channels: 59 -> 42 us at 4000 tokens; 4096: 68 -> 61 at 1000, 137 -> 114 at
-// 2000, 165 -> 133 at 3000, 240 -> 197 at 5000, plain at 4000 (171) and 7503 (301); 8192: 409 -> 368 at 3000; 11008: 580 -> 467 at 2000.
+// 2000, 165 -> 133 at 3000, 240 -> 197 at 5000, 301 -> 305 at 7503, plain at 4000 (171 against 180); 8192: 409 -> 368 at 3000; 11008: 580 -> 467
+// at 2000.  Left-over tiles in more parts: 104 instead of 114 us at 2000 tokens of 4096 channels, 117 instead of 133 at 3000.
 struct AserGramSplit { int chunks, split; };
 static inline AserGramSplit aser_gram_dma_split(int64_t T, int64_t steps, int64_t parts, int64_t steps64) {
     AserGramSplit best = {0, 1};

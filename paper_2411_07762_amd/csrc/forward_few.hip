@@ -3,7 +3,7 @@
 //
 // What bounds it: reading the weight codes once (4096 x 14336 int4: 29 MB, 5.7 us at the rate of a large copy) and
 // the launches.  The tiles of the prefill kernels give such a call m / 256 workgroups that walk the whole
-// contraction one after the other, so here a workgroup owns 16 or 32 outputs and all tokens, and its wavefronts split
+// contraction one after the other, so here a workgroup owns 16, 32 or 64 outputs and up to 128 tokens, and its wavefronts split
 // the contraction: every wavefront streams its own part of the code rows from global memory straight into
 // MFMA operands (a lane's 16 bytes are 16 int8 or 32 int4 channels of its row; the order of the channels inside a
 // step is free as long as both operands agree), nothing goes through LDS on the way.  The int32 partial sums are exact and meet
