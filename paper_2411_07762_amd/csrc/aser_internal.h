@@ -196,7 +196,7 @@ int aser_col_abs_sum_w(aser_ctx* ctx, const float* W, int64_t m, int64_t n, int6
 int aser_transpose_f32(aser_ctx* ctx, const float* A, int64_t rows, int64_t cols, int64_t lda, float* At, int64_t ldat);
 
 // Small dense kernels (one workgroup, matrices in LDS)
-// Upper Cholesky of the b x b block D (ld) in place: upper part <- R (D = R^T R), the part below the diagonal is neither read nor written;
+// Upper Cholesky of the b x b block D (ld) in place: upper part <- R (D = R^T R), the part below the diagonal is not read and may be overwritten with zeros;
 // Rinv (b x b, ld = b) <- R^-1 (upper).  b <= 128.  On a non-positive pivot at column j,
 // atomicMin(info, pivot_base + j + 1) and the factor is meaningless from that column on.  clear_d: D is overwritten with
 // zeros instead of the factor (callers that only need R^-1 and reuse D as an accumulation target).

@@ -269,3 +269,31 @@ def test_reconstruction_at_the_borders_of_its_tiles(m, n):
     want = ref.L_A @ ref.L_B
     got = L_A.double().cpu().numpy() @ L_B.double().cpu().numpy()
     assert np.linalg.norm(got - want) <= 1e-3 * np.linalg.norm(want)
+
+
+@pytest.mark.parametrize("n,pad", [(1, 0), (4, 0), (17, 0), (31, 1), (32, 0), (33, 0), (64, 4), (95, 1), (96, 0), (100, 0), (127, 0), (128, 0),
+                                   (129, 3), (164, 0), (256, 8), (300, 0), (388, 0), (1100, 4), (1283, 0)])
+def test_whitening_factor_at_the_edges_of_the_blocks(n, pad):
+    """S S^T = G and the triangle against fp64; bounds from fp32 sums of n terms and 2^-16 per product (2^-24 up to 1024 channels).
+    A block that is not positive definite is reported at its first failing column, wherever that lies in the block."""
+    rng = np.random.default_rng([91, n])
+    A = rng.standard_normal((2 * n + 8, n)) * rng.uniform(0.5, 4.0, n)
+    G = (A.T @ A).astype(np.float32)
+    ref = np.linalg.cholesky(G.astype(np.float64))
+    ctx = new_ctx()
+    ctx.ensure_workspace(aser.aser_workspace_bytes(n, n, 0))
+    gd = torch.from_numpy(G).to(DEV)
+    S = torch.full((n, n + pad), 7.0, dtype=torch.float32, device=DEV)
+    st, info = aser.aser_whiten(ctx, gd, None, 0.0, S[:, :n])
+    ctx.check(st)
+    assert info == 0
+    got = S.cpu().numpy().astype(np.float64)
+    assert np.all(got[:, n:] == 7.0) and np.all(np.triu(got[:, :n], 1) == 0.0)
+    d = np.sqrt(np.diag(G.astype(np.float64)))
+    assert np.max(np.abs(got[:, :n] @ got[:, :n].T - G) / np.outer(d, d)) <= 1e-5
+    assert np.linalg.norm(got[:, :n] - ref) / np.linalg.norm(ref) <= 2e-5
+    for bad in sorted({0, n // 3, n // 2, max(0, n - 14), n - 1}):
+        broken = G.copy()
+        broken[bad, bad] = -1.0
+        st, info = aser.aser_whiten(ctx, torch.from_numpy(broken).to(DEV), None, 0.0, S[:, :n])
+        assert st == aser.ASER_ERR_NOT_SPD and info == bad + 1
