@@ -359,8 +359,63 @@ __device__ __forceinline__ void store_upper4(const float* M, float* out, int i, 
     *(float4*)out = x;
 }
 
-// The whole block; sm: kCholLdsBytes of LDS.  See aser_chol_block for the arguments.
-__device__ __forceinline__ void chol_block_body(float* sm, float* D, int64_t ld, int b, float* Rinv, int32_t* info, int32_t pivot_base,
+// The upper triangle of the b x b block D on its way to As, padded with the identity: all global loads of a thread are issued before the first
+// LDS store; 16-byte loads when the block allows it (vec).
+struct BlockLoad {
+    static constexpr int kPer = kN * kN / kCholThreads;
+    float4 v[kPer / 4];
+
+    __device__ __forceinline__ void load(const float* D, int64_t ld, int b, bool vec) {
+        const int tid = threadIdx.x;
+        if (vec) {
+#pragma unroll
+            for (int u = 0; u < kPer / 4; ++u) {
+                const int t = tid + u * kCholThreads, i = t >> 5, k = (t & 31) * 4;
+                v[u] = make_float4(k == i ? 1.f : 0.f, k + 1 == i ? 1.f : 0.f, k + 2 == i ? 1.f : 0.f, k + 3 == i ? 1.f : 0.f);
+                if (k + 3 >= i && k < b && i < b) v[u] = *(const float4*)(D + (int64_t)i * ld + k);
+            }
+        } else {
+#pragma unroll
+            for (int u = 0; u < kPer / 4; ++u) {
+                const int t = tid + u * kCholThreads, i = t >> 5, k = (t & 31) * 4;
+                float w[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    w[q] = (k + q == i) ? 1.f : 0.f;
+                    if (k + q >= i && k + q < b && i < b) w[q] = D[(int64_t)i * ld + k + q];
+                }
+                v[u] = make_float4(w[0], w[1], w[2], w[3]);
+            }
+        }
+    }
+    __device__ __forceinline__ void store(float* As) const {
+        const int tid = threadIdx.x;
+#pragma unroll
+        for (int u = 0; u < kPer / 4; ++u) {
+            const int t = tid + u * kCholThreads, i = t >> 5, k = (t & 31) * 4;
+            if (k + 3 >= i) *(float4*)(As + i * kP + k) = v[u];
+        }
+    }
+};
+
+// A block as it stands.  What chol_block_body asks of its source: load brings it to As (Xs is free until the first strips), first and rest finish the
+// 32 x 32 sub-block in the corner (wavefront 0) and everything else (the others, under the first pivot chain).
+struct PlainBlock {
+    const float* D;
+    int64_t ld;
+    int b;
+    __device__ __forceinline__ void load(float* As, float*, bool vec) const {
+        BlockLoad l;
+        l.load(D, ld, b, vec);
+        l.store(As);
+    }
+    __device__ __forceinline__ void first(float*, const float*) const {}
+    __device__ __forceinline__ void rest(float*, const float*, int) const {}
+};
+
+// The whole block; sm: kCholLdsBytes of LDS; see aser_chol_block for the other arguments.
+template <class Source>
+__device__ __forceinline__ void chol_block_body(const Source& source, float* sm, float* D, int64_t ld, int b, float* Rinv, int32_t* info, int32_t pivot_base,
                                                 int clear_d, const float* Lmul, float* Cmul, float* beta_out) {
     float* As = sm;                      // working matrix, upper triangle -> R; what stands below the diagonal is never used
     float* Xs = As + kN * kP;            // R^-1, upper 16 x 16 tiles
@@ -372,37 +427,8 @@ __device__ __forceinline__ void chol_block_body(float* sm, float* D, int64_t ld,
     // 16 x 16 tile roles of this lane
     const int t_i = lane & 15, t_q = lane >> 4;
 
-    // all global loads of a thread are issued before the first LDS store; 16-byte loads when the block allows it; padded with the identity
     const bool vec = (((uintptr_t)D | (uintptr_t)Rinv) & 15) == 0 && (ld & 3) == 0 && (b & 3) == 0;
-    if (vec) {
-        constexpr int kPer = kN * kN / 4 / kCholThreads;
-        float4 v[kPer];
-#pragma unroll
-        for (int u = 0; u < kPer; ++u) {
-            const int t = tid + u * kCholThreads, i = t >> 5, k = (t & 31) * 4;
-            v[u] = make_float4(k == i ? 1.f : 0.f, k + 1 == i ? 1.f : 0.f, k + 2 == i ? 1.f : 0.f, k + 3 == i ? 1.f : 0.f);
-            if (k + 3 >= i && k < b && i < b) v[u] = *(const float4*)(D + (int64_t)i * ld + k);
-        }
-#pragma unroll
-        for (int u = 0; u < kPer; ++u) {
-            const int t = tid + u * kCholThreads, i = t >> 5, k = (t & 31) * 4;
-            if (k + 3 >= i) *(float4*)(As + i * kP + k) = v[u];
-        }
-    } else {
-        constexpr int kPer = kN * kN / kCholThreads;
-        float v[kPer];
-#pragma unroll
-        for (int u = 0; u < kPer; ++u) {
-            const int t = tid + u * kCholThreads, i = t >> 7, k = t & 127;
-            v[u] = (k == i) ? 1.f : 0.f;
-            if (k >= i && k < b && i < b) v[u] = D[(int64_t)i * ld + k];
-        }
-#pragma unroll
-        for (int u = 0; u < kPer; ++u) {
-            const int t = tid + u * kCholThreads, i = t >> 7, k = t & 127;
-            As[i * kP + k] = v[u];
-        }
-    }
+    source.load(As, Xs, vec);
     __syncthreads();
 
     // Round kb factors diagonal sub-block kb (one wavefront), forms its row panel and its block column of the inverse, and
@@ -417,10 +443,12 @@ __device__ __forceinline__ void chol_block_body(float* sm, float* D, int64_t ld,
         // ---- 1. diagonal sub-block
         if (wave == 0) {
             __builtin_amdgcn_s_setprio(3);           // the chain shares its SIMD with one wavefront of the updates
+            if (kb == 0) source.first(As, Xs);
             pivots32(As, ops, piv, o, lane);
             __builtin_amdgcn_s_setprio(0);
         } else {
             const int op = o - kSub;
+            if (kb == 0) source.rest(As, Xs, wave);
             if (kb > 0 && (wave & 3) != 0) {             // six wavefronts: the matrix core of the chain's SIMD is left to it
                 // One place per routine: a launch starts with a cold instruction cache.  kb = 1: blocks (0, 1) (0, 2) (1, 1) (1, 2) (2, 2) and
                 // both strips of Z; 2: (0, 1) (1, 1) and four strips; 3: six strips, long and short ones paired on a SIMD.

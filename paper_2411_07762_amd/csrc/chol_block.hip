@@ -3,12 +3,12 @@
 
 namespace {
 
-__global__ __launch_bounds__(kCholThreads) void chol_block_kernel(float* D, int64_t ld, int b, float* Rinv, int32_t* info,
+__global__ __launch_bounds__(kCholThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void chol_block_kernel(float* D, int64_t ld, int b, float* Rinv, int32_t* info,
                                                                   int32_t pivot_base, int clear_d, const float* Lmul,
                                                                   float* Cmul, float* beta_out, const int* gate) {
     extern __shared__ __align__(16) float sm[];
     if (gate && *gate == 0) return;
-    chol_block_body(sm, D, ld, b, Rinv, info, pivot_base, clear_d, Lmul, Cmul, beta_out);
+    chol_block_body(PlainBlock{D, ld, b}, sm, D, ld, b, Rinv, info, pivot_base, clear_d, Lmul, Cmul, beta_out);
 }
 
 }  // namespace

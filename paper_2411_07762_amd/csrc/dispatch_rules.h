@@ -59,3 +59,14 @@ static inline AserGramSplit aser_gram_dma_split(int64_t T, int64_t steps, int64_
     }
     return best;
 }
+
+// How many finished block rows a whitening step applies at a time to the block rows that are not due yet (whiten.hip).  Fewer keep a step's
+// launch as short as the factorisation of the diagonal block beside it; more read and write the trailing matrix less often, which counts
+// once there are several tiles per compute unit.  The slower tiles (six products, or operands fetched word by word) take one.
+// Measured (us, lag 1, 2, 3, 4): 1536 columns 304, 302, 320, 352; 4096: 801, 793, 860, 973; 6000: 1440, 1324, 1460, 1620; 8192: 2393, 2065, 2101, 2175;
+// 9000: 3221, 2764, 2741, 2857; 11008: 4928, 4016, 3868, 3899; 14336: 9658, 7427, 6882, 6770; (3, 4, 6, 8): 16384: 9578, 9170, 9644, 9981; 20480: 17124,
+// 16288, 16216, 16516; 28672: 41349, 38928, 37149, 36671.  Six products, 1000 columns: 233, 247, 281, 300; word by word, 6001: 2354, 2811, 3660, 4552.
+static inline int aser_whiten_lag(int64_t n, bool slow_tiles) {
+    if (slow_tiles) return 1;
+    return n <= 8192 ? 2 : (n <= 12288 ? 3 : (n <= 18432 ? 4 : (n <= 24576 ? 6 : 8)));
+}

@@ -1,15 +1,20 @@
-// Whitening factor of Eq. 5 / Algorithm 1: S = chol(M^-1 G M^-1), blocked, one block row at a time.
+// Whitening factor of Eq. 5 / Algorithm 1: S = chol(M^-1 G M^-1), blocked, one block row of 128 at a time.
 //
 // The factorisation runs on the upper triangle (G' = R^T R, R = S^T) so that every contraction
 // has the K-major "A^T B" form of the MFMA kernel.  For block row k (rows k .. k+b):
-//   update           G'[k:k+b, k:] -= R[:k, k:k+b]^T R[:k, k:]   (A, B = the finished rows above; K = k)
+//   update           G'[k:k+b, k:] -= R[:k, k:k+b]^T R[:k, k:]   (A, B = the finished rows above)
 //   diagonal block   R11 = chol(D), R11^-1                       (one workgroup, LDS)
 //   row panel        R12 = (R11^-1)^T * G'[k, k+b:]              (A = R11^-1, B = the panel, in place)
+// The chain of diagonal blocks and panels bounds it up to about 8192 columns; the updates run beside the diagonal blocks, and the
+// products of the update from there on.  Measured (ms; update, block and panel one after the other -> this): 1024 columns 0.40 -> 0.23,
+// 2048 0.75 -> 0.40, 4096 1.69 -> 0.79, 6000 2.63 -> 1.32, 8192 3.97 -> 2.07, 11008 6.33 -> 3.87, 16384 -> 9.17, 28672 -> 36.7.
 // A final pass moves R to the lower triangle (S = R^T) and clears the strict upper triangle; writing
 // R12^T from the panel kernel instead cost 4 us per panel in scattered 16-byte stores.
 #include <limits.h>
 
-#include "aser_internal.h"
+#include "chol_block.h"
+#include "dispatch_rules.h"
+#include "gemm_tile.h"
 
 namespace {
 
@@ -95,6 +100,243 @@ __global__ __launch_bounds__(256) void upper_to_lower_kernel(float* S, int64_t n
     }
 }
 
+// One step of the factorisation in one launch (R = S^T in the upper triangle, block rows of 128; j is the current one):
+//   workgroup 0           D = S[j, j] -= R[j - 1, j]^T R[j - 1, j], then its factor and the inverse of that
+//   the next `now` ones   the rest of block row j -= R[j - 1, j]^T R[j - 1, right] (K = 128), 256 columns each
+//   all others            block rows i = j + 1, j + 1 + lag, ... -= R[j - lag .. j - 1, i]^T R[j - lag .. j - 1, right], 256 columns each
+// so a block row has received all finished rows but the last when its turn comes (at j = i - 1, and every `lag` steps before that, `lag` block
+// rows at a time).  The factorisation keeps one compute unit busy for 17 us, and nothing else here is needed before the panel that
+// follows.  Every entry has one writer per launch: with the whole contribution to block row j + 1 formed in one step, split
+// over workgroups that meet in fp32 atomics, the flushes (1.4 TB/s) took 18 of 50 us in the middle of 11008 columns.  A 128 x 256 tile
+// takes 5 us and 1.15 per K step of 32 on eight wavefronts; with operands split into bf16 pairs once, by the panel, and copied straight to LDS
+// a step takes 0.87, which changed the whole by 2 to 5 % and needs rows of whole cache lines, so that was left out.
+struct WhitenStep {
+    float* S;
+    int64_t lds, n, k0;
+    float* Rinv;
+    int32_t* info;
+    int now, lag;
+};
+
+// acc += A^T B over the first `slices` (even) 16-deep slices of a K = 128 product whose operands stand in LDS as four K steps of 32 in the layout of
+// tile_body (chunks [term][k / 8][column]); pa, pb: this lane's chunk of the first step.  Four slices' operands are read at a time.
+template <int IN, int BMA, int BMB>
+__device__ __forceinline__ void mfma_k128(f32x16_t& acc, const uint4* pa, const uint4* pb, int slices) {
+    constexpr int NP = InTraits<IN>::NP, KB = 4;
+    for (int s0 = 0; s0 < slices; s0 += 4) {
+        bf16x8_t a[4][NP], b[4][NP];
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int p = 0; p < NP; ++p) {
+                a[s][p] = __builtin_bit_cast(bf16x8_t, pa[((s >> 1) * NP * KB + p * KB + 2 * (s & 1)) * BMA]);
+                b[s][p] = __builtin_bit_cast(bf16x8_t, pb[((s >> 1) * NP * KB + p * KB + 2 * (s & 1)) * BMB]);
+            }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            if (s == 2 && s0 + 2 >= slices) break;
+#pragma unroll
+            for (int q = NP - 1; q >= 0; --q)             // terms whose orders add up to q, the smallest products first
+#pragma unroll
+                for (int p = 0; p <= q; ++p) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[s][q - p], b[s][p], acc, 0, 0, 0);
+        }
+        pa += 2 * NP * KB * BMA;
+        pb += 2 * NP * KB * BMB;
+    }
+}
+
+// D -= P^T P for the 128 x b block P (the operand form IN), D on its way to As.  Two and three terms of P take 64 and 96 KB; the former fit beside As, so
+// only the corner is finished before the pivot chain starts.
+template <int IN, bool FAST>
+struct UpdatedBlock {
+    static constexpr int NP = InTraits<IN>::NP, kStage = NP * 4 * kNb;      // chunks of one K step of 32
+    static constexpr bool kBeside = (size_t)4 * kStage * 16 <= (size_t)kN * kP * 4;
+    const float* D;
+    const float* P;                                       // null: nothing to subtract
+    int64_t ld;
+    int b;
+
+    // tile t of the ten 32 x 32 tiles of the upper triangle: (0,0) (0,1) (0,2) (0,3) (1,1) (1,2) (1,3) (2,2) (2,3) (3,3)
+    static __device__ __forceinline__ void place(int t, int* ti, int* tj) {
+        *ti = t < 4 ? 0 : (t < 7 ? 1 : (t < 9 ? 2 : 3));
+        *tj = t < 4 ? t : (t < 7 ? t - 3 : (t < 9 ? t - 5 : 3));
+    }
+    static __device__ __forceinline__ void product(const float* stage, int t, f32x16_t& c) {
+        const int lane = threadIdx.x & 63;
+        int ti, tj;
+        place(t, &ti, &tj);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) c[e] = 0.f;
+        const uint4* st = (const uint4*)stage + (lane >> 5) * kNb;
+        mfma_k128<IN, kNb, kNb>(c, st + swz(32 * ti + (lane & 31)), st + swz(32 * tj + (lane & 31)), 8);
+    }
+    __device__ __forceinline__ void subtract(float* As, int t, const f32x16_t& c) const {
+        const int lane = threadIdx.x & 63;
+        int ti, tj;
+        place(t, &ti, &tj);
+        const int col = 32 * tj + (lane & 31), row = 32 * ti + 4 * (lane >> 5);
+        float* out = As + row * kP + col;
+        if (col >= b) return;                             // rows beyond b lie below the diagonal there
+        float old[16];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) old[e] = out[(8 * (e >> 2) + (e & 3)) * kP];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) out[(8 * (e >> 2) + (e & 3)) * kP] = old[e] - c[e];
+    }
+
+    __device__ __forceinline__ void load(float* As, float* Xs, bool vec) const {
+        const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+        BlockLoad d;
+        if (!P) {
+            d.load(D, ld, b, vec);
+            d.store(As);
+            return;
+        }
+        float* stage = kBeside ? Xs : As;
+        Fetch<IN, kNb, FAST> f;
+        Staged r;
+        const int step = tid >> 7;
+        f.init(P, ld, 0, b, 32 * step, kNb, tid & 127);
+        f.load(r, kNb);
+        d.load(D, ld, b, vec);
+        f.store(r, (uint4*)stage + step * kStage);
+        if (kBeside) {
+            d.store(As);
+            return;
+        }
+        __syncthreads();
+        f32x16_t acc[2];
+        product(stage, wave, acc[0]);
+        if (wave < 2) product(stage, 8 + wave, acc[1]);
+        __syncthreads();
+        d.store(As);
+        __syncthreads();
+        subtract(As, wave, acc[0]);
+        if (wave < 2) subtract(As, 8 + wave, acc[1]);
+    }
+    __device__ __forceinline__ void first(float* As, const float* Xs) const {
+        if (!kBeside || !P) return;
+        f32x16_t c;
+        product(Xs, 0, c);
+        subtract(As, 0, c);
+    }
+    __device__ __forceinline__ void rest(float* As, const float* Xs, int wave) const {
+        if (!kBeside || !P) return;
+        for (int t = wave; t < 10; t += 7) {              // wavefronts 1 .. 7; the ones with two tiles are not on the chain's SIMD
+            f32x16_t c;
+            product(Xs, t, c);
+            subtract(As, t, c);
+        }
+    }
+};
+
+template <int IN, bool FAST>
+__global__ __launch_bounds__(kCholThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void whiten_step_kernel(WhitenStep w) {
+    extern __shared__ __align__(16) uint4 smem[];
+    const int64_t rem = w.n - w.k0;
+    if (blockIdx.x == 0) {
+        const int b = (int)(rem < kNb ? rem : kNb);
+        float* D = w.S + w.k0 * w.lds + w.k0;
+        const UpdatedBlock<IN, FAST> source{D, w.k0 ? D - kNb * w.lds : nullptr, w.lds, b};
+        chol_block_body(source, (float*)smem, D, w.lds, b, w.Rinv, w.info, (int32_t)w.k0, 0, nullptr, nullptr, nullptr);
+        return;
+    }
+    int t = (int)blockIdx.x - 1;
+    int64_t kBeg = w.k0 - kNb;
+    int64_t row = w.k0, col = w.k0 + kNb;                 // first row and column of the block row's part
+    if (t >= w.now) {
+        t -= w.now;
+        kBeg = w.k0 > w.lag * kNb ? w.k0 - w.lag * kNb : 0;
+        row = col;
+        for (;;) {
+            const int tiles = (int)((w.n - row + 255) / 256);
+            if (t < tiles) break;
+            t -= tiles;
+            row += w.lag * kNb;
+        }
+        col = row;
+    }
+    GemmArgs g{};
+    g.lda = g.ldb = g.ldc = w.lds;
+    g.alpha = -1.f;
+    g.A = w.S + row;
+    g.B = w.S + col;
+    g.C = w.S + row * w.lds + col;
+    g.M = w.n - row < kNb ? w.n - row : kNb;
+    g.N = w.n - col;
+    g.K = w.k0;
+    tile_body_wide<IN, 128, 256, FAST, true>(g, 0, (int64_t)t * 256, kBeg, w.k0, smem);
+}
+
+template <int IN, bool FAST>
+int launch_step(aser_ctx* ctx, const WhitenStep& w) {
+    static bool attr_set[16] = {false};
+    constexpr size_t lds = kCholLdsBytes > TileCfg<IN, 128, 256>::LDS_BYTES ? kCholLdsBytes : TileCfg<IN, 128, 256>::LDS_BYTES;
+    auto kern = whiten_step_kernel<IN, FAST>;
+    if (ctx->device >= 0 && ctx->device < 16 && !attr_set[ctx->device]) {
+        ASER_HIP(ctx, hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+        attr_set[ctx->device] = true;
+    }
+    int64_t groups = 1 + w.now;
+    if (w.now)
+        for (int64_t row = w.k0 + kNb; row < w.n; row += w.lag * kNb) groups += ceil_div64(w.n - row, 256);
+    hipLaunchKernelGGL(kern, dim3((unsigned)groups), dim3(kCholThreads), lds, ctx->stream, w);
+    return aser_check_launch(ctx, "whiten_step");
+}
+
+// Row panel: the 128 rows from k0 on, right of the diagonal block, become (R11^-1)^T times themselves, 64 columns per workgroup.  K is 128 only, so
+// all operands are fetched at once and there is one wait and one barrier: 4.7 us a launch at 4096 columns (9.4 with four K steps
+// through the tiles of the other products).
+template <int IN, bool FAST>
+__global__ __launch_bounds__(kCholThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void whiten_panel_kernel(WhitenStep w) {
+    extern __shared__ __align__(16) uint4 smem[];
+    constexpr int NP = InTraits<IN>::NP, KB = 4, BN = 64;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    float* C = w.S + w.k0 * w.lds + w.k0 + kNb;
+    const int64_t N = w.n - w.k0 - kNb, J0 = (int64_t)blockIdx.x * BN;
+    uint4* sb = smem + 4 * NP * KB * kNb;
+    const int step = tid >> 7, unit = tid & 127;
+    {
+        Fetch<IN, kNb, true> fa;
+        FetchRows<IN, BN, 4, FAST> fb;
+        Staged ra;
+        uint4 rb[4];
+        fa.init(w.Rinv, kNb, 0, kNb, 32 * step, kNb, unit);
+        fb.init(C, w.lds, J0, N, 32 * step, kNb, unit);
+        fa.load(ra, kNb);
+        fb.load(rb, kNb);
+        __builtin_amdgcn_sched_barrier(0);
+        fa.store(ra, smem + step * NP * KB * kNb);
+        fb.store(rb, sb + step * NP * KB * BN);
+    }
+    __syncthreads();
+    // row tile i needs k < 32 (i + 1): the two wavefronts of a SIMD take a long and a short one
+    const int ti = wave < 4 ? wave : 7 - wave, tj = (wave >> 2) ^ (ti & 1);
+    f32x16_t acc;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+    mfma_k128<IN, kNb, BN>(acc, smem + (lane >> 5) * kNb + swz(32 * ti + (lane & 31)), sb + (lane >> 5) * BN + swz(32 * tj + (lane & 31)), 2 * (ti + 1));
+    const int64_t col = J0 + 32 * tj + (lane & 31);
+    float* out = C + (int64_t)(32 * ti + 4 * (lane >> 5)) * w.lds + col;
+    if (col >= N) return;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) out[(int64_t)(8 * (e >> 2) + (e & 3)) * w.lds] = acc[e];
+}
+
+template <int IN, bool FAST>
+int launch_panel(aser_ctx* ctx, const WhitenStep& w) {
+    static bool attr_set[16] = {false};
+    constexpr size_t lds = (size_t)4 * InTraits<IN>::NP * 4 * (kNb + 64) * 16;
+    auto kern = whiten_panel_kernel<IN, FAST>;
+    if (ctx->device >= 0 && ctx->device < 16 && !attr_set[ctx->device]) {
+        ASER_HIP(ctx, hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+        attr_set[ctx->device] = true;
+    }
+    hipLaunchKernelGGL(kern, dim3((unsigned)ceil_div64(w.n - w.k0 - kNb, 64)), dim3(kCholThreads), lds, ctx->stream, w);
+    return aser_check_launch(ctx, "whiten_panel");
+}
+
 }  // namespace
 
 extern "C" int aser_whiten(aser_ctx* ctx, const float* G, int64_t ldg, int64_t n, const float* mdiag, float damp,
@@ -124,52 +366,18 @@ extern "C" int aser_whiten(aser_ctx* ctx, const float* G, int64_t ldg, int64_t n
                        mdiag, S, lds, (const double*)diag_sum, damp);
     ASER_TRY(aser_check_launch(ctx, "whiten_prep"));
 
-    // Up-looking blocked Cholesky on the upper triangle (R = S^T): block row j first receives the
-    // contribution of all finished rows above it in one product with a long K (split over
-    // workgroups, fp32 atomics), then its diagonal block is factored and the row is multiplied by
-    // the inverse of that factor.  Every entry of the matrix is updated once, by one launch.
-    // Wide matrices take the long-K update for two block rows at a time (256 x 256 tiles convert each
-    // fp32 operand element once per 256 instead of 128 result columns or rows); the second block row of
-    // a pair then still lacks the contribution of the first, a K = 128 update of its own.
-    // measured (ms, one block row at a time / in pairs): 11008 columns 6.3 / 7.2, 14336 9.7 / 10.4, 20480 21.1 / 19.6, 28672 47.7 / 40.1
-    const bool pairs = n >= 16384;
-    const int form = aser_f32_form(ctx, n * n);   // three or six bf16 products per fp32 product
-    const bool six = form == GEMM_IN_F32X6;
-    auto update = [&](int64_t row0, int64_t rows, int64_t kfrom, int64_t klen, int bm, int bn) -> int {
-        GemmArgs u{};
-        u.A = S + kfrom * lds + row0; u.lda = lds; u.B = S + kfrom * lds + row0; u.ldb = lds;
-        u.C = S + row0 * lds + row0; u.ldc = lds; u.Ct = nullptr; u.ldct = 0;
-        u.M = rows; u.N = n - row0; u.K = klen; u.alpha = -1.f;
-        u.in_type = form; u.epi = GEMM_EPI_ATOMIC; u.tiles = GEMM_TILES_ALL; u.krange = GEMM_K_FULL;
-        if (six && bm == 256 && bn == 256) bn = 128;    // the six-product form has no 256 x 256 tile
-        u.bm = bm; u.bn = bn; u.upper_only = 1;
-        const int64_t tiles = ceil_div64(u.M, u.bm) * ceil_div64(u.N, u.bn), ksteps = ceil_div64(klen, 32);
-        u.k_parts = aser_split_k_parts(tiles, ksteps, 4, (double)(bm * bn) / (128.0 * 128.0), ctx->share);
-        return aser_gemm_tn(ctx, u);
-    };
+    // Blocked Cholesky on the upper triangle (R = S^T), a block row at a time: two launches per block row, the step (see WhitenStep) and the row panel.
+    const bool six = aser_f32_form(ctx, n * n) == GEMM_IN_F32X6;     // three or six bf16 products per fp32 product
+    const bool fast = ((uintptr_t)S & 15) == 0 && (lds & 3) == 0 && (n & 3) == 0;
+    const int lag = aser_whiten_lag(n, six || !fast);
     for (int64_t k0 = 0; k0 < n; k0 += kNb) {
-        const int b = (int)((n - k0 < kNb) ? n - k0 : kNb);
-        float* D = S + k0 * lds + k0;
-        if (pairs) {
-            if (k0 % (2 * kNb) == 0) {
-                if (k0 > 0) ASER_TRY(update(k0, (n - k0 < 2 * kNb) ? n - k0 : 2 * kNb, 0, k0, 256, 256));
-            } else {
-                ASER_TRY(update(k0, b, k0 - kNb, kNb, 128, 128));   // K = 128 only, as the row panel: many small tiles
-            }
-        } else if (k0 > 0) {
-            ASER_TRY(update(k0, b, 0, k0, 128, 128));
-        }
-        ASER_TRY(aser_chol_block(ctx, D, lds, b, Rinv, info_dev, (int32_t)k0));
-        const int64_t rem = n - k0 - b;
-        if (rem <= 0) break;
-        float* S12 = S + k0 * lds + (k0 + b);
-        GemmArgs p{};
-        p.A = Rinv; p.lda = b; p.B = S12; p.ldb = lds; p.C = S12; p.ldc = lds;
-        p.Ct = nullptr; p.ldct = 0;
-        p.M = b; p.N = rem; p.K = b; p.alpha = 1.f;
-        p.in_type = form; p.epi = GEMM_EPI_STORE; p.tiles = GEMM_TILES_ALL; p.krange = GEMM_K_FULL;
-        p.k_parts = 1; p.bm = 128; p.bn = 128;           // K = 128 only: twice the workgroups beat the wider tile (16.6 -> 12 us at c1)
-        ASER_TRY(aser_gemm_tn(ctx, p));
+        const int64_t right = n - k0 - kNb;              // columns to the right of the block
+        const WhitenStep w{S, lds, n, k0, Rinv, info_dev, (k0 > 0 && right > 0) ? (int)ceil_div64(right, 256) : 0, lag};
+        ASER_TRY(six ? (fast ? launch_step<GEMM_IN_F32X6, true>(ctx, w) : launch_step<GEMM_IN_F32X6, false>(ctx, w))
+                     : (fast ? launch_step<GEMM_IN_F32X3, true>(ctx, w) : launch_step<GEMM_IN_F32X3, false>(ctx, w)));
+        if (right > 0)
+            ASER_TRY(six ? (fast ? launch_panel<GEMM_IN_F32X6, true>(ctx, w) : launch_panel<GEMM_IN_F32X6, false>(ctx, w))
+                         : (fast ? launch_panel<GEMM_IN_F32X3, true>(ctx, w) : launch_panel<GEMM_IN_F32X3, false>(ctx, w)));
     }
     hipLaunchKernelGGL(upper_to_lower_kernel, dim3((unsigned)(t64 * (t64 + 1) / 2)), dim3(256), 0, ctx->stream, S, n, lds);
     ASER_TRY(aser_check_launch(ctx, "upper_to_lower"));

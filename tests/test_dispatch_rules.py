@@ -103,3 +103,19 @@ def test_gram_chunks_take_the_faster_schedule_and_keep_their_number_of_parts(rul
             per_round = 256 // c
             counts = ([c] if tiles >= per_round else []) + ([c * split] if tiles % per_round else [])
             assert all(parts <= k and 3 * k <= 4 * parts for k in counts), (n, rows, c, split, parts)
+
+
+# columns, slow tiles; us with 1, 2, 3, 4, 6, 8 block rows at a time (None: not measured)
+WHITEN = [
+    (1536, 0, 304, 302, 320, 352, None, None), (4096, 0, 801, 793, 860, 973, None, None), (6000, 0, 1440, 1324, 1460, 1620, None, None),
+    (8192, 0, 2393, 2065, 2101, 2175, None, None), (9000, 0, 3221, 2764, 2741, 2857, None, None), (11008, 0, 4928, 4016, 3868, 3899, None, None),
+    (14336, 0, 9658, 7427, 6882, 6770, None, None), (16384, 0, None, None, 9578, 9170, 9644, 9981), (20480, 0, None, None, 17124, 16288, 16216, 16516),
+    (28672, 0, None, None, 41349, 38928, 37149, 36671), (1000, 1, 233, 247, 281, 300, None, None), (6001, 1, 2354, 2811, 3660, 4552, None, None),
+]
+
+
+def test_block_rows_a_whitening_step_applies_at_a_time(rule):
+    got = rule("whiten", 'printf("%d", aser_whiten_lag(a[0], a[1] != 0));', [q[:2] for q in WHITEN])
+    for q, (lag,) in zip(WHITEN, got):
+        times = dict(zip((1, 2, 3, 4, 6, 8), q[2:]))
+        assert times[lag] <= 1.03 * min(t for t in times.values() if t), q
