@@ -42,9 +42,9 @@ static inline bool aser_select_by_rounds(int64_t n, int f) { return f <= 4 + n *
 // a step and 4.3, 0.165 per flush.  Measured, plain -> LDS-direct: 1536 channels: 59 -> 42 us at 4000 tokens; 4096: 68 -> 61 at 1000, 137 -> 114 at
 // 2000, 165 -> 133 at 3000, 240 -> 197 at 5000, 301 -> 305 at 7503, plain at 4000 (171 against 180); 8192: 409 -> 368 at 3000; 11008: 580 -> 467
 // at 2000.  Left-over tiles in more parts: 104 instead of 114 us at 2000 tokens of 4096 channels, 117 instead of 133 at 3000.
-struct AserGramSplit { int chunks, split; };
+struct AserGramSplit { int chunks, split; double cost; };
 static inline AserGramSplit aser_gram_dma_split(int64_t T, int64_t steps, int64_t parts, int64_t steps64) {
-    AserGramSplit best = {0, 1};
+    AserGramSplit best = {0, 1, 0.0};
     double best_cost = (double)((T * parts + 255) / 256) * (1.97 * (double)steps64 + 4.3) + 0.165 * (double)(T * parts) + 4.1;
     for (int c = 1; c <= 8; c *= 2) {
         const int64_t W = 256 / c, full = T / W, rem = T % W, steps_c = (steps + c - 1) / c;
@@ -54,7 +54,32 @@ static inline AserGramSplit aser_gram_dma_split(int64_t T, int64_t steps, int64_
             const int64_t last = rem ? (steps_c + sp - 1) / sp : 0;
             if (sp > 1 && last < 4) break;                  // the ring is filled once
             const double cost = 0.60 * (double)(full * steps_c + last) + 0.186 * (double)(c * (full * W + rem * sp)) + 8.9;
-            if (cost <= best_cost) { best_cost = cost; best = AserGramSplit{c, (int)sp}; }     // equal: more chunks, fewer XCDs on one slab
+            if (cost <= best_cost) { best_cost = cost; best = AserGramSplit{c, (int)sp, 0.0}; }     // equal: more chunks, fewer XCDs on one slab
+        }
+    }
+    best.cost = best_cost;
+    return best;
+}
+
+// The same call on 256 x 128 tiles whose sums have two levels (gram_seg_kernel): the fp32 chains are half as long as those of `parts` K parts
+// whatever the split, and G is rounded once per chunk (left-over tiles: per chunk and part, at most a third more often than by the plain grid).
+// T: 256 x 128 tiles of the lower triangle.  Root mean square error of the diagonal over four seeds, without -> with, in 1e-8: 4096 channels, four
+// calls of 7503 tokens 10.3 -> 6.9, of 3000 10.9 -> 7.9; 2048, four of 6000 10.6 -> 7.4; 1536, eight of 2000 9.0 -> 7.2; 8192, two of 3000 12.8 -> 8.6.
+// Costs fitted to the same range (half of 200 figures within 3 %): 0.47 us per step of the busiest workgroup, 0.084 per tile flush.  It is taken
+// where it promises 3 %, because the other models are that good.  Measured, without -> with: 1536 channels: 39 -> 31 us at 1000 tokens, 62 -> 53
+// at 6000; 4096: 146 -> 106 at 3000, 203 -> 130 at 4300, 317 -> 179 at 7500, not at 1800 (85 against 93); 6144: 307 -> 230 at 4300; 8192: 367 -> 316
+// at 3000, not at 7500 (605 against 609); 14336: never (728 against 836 at 3000).
+static inline AserGramSplit aser_gram_seg_split(int64_t T, int64_t steps, int64_t parts) {
+    AserGramSplit best = {0, 1, 1e30};
+    for (int c = 1; c <= 8; c *= 2) {
+        if (c > 1 && 3 * c > 4 * parts) break;
+        const int64_t W = 256 / c, full = T / W, rem = T % W, steps_c = (steps + c - 1) / c;
+        for (int64_t sp = 1; sp <= (rem ? W / rem : 1); ++sp) {
+            if (c * sp > 1 && rem && 3 * c * sp > 4 * parts) break;
+            const int64_t last = rem ? (steps_c + sp - 1) / sp : 0;
+            if (sp > 1 && last < 4) break;
+            const double cost = 0.47 * (double)(full * steps_c) + 0.458 * (double)last + 0.084 * (double)(c * (full * W + rem * sp)) + 8.5;
+            if (cost < best.cost) best = AserGramSplit{c, (int)sp, cost};
         }
     }
     return best;

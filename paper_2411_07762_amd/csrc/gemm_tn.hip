@@ -438,6 +438,219 @@ int launch_gram_dma(aser_ctx* ctx, const GemmArgs& g) {
     return aser_check_launch(ctx, "gram_dma");
 }
 
+// One 256 x 128 tile of G over tokens [kBeg, kEnd), with sums in two levels (bound by the operand stream, 24 KB per 0.47 us and compute unit, and by the
+// flush, 0.084 us per tile of the launch; both figures from fits over 70 sizes): every `seg` steps of 32 tokens the accumulators of the MFMAs are
+// added to a second set and start anew, so the fp32 chains are as short as with a flush to G every `seg` steps and G is
+// touched once.  (The 256 x 256 tile has no registers for a second set.)  Data path as in gram_tile_dma, for slabs of 256 and 128 channels in a
+// ring of six stages of 24 KB; four wavefronts of 128 x 64.
+constexpr int kSegStages = 6;
+constexpr int kSegStageBytes = kDmaBK * (512 + 256);
+constexpr size_t kSegLdsBytes = (size_t)kSegStages * kSegStageBytes;
+
+__device__ __forceinline__ void gram_tile_seg(const GemmArgs& g, int64_t I0, int64_t J0, int64_t kBeg, int64_t kEnd, int seg, char* smem) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm0 = (wave >> 1) * 128, wn0 = (wave & 1) * 64;
+
+    // ---- fetch roles: rows 8 wave .. 8 wave + 7 of both slabs; of A two rows of 32 chunks per load (0 .. 3), of B four rows of 16 (4, 5).  Chunk c of
+    // row k stands in slot c ^ 4 (k & 3).
+    const char* zero = (const char*)g_zero_chunk;
+    const int64_t ld_bytes = g.lda * 2;
+    const char* gp[6];
+    int64_t gstep[6];
+    int krow[6];                                          // slab row of this lane in each load
+#pragma unroll
+    for (int t = 0; t < 6; ++t) {
+        krow[t] = 8 * wave + (t < 4 ? 2 * t + (lane >> 5) : 4 * (t - 4) + (lane >> 4));
+        const int chunk = (t < 4 ? (lane & 31) : (lane & 15)) ^ (4 * (krow[t] & 3));
+        const int64_t c = (t < 4 ? I0 : J0) + 8 * chunk;
+        const bool in = c < g.M;                          // M == N
+        gp[t] = in ? (const char*)g.A + c * 2 + (kBeg + krow[t]) * ld_bytes : zero;
+        gstep[t] = in ? kDmaBK * ld_bytes : 0;
+    }
+    const uint32_t ring = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
+    const uint32_t dst_a = ring + wave * 4096, dst_b = ring + kDmaBK * 512 + wave * 2048;
+    auto issue_one = [&](int stage, int t, int64_t first, bool tail) {      // first: token of the stage's first row
+        const char* src = gp[t];
+        if (tail && first + krow[t] >= kEnd) src = zero;
+        const uint32_t dst = (uint32_t)(stage * kSegStageBytes) + (t < 4 ? dst_a + t * 1024 : dst_b + (t - 4) * 1024);
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(dst), "v"(src) : "memory", "m0");
+        gp[t] += gstep[t];
+    };
+
+    // ---- operand read offsets inside a stage, first of the four (k16 slice, half) reads
+    int offa[4], offb[2];
+    {
+        const int kr = 8 * (lane >> 5) + ((lane & 15) >> 2);
+        const int xr = 4 * ((lane & 15) >> 2);
+        const int msub = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int ma = wm0 + 32 * i + msub;
+            offa[i] = kr * 512 + (((ma >> 3) ^ xr) * 16) + (ma & 7) * 2;
+        }
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int mb = wn0 + 32 * j + msub;
+            offb[j] = kDmaBK * 512 + kr * 256 + (((mb >> 3) ^ xr) * 16) + (mb & 7) * 2;
+        }
+    }
+
+    f32x16_t acc[4][2], sum[4][2];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][j][e] = sum[i][j][e] = 0.f;
+
+    const int nsteps = (int)((kEnd - kBeg + kDmaBK - 1) / kDmaBK);
+    const int full_steps = (int)((kEnd - kBeg) / kDmaBK);            // stages without ragged rows
+    __syncthreads();                                     // the previous tile's readers are done with the ring
+    for (int s = 0; s < kSegStages - 1 && s < nsteps; ++s) {
+        const int64_t first = kBeg + (int64_t)s * kDmaBK;
+#pragma unroll
+        for (int t = 0; t < 6; ++t) issue_one(s, t, first, s >= full_steps);
+    }
+    if (nsteps >= kSegStages - 1) __builtin_amdgcn_s_waitcnt(0x4F78);       // vmcnt(24): stage 0 landed
+    else __builtin_amdgcn_s_waitcnt(0x0F70);                         // vmcnt(0)
+    __syncthreads();
+    bf16x8_t a0[4], b0[2], a1[4], b1[2];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) a0[i] = lds_tr_frag(smem + offa[i], 0, 4 * 512);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) b0[j] = lds_tr_frag(smem + offb[j], 0, 4 * 256);
+
+    int stage = 0, left = seg;
+    // STEADY steps have a successor, a stage to fetch and no ragged rows in it
+    auto step = [&](int s, auto steady_tag) {
+        constexpr bool STEADY = decltype(steady_tag)::value;
+        const int nstage = stage == kSegStages - 1 ? 0 : stage + 1, fstage = stage == 0 ? kSegStages - 1 : stage - 1;
+        const char* st = smem + stage * kSegStageBytes;
+        const char* sn = smem + nstage * kSegStageBytes;
+        const bool more = STEADY || s + 1 < nsteps;
+        const bool fetch = STEADY || s + kSegStages - 1 < nsteps;
+        const int64_t first = kBeg + (int64_t)(s + kSegStages - 1) * kDmaBK;
+        const bool tail = !STEADY && s + kSegStages - 1 >= full_steps;
+        // slice 0: the operands of slice 1 are read between its products
+#pragma unroll
+        for (int m = 0; m < 8; ++m) {
+            acc[m >> 1][m & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0[m >> 1], b0[m & 1], acc[m >> 1][m & 1], 0, 0, 0);
+            if (m < 2) b1[m] = lds_tr_frag(st + offb[m], 16 * 256, 20 * 256);
+            else if (m < 6) a1[m - 2] = lds_tr_frag(st + offa[m - 2], 16 * 512, 20 * 512);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        // slice 1: the wait and the barrier, the loads of stage s + 5, the operands of the next step's slice 0
+#pragma unroll
+        for (int m = 0; m < 8; ++m) {
+            acc[m >> 1][m & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1[m >> 1], b1[m & 1], acc[m >> 1][m & 1], 0, 0, 0);
+            if (m == 1 && more) {
+                if (STEADY) __builtin_amdgcn_s_waitcnt(0x4F72);      // vmcnt(18): stage s + 1 has landed, three more may be in flight
+                else __builtin_amdgcn_s_waitcnt(0x0F70);             // vmcnt(0)
+                __syncthreads();                                     // everyone's share landed; stage s - 1 is free
+            }
+            if (m >= 2 && fetch) issue_one(fstage, m - 2, first, tail);
+            if (m >= 2 && more) {
+                if (m < 4) b0[m - 2] = lds_tr_frag(sn + offb[m - 2], 0, 4 * 256);
+                else a0[m - 4] = lds_tr_frag(sn + offa[m - 4], 0, 4 * 512);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        stage = nstage;
+        if (--left == 0 || (!STEADY && s + 1 == nsteps)) {
+            left = seg;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) {
+                        sum[i][j][e] += acc[i][j][e];
+                        acc[i][j][e] = 0.f;
+                    }
+        }
+    };
+    int s = 0;
+    for (; s + kSegStages - 1 < full_steps; ++s) step(s, std::true_type{});
+    for (; s < nsteps; ++s) step(s, std::false_type{});
+
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int64_t col = J0 + wn0 + 32 * j + (lane & 31);
+            const int64_t rbase = I0 + wm0 + 32 * i + 4 * (lane >> 5);
+            if (col >= g.N) continue;
+            float* cbase = g.C + rbase * g.ldc + col;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const int dr = 8 * (e >> 2) + (e & 3);
+                if (rbase + dr < g.M) unsafeAtomicAdd(cbase + (int64_t)dr * g.ldc, sum[i][j][e]);
+            }
+        }
+}
+
+// Tile t of the lower triangle in 256 x 128 tiles: strips of 8 tile columns, row by row, so that 32 consecutive ones are about a 4 x 8 patch.
+__device__ __forceinline__ void tri_strip_half_tile(int64_t t, int nt, int* p_out, int* q_out) {
+    for (int q0 = 0; q0 < 2 * nt; q0 += 8)
+        for (int p = q0 / 2; p < nt; ++p) {
+            const int cnt = (2 * p + 2 - q0 < 8) ? (2 * p + 2 - q0) : 8;
+            if (t < cnt) { *p_out = p; *q_out = q0 + (int)t; return; }
+            t -= cnt;
+        }
+    *p_out = 0; *q_out = 0;
+}
+
+// The schedule of gram_dma_kernel on 256 x 128 tiles with two-level sums.
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))) void gram_seg_kernel(GemmArgs g, int seg) {
+    extern __shared__ uint4 smem[];
+    constexpr int BK = kDmaBK;
+    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+    const int slots = gridDim.x >> 3;
+    const int C = g.k_parts;
+    const int gsz = 8 / C;
+    const int chunk = xcd / gsz, xi = xcd % gsz;
+    const int64_t W = (int64_t)gsz * slots;
+    const int64_t widx = (int64_t)xi * slots + slot;
+    const int nt = (int)((g.N + 255) / 256);
+    const int64_t T = (int64_t)nt * (nt + 1);
+    const int64_t ksteps = (g.K + BK - 1) / BK;
+    const int64_t per = (ksteps + C - 1) / C;
+    const int64_t kx0 = (int64_t)chunk * per * BK;
+    int64_t kx1 = kx0 + per * BK;
+    if (kx1 > g.K) kx1 = g.K;
+    if (kx0 >= kx1) return;
+    const int64_t full = T / W, rem = T % W;
+    const int64_t split = g.split;
+    const int64_t rounds = full + ((rem > 0 && widx < rem * split) ? 1 : 0);
+    for (int64_t round = 0; round < rounds; ++round) {
+        int64_t t = round * W + widx, k0 = kx0, k1 = kx1;
+        if (round == full) {
+            t = full * W + widx % rem;
+            const int64_t xsteps = (kx1 - kx0 + BK - 1) / BK;
+            const int64_t pp = (xsteps + split - 1) / split;
+            k0 = kx0 + (widx / rem) * pp * BK;
+            k1 = k0 + pp * BK;
+            if (k1 > kx1) k1 = kx1;
+            if (k0 >= k1) break;
+        }
+        int p, q;
+        tri_strip_half_tile(t, nt, &p, &q);
+        if ((int64_t)q * 128 >= g.N) continue;           // the second half of a ragged last tile
+        gram_tile_seg(g, (int64_t)p * 256, (int64_t)q * 128, k0, k1, seg, (char*)smem);
+    }
+}
+
+int launch_gram_seg(aser_ctx* ctx, const GemmArgs& g, int seg) {
+    static bool attr_set[16] = {false};
+    if (ctx->device >= 0 && ctx->device < 16 && !attr_set[ctx->device]) {
+        ASER_HIP(ctx, hipFuncSetAttribute((const void*)gram_seg_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSegLdsBytes));
+        attr_set[ctx->device] = true;
+    }
+    hipLaunchKernelGGL(gram_seg_kernel, dim3(256), dim3(kThreads), kSegLdsBytes, ctx->stream, g, seg);
+    return aser_check_launch(ctx, "gram_seg");
+}
+
 template <int IN>
 int launch_gram_persistent(aser_ctx* ctx, const GemmArgs& g) {
     if (operands_fast<IN>(g)) return launch_gram_persistent2<IN, true>(ctx, g);
@@ -506,6 +719,11 @@ int aser_syrk_gram(aser_ctx* ctx, const void* X, int x_dtype, int64_t rows, int6
     // wide channels are all flushes (256 of 3584: 31.5 us against 32.2, of 8192: 148 against 160)
     if (n > 1024 && rows >= (n > 5120 ? 512 : (n > 2560 ? 384 : 256)) && g.in_type == GEMM_IN_BF16 && operands_fast<GEMM_IN_BF16>(g)) {
         const AserGramSplit sp = aser_gram_dma_split(T256, ceil_div64(rows, kDmaBK), parts, ceil_div64(ksteps, parts));
+        const AserGramSplit sg = aser_gram_seg_split(2 * T256, ceil_div64(rows, kDmaBK), parts);
+        if (sg.cost < 0.97 * sp.cost) {
+            g.k_parts = sg.chunks; g.split = sg.split;
+            return launch_gram_seg(ctx, g, (int)ceil_div64(ceil_div64(rows, kDmaBK), 2 * parts));
+        }
         if (sp.chunks > 0) {
             g.k_parts = sp.chunks; g.split = sp.split;
             return launch_gram_dma(ctx, g);

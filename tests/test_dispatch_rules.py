@@ -119,3 +119,25 @@ def test_block_rows_a_whitening_step_applies_at_a_time(rule):
     for q, (lag,) in zip(WHITEN, got):
         times = dict(zip((1, 2, 3, 4, 6, 8), q[2:]))
         assert times[lag] <= 1.03 * min(t for t in times.values() if t), q
+
+
+# channels, tokens; us without the two-level sums, us with them
+GRAM_SEG = [
+    (1040, 1800, 61.8, 48.9), (1536, 1000, 38.8, 31.0), (1536, 6000, 62.1, 53.1), (2048, 512, 30.0, 27.1), (2048, 6000, 78.2, 66.7), (2560, 7500, 139.8, 92.3),
+    (3072, 1000, 50.3, 43.6), (3072, 3000, 74.5, 72.4), (3072, 7500, 181.8, 126.1), (4096, 1000, 67.0, 72.8), (4096, 1800, 85.1, 92.8), (4096, 3000, 145.8, 106.3),
+    (4096, 7500, 317.2, 179.1), (5120, 1800, 92.8, 104.1), (5120, 6000, 399.8, 230.5), (6144, 4300, 307.1, 229.5), (8192, 3000, 367.2, 316.1), (8192, 7500, 605.1, 608.5),
+    (11008, 1000, 263.0, 304.9), (11008, 6000, 780.2, 818.9), (14336, 512, 376.6, 395.1), (14336, 3000, 727.7, 836.0), (14336, 7500, 1432.8, 1684.1),
+]
+
+
+def test_gram_chunks_take_two_level_sums_where_they_are_faster(rule):
+    call = ('AserGramSplit s = aser_gram_dma_split(a[0], a[1], a[2], a[3]), q = aser_gram_seg_split(2 * a[0], a[1], a[2]); '
+            'printf("%d %d %d", q.cost < 0.97 * s.cost, q.chunks, q.split);')
+    for (n, rows, without, with_), (taken, _, _) in zip(GRAM_SEG, rule("seg", call, [gram_query(n, rows) for n, rows, _, _ in GRAM_SEG])):
+        assert (with_ if taken else without) <= 1.03 * min(without, with_), (n, rows)
+    # G is rounded once per chunk and part: at most a third more often than by the plain grid
+    sizes = [(n, rows) for n in range(1032, 14400, 488) for rows in (256, 700, 1500, 2200, 3333, 5000, 7503, 8191)]
+    for (n, rows), (_, c, split) in zip(sizes, rule("segbound", call, [gram_query(n, rows) for n, rows in sizes])):
+        tiles, _, parts, _ = gram_query(n, rows)
+        count = c * (split if 2 * tiles % (256 // c) else 1)
+        assert c in (1, 2, 4, 8) and split >= 1 and (count == 1 or 3 * count <= 4 * parts), (n, rows, c, split, parts)

@@ -297,3 +297,17 @@ def test_whitening_factor_at_the_edges_of_the_blocks(n, pad):
         broken[bad, bad] = -1.0
         st, info = aser.aser_whiten(ctx, torch.from_numpy(broken).to(DEV), None, 0.0, S[:, :n])
         assert st == aser.ASER_ERR_NOT_SPD and info == bad + 1
+
+
+@pytest.mark.parametrize("n,rows", [(1032, 256), (1032, 287), (1160, 3000), (1288, 4097), (2688, 6001), (3080, 4300), (4096, 7503), (4104, 2990)])
+def test_gram_chunks_with_two_level_sums(n, rows):
+    """Last tiles of one to three quarters, ranges of fewer steps than the ring holds, ragged last steps.  Bound per entry as above; the
+    diagonal as a sum of at most ceil(rows / 32) * 2 fp32 roundings of growing partial sums, of which an eighth is never exceeded in the mean square."""
+    spec = synth.mini("gram%d" % n, 64, n, 2 * rows, n_outliers=5, seed_id=1050 + n % 50)
+    X = synth.make_activations(spec)
+    G, _, count = run_gram(new_ctx(), spec, X, chunks=2)
+    ref, _, _ = orc.gram(synth.activations_as_f32(spec, X))
+    d = np.sqrt(np.diag(ref))
+    assert np.max(np.abs(lower(G.cpu().numpy()) - np.tril(ref)) / np.outer(d, d)) <= 2e-5
+    rel = np.diag(G.cpu().numpy()) / np.diag(ref) - 1.0
+    assert np.sqrt(np.mean(rel ** 2)) <= 0.125 * np.ceil(rows / 32) * 2 * 6e-8 and int(count.item()) == 2 * rows
