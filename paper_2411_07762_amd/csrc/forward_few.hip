@@ -8,8 +8,9 @@
 // MFMA operands (a lane's 16 bytes are 16 int8 or 32 int4 channels of its row; the order of the channels inside a
 // step is free as long as both operands agree), nothing goes through LDS on the way.  The int32 partial sums are exact and meet
 // in LDS by integer atomics, so the result does not depend on their order.  The rank-r branch is a kernel in front
-// (few_down_kernel: P summed over up to 2048 channels per workgroup) and r / 4 further steps per output tile in the epilogue;
-// both run on the fp32 MFMA instruction, operands straight from global memory.  In the mode that rounds the factors
+// (few_down_kernel: P summed over up to 2048 channels per workgroup) and r / 4 further steps per output tile in the epilogue, or, with many
+// outputs, P in workgroups of the same launch as the codes (neither needs the other) and those steps in a second, short launch;
+// all on the fp32 MFMA instruction, operands straight from global memory.  In the mode that rounds the factors
 // to bf16 the same three roundings are made (L_B, P, L_A) as in the prefill kernels.
 #include "aser_internal.h"
 
@@ -19,49 +20,65 @@ typedef int v4i_t __attribute__((ext_vector_type(4)));
 
 typedef float f4v __attribute__((ext_vector_type(4)));
 
-constexpr int kDownChunk = 2048;      // channels per partial P: eight wavefronts of 256
+constexpr int kDownChunk = 2048;      // channels per partial P
 
 __device__ __forceinline__ float round_bf16(float x) {
     const uint32_t u = __float_as_uint(x);
     return __uint_as_float((u + 0x7FFFu + ((u >> 16) & 1u)) & 0xFFFF0000u);
 }
 
+struct FewArgs {
+    const int8_t* xq; const float* xs; int rows; int64_t n;
+    const void* wq; const float* ws; int64_t m;
+    float* part; int chunks; const float* L_A; const float* L_B; int r, rp, split, vec_a, vec_b;
+    int down, tiles;                      // workgroups that form P; output tiles
+    float* Y; int64_t ldy;
+};
+
 // part[chunk][t][k] = sum over 2048 channels of xq[t][i] L_B[k][i] (without s_t), k up to rp (r rounded up to 16; zeros
-// behind r).  A workgroup takes 16 rows of L_B and 16 tokens, a wavefront 256 channels of them; lane (l % 16, g = l / 16)
+// behind r).  A workgroup takes 16 rows of L_B and 16 tokens, a wavefront 2048 / NW channels of them; lane (l % 16, g = l / 16)
 // feeds channels 16 s + 4 g + e of its row and of its token to the e-th of four v_mfma_f32_16x16x4_f32 (codes and products
-// exact, fp32 sums).  All loads of a wavefront are in flight at once: they are unconditional (addresses clamped into the
+// exact, fp32 sums).  All loads of a round are in flight at once: they are unconditional (addresses clamped into the
 // operands, the values dropped afterwards), because a load behind a branch is waited for where the branches meet.
-template <bool VEC>
-__global__ __launch_bounds__(512) void few_down_kernel(const int8_t* __restrict__ xq, int rows, int64_t n, const float* __restrict__ L_B,
-                                                       int r, int rp, int split, float* __restrict__ part) {
-    __shared__ float red[8][16][17];
+template <int NW>
+__device__ __forceinline__ void few_down(const FewArgs& g, int task, float (*red)[16][17]) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int li = lane & 15, lg = lane >> 4;
-    const int64_t c0 = (int64_t)blockIdx.x * kDownChunk + wave * 256 + 4 * lg;
-    const int k = blockIdx.y * 16 + li, t = blockIdx.z * 16 + li;
-    const bool kok = k < r, tok = t < rows;
-    const float* bp = L_B + (int64_t)(kok ? k : 0) * n;
-    const int8_t* xp = xq + (int64_t)(tok ? t : 0) * n;
+    const int kt = g.rp / 16, chunk = task % g.chunks, ky = (task / g.chunks) % kt, tz = task / (g.chunks * kt);
+    const int k = ky * 16 + li, t = tz * 16 + li;
+    const bool kok = k < g.r, tok = t < g.rows;
+    const float* bp = g.L_B + (int64_t)(kok ? k : 0) * g.n;
+    const int8_t* xp = g.xq + (int64_t)(tok ? t : 0) * g.n;
     f4v acc = {0.f, 0.f, 0.f, 0.f};
-    if ((int64_t)blockIdx.x * kDownChunk + wave * 256 < n) {
-        float4 b[16];
-        uint32_t x[16];
+    // NS * 16 channels at a time: with 256 the registers of the eight-wavefront kernels would leave room for one workgroup per compute unit
+    constexpr int NS = 8;
+#pragma unroll 1
+    for (int h = 0; h < kDownChunk / NW; h += 16 * NS) {
+        const int64_t c0 = (int64_t)chunk * kDownChunk + wave * (kDownChunk / NW) + h + 4 * lg;
+        if (c0 - 4 * lg >= g.n) break;
+        float4 b[NS];
+        uint32_t x[NS];
+        if (g.vec_b) {
 #pragma unroll
-        for (int s = 0; s < 16; ++s) {
-            const int64_t c = (c0 + 16 * s < n) ? c0 + 16 * s : 0;         // n % 32 == 0: a lane's four channels are whole or absent
-            if (VEC) b[s] = *(const float4*)(bp + c);
-            else b[s] = make_float4(bp[c], bp[c + 1], bp[c + 2], bp[c + 3]);
-            x[s] = *(const uint32_t*)(xp + c);
+            for (int s = 0; s < NS; ++s) b[s] = *(const float4*)(bp + ((c0 + 16 * s < g.n) ? c0 + 16 * s : 0));   // n % 32 == 0: four channels are whole or absent
+        } else {
+#pragma unroll
+            for (int s = 0; s < NS; ++s) {
+                const float* q = bp + ((c0 + 16 * s < g.n) ? c0 + 16 * s : 0);
+                b[s] = make_float4(q[0], q[1], q[2], q[3]);
+            }
         }
 #pragma unroll
-        for (int s = 0; s < 16; ++s) {
-            const bool in = c0 + 16 * s < n;
+        for (int s = 0; s < NS; ++s) x[s] = *(const uint32_t*)(xp + ((c0 + 16 * s < g.n) ? c0 + 16 * s : 0));
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            const bool in = c0 + 16 * s < g.n;
             const uint32_t xs = (in && tok) ? x[s] : 0u;
             const float bb[4] = {b[s].x, b[s].y, b[s].z, b[s].w};
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const float v = (in && kok) ? bb[e] : 0.f;
-                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(split ? v : round_bf16(v), (float)((int)(xs << (24 - 8 * e)) >> 24), acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(g.split ? v : round_bf16(v), (float)((int)(xs << (24 - 8 * e)) >> 24), acc, 0, 0, 0);
             }
         }
     }
@@ -72,33 +89,82 @@ __global__ __launch_bounds__(512) void few_down_kernel(const int8_t* __restrict_
         const int tt = tid >> 4, kk = tid & 15;
         float s = 0.f;
 #pragma unroll
-        for (int w = 0; w < 8; ++w) s += red[w][tt][kk];
-        if (blockIdx.z * 16 + tt < rows) part[((int64_t)blockIdx.x * rows + blockIdx.z * 16 + tt) * rp + blockIdx.y * 16 + kk] = s;
+        for (int w = 0; w < NW; ++w) s += red[w][tt][kk];
+        if (tz * 16 + tt < g.rows) g.part[((int64_t)chunk * g.rows + tz * 16 + tt) * g.rp + ky * 16 + kk] = s;
     }
 }
 
-struct FewArgs {
-    const int8_t* xq; const float* xs; int rows; int64_t n;
-    const void* wq; const float* ws; int64_t m;
-    const float* part; int chunks; const float* L_A; int r, rp, split, vec_a;
-    float* Y; int64_t ldy;
-};
+__global__ __launch_bounds__(512) void few_down_kernel(FewArgs g) {
+    __shared__ float red[8][16][17];
+    few_down<8>(g, blockIdx.x, red);
+}
+
+// y (outputs O .. O + 15 of 16 tokens, this lane's four outputs of token t) += s_t P L_A^T, on the fp32 MFMA instruction.
+__device__ __forceinline__ f4v few_rank(const FewArgs& g, f4v y, int64_t O, int t, bool tok, float sx, int li, int lg) {
+    const int64_t orow = O + li;                             // the row of L_A that this lane feeds
+        const float* ap = g.L_A + (orow < g.m ? orow : 0) * g.r;
+    const float* pp = g.part + (int64_t)(tok ? t : 0) * g.rp;
+    for (int k0 = 0; k0 < g.rp; k0 += 64) {              // four steps of 16 at a time: their loads are in flight together
+        float av[4][4];
+        float4 pv[4];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const int k = k0 + 16 * s + 4 * lg;
+            pv[s] = *(const float4*)(pp + (k < g.rp ? k : 0));
+            if (g.vec_a) {
+                const float4 v = *(const float4*)(ap + (k < g.r ? k : 0));
+                av[s][0] = v.x; av[s][1] = v.y; av[s][2] = v.z; av[s][3] = v.w;
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) av[s][e] = ap[k + e < g.r ? k + e : 0];
+            }
+        }
+#pragma unroll 2
+        for (int c = 1; c < g.chunks; ++c) {
+            const float* pc = pp + (int64_t)c * g.rows * g.rp;
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const int k = k0 + 16 * s + 4 * lg;
+                const float4 v = *(const float4*)(pc + (k < g.rp ? k : 0));
+                pv[s].x += v.x; pv[s].y += v.y; pv[s].z += v.z; pv[s].w += v.w;
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const float p4[4] = {pv[s].x * sx, pv[s].y * sx, pv[s].z * sx, pv[s].w * sx};     // sx is 0 past the last token
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int k = k0 + 16 * s + 4 * lg + e;
+                const float a = (k < g.r && orow < g.m) ? av[s][e] : 0.f, p = k < g.r ? p4[e] : 0.f;
+                y = __builtin_amdgcn_mfma_f32_16x16x4f32(g.split ? a : round_bf16(a), g.split ? p : round_bf16(p), y, 0, 0, 0);
+            }
+        }
+    }
+    return y;
+}
 
 // OT: 16-output tiles per workgroup, TG: 16-token tiles, NW: wavefronts that split the contraction.
 // v_mfma_i32_16x16x64_i8: a lane feeds 16 bytes of row (output, token) lane % 16, and holds the sums of outputs
 // 4 (lane / 16) .. + 3 for token lane % 16.
-template <bool W4, int OT, int TG, int NW>
+// BESIDE: the first workgroups form P, and L_A P is left to few_rank_kernel; otherwise P is there already.
+template <bool W4, int OT, int TG, int NW, bool BESIDE>
 __global__ __launch_bounds__(64 * NW) void few_main_kernel(FewArgs g) {
     constexpr int OUT = 16 * OT, TOK = 16 * TG, NT = 64 * NW;
     constexpr int STEP = W4 ? 128 : 64;                     // channels per step: 16 bytes of codes per lane
     constexpr int U = (TG >= 4) ? 2 : 4;                    // steps in flight
     constexpr int OP = OUT + 4;
-    __shared__ int red[TOK * OP];
+    constexpr int kRed = (!BESIDE || TOK * OP > NW * 16 * 17) ? TOK * OP : NW * 16 * 17;
+    __shared__ int red[kRed];
+    if (BESIDE && (int)blockIdx.x < g.down) {
+        few_down<NW>(g, blockIdx.x, (float(*)[16][17])red);
+        return;
+    }
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int li = lane & 15, lg = lane >> 4;
-    const int64_t O0 = (int64_t)blockIdx.x * OUT;
-    const int T0 = blockIdx.y * TOK;
+    const int work = (int)blockIdx.x - (BESIDE ? g.down : 0);
+    const int64_t O0 = (int64_t)(work % g.tiles) * OUT;
+    const int T0 = work / g.tiles * TOK;
     const int64_t steps = (g.n + STEP - 1) / STEP, per = (steps + NW - 1) / NW;
     const int64_t s0 = wave * per, s1 = (s0 + per < steps) ? s0 + per : steps;
 
@@ -206,45 +272,7 @@ __global__ __launch_bounds__(64 * NW) void few_main_kernel(FewArgs g) {
         f4v y;
 #pragma unroll
         for (int e = 0; e < 4; ++e) y[e] = (float)red[(16 * j + li) * OP + 16 * i + 4 * lg + e] * (sx * (o4 + e < g.m ? g.ws[o4 + e] * wfix : 0.f));
-        const int64_t orow = O0 + 16 * i + li;               // the row of L_A that this lane feeds
-        const float* ap = g.L_A + (orow < g.m ? orow : 0) * g.r;
-        const float* pp = g.part + (int64_t)(tok ? t : 0) * g.rp;
-        for (int k0 = 0; k0 < g.rp; k0 += 64) {              // four steps of 16 at a time: their loads are in flight together
-            float av[4][4];
-            float4 pv[4];
-#pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                const int k = k0 + 16 * s + 4 * lg;
-                pv[s] = *(const float4*)(pp + (k < g.rp ? k : 0));
-                if (g.vec_a) {
-                    const float4 v = *(const float4*)(ap + (k < g.r ? k : 0));
-                    av[s][0] = v.x; av[s][1] = v.y; av[s][2] = v.z; av[s][3] = v.w;
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) av[s][e] = ap[k + e < g.r ? k + e : 0];
-                }
-            }
-#pragma unroll 2
-            for (int c = 1; c < g.chunks; ++c) {
-                const float* pc = pp + (int64_t)c * g.rows * g.rp;
-#pragma unroll
-                for (int s = 0; s < 4; ++s) {
-                    const int k = k0 + 16 * s + 4 * lg;
-                    const float4 v = *(const float4*)(pc + (k < g.rp ? k : 0));
-                    pv[s].x += v.x; pv[s].y += v.y; pv[s].z += v.z; pv[s].w += v.w;
-                }
-            }
-#pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                const float p4[4] = {pv[s].x * sx, pv[s].y * sx, pv[s].z * sx, pv[s].w * sx};     // sx is 0 past the last token
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int k = k0 + 16 * s + 4 * lg + e;
-                    const float a = (k < g.r && orow < g.m) ? av[s][e] : 0.f, p = k < g.r ? p4[e] : 0.f;
-                    y = __builtin_amdgcn_mfma_f32_16x16x4f32(g.split ? a : round_bf16(a), g.split ? p : round_bf16(p), y, 0, 0, 0);
-                }
-            }
-        }
+        if (!BESIDE) y = few_rank(g, y, O0 + 16 * i, t, tok, sx, li, lg);
         if (!tok) continue;
         float* yr = g.Y + (int64_t)t * g.ldy + o4;
 #pragma unroll
@@ -253,10 +281,45 @@ __global__ __launch_bounds__(64 * NW) void few_main_kernel(FewArgs g) {
     }
 }
 
+// The second launch where P was formed beside the codes: a 16 x 16 tile per wavefront, 64 outputs of 16 tokens per workgroup.
+__global__ __launch_bounds__(256) void few_rank_kernel(FewArgs g) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, li = lane & 15, lg = lane >> 4;
+    const int64_t O = (int64_t)blockIdx.x * 64 + 16 * wave, o4 = O + 4 * lg;
+    if (O >= g.m) return;
+    const int t = blockIdx.y * 16 + li;
+    const bool tok = t < g.rows;
+    float* yr = g.Y + (int64_t)(tok ? t : 0) * g.ldy;
+    f4v y;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) y[e] = yr[o4 + e < g.m ? o4 + e : g.m - 1];
+    y = few_rank(g, y, O, t, tok, tok ? g.xs[t] : 0.f, li, lg);
+    if (!tok) return;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        if (o4 + e < g.m) yr[o4 + e] = y[e];
+}
+
 template <bool W4, int OT, int TG, int NW>
-int launch_few(aser_ctx* ctx, const FewArgs& g) {
-    dim3 grid((unsigned)ceil_div64(g.m, 16 * OT), (unsigned)ceil_div64(g.rows, 16 * TG));
-    hipLaunchKernelGGL((few_main_kernel<W4, OT, TG, NW>), grid, dim3(64 * NW), 0, ctx->stream, g);
+int launch_few(aser_ctx* ctx, FewArgs g) {
+    g.tiles = (int)ceil_div64(g.m, 16 * OT);
+    const int64_t work = g.tiles * ceil_div64(g.rows, 16 * TG);
+    // P beside the codes: where the output tiles are small workgroups, one or two per compute unit, and long enough to hide P.  Measured (us, P in front
+    // -> beside; channels, outputs, one token / 16 tokens, r = 64, int4): 2048, 8224: 13.5 -> 12.4 / 18.1 -> 17.0; 4096, 10240: 17.6 -> 14.9 / 23.8 -> 19.9; 4096,
+    // 14336: 18.3 -> 15.7 / 24.2 -> 20.3; 14336, 8224: 32.1 -> 29.3 / 46.4 -> 40.0.  Not at 1024, 14336: 10.9 -> 11.7 / 13.5 -> 13.8, nor with eight wavefronts per
+    // tile (8192, 8192: 17.8 -> 19.2 / 27.0 -> 28.4; 4096, 4096: 12.0 -> 13.8 / 16.5 -> 19.1) or 64 outputs (8192, 16384: 25.5 -> 24.9 / 33.9 -> 34.1).
+    if constexpr (TG == 1 && NW == 4 && OT == 2) {
+        if (g.r > 0 && g.n >= 2048) {
+            hipLaunchKernelGGL((few_main_kernel<W4, OT, TG, NW, true>), dim3((unsigned)(g.down + work)), dim3(64 * NW), 0, ctx->stream, g);
+            ASER_TRY(aser_check_launch(ctx, "compensated_forward_few"));
+            hipLaunchKernelGGL(few_rank_kernel, dim3((unsigned)ceil_div64(g.m, 64), (unsigned)ceil_div64(g.rows, 16)), dim3(256), 0, ctx->stream, g);
+            return aser_check_launch(ctx, "compensated_forward_few_rank");
+        }
+    }
+    if (g.r > 0) {
+        hipLaunchKernelGGL(few_down_kernel, dim3((unsigned)g.down), dim3(512), 0, ctx->stream, g);
+        ASER_TRY(aser_check_launch(ctx, "compensated_forward_few_down"));
+    }
+    hipLaunchKernelGGL((few_main_kernel<W4, OT, TG, NW, false>), dim3((unsigned)work), dim3(64 * NW), 0, ctx->stream, g);
     return aser_check_launch(ctx, "compensated_forward_few");
 }
 
@@ -296,12 +359,9 @@ int aser_forward_few(aser_ctx* ctx, const int8_t* xq, const float* xs, int rows,
         g.part = scratch;
         g.chunks = (int)ceil_div64(n, kDownChunk);
         g.vec_a = (((uintptr_t)L_A & 15) == 0 && (r & 3) == 0) ? 1 : 0;
-        dim3 grid((unsigned)g.chunks, (unsigned)(g.rp / 16), (unsigned)ceil_div64(rows, 16));
-        if (((uintptr_t)L_B & 15) == 0)
-            hipLaunchKernelGGL(few_down_kernel<true>, grid, dim3(512), 0, ctx->stream, xq, rows, n, L_B, r, g.rp, split ? 1 : 0, scratch);
-        else
-            hipLaunchKernelGGL(few_down_kernel<false>, grid, dim3(512), 0, ctx->stream, xq, rows, n, L_B, r, g.rp, split ? 1 : 0, scratch);
-        ASER_TRY(aser_check_launch(ctx, "compensated_forward_few_down"));
+        g.L_B = L_B;
+        g.vec_b = ((uintptr_t)L_B & 15) == 0 ? 1 : 0;
+        g.down = g.chunks * (g.rp / 16) * (int)ceil_div64(rows, 16);
     }
     return w4 ? dispatch_few<true>(ctx, g) : dispatch_few<false>(ctx, g);
 }

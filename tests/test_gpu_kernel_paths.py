@@ -311,3 +311,32 @@ def test_gram_chunks_with_two_level_sums(n, rows):
     assert np.max(np.abs(lower(G.cpu().numpy()) - np.tril(ref)) / np.outer(d, d)) <= 2e-5
     rel = np.diag(G.cpu().numpy()) / np.diag(ref) - 1.0
     assert np.sqrt(np.mean(rel ** 2)) <= 0.125 * np.ceil(rows / 32) * 2 * 6e-8 and int(count.item()) == 2 * rows
+
+
+@pytest.mark.parametrize("rows,n,m,r,packed", [(1, 2048, 8193, 1, True), (1, 4128, 16384, 64, True), (3, 2080, 8200, 40, False), (16, 2048, 8225, 128, True),
+                                               (16, 6176, 9000, 24, False), (2, 2016, 8200, 64, True)])
+def test_forward_of_a_few_tokens_with_many_outputs(rows, n, m, r, packed):
+    """The rank-r branch beside the codes and on top of them in a second launch; bars as in test_forward_of_a_few_tokens."""
+    rng = np.random.default_rng([78, rows, n, m, r])
+    xq = rng.integers(-127, 128, (rows, n)).astype(np.int8)
+    xs = rng.uniform(0.01, 0.05, rows).astype(np.float32)
+    q = rng.integers(-7, 8, (m, n)).astype(np.int8) if packed else rng.integers(-127, 128, (m, n)).astype(np.int8)
+    ws = rng.uniform(0.001, 0.003, m).astype(np.float32)
+    L_A = rng.standard_normal((m, r)).astype(np.float32)
+    L_B = (rng.standard_normal((r, n)) * 0.01).astype(np.float32)
+    X = xq.astype(np.float64) * xs.astype(np.float64)[:, None]
+    want = X @ (q.astype(np.float64) * ws.astype(np.float64)[:, None]).T + (X @ L_B.astype(np.float64).T) @ L_A.astype(np.float64).T
+    ctx = new_ctx()
+    ctx.ensure_workspace(aser.aser_forward_workspace_bytes(rows, n, m, r))
+    wq = torch.from_numpy(orc.pack_int4(q) if packed else q).to(DEV)
+    lb = torch.zeros(L_B.size + 1, dtype=torch.float32, device=DEV)
+    lb[1:] = torch.from_numpy(L_B.reshape(-1)).to(DEV)
+    for lbd in (lb[1:].view(L_B.shape), torch.from_numpy(L_B).to(DEV)):       # 4-byte aligned, 16-byte aligned
+        for split, bar in ((True, 2e-5), (False, 4e-3)):
+            Y = torch.full((rows, m + 3), 7.0, dtype=torch.float32, device=DEV)
+            ctx.check(aser.aser_compensated_forward(ctx, torch.from_numpy(xq).to(DEV), torch.from_numpy(xs).to(DEV), wq,
+                                                    aser.ASER_CODES_INT4_PACKED if packed else aser.ASER_CODES_INT8, torch.from_numpy(ws).to(DEV),
+                                                    torch.from_numpy(L_A).to(DEV), lbd, r, split, Y[:, :m]))
+            got = Y.cpu().numpy()
+            assert np.all(got[:, m:] == 7.0)
+            assert np.linalg.norm(got[:, :m] - want) / np.linalg.norm(want) <= bar
