@@ -733,19 +733,52 @@ int tridiagonalize(aser_ctx* ctx, double* B, int64_t k, double* const* vec, doub
 // stored reflectors.  No iteration count, no start block: what the iterative path approximates.
 
 // out[i][j] = sum_{l >= j} T[i][l] S[l][j] in fp64 (S lower triangular); TRANSPOSED: stored as out[j][i].
+// 16 x 64 outputs per workgroup, four rows per thread; operands through LDS, the next 32 rows of S on their way while these are multiplied (a
+// thread per output that read both operands from memory: 70 us at 256 x 256, this 20).  Sums run over l in ascending order.
 template <bool TRANSPOSED>
 __global__ __launch_bounds__(256) void ts_f64_kernel(const float* __restrict__ T, int64_t m, int64_t n, int64_t ldt,
                                                      const float* __restrict__ S, int64_t lds, double* __restrict__ out) {
-    const int64_t j = (int64_t)blockIdx.x * 64 + (threadIdx.x & 63);
-    const int64_t i = (int64_t)blockIdx.y * 4 + (threadIdx.x >> 6);
-    if (i >= m || j >= n) return;
-    const float* trow = T + i * ldt;
-    double acc = 0.0;
-    // from the first row that any column of this workgroup needs (the entries above the diagonal do not count), so that the
-    // loop is uniform and its loads run ahead
+    __shared__ float st[16][32], ss[32][64];
+    const int tid = threadIdx.x, tx = tid & 63, ty = tid >> 6;
+    const int64_t j = (int64_t)blockIdx.x * 64 + tx, i0 = (int64_t)blockIdx.y * 16;
+    float rt[2], rs[8];
+    auto load = [&](int64_t l0) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int64_t i = i0 + (tid >> 5) + 8 * u, l = l0 + (tid & 31);
+            rt[u] = (i < m && l < n) ? T[i * ldt + l] : 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int64_t l = l0 + ty + 4 * u;
+            rs[u] = (l < n && j < n && l >= j) ? S[l * lds + j] : 0.f;
+        }
+    };
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    int64_t l0 = (int64_t)blockIdx.x * 64;                // the entries above the diagonal do not count
+    load(l0);
+    for (; l0 < n; l0 += 32) {
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < 2; ++u) st[(tid >> 5) + 8 * u][tid & 31] = rt[u];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) ss[ty + 4 * u][tx] = rs[u];
+        __syncthreads();
+        if (l0 + 32 < n) load(l0 + 32);
 #pragma unroll 8
-    for (int64_t l = (int64_t)blockIdx.x * 64; l < n; ++l) acc = fma((double)trow[l], l >= j ? (double)S[l * lds + j] : 0.0, acc);
-    if (TRANSPOSED) out[j * m + i] = acc; else out[i * n + j] = acc;
+        for (int l = 0; l < 32; ++l) {
+            const double b = (double)ss[l][tx];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) acc[q] = fma((double)st[4 * ty + q][l], b, acc[q]);
+        }
+    }
+    if (j >= n) return;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int64_t i = i0 + 4 * ty + q;
+        if (i >= m) break;
+        if (TRANSPOSED) out[j * m + i] = acc[q]; else out[i * n + j] = acc[q];
+    }
 }
 
 __device__ __forceinline__ uint32_t hash32(uint32_t x) {
@@ -824,45 +857,69 @@ __device__ __forceinline__ double invit_start_value(int64_t t) {
 // Eigenvectors of the symmetric tridiagonal matrix (d, e) for the r largest eigenvalues lam[0 .. r),
 // as rows of X (r x k).  One workgroup (small problems).  Three rounds of: thread c solves (T - lam_c I) y = x_c,
 // then the vectors are orthonormalised in order (classical Gram-Schmidt, twice).  scr: r x 3 k doubles.
-__global__ __launch_bounds__(256) void tridiag_invit_kernel(int64_t k, int r, const double* __restrict__ d,
-                                                            const double* __restrict__ e, const double* __restrict__ lam,
-                                                            double* __restrict__ X, double* __restrict__ scr) {
+// LOCAL: everything stands in LDS, (2 + 4 r) k doubles with a word of padding per vector, and X receives the result; the solves are chains of
+// dependent steps on one thread each and the orthonormalisation short passes between barriers, so what bounds both is the latency of
+// what they read (k = 256, r = 8: 345 us from memory, 250 from LDS).
+constexpr int kInvitLds = 150 * 1024;
+__host__ __device__ static inline size_t invit_lds_bytes(int64_t k, int r) { return (size_t)(2 * k + (int64_t)r * 4 * (k + 1)) * 8; }
+template <bool LOCAL>
+__global__ __launch_bounds__(256) void tridiag_invit_kernel(int64_t k, int r, const double* __restrict__ dg,
+                                                            const double* __restrict__ eg, const double* __restrict__ lam,
+                                                            double* __restrict__ Xg, double* __restrict__ scrg) {
     __shared__ double dots[256];                      // r <= 256
     __shared__ double red[4];
+    extern __shared__ __align__(16) double mem[];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const double tiny = fmax(tridiag_norm(k, d, e) * 2.3e-16, 1e-300);
-    for (int64_t t = tid; t < (int64_t)r * k; t += 256) X[t] = invit_start_value(t);
+    const int64_t ld = LOCAL ? k + 1 : k;
+    const double *d = dg, *e = eg;
+    double *X = Xg, *scr = scrg;
+    if constexpr (LOCAL) {
+        double *dl = mem, *el = mem + k;
+        for (int64_t i = tid; i < k; i += 256) {
+            dl[i] = dg[i];
+            el[i] = i + 1 < k ? eg[i] : 0.0;
+        }
+        d = dl;
+        e = el;
+        X = mem + 2 * k;
+        scr = X + (int64_t)r * ld;
+        __syncthreads();
+    }
+    double tnorm = 0.0;
+    for (int64_t l = lane; l < k; l += 64) tnorm = fmax(tnorm, fabs(d[l]) + (l + 1 < k ? fabs(e[l]) : 0.0) + (l > 0 ? fabs(e[l - 1]) : 0.0));
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) tnorm = fmax(tnorm, __shfl_xor(tnorm, o, 64));
+    const double tiny = fmax(tnorm * 2.3e-16, 1e-300);
+    for (int64_t t = tid; t < (int64_t)r * k; t += 256) X[t / k * ld + t % k] = invit_start_value(t);
     __syncthreads();
     for (int round = 0; round < 3; ++round) {
         if (tid < r) {
             const int c = tid;
-            double* dd = scr + (int64_t)c * 3 * k;
-            invit_solve_one(k, d, e, lam[c], tiny, X + (int64_t)c * k, dd, dd + k, dd + 2 * k);
+            double* dd = scr + (int64_t)c * 3 * ld;
+            invit_solve_one(k, d, e, lam[c], tiny, X + (int64_t)c * ld, dd, dd + ld, dd + 2 * ld);
         }
         __syncthreads();
         for (int c = 0; c < r; ++c) {
-            double* x = X + (int64_t)c * k;
+            double* x = X + (int64_t)c * ld;
             for (int pass = 0; pass < 2; ++pass) {
                 for (int j = wave; j < c; j += 4) {
-                    const double* y = X + (int64_t)j * k;
+                    const double* y = X + (int64_t)j * ld;
                     double s = 0.0;
                     for (int64_t i = lane; i < k; i += 64) s += y[i] * x[i];
-#pragma unroll
-                    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+                    s = wave_sum(s);
                     if (lane == 0) dots[j] = s;
                 }
                 __syncthreads();
                 for (int64_t i = tid; i < k; i += 256) {
                     double v = x[i];
-                    for (int j = 0; j < c; ++j) v -= dots[j] * X[(int64_t)j * k + i];
+                    for (int j = 0; j < c; ++j) v -= dots[j] * X[(int64_t)j * ld + i];
                     x[i] = v;
                 }
                 __syncthreads();
             }
             double s = 0.0;
             for (int64_t i = tid; i < k; i += 256) s += x[i] * x[i];
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+            s = wave_sum(s);
             if (lane == 0) red[wave] = s;
             __syncthreads();
             const double nrm = sqrt(red[0] + red[1] + red[2] + red[3]);
@@ -871,6 +928,8 @@ __global__ __launch_bounds__(256) void tridiag_invit_kernel(int64_t k, int r, co
             __syncthreads();
         }
     }
+    if constexpr (LOCAL)
+        for (int64_t t = tid; t < (int64_t)r * k; t += 256) Xg[t] = X[t / k * ld + t % k];
 }
 
 // The same computation for large problems, one launch per step, because the orthonormalisation is r^2 k work that
@@ -951,35 +1010,40 @@ __global__ __launch_bounds__(256) void backtransform_kernel(int64_t k, const dou
     }
 }
 
-// The same for k <= 64 PER: one wavefront per vector with the vector in registers, the next reflector on its way while the current one is
-// applied (k = 256: 194 us with a workgroup per vector and two barriers per reflector).
+// The same for k <= 64 PER: one wavefront per vector with the vector in registers and the next four reflectors on their way, sums by
+// lane shifts (k = 256: 194 us with a workgroup per vector and two barriers per reflector, 144 with one reflector ahead and sums by
+// lane exchanges through LDS, 63 like this).
 template <int PER>
 __global__ __launch_bounds__(64) void backtransform_wave_kernel(int64_t k, const double* __restrict__ vstore,
                                                                 const double* __restrict__ taustore, double* __restrict__ X) {
+    constexpr int kAhead = 4;
     const int lane = threadIdx.x;
     double* x = X + (int64_t)blockIdx.x * k;
-    double xv[PER], v[PER], vn[PER];
+    double xv[PER], v[kAhead][PER], tau[kAhead];
 #pragma unroll
     for (int u = 0; u < PER; ++u) xv[u] = lane + 64 * u < k ? x[lane + 64 * u] : 0.0;
-    auto load = [&](int64_t j, double (&t)[PER]) {                   // entries up to j are zero in the store
+    auto load = [&](int64_t j, double (&t)[PER], double& tt) {       // entries up to j are zero in the store
+        if (j < 0) j = 0;                                            // not used
 #pragma unroll
         for (int u = 0; u < PER; ++u) t[u] = lane + 64 * u < k ? vstore[j * k + lane + 64 * u] : 0.0;
+        tt = taustore[j];
     };
-    if (k >= 3) load(k - 3, v);
-    double tau = k >= 3 ? taustore[k - 3] : 0.0;
-    for (int64_t j = k - 3; j >= 0; --j) {
-        const int64_t nx = j > 0 ? j - 1 : 0;
-        load(nx, vn);
-        const double taun = taustore[nx];
-        double s = 0.0;
+    if (k >= 3) {
 #pragma unroll
-        for (int u = 0; u < PER; ++u) s += v[u] * xv[u];
+        for (int q = 0; q < kAhead; ++q) load(k - 3 - q, v[q], tau[q]);
+    }
+    for (int64_t j = k - 3; j >= 0; j -= kAhead) {
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-        s *= tau;
+        for (int q = 0; q < kAhead; ++q) {
+            if (j - q < 0) break;
+            double s = 0.0;
 #pragma unroll
-        for (int u = 0; u < PER; ++u) { xv[u] -= s * v[u]; v[u] = vn[u]; }
-        tau = taun;
+            for (int u = 0; u < PER; ++u) s += v[q][u] * xv[u];
+            s = wave_sum(s) * tau[q];
+#pragma unroll
+            for (int u = 0; u < PER; ++u) xv[u] -= s * v[q][u];
+            load(j - q - kAhead, v[q], tau[q]);
+        }
     }
 #pragma unroll
     for (int u = 0; u < PER; ++u)
@@ -1124,7 +1188,7 @@ int aser_exact_reconstruct(aser_ctx* ctx, const float* T, int64_t m, int64_t n, 
         else ASER_TRY(gram_f64<float>(ctx, A, m, k, n, B));
     } else {
         // A = T S in fp64; for m <= n stored transposed (n x m), which is the K-major operand of A A^T
-        dim3 grid((unsigned)ceil_div64(n, 64), (unsigned)ceil_div64(m, 4));
+        dim3 grid((unsigned)ceil_div64(n, 64), (unsigned)ceil_div64(m, 16));
         if (left) hipLaunchKernelGGL(ts_f64_kernel<true>, grid, dim3(256), 0, ctx->stream, T, m, n, ldt, S, lds, A64);
         else hipLaunchKernelGGL(ts_f64_kernel<false>, grid, dim3(256), 0, ctx->stream, T, m, n, ldt, S, lds, A64);
         ASER_TRY(aser_check_launch(ctx, "ts_f64"));
@@ -1156,8 +1220,15 @@ int aser_exact_reconstruct(aser_ctx* ctx, const float* T, int64_t m, int64_t n, 
             ASER_TRY(aser_check_launch(ctx, "tridiag_invit (multi-launch)"));
         }
     } else {
-        hipLaunchKernelGGL(tridiag_invit_kernel, dim3(1), dim3(256), 0, ctx->stream, k, r, (const double*)vec[4], (const double*)vec[5],
-                           (const double*)lam, X, scr);
+        const size_t local = invit_lds_bytes(k, r);
+        if (local <= kInvitLds) {
+            ASER_HIP(ctx, hipFuncSetAttribute((const void*)tridiag_invit_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize, kInvitLds));
+            hipLaunchKernelGGL(tridiag_invit_kernel<true>, dim3(1), dim3(256), local, ctx->stream, k, r, (const double*)vec[4], (const double*)vec[5],
+                               (const double*)lam, X, scr);
+        } else {
+            hipLaunchKernelGGL(tridiag_invit_kernel<false>, dim3(1), dim3(256), 0, ctx->stream, k, r, (const double*)vec[4], (const double*)vec[5],
+                               (const double*)lam, X, scr);
+        }
         ASER_TRY(aser_check_launch(ctx, "tridiag_invit"));
     }
     if (k <= 256)

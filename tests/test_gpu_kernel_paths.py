@@ -340,3 +340,28 @@ def test_forward_of_a_few_tokens_with_many_outputs(rows, n, m, r, packed):
             got = Y.cpu().numpy()
             assert np.all(got[:, m:] == 7.0)
             assert np.linalg.norm(got[:, :m] - want) / np.linalg.norm(want) <= bar
+
+
+@pytest.mark.parametrize("m,n,r", [(3, 5, 1), (16, 33, 3), (64, 64, 7), (65, 130, 9), (256, 256, 17), (256, 300, 18), (257, 200, 40), (300, 257, 3), (700, 513, 20),
+                                   (1000, 1040, 5), (40, 2000, 12)])
+def test_dense_solver_at_the_edges_of_its_kernels(m, n, r):
+    """Factors of small layers against the SVD in fp64: inputs in fp32, everything behind them in fp64, results in fp32 (2^-24 relative, bar 1e-6);
+    the residual as a norm of fp64 differences of fp32 factors (bar 1e-5)."""
+    rng = np.random.default_rng([93, m, n, r])
+    k = min(m, n)
+    U, V = np.linalg.qr(rng.standard_normal((m, k)))[0], np.linalg.qr(rng.standard_normal((n, k)))[0]
+    S = (np.tril(rng.standard_normal((n, n))) * 0.05 + np.diag(rng.uniform(1.0, 3.0, n))).astype(np.float32)
+    A = (U * np.where(np.arange(k) < r, 8.0 + np.arange(k)[::-1] / k, 0.5)) @ V.T          # a gap behind the r-th singular value
+    T = np.ascontiguousarray(np.linalg.solve(S.astype(np.float64).T, A.T).T).astype(np.float32)
+    A = T.astype(np.float64) @ S.astype(np.float64)
+    u, sg, _ = np.linalg.svd(A, full_matrices=False)
+    want = u[:, :r] @ (u[:, :r].T @ T.astype(np.float64))
+    ctx = new_ctx()
+    ctx.ensure_workspace(aser.aser_workspace_bytes(m, n, r))
+    L_A, L_B, sigma = (torch.empty(shape, dtype=torch.float32, device=DEV) for shape in ((m, r), (r, n), (r,)))
+    st, err, iters = aser.aser_error_reconstruct(ctx, torch.from_numpy(T).to(DEV), torch.from_numpy(S).to(DEV), r, L_A, L_B, sigma)
+    ctx.check(st)
+    got = L_A.cpu().numpy().astype(np.float64) @ L_B.cpu().numpy().astype(np.float64)
+    assert iters == 0 and np.max(np.abs(sigma.cpu().numpy() / sg[:r] - 1.0)) <= 1e-6
+    assert np.linalg.norm(got - want) / np.linalg.norm(want) <= 1e-5
+    assert abs(err - np.sqrt(np.sum(sg[r:] ** 2))) <= 1e-5 * np.linalg.norm(sg)
