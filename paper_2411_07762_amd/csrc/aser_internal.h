@@ -200,13 +200,11 @@ int aser_transpose_f32(aser_ctx* ctx, const float* A, int64_t rows, int64_t cols
 // Rinv (b x b, ld = b) <- R^-1 (upper).  b <= 128.  On a non-positive pivot at column j,
 // atomicMin(info, pivot_base + j + 1) and the factor is meaningless from that column on.  clear_d: D is overwritten with
 // zeros instead of the factor (callers that only need R^-1 and reuse D as an accumulation target).
-// Lmul / Cmul (both may be null): Cmul = Lmul R^-1 for an upper triangular b x b Lmul (ld = b).
 // beta_out (device, two words, may be null): word 0 receives -(0.9 s^2 / 2)^2 as a float, s the smallest diagonal
 // entry of R; word 1 receives, as an int, 1 when the largest diagonal entry of R exceeds 64 s and else 0.
 // gate (device, may be null): the kernel returns at once when *gate == 0.
 int aser_chol_block(aser_ctx* ctx, float* D, int64_t ld, int b, float* Rinv, int32_t* info, int32_t pivot_base,
-                    bool clear_d = false, const float* Lmul = nullptr, float* Cmul = nullptr, float* beta_out = nullptr,
-                    const int* gate = nullptr);
+                    bool clear_d = false, float* beta_out = nullptr, const int* gate = nullptr);
 // Symmetric eigen-decomposition of the b x b matrix Mb (ld = b) by cyclic Jacobi: eigenvalues
 // descending into lambda (b), eigenvectors as columns of V (b x b, ld = b).  b <= 128, b even.
 // `gate` (device, may be null): the kernel returns at once when *gate == 0.
@@ -219,13 +217,15 @@ int aser_tridiag_eig(aser_ctx* ctx, const float* Mb, int b, float* lambda, float
 // C (rows x c) = A (rows x k) * B (k x c), fp32 MFMA; k, c <= 128, k % 4 == 0, A 16-byte aligned with
 // lda % 4 == 0.  C may not alias A.  The first clear_rows rows of A (k columns each; may exceed `rows`) are
 // set to zero after they have been read.  transposed: the result is stored as C^T (c x rows, leading dimension ldc).
+// A2 / C2 (k x k and k x c, dense; both may be null): the same launch also forms C2 = A2 B.
 // C (rows x b) = (A1 + alpha A2 P) B1 (A2 null: C = A1 B1); tall blocks and b x b factors, all with leading
 // dimension b <= 128 (b % 4 == 0), 16-byte aligned; alpha is read from device memory.  Afterwards the rows of A1
 // and the first zrows rows of Zclr (may be null) are zero.
 int aser_combine_f32(aser_ctx* ctx, float* A1, const float* B1, const float* A2, const float* P, const float* alpha_dev,
                      float* C, int64_t rows, int b, float* Zclr, int64_t zrows);
 int aser_gemm_small_f32(aser_ctx* ctx, float* A, int64_t lda, const float* B, int64_t ldb,
-                        float* C, int64_t ldc, int64_t rows, int k, int c, int64_t clear_rows = 0, bool transposed = false);
+                        float* C, int64_t ldc, int64_t rows, int k, int c, int64_t clear_rows = 0, bool transposed = false, float* A2 = nullptr,
+                        float* C2 = nullptr);
 
 // The compensated layer for a few tokens (forward_few.hip); arguments as aser_compensated_forward has checked them.
 // scratch: ceil(n / 2048) * rows * (r rounded up to 16) floats when r > 0, 16-byte aligned.

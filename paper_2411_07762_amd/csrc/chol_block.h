@@ -41,31 +41,6 @@ constexpr int kCholThreads = 512;
 constexpr int kWaves = kCholThreads / 64;
 constexpr size_t kCholLdsBytes = (size_t)(2 * kN * kP + 96 * kPZ + kN + 20 * 64) * sizeof(float);
 
-// acc(16 x 16) += sum over nk4 * 4 values of k of  sa * Aop(i, k) * Bop(k, c).  pa points at
-// Aop(lane & 15, lane >> 4), pb at Bop(lane >> 4, lane & 15); sak / sbk are the strides along k.  nk4 is a multiple of 4; the
-// operands of four instructions are read while the four before them execute.
-__device__ __forceinline__ f4v mma16(f4v acc, const float* pa, int sak, const float* pb, int sbk, int nk4, float sa) {
-    float a[2][4], b[2][4];
-    auto load = [&](int u, int s) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) { a[u][q] = pa[(s + q) * 4 * sak]; b[u][q] = pb[(s + q) * 4 * sbk]; }
-        __builtin_amdgcn_sched_barrier(0);               // else the reads are moved down to their uses
-    };
-    auto mul = [&](int u) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][q] * sa, b[u][q], acc, 0, 0, 0);
-    };
-    load(0, 0);
-    for (int s = 0; s < nk4; s += 8) {
-        if (s + 4 < nk4) load(1, s + 4);
-        mul(0);
-        if (s + 4 >= nk4) break;
-        if (s + 8 < nk4) load(0, s + 8);
-        mul(1);
-    }
-    return acc;
-}
-
 // Trailing update of one 16 x 16 tile behind the sub-block at offset o: A[i][c] -= sum_k P[k][i] P[k][c]
 // with the row panel P in rows o .. o + 31, tile (ti <= tc) counted from column o + 32.
 __device__ __forceinline__ void trailing_tile(float* As, int o, int ti, int tc, int t_i, int t_q) {
@@ -416,7 +391,7 @@ struct PlainBlock {
 // The whole block; sm: kCholLdsBytes of LDS; see aser_chol_block for the other arguments.
 template <class Source>
 __device__ __forceinline__ void chol_block_body(const Source& source, float* sm, float* D, int64_t ld, int b, float* Rinv, int32_t* info, int32_t pivot_base,
-                                                int clear_d, const float* Lmul, float* Cmul, float* beta_out) {
+                                                int clear_d, float* beta_out) {
     float* As = sm;                      // working matrix, upper triangle -> R; what stands below the diagonal is never used
     float* Xs = As + kN * kP;            // R^-1, upper 16 x 16 tiles
     float* Zs = Xs + kN * kP;            // 96 x 32 scratch
@@ -534,7 +509,6 @@ __device__ __forceinline__ void chol_block_body(const Source& source, float* sm,
             }
         }
     }
-    if (!Lmul && !beta_out) return;
     // ---- optional: the momentum coefficient of the subspace iteration, -(0.9 s^2 / 2)^2 with s the smallest
     // diagonal entry of R, and whether the diagonal of R spans more than a factor of 64
     if (beta_out) {
@@ -552,43 +526,6 @@ __device__ __forceinline__ void chol_block_body(const Source& source, float* sm,
             beta_out[0] = -hbeta * hbeta;
             ((int*)beta_out)[1] = (fmaxf(Zs[2], Zs[3]) > 64.f * s) ? 1 : 0;
         }
-    }
-    if (!Lmul) return;
-
-    // ---- optional: Cmul = Lmul R^-1 for an upper triangular b x b Lmul (ld = b), with R^-1 still in LDS
-    __syncthreads();                                      // everyone has read R out of As
-    {
-        constexpr int kPer = kN * kN / kCholThreads;
-        float v[kPer];
-#pragma unroll
-        for (int u = 0; u < kPer; ++u) {
-            const int t = tid + u * kCholThreads, i = t >> 7, k = t & 127;
-            v[u] = (k >= i && k < b) ? Lmul[i * b + k] : 0.f;
-        }
-#pragma unroll
-        for (int u = 0; u < kPer; ++u) {
-            const int t = tid + u * kCholThreads, i = t >> 7, k = t & 127;
-            As[i * kP + k] = v[u];
-        }
-    }
-    const float alpha = 1.f;
-    __syncthreads();
-    // 36 upper tiles of 16 x 16, longest k range first: tile (ti, tj) needs k in [16 ti, 16 tj + 16)
-    for (int job = wave; job < 36; job += kWaves) {
-        int d = 7, first = 0;
-        while (job >= first + (8 - d)) { first += 8 - d; --d; }
-        const int ti = job - first, tj = ti + d;
-        f4v acc = {0.f, 0.f, 0.f, 0.f};
-        acc = mma16(acc, As + (16 * ti + t_i) * kP + 16 * ti + t_q, 1, Xs + (16 * ti + t_q) * kP + 16 * tj + t_i, kP, 4 * (d + 1), alpha);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int i = 16 * ti + 4 * t_q + e, j = 16 * tj + t_i;
-            if (i < b && j < b) Cmul[i * b + j] = acc[e];
-        }
-    }
-    for (int t = tid; t < b * b; t += kCholThreads) {
-        const int i = t / b, j = t % b;
-        if ((i >> 4) > (j >> 4)) Cmul[t] = 0.f;
     }
 }
 

@@ -144,13 +144,18 @@ __device__ __forceinline__ void small_product(gs_f4v (&acc)[4], const float* As,
 
 __global__ __launch_bounds__(256) void gemm_small_kernel(float* __restrict__ A, int64_t lda, const float* __restrict__ B,
                                                          int64_t ldb, float* __restrict__ C, int64_t ldc, int64_t rows,
-                                                         int k, int c, int64_t clear_rows, int vec_b, int transposed) {
+                                                         int k, int c, int64_t clear_rows, int vec_b, int transposed,
+                                                         float* A2, float* C2, int first2) {
     extern __shared__ __align__(16) float gs_sm[];
     float* As = gs_sm;                          // [32][132]
     float* Bs = gs_sm + kGsRows * kGsPitch;     // [128][132]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int t_i = lane & 15, t_q = lane >> 4, rt = wave >> 1, ct0 = (wave & 1) * 4;
-    const int64_t r0 = (int64_t)blockIdx.x * kGsRows;
+    int64_t r0 = (int64_t)blockIdx.x * kGsRows;
+    if ((int)blockIdx.x >= first2) {            // the k rows of the second operand, stored like the first
+        r0 -= (int64_t)first2 * kGsRows;
+        A = A2; lda = k; C = C2; ldc = c; rows = k; clear_rows = 0; transposed = 0;
+    }
 
     // A: 32 rows x 128 k = 1024 float4, four per thread (k is a multiple of 4 and rows are 16-byte aligned)
     float4 av[4];
@@ -319,10 +324,10 @@ int aser_jacobi_eig(aser_ctx* ctx, const float* Mb, int b, float* lambda, float*
 }
 
 int aser_gemm_small_f32(aser_ctx* ctx, float* A, int64_t lda, const float* B, int64_t ldb, float* C, int64_t ldc,
-                        int64_t rows, int k, int c, int64_t clear_rows, bool transposed) {
+                        int64_t rows, int k, int c, int64_t clear_rows, bool transposed, float* A2, float* C2) {
     if (rows <= 0) return ASER_OK;
     if (k <= 0 || c <= 0 || k > 128 || c > 128 || (k & 3)) ASER_FAIL(ctx, ASER_ERR_SHAPE, "gemm_small: need 0 < k, c <= 128, k %% 4 == 0");
-    if (((uintptr_t)A & 15) || (lda & 3)) ASER_FAIL(ctx, ASER_ERR_INVALID_ARG, "gemm_small: A must be 16-byte aligned with lda %% 4 == 0");
+    if (((uintptr_t)A & 15) || (lda & 3) || ((uintptr_t)A2 & 15)) ASER_FAIL(ctx, ASER_ERR_INVALID_ARG, "gemm_small: A must be 16-byte aligned with lda %% 4 == 0");
     const int vec_b = (((uintptr_t)B & 15) == 0 && (ldb & 3) == 0 && (c & 3) == 0) ? 1 : 0;
     static bool attr_set[16] = {false};
     const size_t lds = (size_t)(kGsRows + 128) * kGsPitch * sizeof(float);
@@ -331,8 +336,9 @@ int aser_gemm_small_f32(aser_ctx* ctx, float* A, int64_t lda, const float* B, in
         attr_set[ctx->device] = true;
     }
     const int64_t cover = rows > clear_rows ? rows : clear_rows;
-    hipLaunchKernelGGL(gemm_small_kernel, dim3((unsigned)ceil_div64(cover, kGsRows)), dim3(256), lds, ctx->stream, A, lda, B, ldb,
-                       C, ldc, rows, k, c, clear_rows, vec_b, transposed ? 1 : 0);
+    const int first2 = (int)ceil_div64(cover, kGsRows), more = A2 ? (int)ceil_div64(k, kGsRows) : 0;
+    hipLaunchKernelGGL(gemm_small_kernel, dim3((unsigned)(first2 + more)), dim3(256), lds, ctx->stream, A, lda, B, ldb,
+                       C, ldc, rows, k, c, clear_rows, vec_b, transposed ? 1 : 0, A2, C2, first2);
     return aser_check_launch(ctx, "gemm_small");
 }
 

@@ -154,13 +154,13 @@ constexpr int32_t kPivotBase = -1000;
 
 // out (rows x b) = Y R^-1 with R^T R = Y^T Y (Cholesky-QR); R^-1 is left in Rinv.  Mb must be zero on
 // entry and is zero again on return.  The first clear_rows rows of Y are cleared after they have
-// been read (0: Y is left alone).  Lmul / Cmul: the factorisation kernel also leaves Cmul = Lmul R^-1
-// (see aser_chol_block); both null: nothing.
+// been read (0: Y is left alone).  Lmul / Cmul (b x b): the last launch also leaves Cmul = Lmul R^-1 (in the factorisation kernel, one
+// workgroup, that took 6 us); both null: nothing.
 int chol_qr(aser_ctx* ctx, int form, float* Y, float* out, int64_t rows, int64_t clear_rows, int b, float* Mb, float* Rinv,
-            int32_t* info, const float* Lmul = nullptr, float* Cmul = nullptr) {
+            int32_t* info, float* Lmul = nullptr, float* Cmul = nullptr) {
     ASER_TRY(gemm_tn_atomic(ctx, form, Y, b, Y, b, Mb, b, b, b, rows, 128, 128, false, /*upper_only=*/true));
-    ASER_TRY(aser_chol_block(ctx, Mb, b, b, Rinv, info, kPivotBase, /*clear_d=*/true, Lmul, Cmul));
-    return aser_gemm_small_f32(ctx, Y, b, Rinv, b, out, b, rows, b, b, clear_rows);
+    ASER_TRY(aser_chol_block(ctx, Mb, b, b, Rinv, info, kPivotBase, /*clear_d=*/true));
+    return aser_gemm_small_f32(ctx, Y, b, Rinv, b, out, b, rows, b, b, clear_rows, false, Lmul, Cmul);
 }
 
 // The plan with the block width made legal for the shape: ASER_OK, or ASER_ERR_SHAPE with a text in *why.
@@ -325,7 +325,7 @@ extern "C" int aser_error_reconstruct_enqueue(aser_ctx* ctx, const float* T, int
                 GemmArgs gz = atomic_args(ctx->share, form, Zt, b, Zt, b, Mb, b, b, b, n, 128, 128, /*upper_only=*/true);
                 gz.gate = gate;
                 ASER_TRY(aser_gemm_tn(ctx, gz));
-                ASER_TRY(aser_chol_block(ctx, Mb, b, b, Rz_inv, info, kPivotBase, /*clear_d=*/true, nullptr, nullptr, beta_dev, gate));
+                ASER_TRY(aser_chol_block(ctx, Mb, b, b, Rz_inv, info, kPivotBase, /*clear_d=*/true, beta_dev, gate));
             }
             ASER_TRY(gemm_tn_atomic(ctx, form, At, m, Zt, b, Qraw, b, m, b, n, bm(m), bnB, false)); // A Zt
             // (A Zt + beta' Q_{k-1} P_k) R~^-1; Qraw and Zt are zero again afterwards

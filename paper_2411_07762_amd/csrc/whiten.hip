@@ -239,7 +239,7 @@ __global__ __launch_bounds__(kCholThreads) __attribute__((amdgpu_waves_per_eu(2,
         const int b = (int)(rem < kNb ? rem : kNb);
         float* D = w.S + w.k0 * w.lds + w.k0;
         const UpdatedBlock<IN, FAST> source{D, w.k0 ? D - kNb * w.lds : nullptr, w.lds, b};
-        chol_block_body(source, (float*)smem, D, w.lds, b, w.Rinv, w.info, (int32_t)w.k0, 0, nullptr, nullptr, nullptr);
+        chol_block_body(source, (float*)smem, D, w.lds, b, w.Rinv, w.info, (int32_t)w.k0, 0, nullptr);
         return;
     }
     int t = (int)blockIdx.x - 1;
