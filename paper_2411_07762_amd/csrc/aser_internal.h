@@ -209,11 +209,11 @@ int aser_chol_block(aser_ctx* ctx, float* D, int64_t ld, int b, float* Rinv, int
 // descending into lambda (b), eigenvectors as columns of V (b x b, ld = b).  b <= 128, b even.
 // `gate` (device, may be null): the kernel returns at once when *gate == 0.
 int aser_jacobi_eig(aser_ctx* ctx, const float* Mb, int b, float* lambda, float* V, const int* gate);
-// Same result by tridiagonalisation + multisection + twisted factorisation (much faster).  Scratch: refl
-// (b * 128 floats) and tri (384 floats).  *cluster_flag (device) is written: 1 when two eigenvalues are too
-// close for that method, else 0; the caller then runs aser_jacobi_eig gated on the flag.  2 <= b <= 128.
+// The same for the `need` largest eigenvalues by tridiagonalisation + multisection + twisted factorisation (much faster; the other
+// entries of lambda and columns of V are left alone).  Scratch: refl (b * 128 floats) and tri (384 floats).  *cluster_flag (device) is
+// written: 1 when one of these and the next smaller eigenvalue are too close for that method, else 0; the caller then runs aser_jacobi_eig gated on the flag.  2 <= b <= 128.
 int aser_tridiag_eig(aser_ctx* ctx, const float* Mb, int b, float* lambda, float* V, float* refl, float* tri,
-                     int* cluster_flag);
+                     int* cluster_flag, int need);
 // C (rows x c) = A (rows x k) * B (k x c), fp32 MFMA; k, c <= 128, k % 4 == 0, A 16-byte aligned with
 // lda % 4 == 0.  C may not alias A.  The first clear_rows rows of A (k columns each; may exceed `rows`) are
 // set to zero after they have been read.  transposed: the result is stored as C^T (c x rows, leading dimension ldc).

@@ -1,20 +1,23 @@
 // Symmetric eigen-solver for the Rayleigh-Ritz step of the truncated SVD (Eq. 6): all eigenpairs
-// of a b x b matrix (b <= 128), eigenvalues descending.  Two kernels:
+// of a b x b matrix (b <= 128), eigenvalues descending; the `need` largest are wanted.  Two kernels:
 //
 //   tridiag_kernel   one workgroup of 256 threads, the matrix lives in registers (8 x 8 elements per
 //                    thread, rows and columns dealt cyclically).
 //                    Householder tridiagonalisation M = Q T Q^T in fp32: per reflector one
 //                    mat-vec reduced along 16-lane DPP rows, one rank-2 update, two barriers.
-//   ritz_pair_kernel one wavefront per eigenvalue, b wavefronts spread over the chip.  In fp64:
-//                    65-section on Sturm counts (8 rounds), twisted factorisation of T - lambda I
+//   ritz_pair_kernel one wavefront per wanted eigenvalue, spread over the chip.  In fp64:
+//                    65-section on Sturm counts (9 rounds), twisted factorisation of T - lambda I
 //                    (forward and backward recurrences side by side in two lanes), eigenvector from
 //                    the twist index; then back-transformation through the b - 2 reflectors in fp32.
 //
 // The tridiagonal problem is solved in fp64 because the spectrum it sees (squared singular values
 // of a quantisation-error matrix) has a dense bulk whose spacing is close to fp32 resolution of
 // the largest eigenvalue; in fp64 the vectors of distinct eigenvalues come out orthogonal to about
-// 1e-16 / relative gap.  If two eigenvalues are closer than 1e-8 of the spectral radius a flag is
-// raised instead and the caller runs the Jacobi solver, which does not care about clusters.
+// 1e-16 / relative gap.  If a wanted eigenvalue is closer than 1e-9 of the spectral radius to the next smaller one a flag is
+// raised instead and the caller runs the Jacobi solver (2.6 ms), which does not care about clusters.  Nine rounds leave an interval of
+// 5e-17 of the radius, below the rounding of the counts: neighbouring vectors at a distance of 1e-9 are orthogonal to 8e-8, against 3e-7 at
+// 1e-8 with eight rounds (interval 3e-15; emulated in fp64 on the CPU).  With that limit, and the unwanted half of the block looked at too, bulk
+// neighbours met it in four of six passes over a 14336 x 4096 layer whose leading eigenvalue is far above the bulk.
 #include <type_traits>
 
 #include "aser_internal.h"
@@ -240,7 +243,7 @@ __device__ __forceinline__ int sturm_count(const double* d, const double* e2, in
     return cnt;
 }
 
-// One wavefront: eigenvalue number blockIdx.x (ascending) of the tridiagonal and its eigenvector,
+// One wavefront: eigenvalue number blockIdx.x (descending; m counts ascending) of the tridiagonal and its eigenvector,
 // mapped back through the reflectors.  Writes lambda[b - 1 - m] and column b - 1 - m of Vout.
 __global__ __launch_bounds__(64) void ritz_pair_kernel(const float* __restrict__ tri, const float* __restrict__ refl, int b,
                                                        float* __restrict__ lambda, float* __restrict__ Vout,
@@ -249,7 +252,7 @@ __global__ __launch_bounds__(64) void ritz_pair_kernel(const float* __restrict__
     __shared__ float ef[kB], tau[kB];
     extern __shared__ __align__(16) float rl[];     // [b - 2][kB] reflectors, read once up front
     const int lane = threadIdx.x;
-    const int m = blockIdx.x;
+    const int m = b - 1 - (int)blockIdx.x;
     // the reflectors, 16 float4 per lane in flight at a time
     for (int t0 = 0; t0 < (b - 2) * (kB / 4); t0 += 64 * 16) {
         float4 v[16];
@@ -288,7 +291,7 @@ __global__ __launch_bounds__(64) void ritz_pair_kernel(const float* __restrict__
 
     // ---- eigenvalue: 64 interior points per round
     double lo = glo - 1e-12 * radius - tiny, hi = ghi + 1e-12 * radius + tiny;
-    for (int round = 0; round < 8; ++round) {
+    for (int round = 0; round < 9; ++round) {
         const double x = lo + (hi - lo) * ((double)(lane + 1) * (1.0 / 65.0));
         const int cnt = sturm_count(dd, e2, b, x, tiny);
         const double clo = wave_max_d((cnt <= m) ? x : lo);
@@ -298,7 +301,7 @@ __global__ __launch_bounds__(64) void ritz_pair_kernel(const float* __restrict__
     }
     const double lam = 0.5 * (lo + hi);
     int bad = 0;
-    if (m + 1 < b) bad = sturm_count(dd, e2, b, lam + 1e-8 * radius, tiny) > m + 1;
+    if (m > 0) bad = sturm_count(dd, e2, b, lam - 1e-9 * radius, tiny) < m;
 
     // ---- twisted factorisation: lane 0 runs D+ downwards, lane 1 runs D- upwards
     {
@@ -384,7 +387,8 @@ __global__ __launch_bounds__(64) void ritz_pair_kernel(const float* __restrict__
 
 }  // namespace
 
-int aser_tridiag_eig(aser_ctx* ctx, const float* Mb, int b, float* lambda, float* V, float* refl, float* tri, int* cluster_flag) {
+int aser_tridiag_eig(aser_ctx* ctx, const float* Mb, int b, float* lambda, float* V, float* refl, float* tri, int* cluster_flag, int need) {
+    if (need < 1 || need > b) ASER_FAIL(ctx, ASER_ERR_SHAPE, "sym_eig: 1 to b eigenpairs");
     if (b < 2 || b > kB) ASER_FAIL(ctx, ASER_ERR_SHAPE, "sym_eig: block size must be in [2, 128]");
     static bool attr_set[16] = {false};
     const size_t lds = (size_t)(6 + (kB - 2)) * kB * sizeof(float);
@@ -395,7 +399,7 @@ int aser_tridiag_eig(aser_ctx* ctx, const float* Mb, int b, float* lambda, float
         attr_set[ctx->device] = true;
     }
     hipLaunchKernelGGL(tridiag_kernel, dim3(1), dim3(256), lds, ctx->stream, Mb, b, refl, tri, cluster_flag);
-    hipLaunchKernelGGL(ritz_pair_kernel, dim3(b), dim3(64), lds_r, ctx->stream, (const float*)tri, (const float*)refl, b, lambda, V,
+    hipLaunchKernelGGL(ritz_pair_kernel, dim3(need), dim3(64), lds_r, ctx->stream, (const float*)tri, (const float*)refl, b, lambda, V,
                        cluster_flag);
     return aser_check_launch(ctx, "tridiag_eig");
 }

@@ -345,8 +345,8 @@ extern "C" int aser_error_reconstruct_enqueue(aser_ctx* ctx, const float* T, int
         float* Zp = Zt;
         float* tp = Qraw;
         ASER_TRY(gemm_tn_atomic(ctx, form, Zp, b, Zp, b, Mb, b, b, b, n, 128, 128, false));
-        ASER_TRY(aser_tridiag_eig(ctx, Mb, b, lambda, Uhat, refl, tri, cluster));
-        ASER_TRY(aser_jacobi_eig(ctx, Mb, b, lambda, Uhat, cluster));      // only runs if eigenvalues cluster
+        ASER_TRY(aser_tridiag_eig(ctx, Mb, b, lambda, Uhat, refl, tri, cluster, (int)r));
+        ASER_TRY(aser_jacobi_eig(ctx, Mb, b, lambda, Uhat, cluster));      // only runs if wanted eigenvalues cluster
         hipLaunchKernelGGL(ritz_factors_kernel, dim3(16), dim3(256), 0, ctx->stream, (const float*)lambda, (const float*)Uhat, b,
                            (int)r, sigma, WA, WBt);
         ASER_TRY(aser_check_launch(ctx, "ritz_factors"));

@@ -365,3 +365,31 @@ def test_dense_solver_at_the_edges_of_its_kernels(m, n, r):
     assert iters == 0 and np.max(np.abs(sigma.cpu().numpy() / sg[:r] - 1.0)) <= 1e-6
     assert np.linalg.norm(got - want) / np.linalg.norm(want) <= 1e-5
     assert abs(err - np.sqrt(np.sum(sg[r:] ** 2))) <= 1e-5 * np.linalg.norm(sg)
+
+
+@pytest.mark.parametrize("m,n,r,wanted", [(1100, 1028, 8, "apart"), (1100, 1028, 8, "equal"), (1030, 1200, 1, "apart"), (1029, 1100, 32, "apart"), (1100, 1028, 64, "equal")])
+def test_reconstruction_with_equal_singular_values(m, n, r, wanted):
+    """A bulk of equal singular values behind the wanted ones, whose pairs nobody asks for, and equal ones among these.  Bars: the product 1e-3 as
+    elsewhere; squared singular values 128 * 2^-24 of the largest (fp32 reflectors of a block of 128); columns of L_A orthogonal to twice that,
+    measured in their norms, with 2^-17 for the products that form the basis."""
+    rng = np.random.default_rng([94, m, n, r])
+    k = min(m, n)
+    sg = np.full(k, 0.5)
+    sg[:r] = np.linspace(3.0, 2.0, r) if wanted == "apart" else 2.0
+    sg[0] = 40.0
+    U, V = np.linalg.qr(rng.standard_normal((m, k)))[0], np.linalg.qr(rng.standard_normal((n, k)))[0]
+    S = (np.tril(rng.standard_normal((n, n)), -1) * 0.01 + np.diag(rng.uniform(1.0, 3.0, n))).astype(np.float32)
+    A = (U * sg) @ V.T
+    T = np.ascontiguousarray(np.linalg.solve(S.astype(np.float64).T, A.T).T).astype(np.float32)
+    want = U[:, :r] @ (U[:, :r].T @ T.astype(np.float64))
+    ctx = new_ctx()
+    ctx.ensure_workspace(aser.aser_workspace_bytes(m, n, r))
+    L_A, L_B, sigma = (torch.empty(shape, dtype=torch.float32, device=DEV) for shape in ((m, r), (r, n), (r,)))
+    st, err, iters = aser.aser_error_reconstruct(ctx, torch.from_numpy(T).to(DEV), torch.from_numpy(S).to(DEV), r, L_A, L_B, sigma)
+    ctx.check(st)
+    la, s = L_A.double().cpu().numpy(), sigma.double().cpu().numpy()
+    assert iters > 0 and abs(err - 0.5 * np.sqrt(k - r)) <= 1e-4 * err
+    assert np.linalg.norm(la @ L_B.double().cpu().numpy() - want) <= 1e-3 * np.linalg.norm(want)
+    assert np.max(np.abs(s ** 2 - sg[:r] ** 2)) <= 128 * 2.0 ** -24 * sg[0] ** 2
+    u = la / np.linalg.norm(la, axis=0)
+    assert np.max(np.abs(u.T @ u - np.eye(r))) <= 256 * 2.0 ** -24 + 2.0 ** -17
