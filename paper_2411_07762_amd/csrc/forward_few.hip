@@ -102,7 +102,7 @@ __global__ __launch_bounds__(512) void few_down_kernel(FewArgs g) {
 // y (outputs O .. O + 15 of 16 tokens, this lane's four outputs of token t) += s_t P L_A^T, on the fp32 MFMA instruction.
 __device__ __forceinline__ f4v few_rank(const FewArgs& g, f4v y, int64_t O, int t, bool tok, float sx, int li, int lg) {
     const int64_t orow = O + li;                             // the row of L_A that this lane feeds
-        const float* ap = g.L_A + (orow < g.m ? orow : 0) * g.r;
+    const float* ap = g.L_A + (orow < g.m ? orow : 0) * g.r;
     const float* pp = g.part + (int64_t)(tok ? t : 0) * g.rp;
     for (int k0 = 0; k0 < g.rp; k0 += 64) {              // four steps of 16 at a time: their loads are in flight together
         float av[4][4];
