@@ -21,6 +21,8 @@ typedef int v4i_t __attribute__((ext_vector_type(4)));
 typedef float f4v __attribute__((ext_vector_type(4)));
 
 constexpr int kDownChunk = 2048;      // channels per partial P
+constexpr int kDownSum = 256;         // channels per sum inside one
+constexpr int kDownSums = kDownChunk / kDownSum;
 
 __device__ __forceinline__ float round_bf16(float x) {
     const uint32_t u = __float_as_uint(x);
@@ -36,7 +38,8 @@ struct FewArgs {
 };
 
 // part[chunk][t][k] = sum over 2048 channels of xq[t][i] L_B[k][i] (without s_t), k up to rp (r rounded up to 16; zeros
-// behind r).  A workgroup takes 16 rows of L_B and 16 tokens, a wavefront 2048 / NW channels of them; lane (l % 16, g = l / 16)
+// behind r).  A workgroup takes 16 rows of L_B and 16 tokens, a wavefront 2048 / NW channels of them, in fp32 sums of 256 channels
+// each, so that P does not depend on NW; lane (l % 16, g = l / 16)
 // feeds channels 16 s + 4 g + e of its row and of its token to the e-th of four v_mfma_f32_16x16x4_f32 (codes and products
 // exact, fp32 sums).  All loads of a round are in flight at once: they are unconditional (addresses clamped into the
 // operands, the values dropped afterwards), because a load behind a branch is waited for where the branches meet.
@@ -49,53 +52,56 @@ __device__ __forceinline__ void few_down(const FewArgs& g, int task, float (*red
     const bool kok = k < g.r, tok = t < g.rows;
     const float* bp = g.L_B + (int64_t)(kok ? k : 0) * g.n;
     const int8_t* xp = g.xq + (int64_t)(tok ? t : 0) * g.n;
-    f4v acc = {0.f, 0.f, 0.f, 0.f};
     // NS * 16 channels at a time: with 256 the registers of the eight-wavefront kernels would leave room for one workgroup per compute unit
     constexpr int NS = 8;
 #pragma unroll 1
-    for (int h = 0; h < kDownChunk / NW; h += 16 * NS) {
-        const int64_t c0 = (int64_t)chunk * kDownChunk + wave * (kDownChunk / NW) + h + 4 * lg;
-        if (c0 - 4 * lg >= g.n) break;
-        float4 b[NS];
-        uint32_t x[NS];
-        if (g.vec_b) {
+    for (int w = wave * (kDownSums / NW); w < (wave + 1) * (kDownSums / NW); ++w) {
+        f4v acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+        for (int h = 0; h < kDownSum; h += 16 * NS) {
+            const int64_t c0 = (int64_t)chunk * kDownChunk + w * kDownSum + h + 4 * lg;
+            if (c0 - 4 * lg >= g.n) break;
+            float4 b[NS];
+            uint32_t x[NS];
+            if (g.vec_b) {
 #pragma unroll
-            for (int s = 0; s < NS; ++s) b[s] = *(const float4*)(bp + ((c0 + 16 * s < g.n) ? c0 + 16 * s : 0));   // n % 32 == 0: four channels are whole or absent
-        } else {
+                for (int s = 0; s < NS; ++s) b[s] = *(const float4*)(bp + ((c0 + 16 * s < g.n) ? c0 + 16 * s : 0));   // n % 32 == 0: four channels are whole or absent
+            } else {
+#pragma unroll
+                for (int s = 0; s < NS; ++s) {
+                    const float* q = bp + ((c0 + 16 * s < g.n) ? c0 + 16 * s : 0);
+                    b[s] = make_float4(q[0], q[1], q[2], q[3]);
+                }
+            }
+#pragma unroll
+            for (int s = 0; s < NS; ++s) x[s] = *(const uint32_t*)(xp + ((c0 + 16 * s < g.n) ? c0 + 16 * s : 0));
 #pragma unroll
             for (int s = 0; s < NS; ++s) {
-                const float* q = bp + ((c0 + 16 * s < g.n) ? c0 + 16 * s : 0);
-                b[s] = make_float4(q[0], q[1], q[2], q[3]);
+                const bool in = c0 + 16 * s < g.n;
+                const uint32_t xs = (in && tok) ? x[s] : 0u;
+                const float bb[4] = {b[s].x, b[s].y, b[s].z, b[s].w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float v = (in && kok) ? bb[e] : 0.f;
+                    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(g.split ? v : round_bf16(v), (float)((int)(xs << (24 - 8 * e)) >> 24), acc, 0, 0, 0);
+                }
             }
         }
 #pragma unroll
-        for (int s = 0; s < NS; ++s) x[s] = *(const uint32_t*)(xp + ((c0 + 16 * s < g.n) ? c0 + 16 * s : 0));
-#pragma unroll
-        for (int s = 0; s < NS; ++s) {
-            const bool in = c0 + 16 * s < g.n;
-            const uint32_t xs = (in && tok) ? x[s] : 0u;
-            const float bb[4] = {b[s].x, b[s].y, b[s].z, b[s].w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const float v = (in && kok) ? bb[e] : 0.f;
-                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(g.split ? v : round_bf16(v), (float)((int)(xs << (24 - 8 * e)) >> 24), acc, 0, 0, 0);
-            }
-        }
+        for (int e = 0; e < 4; ++e) red[w][li][4 * lg + e] = acc[e];     // (token li, row 4 lg + e)
     }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) red[wave][li][4 * lg + e] = acc[e];      // (token li, row 4 lg + e)
     __syncthreads();
     if (tid < 256) {
         const int tt = tid >> 4, kk = tid & 15;
         float s = 0.f;
 #pragma unroll
-        for (int w = 0; w < NW; ++w) s += red[w][tt][kk];
+        for (int w = 0; w < kDownSums; ++w) s += red[w][tt][kk];
         if (tz * 16 + tt < g.rows) g.part[((int64_t)chunk * g.rows + tz * 16 + tt) * g.rp + ky * 16 + kk] = s;
     }
 }
 
 __global__ __launch_bounds__(512) void few_down_kernel(FewArgs g) {
-    __shared__ float red[8][16][17];
+    __shared__ float red[kDownSums][16][17];
     few_down<8>(g, blockIdx.x, red);
 }
 
@@ -153,7 +159,7 @@ __global__ __launch_bounds__(64 * NW) void few_main_kernel(FewArgs g) {
     constexpr int STEP = W4 ? 128 : 64;                     // channels per step: 16 bytes of codes per lane
     constexpr int U = (TG >= 4) ? 2 : 4;                    // steps in flight
     constexpr int OP = OUT + 4;
-    constexpr int kRed = (!BESIDE || TOK * OP > NW * 16 * 17) ? TOK * OP : NW * 16 * 17;
+    constexpr int kRed = (!BESIDE || TOK * OP > kDownSums * 16 * 17) ? TOK * OP : kDownSums * 16 * 17;
     __shared__ int red[kRed];
     if (BESIDE && (int)blockIdx.x < g.down) {
         few_down<NW>(g, blockIdx.x, (float(*)[16][17])red);

@@ -342,6 +342,27 @@ def test_forward_of_a_few_tokens_with_many_outputs(rows, n, m, r, packed):
             assert np.linalg.norm(got[:, :m] - want) / np.linalg.norm(want) <= bar
 
 
+@pytest.mark.parametrize("rows,n,m,r,packed", [(1, 2048, 8193, 64, True), (16, 4096, 14336, 40, True), (5, 6176, 16384, 16, False), (13, 11008, 8200, 128, False)])
+def test_forward_of_a_few_tokens_does_not_depend_on_the_number_of_outputs(rows, n, m, r, packed):
+    """The sums behind P and an output are the same, in the same order, whether P is formed in front of the codes or beside them: bit for bit."""
+    rng = np.random.default_rng([79, rows, n, m, r])
+    xq = torch.from_numpy(rng.integers(-127, 128, (rows, n)).astype(np.int8)).to(DEV)
+    xs = torch.from_numpy(rng.uniform(0.01, 0.05, rows).astype(np.float32)).to(DEV)
+    q = rng.integers(-7, 8, (m, n)).astype(np.int8) if packed else rng.integers(-127, 128, (m, n)).astype(np.int8)
+    wq = torch.from_numpy(orc.pack_int4(q) if packed else q).to(DEV)
+    ws = torch.from_numpy(rng.uniform(0.001, 0.003, m).astype(np.float32)).to(DEV)
+    L_A = torch.from_numpy(rng.standard_normal((m, r)).astype(np.float32)).to(DEV)
+    L_B = torch.from_numpy((rng.standard_normal((r, n)) * 0.01).astype(np.float32)).to(DEV)
+    ctx = new_ctx()
+    ctx.ensure_workspace(aser.aser_forward_workspace_bytes(rows, n, m, r))
+    layout = aser.ASER_CODES_INT4_PACKED if packed else aser.ASER_CODES_INT8
+    for split in (True, False):
+        Y, part = (torch.empty((rows, k), dtype=torch.float32, device=DEV) for k in (m, 4096))
+        ctx.check(aser.aser_compensated_forward(ctx, xq, xs, wq, layout, ws, L_A, L_B, r, split, Y))
+        ctx.check(aser.aser_compensated_forward(ctx, xq, xs, wq[:4096], layout, ws[:4096], L_A[:4096], L_B, r, split, part))
+        assert np.array_equal(Y[:, :4096].cpu().numpy(), part.cpu().numpy())
+
+
 @pytest.mark.parametrize("m,n,r", [(3, 5, 1), (16, 33, 3), (64, 64, 7), (65, 130, 9), (256, 256, 17), (256, 300, 18), (257, 200, 40), (300, 257, 3), (700, 513, 20),
                                    (1000, 1040, 5), (40, 2000, 12)])
 def test_dense_solver_at_the_edges_of_its_kernels(m, n, r):
