@@ -69,6 +69,19 @@ static inline AserGramSplit aser_gram_dma_split(int64_t T, int64_t steps, int64_
 // where it promises 3 %, because the other models are that good.  Measured, without -> with: 1536 channels: 39 -> 31 us at 1000 tokens, 62 -> 53
 // at 6000; 4096: 146 -> 106 at 3000, 203 -> 130 at 4300, 317 -> 179 at 7500, not at 1800 (85 against 93); 6144: 307 -> 230 at 4300; 8192: 367 -> 316
 // at 3000, not at 7500 (605 against 609); 14336: never (728 against 836 at 3000).
+// No range is shorter than the loads that are in flight at its start (aser_gram_shortest); the costs alone keep to 8 steps and more.
+constexpr int kAserGramSegAhead = 5;
+// The shortest range of `steps` in c chunks, each of them in sp parts (rounded up to whole steps; the last chunk and part get what is left).
+static inline int64_t aser_gram_shortest(int64_t steps, int64_t c, int64_t sp) {
+    const int64_t chunk = (steps + c - 1) / c;
+    const int64_t chunks[2] = {chunk, steps - (steps - 1) / chunk * chunk};
+    int64_t least = steps;
+    for (int64_t k : chunks) {
+        const int64_t part = (k + sp - 1) / sp, left = k - (k - 1) / part * part;
+        least = left < least ? left : least;
+    }
+    return least;
+}
 static inline AserGramSplit aser_gram_seg_split(int64_t T, int64_t steps, int64_t parts) {
     AserGramSplit best = {0, 1, 1e30};
     for (int c = 1; c <= 8; c *= 2) {
@@ -76,8 +89,8 @@ static inline AserGramSplit aser_gram_seg_split(int64_t T, int64_t steps, int64_
         const int64_t W = 256 / c, full = T / W, rem = T % W, steps_c = (steps + c - 1) / c;
         for (int64_t sp = 1; sp <= (rem ? W / rem : 1); ++sp) {
             if (c * sp > 1 && rem && 3 * c * sp > 4 * parts) break;
+            if (aser_gram_shortest(steps, c, sp) < kAserGramSegAhead) continue;
             const int64_t last = rem ? (steps_c + sp - 1) / sp : 0;
-            if (sp > 1 && last < 4) break;
             const double cost = 0.47 * (double)(full * steps_c) + 0.458 * (double)last + 0.084 * (double)(c * (full * W + rem * sp)) + 8.5;
             if (cost < best.cost) best = AserGramSplit{c, (int)sp, cost};
         }

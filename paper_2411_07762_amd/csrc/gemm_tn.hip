@@ -444,6 +444,7 @@ int launch_gram_dma(aser_ctx* ctx, const GemmArgs& g) {
 // touched once.  (The 256 x 256 tile has no registers for a second set.)  Data path as in gram_tile_dma, for slabs of 256 and 128 channels in a
 // ring of six stages of 24 KB; four wavefronts of 128 x 64.
 constexpr int kSegStages = 6;
+static_assert(kSegStages - 1 == kAserGramSegAhead, "the rule keeps ranges that fill the ring");
 constexpr int kSegStageBytes = kDmaBK * (512 + 256);
 constexpr size_t kSegLdsBytes = (size_t)kSegStages * kSegStageBytes;
 
@@ -507,13 +508,12 @@ __device__ __forceinline__ void gram_tile_seg(const GemmArgs& g, int64_t I0, int
     const int nsteps = (int)((kEnd - kBeg + kDmaBK - 1) / kDmaBK);
     const int full_steps = (int)((kEnd - kBeg) / kDmaBK);            // stages without ragged rows
     __syncthreads();                                     // the previous tile's readers are done with the ring
-    for (int s = 0; s < kSegStages - 1 && s < nsteps; ++s) {
+    for (int s = 0; s < kSegStages - 1; ++s) {           // a range has at least as many steps
         const int64_t first = kBeg + (int64_t)s * kDmaBK;
 #pragma unroll
         for (int t = 0; t < 6; ++t) issue_one(s, t, first, s >= full_steps);
     }
-    if (nsteps >= kSegStages - 1) __builtin_amdgcn_s_waitcnt(0x4F78);       // vmcnt(24): stage 0 landed
-    else __builtin_amdgcn_s_waitcnt(0x0F70);                         // vmcnt(0)
+    __builtin_amdgcn_s_waitcnt(0x4F78);                              // vmcnt(24): stage 0 landed
     __syncthreads();
     bf16x8_t a0[4], b0[2], a1[4], b1[2];
 #pragma unroll

@@ -141,3 +141,19 @@ def test_gram_chunks_take_two_level_sums_where_they_are_faster(rule):
         tiles, _, parts, _ = gram_query(n, rows)
         count = c * (split if 2 * tiles % (256 // c) else 1)
         assert c in (1, 2, 4, 8) and split >= 1 and (count == 1 or 3 * count <= 4 * parts), (n, rows, c, split, parts)
+
+
+def test_two_level_ranges_fill_the_ring(rule):
+    """Every range of tokens of a workgroup is at least as long as the loads in flight at its start (walked as the kernel cuts it)."""
+    def ranges(steps, chunks, split):
+        per = -(-steps // chunks)
+        for a in range(0, steps, per):
+            part = -(-min(per, steps - a) // split)
+            yield from (min(part, min(a + per, steps) - b) for b in range(a, min(a + per, steps), part))
+    cuts = [(steps, c, sp) for steps in (5, 8, 9, 17, 33, 94, 129, 235) for c in (1, 2, 4, 8) for sp in (1, 2, 3, 7, 16)]
+    for cut, (got,) in zip(cuts, rule("shortest", 'printf("%d", (int)aser_gram_shortest(a[0], a[1], a[2]));', cuts)):
+        assert got == min(ranges(*cut)), cut
+    sizes = [(n, rows) for n in range(1032, 3600, 232) for rows in (256, 287, 300, 417, 600, 1090, 9001)]
+    call = 'AserGramSplit q = aser_gram_seg_split(2 * a[0], a[1], a[2]); printf("%d %d %d", q.chunks, q.split, kAserGramSegAhead);'
+    for (n, rows), (c, split, ahead) in zip(sizes, rule("ring", call, [gram_query(n, rows) for n, rows in sizes])):
+        assert min(ranges(-(-rows // 32), c, split)) >= ahead, (n, rows, c, split)
