@@ -163,8 +163,8 @@ int aser_gemm_tn(aser_ctx* ctx, const GemmArgs& g);
 // step; every workgroup adds 0.06 u of atomic traffic that the others wait behind.  More parts shorten
 // the K loop but multiply the atomics, and one workgroup more than 256 doubles the rounds.
 // A part keeps at least min_steps K steps.
-// A step of the 128 x 128 tile has become shorter since the fit (0.5 us); slopes of 0.5 to 0.75 and 0.04 to 0.06 per workgroup give whitenings
-// of 1536 to 11008 columns and reconstructions of 1024 x 4096 to 14336 x 4096 within 1 % of each other, so the constants stand.
+// A step of the 128 x 128 tile has become shorter since the fit (0.5 us); slopes of 0.5 to 0.75 and 0.04 to 0.06 per workgroup give
+// reconstructions of 1024 x 4096 to 14336 x 4096 within 1 % of each other, so the constants stand.
 // share > 1: that many layers are in flight on the device (aser_calibrate_layers).  What a launch costs the
 // other layers is the compute-unit time it holds, workgroups x their duration / 256, and every other layer
 // pays it; the cost then is the launch's own duration plus (share - 1) times that.
@@ -196,7 +196,8 @@ int aser_col_abs_sum_w(aser_ctx* ctx, const float* W, int64_t m, int64_t n, int6
 int aser_transpose_f32(aser_ctx* ctx, const float* A, int64_t rows, int64_t cols, int64_t lda, float* At, int64_t ldat);
 
 // Small dense kernels (one workgroup, matrices in LDS)
-// Upper Cholesky of the b x b block D (ld) in place: upper part <- R (D = R^T R), the part below the diagonal is not read and may be overwritten with zeros;
+// Upper Cholesky of the b x b block D (ld) in place: upper part <- R (D = R^T R).  The part below the diagonal does not count and may
+// be overwritten with zeros, but has to hold finite numbers inside the 4 x 4 blocks on the diagonal (they meet exact zeros in products).
 // Rinv (b x b, ld = b) <- R^-1 (upper).  b <= 128.  On a non-positive pivot at column j,
 // atomicMin(info, pivot_base + j + 1) and the factor is meaningless from that column on.  clear_d: D is overwritten with
 // zeros instead of the factor (callers that only need R^-1 and reuse D as an accumulation target).

@@ -32,13 +32,12 @@ namespace {
 typedef float f4v __attribute__((ext_vector_type(4)));
 
 constexpr int kN = 128;       // largest block
-// LDS pitches: multiples of four for 16-byte accesses; 12 (and 4) modulo 64 banks, so that the MFMA operand reads, four consecutive
-// words of sixteen rows or sixteen of four rows, have no or few conflicts
+// LDS pitches: multiples of four for 16-byte accesses; 12 and 36 modulo 64 banks, so that sixteen rows start at the sixteen multiples of
+// four and the MFMA operand reads of four consecutive words of each have no conflicts
 constexpr int kP = 140;
 constexpr int kPZ = 36;
 constexpr int kSub = 32;
 constexpr int kCholThreads = 512;
-constexpr int kWaves = kCholThreads / 64;
 constexpr size_t kCholLdsBytes = (size_t)(2 * kN * kP + 96 * kPZ + kN + 20 * 64) * sizeof(float);
 
 // Trailing update of one 16 x 16 tile behind the sub-block at offset o: A[i][c] -= sum_k P[k][i] P[k][c]

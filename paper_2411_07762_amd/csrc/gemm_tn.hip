@@ -1,10 +1,11 @@
 // MFMA contraction kernel of the ASER calibration path for gfx950 (CDNA4).
 //
-// One kernel form serves every dense contraction of the path:  C (op)= alpha * A^T B  with
+// One kernel form serves the dense contractions of the path:  C (op)= alpha * A^T B  with
 // both operands stored K-major (A: K x M, B: K x N, row-major).  The Gram matrix of Eq. 5
-// (G = X^T X with X tokens x channels) has exactly this form, and the Cholesky panels and
-// trailing updates, the whitened error T S, the subspace-iteration products and the small
-// Gram matrices of the orthogonalisation are arranged by their callers to have it too.
+// (G = X^T X with X tokens x channels) has exactly this form, and the whitened error T S, the
+// subspace-iteration products and the small Gram matrices of the orthogonalisation are arranged
+// by their callers to have it too.  (The updates and panels of the whitening have it as well and
+// share the tile of gemm_tile.h, in the launches of whiten.hip.)
 //
 // Data path.  Each workgroup (256 threads = 4 waves in a 2 x 2 grid; 512 threads and 8 waves for 256 x 128) owns a BM x BN
 // tile of C.

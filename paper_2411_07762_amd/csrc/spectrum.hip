@@ -861,9 +861,12 @@ __device__ __forceinline__ void invit_solve_one(int64_t k, const double* __restr
     for (int64_t i = 0; i < k; ++i) x[i] *= sc;
 }
 
-__device__ __forceinline__ double tridiag_norm(int64_t k, const double* __restrict__ d, const double* __restrict__ e) {
+// Largest row sum of the tridiagonal matrix (d, e), by a whole wavefront.
+__device__ __forceinline__ double tridiag_norm(int64_t k, const double* d, const double* e) {
     double tnorm = 0.0;
-    for (int64_t l = 0; l < k; ++l) tnorm = fmax(tnorm, fabs(d[l]) + (l + 1 < k ? fabs(e[l]) : 0.0) + (l > 0 ? fabs(e[l - 1]) : 0.0));
+    for (int64_t l = threadIdx.x & 63; l < k; l += 64) tnorm = fmax(tnorm, fabs(d[l]) + (l + 1 < k ? fabs(e[l]) : 0.0) + (l > 0 ? fabs(e[l - 1]) : 0.0));
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) tnorm = fmax(tnorm, __shfl_xor(tnorm, o, 64));
     return tnorm;
 }
 
@@ -902,11 +905,7 @@ __global__ __launch_bounds__(256) void tridiag_invit_kernel(int64_t k, int r, co
         scr = X + (int64_t)r * ld;
         __syncthreads();
     }
-    double tnorm = 0.0;
-    for (int64_t l = lane; l < k; l += 64) tnorm = fmax(tnorm, fabs(d[l]) + (l + 1 < k ? fabs(e[l]) : 0.0) + (l > 0 ? fabs(e[l - 1]) : 0.0));
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) tnorm = fmax(tnorm, __shfl_xor(tnorm, o, 64));
-    const double tiny = fmax(tnorm * 2.3e-16, 1e-300);
+    const double tiny = fmax(tridiag_norm(k, d, e) * 2.3e-16, 1e-300);
     for (int64_t t = tid; t < (int64_t)r * k; t += 256) X[t / k * ld + t % k] = invit_start_value(t);
     __syncthreads();
     for (int round = 0; round < 3; ++round) {
@@ -962,8 +961,8 @@ __global__ __launch_bounds__(64) void invit_solve_kernel(int64_t k, int r, const
                                                          const double* __restrict__ e, const double* __restrict__ lam,
                                                          double* __restrict__ X, double* __restrict__ scr) {
     const int c = blockIdx.x * 64 + threadIdx.x;
-    if (c >= r) return;
     const double tiny = fmax(tridiag_norm(k, d, e) * 2.3e-16, 1e-300);
+    if (c >= r) return;
     double* dd = scr + (int64_t)c * 3 * k;
     invit_solve_one(k, d, e, lam[c], tiny, X + (int64_t)c * k, dd, dd + k, dd + 2 * k);
 }
