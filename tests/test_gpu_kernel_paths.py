@@ -1,5 +1,7 @@
 """The dispatch borders of single kernels: sizes at the edges of tiles and of the rules that pick a kernel, against
 NumPy or the oracle."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -445,3 +447,54 @@ def test_reconstruction_with_equal_singular_values(m, n, r, wanted):
     assert np.max(np.abs(s ** 2 - sg[:r] ** 2)) <= 128 * 2.0 ** -24 * sg[0] ** 2
     u = la / np.linalg.norm(la, axis=0)
     assert np.max(np.abs(u.T @ u - np.eye(r))) <= 256 * 2.0 ** -24 + 2.0 ** -17
+
+
+def double_well(b, distance, rng):
+    """A symmetric tridiagonal matrix of few-bit entries whose two largest eigenvalues (all it has come in pairs) lie `distance`, within a tenth,
+    of its radius apart: two mirrored halves that a small entry couples.  Tridiagonal already and exact in fp32, so the solver sees it unrounded."""
+    h = b // 2
+    for _ in range(100000):
+        d, e, c = rng.integers(64, 192, h) / 64.0, rng.integers(8, 64, h - 1) / 64.0, 2.0 ** -float(rng.integers(4, 28))
+        half = np.diag(d) + np.diag(e, 1) + np.diag(e, -1)
+        w, v = np.linalg.eigh(half)
+        rows = d + np.concatenate([[0.0], e]) + np.concatenate([e, [c]])
+        guess = 2.0 * c * v[-1, -1] ** 2 / rows.max()
+        if not 0.5 * distance < guess < 2.0 * distance:
+            continue
+        half[-1, -1] += c
+        up = np.linalg.eigvalsh(half)[-1]
+        half[-1, -1] -= 2.0 * c
+        down = np.linalg.eigvalsh(half)[-1]
+        if abs((up - down) / rows.max() / distance - 1.0) < 0.1:
+            full = np.diag(np.concatenate([d, d[::-1]])).astype(np.float32)
+            off = np.concatenate([e, [c], e[::-1]])
+            return full + np.diag(off, 1).astype(np.float32) + np.diag(off, -1).astype(np.float32), np.array([up, down])
+    raise AssertionError("none found")
+
+
+@pytest.mark.parametrize("b,need", [(128, 2), (128, 1), (96, 2), (40, 2)])
+@pytest.mark.parametrize("distance,apart", [(2e-10, False), (7e-10, False), (1.3e-9, True), (3e-9, True), (8e-9, True), (1e-7, True)])
+def test_ritz_pairs_at_the_distance_where_the_fallback_takes_over(b, need, distance, apart):
+    """The eigen-solvers of the Ritz problem, called as the reconstruction calls them: from 1e-9 of the radius on the vectors are those of the
+    twisted factorisation, below they are the Jacobi solver's, also where only one of the pair is wanted.  Orthogonality: 2^-23 for fp32
+    entries, and an error of 2^-52 of the radius in each eigenvalue over their distance (an interval of 3e-15, as after eight rounds of
+    the multisection, would leave up to 2.5e-6 at the smallest distance); after about ten sweeps of 127 fp32 rotations 1e-4."""
+    M, pair = double_well(b, distance, np.random.default_rng([95, b, need, int(distance * 1e11)]))
+    lib, ctx = aser.load_library(), new_ctx()
+    Md = torch.from_numpy(M).to(DEV)
+    lam, V, refl, tri = (torch.full(shape, 7.0, dtype=torch.float32, device=DEV) for shape in ((b,), (b, b), (b, 128), (384,)))
+    flag = torch.zeros(1, dtype=torch.int32, device=DEV)
+    p = lambda t: ctypes.c_void_p(t.data_ptr())
+    ctx.check(lib["_Z16aser_tridiag_eigP8aser_ctxPKfiPfS3_S3_S3_Pii"](ctx.handle, p(Md), b, p(lam), p(V), p(refl), p(tri), p(flag), need))
+    torch.cuda.synchronize()
+    before = V.cpu().numpy()
+    assert int(flag.item()) == (0 if apart else 1) and np.all(before[:, need:] == 7.0)
+    ctx.check(lib["_Z15aser_jacobi_eigP8aser_ctxPKfiPfS3_PKi"](ctx.handle, p(Md), b, p(lam), p(V), p(flag)))
+    torch.cuda.synchronize()
+    got, pair = V.double().cpu().numpy()[:, :need], pair[:need]
+    assert not apart or np.array_equal(V.cpu().numpy(), before)
+    off = np.max(np.abs(got.T @ got - np.eye(need)))
+    print("distance %.1e: vectors orthogonal to %.1e" % (distance, off))
+    assert off <= (2.0 ** -23 + 2.0 * 2.0 ** -52 / distance if apart else 1e-4)
+    assert np.max(np.abs(lam.cpu().numpy()[:need] / pair - 1.0)) <= (2.0 ** -23 if apart else 1e-4)
+    assert np.max(np.abs(M.astype(np.float64) @ got - got * pair)) <= (2.0 ** -22 if apart else 1e-4) * pair[0]
