@@ -15,9 +15,10 @@
 // the largest eigenvalue; in fp64 the vectors of distinct eigenvalues come out orthogonal to about
 // 1e-16 / relative gap.  If a wanted eigenvalue is closer than 1e-9 of the spectral radius to the next smaller one a flag is
 // raised instead and the caller runs the Jacobi solver (2.6 ms), which does not care about clusters.  Nine rounds leave an interval of
-// 5e-17 of the radius, below the rounding of the counts: neighbouring vectors at a distance of 1e-9 are orthogonal to 8e-8, against 3e-7 at
-// 1e-8 with eight rounds (interval 3e-15; emulated in fp64 on the CPU).  With that limit, and the unwanted half of the block looked at too, bulk
-// neighbours met it in four of six passes over a 14336 x 4096 layer whose leading eigenvalue is far above the bulk.
+// 5e-17 of the radius, below the rounding of the counts: neighbouring vectors at a distance of 1.3e-9 are orthogonal to 8e-8 (measured; the Jacobi solver's
+// are to 2e-6 to 8e-6), against 3e-7 at 1e-8 with eight rounds (interval 3e-15; emulated in fp64 on the CPU).  With that limit, and the unwanted
+// half of the block looked at too, bulk neighbours met it in four of six traced passes over one 14336 x 4096 layer whose leading eigenvalue is
+// far above the bulk; with this one in none.
 #include <type_traits>
 
 #include "aser_internal.h"

@@ -313,6 +313,8 @@ int launch_few(aser_ctx* ctx, FewArgs g) {
     // -> beside; channels, outputs, one token / 16 tokens, r = 64, int4): 2048, 8224: 13.5 -> 12.4 / 18.1 -> 17.0; 4096, 10240: 17.6 -> 14.9 / 23.8 -> 19.9; 4096,
     // 14336: 18.3 -> 15.7 / 24.2 -> 20.3; 14336, 8224: 32.1 -> 29.3 / 46.4 -> 40.0.  Not at 1024, 14336: 10.9 -> 11.7 / 13.5 -> 13.8, nor with eight wavefronts per
     // tile (8192, 8192: 17.8 -> 19.2 / 27.0 -> 28.4; 4096, 4096: 12.0 -> 13.8 / 16.5 -> 19.1) or 64 outputs (8192, 16384: 25.5 -> 24.9 / 33.9 -> 34.1).
+    // int8, 4096, 14336: 23.5 -> 20.3 / 30.9 -> 25.2; r = 1: 21.7 -> 17.9 / 26.2 -> 23.3; with weights that rotate through 0.7 GB (r = 64): int4 20.9 -> 18.6 /
+    // 27.5 -> 22.5, int8 25.8 -> 21.8 / 33.6 -> 27.5.  Over 504 such calls (r 1 to 128) at worst 37.7 -> 38.5 (int4, 11008, 16384, r = 128, one token, rotating).
     if constexpr (TG == 1 && NW == 4 && OT == 2) {
         if (g.r > 0 && g.n >= 2048) {
             hipLaunchKernelGGL((few_main_kernel<W4, OT, TG, NW, true>), dim3((unsigned)(g.down + work)), dim3(64 * NW), 0, ctx->stream, g);
