@@ -21,7 +21,7 @@ CLIENT = os.path.join(PKG, "aser_abi_client")            # tests/native/abi_clie
 CLIENT_SRC = os.path.join(ROOT, "tests", "native", "abi_client.cpp")
 OBJDIR = os.path.join(PKG, "_build")
 
-SOURCES = ["api.hip", "gemm_tn.hip", "bandwidth.hip", "smooth.hip", "dense_small.hip", "chol_block.hip", "eig_sym.hip", "whiten.hip", "reconstruct.hip", "spectrum.hip", "evaluate.hip", "forward.hip", "forward_few.hip", "probe.hip", "layers.hip"]
+SOURCES = ["api.hip", "gemm_tn.hip", "bandwidth.hip", "smooth.hip", "dense_small.hip", "chol_block.hip", "eig_sym.hip", "whiten.hip", "reconstruct.hip", "spectrum.hip", "tridiag_resident.hip", "evaluate.hip", "forward.hip", "forward_few.hip", "probe.hip", "layers.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wno-unused-command-line-argument", "-I", INCLUDE, "-I", CSRC]

@@ -5,12 +5,13 @@
 // A truncated solver does not produce the sum over ALL singular values that Eq. 9 divides by, so this
 // path computes every one of them, in fp64 behind the product T S:
 //   B = Z Z^T  (k x k, k = min(m, n), Z = T S or its transpose)   fp64 accumulation of exact fp32 products
-//   B -> tridiagonal (d, e) by Householder reflections            one launch per column, see below
+//   B -> tridiagonal (d, e) by Householder reflections            on the chip up to 4096 columns (tridiag_resident.hip), else see below
 //   eigenvalues of (d, e) by multisection on Sturm counts         16 to 64 lanes per eigenvalue
 //   sigma_i = sqrt(lambda_i), descending.
 // The singular values of T S and of (T S)^T agree, so B is formed on the shorter side.
 //
-// Tridiagonalisation.  Step j turns column j into (d_j, e_j, 0, ...) with H = I - tau v v^T and needs
+// Tridiagonalisation, where the matrix does not stay on the chip: more than 4096 columns left, fewer than kResidentLeast, several layers in
+// flight (the cooperative launch would hold every compute unit), a stream under capture.  Step j turns column j into (d_j, e_j, 0, ...) with H = I - tau v v^T and needs
 // p = tau B22 v and the rank-2 update B22 -= v w^T + w v^T with w = p - (tau / 2)(v^T p) v.  A step is one launch:
 // a pass over the trailing matrix that forms B22 v with the updates of the last (up to four) steps applied on the fly, of
 // which one in up to four also writes the updated matrix, and in the workgroup that finishes last the reflector of the next
@@ -21,6 +22,8 @@
 #include <math.h>
 
 #include "aser_internal.h"
+#include "tridiag_resident.h"
+#include "wave_f64.h"
 
 namespace {
 
@@ -111,7 +114,7 @@ __device__ __forceinline__ double block_sum(double v, double* red) {   // blockD
 __device__ __forceinline__ void publish(double* p, double v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ double published(const double* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
-constexpr int kTriThreads = 512, kTriRows = 8, kTriPairs = 4;
+constexpr int kTriThreads = 512, kTriRows = 8, kTriPairs = 4, kResidentLeast = 320;
 
 struct TridiagStep {
     int64_t c0, k;
@@ -291,35 +294,6 @@ __global__ __launch_bounds__(kTriThreads) void tridiag_step_kernel(TridiagStep a
     }
 }
 
-// Sum over the wavefront by lane-shifted additions; every lane returns it.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ double shifted(double v) {
-    const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
-    const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)u, CTRL, ROWS, 0xf, false);
-    const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(u >> 32), CTRL, ROWS, 0xf, false);
-    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
-}
-__device__ __forceinline__ double lane_value(double v, int lane) {       // lane: the same in the whole wavefront
-    const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
-    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)u, lane), hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(u >> 32), lane);
-    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
-}
-__device__ __forceinline__ double wave_sum(double v) {
-    v += shifted<0x111, 0xf>(v);                          // within rows of 16 lanes: 1, 2, 4, 8 to the right
-    v += shifted<0x112, 0xf>(v);
-    v += shifted<0x114, 0xf>(v);
-    v += shifted<0x118, 0xf>(v);
-    v += shifted<0x142, 0xa>(v);                          // the last lane of rows 0 and 2 to rows 1 and 3
-    v += shifted<0x143, 0xc>(v);                          // the last lane of row 1 to rows 2 and 3
-    return lane_value(v, 63);
-}
-
-__device__ __forceinline__ double rcp_f64(double q) {          // full precision: hardware estimate and two Newton steps
-    double r = __builtin_amdgcn_rcp(q);
-    r = fma(fma(-q, r, 1.0), r, r);
-    return fma(fma(-q, r, 1.0), r, r);
-}
-
 // The rest of the chain in one workgroup once at most 256 rows and columns are left, with at most one pair pending.  They are
 // numbered so that the last one is 255.  Wavefront w owns the rows w + 16 q and lane l the columns l + 64 t, so that an
 // element always belongs to the same thread, and nothing but the reflectors that the caller asked for leaves the
@@ -331,12 +305,7 @@ __device__ __forceinline__ double rcp_f64(double q) {          // full precision
 // barriers are less than the 350 that one wavefront with four columns per lane needs (k = 256: 715 -> 665 us).  A step costs
 // 1.6 us below 100 rows, 2.1 at 192 and 4.2 at 256; a launch per column is 7.7 us, the chain of k = 256 was 1960 us.
 // Kept in B instead of LDS, the first 64 rows and columns made it 970.
-constexpr int kTailRows = 256, kTailWaves = 16, kTailMem = 64;
-__device__ __forceinline__ void lds_barrier() {           // leaves stores to memory on their way
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-}
+constexpr int kTailRows = kAserTridiagTail, kTailWaves = 16, kTailMem = 64;
 __global__ __launch_bounds__(64 * kTailWaves) void tridiag_tail_kernel(TridiagStep a) {
     constexpr int Q = kTailRows / kTailWaves, T = kTailRows / 64, Q0 = kTailMem / kTailWaves, T0 = kTailMem / 64;
     constexpr int kLow = kTailRows - kTailMem;
@@ -717,12 +686,28 @@ int tridiagonalize(aser_ctx* ctx, double* B, int64_t k, double* const* vec, doub
     a.vnext = v_of(0); a.tau_next = tau;
     hipLaunchKernelGGL(tridiag_first_kernel, dim3(1), dim3(kTriThreads), 0, ctx->stream, a);
     ASER_TRY(aser_check_launch(ctx, "tridiag_first"));
+    bool tried = false;
     int64_t pending = 0;                                   // steps s - pending .. s - 1 have not been applied to B
     for (int64_t s = 0; s + 2 < k; ++s) {                  // reflector s acts on rows and columns s + 1 ..
         a.c0 = s + 1;
         for (int64_t q = 0; q < pending; ++q) { a.v[q] = v_of(s - pending + q); a.w[q] = w_of(s - pending + q); }
         a.vn = v_of(s); a.wn = w_of(s); a.vnext = v_of(s + 1);
         a.tau_cur = tau + (s & 1); a.tau_next = tau + ((s + 1) & 1);
+        // the columns up to the last 256 on the chip, once six rows that the chain has left behind (and that hold no pair) are there for the
+        // exchange.  A column costs 2.8 us there against 7.7 (and more) for a launch; kResidentLeast: less than that is not worth two launches
+        const int64_t gone = s < kFirst ? 0 : 2 * kSlots;
+        if (!tried && k - a.c0 <= kAserResidentMost && k - a.c0 >= kResidentLeast && pending <= 1 && a.c0 >= gone + 6 && ctx->share == 1) {
+            tried = true;
+            const AserTridiagResident r{k, a.c0, B, a.vn, pending ? a.v[0] : nullptr, pending ? a.w[0] : nullptr, a.tau_cur,
+                                        vec[0], vec[1], vec[2], a.tau_next, a.d, a.e, vstore, taustore, (uint64_t*)(B + gone * k)};
+            if (aser_tridiag_resident(ctx, r)) {
+                s = k - kTailRows - 1;
+                a.c0 = s + 1;
+                a.vn = vec[0]; a.v[0] = vec[1]; a.w[0] = vec[2];
+                a.tau_cur = r.tau_out;
+                pending = 1;
+            }
+        }
         if (k - a.c0 <= kTailRows && pending <= 1) {       // what the registers and the LDS of one compute unit hold
             if (pending == 0) a.v[0] = a.w[0] = nullptr;
             constexpr int lds = (kTailMem * (kTailRows - kTailMem) + kTailMem * kTailMem / 2) * 8;
