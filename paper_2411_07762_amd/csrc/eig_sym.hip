@@ -6,7 +6,7 @@
 //                    Householder tridiagonalisation M = Q T Q^T in fp32: per reflector one
 //                    mat-vec reduced along 16-lane DPP rows, one rank-2 update, two barriers.
 //   ritz_pair_kernel one wavefront per wanted eigenvalue, spread over the chip.  In fp64:
-//                    65-section on Sturm counts (9 rounds), twisted factorisation of T - lambda I
+//                    65-section on Sturm counts (9 rounds; wave_f64.h), twisted factorisation of T - lambda I
 //                    (forward and backward recurrences side by side in two lanes), eigenvector from
 //                    the twist index; then back-transformation through the b - 2 reflectors in fp32.
 //
@@ -22,6 +22,7 @@
 #include <type_traits>
 
 #include "aser_internal.h"
+#include "wave_f64.h"
 
 namespace {
 
@@ -213,13 +214,6 @@ __global__ __launch_bounds__(256) void tridiag_kernel(const float* __restrict__ 
     for (int t = tid; t < 3 * kB; t += 256) tri[t] = td[t];
 }
 
-__device__ __forceinline__ double fast_rcp(double q) {
-    double r = __builtin_amdgcn_rcp(q);
-    r = fma(fma(-q, r, 1.0), r, r);
-    r = fma(fma(-q, r, 1.0), r, r);
-    return r;
-}
-
 __device__ __forceinline__ double wave_max_d(double v) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
@@ -231,17 +225,12 @@ __device__ __forceinline__ double wave_min_d(double v) {
     return v;
 }
 
-// number of eigenvalues of the tridiagonal (d, e^2) below x
-__device__ __forceinline__ int sturm_count(const double* d, const double* e2, int b, double x, double tiny) {
-    double q = d[0] - x;
-    if (fabs(q) < tiny) q = -tiny;
-    int cnt = q < 0.0;
-    for (int i = 1; i < b; ++i) {
-        q = fma(-e2[i - 1], fast_rcp(q), d[i] - x);
-        if (fabs(q) < tiny) q = -tiny;
-        cnt += q < 0.0;
-    }
-    return cnt;
+// number of eigenvalues of the tridiagonal (padded to a multiple of kSturmTerms) below x
+__device__ __forceinline__ int sturm_count(const double2* de, int padded, double x) {
+    SturmChain c[1];
+    const double xs[1] = {x};
+    for (int i = 0; i < padded; i += kSturmTerms) sturm_terms(c, de + i, xs);
+    return c[0].count;
 }
 
 // One wavefront: eigenvalue number blockIdx.x (descending; m counts ascending) of the tridiagonal and its eigenvector,
@@ -249,8 +238,9 @@ __device__ __forceinline__ int sturm_count(const double* d, const double* e2, in
 __global__ __launch_bounds__(64) void ritz_pair_kernel(const float* __restrict__ tri, const float* __restrict__ refl, int b,
                                                        float* __restrict__ lambda, float* __restrict__ Vout,
                                                        int* __restrict__ cluster_flag) {
-    __shared__ double dd[kB], e2[kB], Dp[kB], Dm[kB], zz[kB];
-    __shared__ float ef[kB], tau[kB];
+    __shared__ __align__(16) double2 de[kB];        // (d_i, e_{i-1}^2), scaled by a power of two
+    __shared__ double es[kB], Dp[kB], Dm[kB], zz[kB];
+    __shared__ float tau[kB];
     extern __shared__ __align__(16) float rl[];     // [b - 2][kB] reflectors, read once up front
     const int lane = threadIdx.x;
     const int m = b - 1 - (int)blockIdx.x;
@@ -270,31 +260,41 @@ __global__ __launch_bounds__(64) void ritz_pair_kernel(const float* __restrict__
     }
 
     double glo = 1e300, ghi = -1e300;
-    for (int i = lane; i < kB; i += 64) {
-        const float di = (i < b) ? tri[i] : 0.f;
-        const float ei = (i + 1 < b) ? tri[kB + i] : 0.f;
-        const float el = (i > 0 && i < b) ? tri[kB + i - 1] : 0.f;
-        dd[i] = (double)di;
-        e2[i] = (double)ei * (double)ei;
-        ef[i] = ei;
+    float df[2], el[2], ei[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const int i = lane + 64 * u;
+        df[u] = (i < b) ? tri[i] : 0.f;
+        ei[u] = (i + 1 < b) ? tri[kB + i] : 0.f;
+        el[u] = (i > 0 && i < b) ? tri[kB + i - 1] : 0.f;
         tau[i] = (i + 2 < b) ? tri[2 * kB + i] : 0.f;
         if (i < b) {
-            const double rad = fabs((double)ei) + fabs((double)el);
-            glo = fmin(glo, (double)di - rad);
-            ghi = fmax(ghi, (double)di + rad);
+            const double rad = fabs((double)ei[u]) + fabs((double)el[u]);
+            glo = fmin(glo, (double)df[u] - rad);
+            ghi = fmax(ghi, (double)df[u] + rad);
         }
     }
     glo = wave_min_d(glo);
     ghi = wave_max_d(ghi);
+    const double scale = sturm_scale(fmax(fabs(glo), fabs(ghi)));
+    glo *= scale;
+    ghi *= scale;
     const double radius = fmax(fabs(glo), fabs(ghi));
     const double tiny = fmax(radius * 1e-60, 1e-290);
+    const int padded = (b + kSturmTerms - 1) / kSturmTerms * kSturmTerms;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const int i = lane + 64 * u;
+        de[i] = i < b ? sturm_entry((double)df[u], (double)el[u], scale) : sturm_past_end();
+        es[i] = (double)ei[u] * scale;
+    }
     __syncthreads();
 
     // ---- eigenvalue: 64 interior points per round
     double lo = glo - 1e-12 * radius - tiny, hi = ghi + 1e-12 * radius + tiny;
     for (int round = 0; round < 9; ++round) {
         const double x = lo + (hi - lo) * ((double)(lane + 1) * (1.0 / 65.0));
-        const int cnt = sturm_count(dd, e2, b, x, tiny);
+        const int cnt = sturm_count(de, padded, x);
         const double clo = wave_max_d((cnt <= m) ? x : lo);
         const double chi = wave_min_d((cnt > m) ? x : hi);
         lo = clo;
@@ -302,7 +302,7 @@ __global__ __launch_bounds__(64) void ritz_pair_kernel(const float* __restrict__
     }
     const double lam = 0.5 * (lo + hi);
     int bad = 0;
-    if (m > 0) bad = sturm_count(dd, e2, b, lam - 1e-9 * radius, tiny) < m;
+    if (m > 0) bad = sturm_count(de, padded, lam - 1e-9 * radius) < m;
 
     // ---- twisted factorisation: lane 0 runs D+ downwards, lane 1 runs D- upwards
     {
@@ -310,8 +310,8 @@ __global__ __launch_bounds__(64) void ritz_pair_kernel(const float* __restrict__
         double q = 0.0;
         for (int t = 0; t < b; ++t) {
             const int i = dir ? (b - 1 - t) : t;
-            const double dx = dd[i] - lam;
-            q = (t == 0) ? dx : fma(-e2[dir ? i : i - 1], fast_rcp(q), dx);
+            const double dx = de[i].x - lam;
+            q = (t == 0) ? dx : fma(-de[dir ? i + 1 : i].y, rcp_f64(q), dx);
             if (fabs(q) < tiny) q = tiny;
             if (lane < 2) (dir ? Dm : Dp)[i] = q;
         }
@@ -322,7 +322,7 @@ __global__ __launch_bounds__(64) void ritz_pair_kernel(const float* __restrict__
         double best = 1e300;
         int bi = 0;
         for (int i = lane; i < b; i += 64) {
-            const double g = fabs(Dp[i] + Dm[i] - (dd[i] - lam));
+            const double g = fabs(Dp[i] + Dm[i] - (de[i].x - lam));
             if (g < best) { best = g; bi = i; }
         }
 #pragma unroll
@@ -336,8 +336,8 @@ __global__ __launch_bounds__(64) void ritz_pair_kernel(const float* __restrict__
     // z_twist = 1; z_i = -(e_i / D+_i) z_{i+1} above it, z_i = -(e_{i-1} / D-_i) z_{i-1} below it
     for (int i = lane; i < b; i += 64) {
         double rat = 1.0;
-        if (i < twist) rat = -(double)ef[i] * fast_rcp(Dp[i]);
-        if (i > twist) rat = -(double)ef[i - 1] * fast_rcp(Dm[i]);
+        if (i < twist) rat = -es[i] * rcp_f64(Dp[i]);
+        if (i > twist) rat = -es[i - 1] * rcp_f64(Dm[i]);
         zz[i] = rat;
     }
     __syncthreads();
@@ -381,7 +381,7 @@ __global__ __launch_bounds__(64) void ritz_pair_kernel(const float* __restrict__
         }
     }
     const int c = b - 1 - m;
-    if (lane == 0) lambda[c] = (float)lam;
+    if (lane == 0) lambda[c] = (float)(lam / scale);
     if (lane < b) Vout[lane * b + c] = y0;
     if (lane + 64 < b) Vout[(lane + 64) * b + c] = y1;
 }

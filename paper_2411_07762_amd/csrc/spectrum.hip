@@ -472,108 +472,101 @@ __global__ __launch_bounds__(64 * kTailWaves) void tridiag_tail_kernel(TridiagSt
     }
 }
 
-// Every eigenvalue of the symmetric tridiagonal matrix (d, e) by multisection on Sturm counts: the count of x (number of
-// eigenvalues below x) is the number of negative terms of q_0 = d_0 - x, q_l = d_l - x - e_{l-1}^2 / q_{l-1}.
-// L lanes share an eigenvalue: they take the counts of L points that cut its interval into L + 1 parts, and
-// the interval shrinks to the part where the count passes i; `rounds` rounds for 60 halvings.  (d_l, e_{l-1}^2) lie in LDS and are
-// read by all lanes at once (in pieces of kSturmLds when k is larger), so a step is the recurrence alone: one
-// reciprocal and six fp64 operations, a chain of about 100 cycles.  More lanes per eigenvalue mean fewer rounds but more
-// wavefronts per SIMD; past one or two of them the chain is no longer what bounds it.  sigma[k - 1 - i] = sqrt(max(lambda_i, 0)).
+// Every eigenvalue of the symmetric tridiagonal matrix (d, e) by multisection on Sturm counts (wave_f64.h).
+// L lanes share an eigenvalue: they take the counts of L P points that cut its interval into L P + 1 parts, and
+// the interval shrinks to the part where the count passes i; `rounds` rounds for 60 halvings.  The terms lie in LDS (in pieces of kSturmLds
+// when k is larger).  More points per eigenvalue mean fewer rounds but more chains: one wavefront per SIMD hides nothing, a
+// second chain in it costs a third more and shares the terms, and at k = 4096 sixteen lanes of two points are one wavefront per SIMD
+// (2570 us with quotients and one point per lane in 15 rounds, 1110 now).  Where the chip is empty anyway a wavefront of 64 points takes an eigenvalue, alone in its workgroup (k = 256: 103 -> 40 us).
+// sigma[k - 1 - i] = sqrt(max(lambda_i, 0)).
 constexpr int kSturmLds = 4096;
 
-template <int L>
-__global__ __launch_bounds__(256) void tridiag_eigenvalues_kernel(int64_t k, const double* __restrict__ d, const double* __restrict__ e,
-                                                                  int rounds, double* __restrict__ sigma, double* __restrict__ lam_desc) {
-    extern __shared__ __align__(16) double2 de[];               // (d_l, e_{l-1}^2), padded to a multiple of 8
-    __shared__ double red[3][4];
+template <int L, int P, int THREADS>
+__global__ __launch_bounds__(THREADS) void tridiag_eigenvalues_kernel(int64_t k, const double* __restrict__ d, const double* __restrict__ e,
+                                                                      int rounds, double* __restrict__ sigma, double* __restrict__ lam_desc) {
+    extern __shared__ __align__(16) double2 de[];               // (d_l, e_{l-1}^2), scaled and padded to a multiple of kSturmTerms
+    __shared__ double red[2][THREADS / 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int64_t i = (int64_t)blockIdx.x * (256 / L) + tid / L;
+    const int64_t i = (int64_t)blockIdx.x * (THREADS / L) + tid / L;
     const int sub = tid % L;
-    // Gershgorin interval and the smallest pivot magnitude
-    double lo = 1e300, hi = -1e300, emax2 = 0.0;
-    for (int64_t l = tid; l < k; l += 256) {
+    // Gershgorin interval
+    double lo = 1e300, hi = -1e300;
+    for (int64_t l = tid; l < k; l += THREADS) {
         const double dl = d[l], el = (l + 1 < k) ? fabs(e[l]) : 0.0, ep = (l > 0) ? fabs(e[l - 1]) : 0.0;
         lo = fmin(lo, dl - el - ep);
         hi = fmax(hi, dl + el + ep);
-        emax2 = fmax(emax2, el * el);
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
         lo = fmin(lo, __shfl_xor(lo, o, 64));
         hi = fmax(hi, __shfl_xor(hi, o, 64));
-        emax2 = fmax(emax2, __shfl_xor(emax2, o, 64));
     }
-    if (lane == 0) { red[0][wave] = lo; red[1][wave] = hi; red[2][wave] = emax2; }
+    if (lane == 0) { red[0][wave] = lo; red[1][wave] = hi; }
     __syncthreads();
-    lo = fmin(fmin(red[0][0], red[0][1]), fmin(red[0][2], red[0][3]));
-    hi = fmax(fmax(red[1][0], red[1][1]), fmax(red[1][2], red[1][3]));
-    emax2 = fmax(fmax(red[2][0], red[2][1]), fmax(red[2][2], red[2][3]));
+#pragma unroll
+    for (int g = 0; g < THREADS / 64; ++g) {
+        lo = fmin(lo, red[0][g]);
+        hi = fmax(hi, red[1][g]);
+    }
+    const double radius = fmax(fabs(lo), fabs(hi)), scale = sturm_scale(radius);
+    lo *= scale;
+    hi *= scale;
     const double span = fmax(hi - lo, 1e-300);
-    const double pivmin = fmax(emax2 * 2.2e-308 * 4.0, 1e-300);
     double a = lo - 1e-12 * span, b = hi + 1e-12 * span;
     const bool once = k <= kSturmLds;
     for (int it = 0; it < rounds; ++it) {
-        const double x = a + (b - a) * ((double)(sub + 1) * (1.0 / (L + 1)));
-        double q = 1.0;
-        int cnt = 0;
+        double x[P];
+        SturmChain c[P];
+#pragma unroll
+        for (int u = 0; u < P; ++u) x[u] = a + (b - a) * ((double)(P * sub + u + 1) * (1.0 / (L * P + 1)));
         for (int64_t l0 = 0; l0 < k; l0 += kSturmLds) {
-            const int len = (int)((k - l0 < kSturmLds) ? k - l0 : kSturmLds), padded = (len + 7) & ~7;
+            const int len = (int)((k - l0 < kSturmLds) ? k - l0 : kSturmLds), padded = (len + kSturmTerms - 1) / kSturmTerms * kSturmTerms;
             if (!once || it == 0) {
                 __syncthreads();                                // the previous piece has been read
-                for (int t = tid; t < padded; t += 256) {
+                for (int t = tid; t < padded; t += THREADS) {
                     const int64_t l = l0 + t;
-                    const double el = (l > 0 && l < k) ? e[l - 1] : 0.0;
-                    de[t] = make_double2(l < k ? d[l] : 1e305, el * el);    // past the end: a positive term
+                    de[t] = l < k ? sturm_entry(d[l], l > 0 ? e[l - 1] : 0.0, scale) : sturm_past_end();
                 }
                 __syncthreads();
             }
-            for (int t = 0; t < padded; t += 8) {
-                double2 v[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) v[u] = de[t + u];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    q = fma(-v[u].y, rcp_f64(q), v[u].x - x);
-                    if (fabs(q) < pivmin) q = -pivmin;
-                    cnt += (int)((uint32_t)__double2hiint(q) >> 31);
-                }
-            }
+            for (int t = 0; t < padded; t += kSturmTerms) sturm_terms(c, de + t, x);
         }
-        if (q != q) cnt = 0;             // a NaN in d or e reaches the last term and would count by its sign; with zeros sigma is 0
-        // the count grows with x: the points with cnt <= i are the first p of the group
-        const uint64_t below = __builtin_amdgcn_ballot_w64((int64_t)cnt <= i) >> (lane / L * L);
-        const int p = __popcll(L == 64 ? below : (below & ((1ull << (L & 63)) - 1)));
-        const int first = lane / L * L;
-        const double xa = __shfl(x, first + (p > 0 ? p - 1 : 0), 64), xb = __shfl(x, first + (p < L ? p : L - 1), 64);
-        const double na = p > 0 ? xa : a, nb = p < L ? xb : b;
+        // the count grows with x: the points with cnt <= i are the first p of the group.  (A NaN in d or e reaches the last term and would count
+        // by its sign; counted as nothing, sigma is 0.)
+        int mine = 0;
+#pragma unroll
+        for (int u = 0; u < P; ++u) mine += (c[u].p != c[u].p || (int64_t)c[u].count <= i) ? 1 : 0;
+        int p = 0;
+#pragma unroll
+        for (int u = 0; u < P; ++u) {
+            const uint64_t have = __builtin_amdgcn_ballot_w64(mine > u) >> (lane / L * L);
+            p += __popcll(L == 64 ? have : (have & ((1ull << (L & 63)) - 1)));
+        }
+        const double na = p > 0 ? a + (b - a) * ((double)p * (1.0 / (L * P + 1))) : a, nb = p < L * P ? a + (b - a) * ((double)(p + 1) * (1.0 / (L * P + 1))) : b;
         a = na;
         b = nb;
     }
     if (sub == 0 && i < k) {
-        const double lam = 0.5 * (a + b);
+        const double lam = radius > 0.0 ? 0.5 * (a + b) / scale : 0.0;
         sigma[k - 1 - i] = lam > 0.0 ? sqrt(lam) : 0.0;
         if (lam_desc) lam_desc[k - 1 - i] = lam;
     }
 }
 
-int tridiag_eigenvalues(aser_ctx* ctx, int64_t k, const double* d, const double* e, double* sigma, double* lam_desc) {
-    const size_t lds = (size_t)((k < kSturmLds ? (k + 7) / 8 * 8 : kSturmLds)) * sizeof(double2);
-    static bool attr_set[16] = {false};
-    if (ctx->device >= 0 && ctx->device < 16 && !attr_set[ctx->device]) {
-        const int most = (int)(kSturmLds * sizeof(double2));
-        ASER_HIP(ctx, hipFuncSetAttribute((const void*)tridiag_eigenvalues_kernel<64>, hipFuncAttributeMaxDynamicSharedMemorySize, most));
-        ASER_HIP(ctx, hipFuncSetAttribute((const void*)tridiag_eigenvalues_kernel<32>, hipFuncAttributeMaxDynamicSharedMemorySize, most));
-        ASER_HIP(ctx, hipFuncSetAttribute((const void*)tridiag_eigenvalues_kernel<16>, hipFuncAttributeMaxDynamicSharedMemorySize, most));
-        attr_set[ctx->device] = true;
-    }
-    // 65^10, 33^12 and 17^15 are all above 2^60
-    if (k <= 1024)
-        hipLaunchKernelGGL(tridiag_eigenvalues_kernel<64>, dim3((unsigned)ceil_div64(k, 4)), dim3(256), lds, ctx->stream, k, d, e, 10, sigma, lam_desc);
-    else if (k <= 2048)
-        hipLaunchKernelGGL(tridiag_eigenvalues_kernel<32>, dim3((unsigned)ceil_div64(k, 8)), dim3(256), lds, ctx->stream, k, d, e, 12, sigma, lam_desc);
-    else
-        hipLaunchKernelGGL(tridiag_eigenvalues_kernel<16>, dim3((unsigned)ceil_div64(k, 16)), dim3(256), lds, ctx->stream, k, d, e, 15, sigma, lam_desc);
+template <int L, int P, int THREADS>
+int launch_eigenvalues(aser_ctx* ctx, int64_t k, const double* d, const double* e, int rounds, double* sigma, double* lam_desc) {
+    const size_t lds = (size_t)(k < kSturmLds ? (k + kSturmTerms - 1) / kSturmTerms * kSturmTerms : kSturmLds) * sizeof(double2);
+    auto kern = tridiag_eigenvalues_kernel<L, P, THREADS>;
+    ASER_HIP(ctx, hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kSturmLds * sizeof(double2))));
+    hipLaunchKernelGGL(kern, dim3((unsigned)ceil_div64(k, THREADS / L)), dim3(THREADS), lds, ctx->stream, k, d, e, rounds, sigma, lam_desc);
     return aser_check_launch(ctx, "tridiag_eigenvalues");
+}
+
+int tridiag_eigenvalues(aser_ctx* ctx, int64_t k, const double* d, const double* e, double* sigma, double* lam_desc) {
+    // 65^10 and 33^12 are above 2^60
+    if (k <= 1024) return launch_eigenvalues<64, 1, 64>(ctx, k, d, e, 10, sigma, lam_desc);
+    if (k <= 2048) return launch_eigenvalues<32, 2, 256>(ctx, k, d, e, 10, sigma, lam_desc);
+    return launch_eigenvalues<16, 2, 256>(ctx, k, d, e, 12, sigma, lam_desc);
 }
 
 // Eq. 9 on a descending spectrum: running sums in index order; r = number of leading indices whose

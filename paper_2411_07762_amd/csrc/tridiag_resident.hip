@@ -26,7 +26,7 @@
 //
 // What bounds it: the exchange, 2.0 us at 1024 columns left and 4.2 at 4096 (every workgroup reads 16 bytes per column past its L2), then
 // the pass, 768 fp64 operations per thread at 4096 columns.  A column costs 2.8 us while at most 1024 are left, 5 on average at
-// k = 4096.  Whole spectra: k = 700: 4.4 -> 2.1 ms, 1030: 7.3 -> 3.4, 2049: 22 -> 7.7, 4096: 81 -> 24.7.
+// k = 4096.  Whole spectra: k = 700: 5.2 -> 2.1 ms, 1030: 9.2 -> 3.4, 2049: 24.0 -> 7.7, 4096: 82 -> 24.9.
 #include <math.h>
 
 #include <type_traits>

@@ -66,3 +66,51 @@ __device__ __forceinline__ void lds_barrier() {           // leaves stores to me
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
 }
+
+// Sturm counts of a symmetric tridiagonal matrix.  The leading principal minors of T - x I follow p_{l+1} = (d_l - x) p_l - e_{l-1}^2 p_{l-1},
+// and the number of eigenvalues below x is the number of sign changes along them.  The matrix is scaled by a power of two to a radius of at
+// most one, so that sixteen terms cannot overflow and (p, its predecessor) are brought back to the size of one behind every sixteen; that
+// changes no sign.  Three fp64 operations per term, one of them in the chain, against a reciprocal and its two Newton steps of the quotients
+// q_l = p_{l+1} / p_l (a chain of 100 cycles).  Squares below kSturmLeast (an e of 1e-18 of the radius) are raised to it, so that a
+// minor of exactly zero is followed by one that is not; either sign of the zero gives one change over the two terms.  Sixteen terms
+// shrink a minor by 1e-288 at most.
+constexpr double kSturmLeast = 1e-36;
+constexpr int kSturmTerms = 16;
+struct SturmChain {
+    double p = 1.0, before = 0.0;
+    uint32_t signs = 0;                                   // of the last terms, the newest in bit 0
+    int count = 0;
+};
+// The entry of a term; past the end of the matrix: a positive quotient.
+__device__ __forceinline__ double2 sturm_entry(double d, double e, double scale) {
+    const double es = e * scale, e2 = es * es;
+    return make_double2(d * scale, e2 < kSturmLeast ? kSturmLeast : e2);        // a NaN stays
+}
+__device__ __forceinline__ double2 sturm_past_end() { return make_double2(4.0, 0.0); }
+// The next kSturmTerms terms of P chains that share the matrix: a term comes out of LDS, all lanes reading the same 16 bytes, once for all
+// of them (eight cycles of the compute unit's LDS per wavefront).
+template <int P>
+__device__ __forceinline__ void sturm_terms(SturmChain (&c)[P], const double2* de, const double (&x)[P]) {
+#pragma unroll
+    for (int u = 0; u < kSturmTerms; ++u) {
+        const double2 v = de[u];
+#pragma unroll
+        for (int i = 0; i < P; ++i) {
+            const double next = fma(v.x - x[i], c[i].p, -(v.y * c[i].before));
+            c[i].before = c[i].p;
+            c[i].p = next;
+            c[i].signs = __builtin_amdgcn_alignbit(c[i].signs, (uint32_t)__double2hiint(next), 31);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+        c[i].count += __popc((c[i].signs ^ (c[i].signs >> 1)) & ((1u << kSturmTerms) - 1));
+        const int ex = __builtin_amdgcn_frexp_exp(fmax(fabs(c[i].p), fabs(c[i].before)));
+        c[i].p = __builtin_amdgcn_ldexp(c[i].p, -ex);
+        c[i].before = __builtin_amdgcn_ldexp(c[i].before, -ex);
+    }
+}
+// A power of two that brings `radius` to [0.5, 1); 1 where there is none.
+__device__ __forceinline__ double sturm_scale(double radius) {
+    return (radius > 1e-290 && radius < 1e290) ? __builtin_amdgcn_ldexp(1.0, -__builtin_amdgcn_frexp_exp(radius)) : 1.0;
+}

@@ -33,13 +33,21 @@ def test_singular_values_against_lapack(k):
     assert np.abs(got - ref).max() <= 4 * k * 2.2e-16 * ref[0]
 
 
-@pytest.mark.parametrize("k", [400, 1500])
+@pytest.mark.parametrize("k", [5, 100, 400, 1500])
 def test_degenerate_matrices(k):
     ctx = new_ctx()
     T = torch.zeros((k, k), device=DEV)
     assert np.all(spectrum(ctx, T) == 0.0)
     T.diagonal().copy_(torch.arange(k, 0, -1, device=DEV, dtype=torch.float32))      # nothing to reflect: every sub-column is zero
     assert np.allclose(spectrum(ctx, T), np.arange(k, 0, -1.0), rtol=1e-12, atol=0)
+    # blocks that do not touch each other, every value many times over, and half of them zero
+    T.zero_()
+    T.diagonal()[::2] = 3.0
+    n3 = (k + 1) // 2
+    got = spectrum(ctx, T)
+    assert np.allclose(got[:n3], 3.0, rtol=1e-12, atol=0) and np.all(got[n3:] <= 3e-8)     # a square of zero to 1e-16 of 9
+    T *= 1e-18                                                                              # squares of 9e-36
+    assert np.allclose(spectrum(ctx, T)[:n3], 3e-18, rtol=1e-6, atol=0)
     T[k // 2, k // 3] = float("nan")
     assert np.all(spectrum(ctx, T) == 0.0)               # refused by the rank rule
 
