@@ -48,31 +48,6 @@ __device__ __forceinline__ uint32_t bf16_rne(float x) {
     return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
 }
 
-// Both factors as bf16 planes in one launch: hi = bf16(x), lo = bf16(x - hi).  L_A (m x r) goes to [m][r_pad]
-// with zero columns r .. r_pad, L_B (r x n) to [r_pad][n] with zero rows r .. r_pad.
-__global__ __launch_bounds__(256) void split_factors_kernel(const float* __restrict__ L_A, const float* __restrict__ L_B, int64_t m,
-                                                            int64_t n, int64_t r, int64_t r_pad, uint16_t* __restrict__ la_hi,
-                                                            uint16_t* __restrict__ la_lo, uint16_t* __restrict__ lb_hi,
-                                                            uint16_t* __restrict__ lb_lo) {
-    const int64_t ta = m * r_pad, total = ta + r_pad * n;
-    for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < total; t += (int64_t)gridDim.x * 256) {
-        float x;
-        uint16_t *hi, *lo;
-        if (t < ta) {
-            const int64_t i = t / r_pad, j = t % r_pad;
-            x = j < r ? L_A[i * r + j] : 0.f;
-            hi = la_hi + t; lo = la_lo + t;
-        } else {
-            const int64_t u = t - ta, k = u / n;
-            x = k < r ? L_B[u] : 0.f;
-            hi = lb_hi + u; lo = lb_lo + u;
-        }
-        const uint32_t h = bf16_rne(x);
-        *hi = (uint16_t)h;
-        *lo = (uint16_t)bf16_rne(x - __uint_as_float(h << 16));
-    }
-}
-
 // byte offset of 16-byte chunk c (0..3) of row r inside a [rows][64 bytes] LDS tile
 __device__ __forceinline__ int chunk_off(int r, int c) { return r * 64 + ((c ^ ((r >> 2) & 3)) << 4); }
 
@@ -562,187 +537,164 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     }
 }
 
-// P[t][k] = s_t sum_i xq[t][i] L_B[k][i] for 128 tokens per workgroup and all r_pad columns (RB blocks of
-// 32).  L_B comes as bf16 planes [r_pad][n] (hi, lo).  Per step 64 channels: the code tile as in the main
-// kernel (no reordering), the L_B tiles as 16-byte chunks of 8 bf16 with an XOR swizzle; codes become bf16
-// exactly (|q| <= 128) on their way into the MFMA.  The launch is one workgroup per compute unit for 32768
-// tokens, and a step is a chain of waits (tile stores, barrier, fragment reads, conversion, MFMA), so the
-// workgroup has eight wavefronts, two per SIMD: wavefront w takes tokens 32 (w % 4) .. + 32 and the 16-channel
-// slices 2 (w / 4), 2 (w / 4) + 1 of every step; the two halves of the sum meet in LDS at the end.  The loads
-// of step s + 3 are issued in step s (three register stages, the step loop unrolled by three so that they are
-// named at compile time), the LDS tiles are double buffered, one barrier per step.
-constexpr int kDownThreads = 512;
+// Both factors as bf16 planes: hi = bf16(x), with SPLIT also lo = bf16(x - hi).  L_A (m x r) as [m][r_pad] with zeros behind r; L_B (r x n) in the
+// order in which rank_down_kernel feeds it to the MFMA: [32 channels][plane][32 rows][8-channel slice][lane][8 channels], lane 32 h + i holding
+// channels 16 h + 8 slice .. + 7 of row i, zeros past r and n.
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+typedef float f32x2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t bf16_pair(float a, float b) {         // rounded to nearest even
+    const f32x2_t v = {a, b};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
+}
 
-template <int RB, bool SPLIT>
-__global__ __launch_bounds__(kDownThreads) void cf_down_kernel(const int8_t* __restrict__ xq, const float* __restrict__ xs, int64_t rows,
-                                                               int64_t n, const uint16_t* __restrict__ lb_hi,
-                                                               const uint16_t* __restrict__ lb_lo, uint16_t* __restrict__ p_hi,
-                                                               uint16_t* __restrict__ p_lo, int64_t ldp) {
-    extern __shared__ __align__(16) char smem[];
-    constexpr int RP = 32 * RB;                              // r_pad
-    constexpr int A_BYTES = 128 * 64, B_BYTES = RP * 128;    // 64 bf16 per row
-    constexpr int BUF = A_BYTES + 2 * B_BYTES;
-    constexpr int BCHUNKS = RP * 8;                          // 16-byte chunks of a B plane per step
-    constexpr int BCH = (BCHUNKS + kDownThreads - 1) / kDownThreads;
-    constexpr int kAhead = 3;
-    static_assert(2 * BUF >= 4 * RB * 16 * 64 * 4 + 128 * 4, "the partial sums of wavefronts 4 .. 7 and the token scales must fit the tile buffers");
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int tb = wave & 3, sh = wave >> 2;
-    const int64_t T0 = (int64_t)blockIdx.x * 128;
-    // staging role: 16-byte chunk tid % 4 of code row tid / 4
-    const int srow = tid >> 2, sc = tid & 3;
-    const bool srow_ok = T0 + srow < rows;
-    const char* ap = (const char*)xq + (srow_ok ? T0 + srow : 0) * n + 16 * sc;
-    const uint32_t amask = srow_ok ? 0xFFFFFFFFu : 0u;       // rows past the end read row 0 and drop it
+template <bool SPLIT>
+__global__ __launch_bounds__(256) void split_factors_kernel(const float* __restrict__ L_A, const float* __restrict__ L_B, int64_t m,
+                                                            int64_t n, int r, int r_pad, uint16_t* __restrict__ la_hi,
+                                                            uint16_t* __restrict__ la_lo, uint4* __restrict__ lb, int64_t lb_blocks) {
+    if ((int64_t)blockIdx.x < lb_blocks) {                   // eight rows, 256 channels
+        const int64_t k = ((int64_t)blockIdx.x % ((n + 255) / 256)) * 256 + 8 * (threadIdx.x & 31);
+        const int row = (int)((int64_t)blockIdx.x / ((n + 255) / 256)) * 8 + (threadIdx.x >> 5);
+        if (k >= (n + 31) / 32 * 32) return;
+        float f[8];
+        const float* src = L_B + (int64_t)(row < r ? row : 0) * n;
+        if (((uintptr_t)src & 15) == 0 && k + 8 <= n) {
+            const float4 x = *(const float4*)(src + k), y = *(const float4*)(src + k + 4);
+            f[0] = x.x; f[1] = x.y; f[2] = x.z; f[3] = x.w; f[4] = y.x; f[5] = y.y; f[6] = y.z; f[7] = y.w;
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) f[e] = k + e < n ? src[k + e] : 0.f;
+        }
+        uint32_t hi[4], lo[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const float f0 = row < r ? f[2 * q] : 0.f, f1 = row < r ? f[2 * q + 1] : 0.f;
+            hi[q] = bf16_pair(f0, f1);
+            lo[q] = bf16_pair(f0 - __uint_as_float(hi[q] << 16), f1 - __uint_as_float(hi[q] & 0xFFFF0000u));
+        }
+        const int c8 = (int)(k & 31) >> 3, h = c8 >> 1, sl = c8 & 1, blocks = r_pad / 32;
+        const int64_t at = ((k / 32 * (SPLIT ? 2 : 1) * blocks + row / 32) * 2 + sl) * 64 + 32 * h + (row & 31);
+        lb[at] = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+        if (SPLIT) lb[at + blocks * 128] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+        return;
+    }
+    const int64_t total = m * r_pad;
+    for (int64_t t = ((int64_t)blockIdx.x - lb_blocks) * 256 + threadIdx.x; t < total; t += ((int64_t)gridDim.x - lb_blocks) * 256) {
+        const int64_t i = t / r_pad;
+        const int j = (int)(t % r_pad);
+        const float x = j < r ? L_A[i * r + j] : 0.f;
+        const uint32_t hi = bf16_rne(x);
+        la_hi[t] = (uint16_t)hi;
+        if (SPLIT) la_lo[t] = (uint16_t)bf16_rne(x - __uint_as_float(hi << 16));
+    }
+}
+
+// P[t][k] = s_t sum_i xq[t][i] L_B[k][i] as bf16 planes, for 32 tokens per workgroup and all r_pad columns (RB blocks of 32).  NW
+// wavefronts share the contraction, and all operands come straight from memory into MFMA registers: a lane's 16 channels of its token
+// (the codes become bf16 there, exactly, |q| <= 128), and the planes of L_B in the order split_factors_kernel left them, a kilobyte per load.
+// kAhead steps of loads are in flight, nothing waits for another wavefront, and the NW sums meet in LDS once, in a fixed order.
+// What bounds it: instructions (a step of 32 channels is 24 conversions, 2 RB NP MFMAs and as much again for loads and addresses),
+// hence four wavefronts per SIMD where the sums fit the LDS (r <= 64), which are 15 us at 8192 tokens of 4096 channels, r = 64, against 18
+// with two; 36 with 128 tokens per workgroup (64 compute units) and both operands staged through LDS.  32768 tokens: 55 -> 49 us.  Reading L_B
+// itself costs more than the launch it saves: 50 us with a lane's 64 bytes of a row each, 29 in whole lines (a row is 16 KB, so the rows of
+// a load share a channel of the L2).
+struct DownArgs {
+    const int8_t* xq; int64_t ldq; const float* xs; int64_t rows;   // codes: rows of ldq bytes, 16-byte aligned, finite from channel n to the next multiple of 32
+    int64_t n; const uint4* lb; int r_pad;
+    uint16_t* p_hi; uint16_t* p_lo;
+};
+
+template <int RB, bool SPLIT, int NW>
+__global__ __launch_bounds__(64 * NW) void rank_down_kernel(DownArgs g) {
+    extern __shared__ __align__(16) float part[];
+    __shared__ float sx[32];
+    constexpr int NP = SPLIT ? 2 : 1, kAhead = 2;
+    const int tid = threadIdx.x, lane = tid & 63, li = lane & 31, h = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t T0 = (int64_t)blockIdx.x * 32;
+    const int steps = (int)((g.n + 31) / 32);
+    if (tid < 32) sx[tid] = T0 + tid < g.rows ? g.xs[T0 + tid] : 0.f;
+    const char* const ap = (const char*)g.xq + (T0 + li < g.rows ? T0 + li : g.rows - 1) * g.ldq + 16 * h;      // past the end: the last token again, not stored
     f32x16_t acc[RB];
 #pragma unroll
     for (int j = 0; j < RB; ++j)
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[j][e] = 0.f;
-    uint4 ar[kAhead], bh[kAhead][BCH], bl[kAhead][BCH];
-    // STEADY: all 64 channels of the step exist; the loads are unconditional (clamped addresses, the value
-    // dropped afterwards), so that the loop body is straight-line code and the compiler's counting of the
-    // loads in flight stays exact
-    auto fetch = [&](auto utag, int64_t s, auto steady_tag) {
-        constexpr int U = decltype(utag)::value;
-        constexpr bool STEADY = decltype(steady_tag)::value;
-        const int64_t k0 = s * 64;
-        if (STEADY) {
-            const uint4 v = *(const uint4*)(ap + k0);
-            ar[U] = make_uint4(v.x & amask, v.y & amask, v.z & amask, v.w & amask);
-        } else {
-            ar[U] = make_uint4(0u, 0u, 0u, 0u);
-            if (srow_ok && k0 + 16 * sc < n) ar[U] = *(const uint4*)(ap + k0);      // n % 32 == 0: a chunk of 16 is whole or absent
-        }
+    uint4 ar[kAhead], br[kAhead][NP][RB][2];
+    const uint4* const bl = g.lb + lane;
+    auto load = [&](int s, int buf) {                        // steps past the end read the last one and are not used
+        const int sc = s < steps ? s : steps - 1;
+        ar[buf] = *(const uint4*)(ap + 32 * sc);
+        const uint4* b = bl + (int64_t)sc * (NP * RB * 128);
 #pragma unroll
-        for (int u = 0; u < BCH; ++u) {
-            const int q = tid + kDownThreads * u, c = q & 7;
-            const int row = (q >> 3) < RP ? (q >> 3) : RP - 1;
-            const int64_t k = k0 + 8 * c;
-            if (STEADY) {
-                bh[U][u] = *(const uint4*)(lb_hi + (int64_t)row * n + k);
-                if (SPLIT) bl[U][u] = *(const uint4*)(lb_lo + (int64_t)row * n + k);
-            } else {
-                bh[U][u] = make_uint4(0u, 0u, 0u, 0u);
-                bl[U][u] = make_uint4(0u, 0u, 0u, 0u);
-                if (k < n) {
-                    bh[U][u] = *(const uint4*)(lb_hi + (int64_t)row * n + k);
-                    if (SPLIT) bl[U][u] = *(const uint4*)(lb_lo + (int64_t)row * n + k);
-                }
-            }
-        }
+        for (int p = 0; p < NP; ++p)
+#pragma unroll
+            for (int j = 0; j < RB; ++j)
+#pragma unroll
+                for (int sl = 0; sl < 2; ++sl) br[buf][p][j][sl] = b[((p * RB + j) * 2 + sl) * 64];
     };
-    const int64_t steps = (n + 63) / 64;
-    const int64_t full_steps = n / 64;
-    fetch(std::integral_constant<int, 0>{}, 0, std::false_type{});
-    if (steps > 1) fetch(std::integral_constant<int, 1>{}, 1, std::false_type{});
-    if (steps > 2) fetch(std::integral_constant<int, 2>{}, 2, std::false_type{});
-    auto step = [&](auto utag, int64_t s, auto steady_tag) {
-        constexpr int U = decltype(utag)::value;
-        constexpr bool STEADY = decltype(steady_tag)::value;
-        // buffer s % 2 was last read in step s - 2; every wavefront has left that step's reads behind it when
-        // the first one passes the barrier of step s - 1
-        char* sA = smem + (int)(s & 1) * BUF;
-        char* sBh = sA + A_BYTES;
-        char* sBl = sBh + B_BYTES;
-        *(uint4*)(sA + chunk_off(srow, sc)) = ar[U];
+    auto multiply = [&](int buf) {
 #pragma unroll
-        for (int u = 0; u < BCH; ++u) {
-            const int q = tid + kDownThreads * u, row = q >> 3, c = q & 7;
-            const int off = row * 128 + ((c ^ ((row >> 1) & 7)) << 4);
-            if (q < BCHUNKS) {
-                *(uint4*)(sBh + off) = bh[U][u];
-                if (SPLIT) *(uint4*)(sBl + off) = bl[U][u];
-            }
-        }
-        if (STEADY) fetch(utag, s + kAhead, std::true_type{});
-        else if (s + kAhead < steps) fetch(utag, s + kAhead, std::false_type{});
-        __syncthreads();
-        const int arow = tb * 32 + (lane & 31);
-#pragma unroll
-        for (int ss = 0; ss < 2; ++ss) {                     // 16 channels per slice; this lane's 8: bytes [16 sl + 8 g, +8) of its row
-            const int sl = 2 * sh + ss;
-            const int g8 = lane >> 5;
-            const uint2 raw = *(const uint2*)(sA + chunk_off(arow, sl) + 8 * g8);
-            const uint32_t w2[2] = {raw.x ^ 0x80808080u, raw.y ^ 0x80808080u};      // q + 128 as unsigned bytes
+        for (int sl = 0; sl < 2; ++sl) {                     // channels 16 h + 8 sl .. + 7 of the step
+            const uint4 v = ar[buf];
+            const uint32_t w2[2] = {sl ? v.z : v.x, sl ? v.w : v.y};
             uint32_t pk[4];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
+            for (int q = 0; q < 4; ++q) {                    // a byte is converted by one instruction, and the upper halves of two floats are a pair
                 const uint32_t w = w2[q >> 1];
-                const int b0 = 2 * (q & 1);
-                const float f0 = (float)((w >> (8 * b0)) & 0xFFu) - 128.0f;
-                const float f1 = (float)((w >> (8 * b0 + 8)) & 0xFFu) - 128.0f;
-                pk[q] = bf16_hi_pair(f0, f1);
+                const int b0 = 16 * (q & 1);
+                pk[q] = __builtin_amdgcn_perm(__float_as_uint((float)(int)(int8_t)(w >> (b0 + 8))), __float_as_uint((float)(int)(int8_t)(w >> b0)), 0x07060302u);
             }
             const bf16x8_t a = __builtin_bit_cast(bf16x8_t, make_uint4(pk[0], pk[1], pk[2], pk[3]));
-            const int c = 2 * sl + g8;
 #pragma unroll
-            for (int j = 0; j < RB; ++j) {
-                const int brow = 32 * j + (lane & 31);
-                const int off = brow * 128 + ((c ^ ((brow >> 1) & 7)) << 4);
-                const bf16x8_t bhv = *(const bf16x8_t*)(sBh + off);
-                if (SPLIT) {
-                    const bf16x8_t blv = *(const bf16x8_t*)(sBl + off);
-                    acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, blv, acc[j], 0, 0, 0);
-                }
-                acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, bhv, acc[j], 0, 0, 0);
-            }
+            for (int p = NP - 1; p >= 0; --p)
+#pragma unroll
+                for (int j = 0; j < RB; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, __builtin_bit_cast(bf16x8_t, br[buf][p][j][sl]), acc[j], 0, 0, 0);
         }
     };
-    int64_t s = 0;
-    // Twelve steps per trip first: the compiler lets all loads in flight land at a loop's head, and that wait
-    // should come once in twelve steps, not once in three.  The steps fetched, up to s + 14, are whole.
-    for (; s + 5 * kAhead <= full_steps; s += 4 * kAhead) {
+    // four steps in a row, a whole line of a token's codes, where there are enough of them for all wavefronts
+    const int run = steps >= 8 * NW ? 2 : 0;
+    auto step_of = [&](int t) { return (((t >> run) * NW + wave) << run) + (t & ((1 << run) - 1)); };
 #pragma unroll
-        for (int rep = 0; rep < 4; ++rep) {
-            step(std::integral_constant<int, 0>{}, s + 3 * rep, std::true_type{});
-            step(std::integral_constant<int, 1>{}, s + 3 * rep + 1, std::true_type{});
-            step(std::integral_constant<int, 2>{}, s + 3 * rep + 2, std::true_type{});
+    for (int u = 0; u < kAhead; ++u) load(step_of(u), u);
+    for (int t = 0; step_of(t) < steps; t += kAhead) {
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            if (step_of(t + u) < steps) multiply(u);
+            load(step_of(t + u + kAhead), u);
         }
     }
-    for (; s + 2 * kAhead <= full_steps; s += kAhead) {     // the steps these three fetch, up to s + 5, are whole
-        step(std::integral_constant<int, 0>{}, s, std::true_type{});
-        step(std::integral_constant<int, 1>{}, s + 1, std::true_type{});
-        step(std::integral_constant<int, 2>{}, s + 2, std::true_type{});
-    }
-    for (; s < steps; s += kAhead) {
-        step(std::integral_constant<int, 0>{}, s, std::false_type{});
-        if (s + 1 < steps) step(std::integral_constant<int, 1>{}, s + 1, std::false_type{});
-        if (s + 2 < steps) step(std::integral_constant<int, 2>{}, s + 2, std::false_type{});
-    }
-    // the sums over slices 2, 3 (wavefronts 4 .. 7) join those over slices 0, 1 of the same tokens; the tile's
-    // token scales go through LDS as well (one load per token instead of one per accumulator register)
+    // the sums: [wavefront][column block, register][lane]
+    constexpr int PER = RB * 16 * 64;
+#pragma unroll
+    for (int j = 0; j < RB; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) part[wave * PER + (j * 16 + e) * 64 + lane] = acc[j][e];
     __syncthreads();
-    float* part = (float*)smem;
-    float* xsl = part + 4 * RB * 16 * 64;
-    if (tid < 128) xsl[tid] = (T0 + tid < rows) ? xs[T0 + tid] : 0.f;
-    if (sh == 1) {
+    float v[PER / (64 * NW)];
 #pragma unroll
-        for (int j = 0; j < RB; ++j)
+    for (int u = 0; u < PER / (64 * NW); ++u) {
+        const int o = tid + 64 * NW * u, e = (o >> 6) & 15;
+        v[u] = 0.f;
 #pragma unroll
-            for (int e = 0; e < 16; ++e) part[((tb * RB + j) * 16 + e) * 64 + lane] = acc[j][e];
+        for (int w = 0; w < NW; ++w) v[u] += part[w * PER + o];
+        v[u] *= sx[8 * (e >> 2) + 4 * h + (e & 3)];
     }
-    __syncthreads();
-    if (sh == 1) return;
 #pragma unroll
-    for (int j = 0; j < RB; ++j) {
-        const int col = 32 * j + (lane & 31);
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            const int64_t row = T0 + tb * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
-            if (row < rows) {
-                const float pv = (acc[j][e] + part[((tb * RB + j) * 16 + e) * 64 + lane]) * xsl[row - T0];
-                const uint32_t h = bf16_rne(pv);
-                p_hi[row * ldp + col] = (uint16_t)h;
-                if (SPLIT) p_lo[row * ldp + col] = (uint16_t)bf16_rne(pv - __uint_as_float(h << 16));
-            }
+    for (int u = 0; u < PER / (64 * NW); ++u) {
+        const int o = tid + 64 * NW * u, e = (o >> 6) & 15, j = o >> 10;
+        const int64_t row = T0 + 8 * (e >> 2) + 4 * h + (e & 3);
+        if (row < g.rows) {
+            const int64_t at = row * g.r_pad + 32 * j + li;
+            const uint32_t hi = bf16_rne(v[u]);
+            g.p_hi[at] = (uint16_t)hi;
+            if (SPLIT) g.p_lo[at] = (uint16_t)bf16_rne(v[u] - __uint_as_float(hi << 16));
         }
     }
 }
 
 struct FwdPlan {
     int r_pad;
-    size_t off_p, off_lah, off_lal, off_lbh, off_lbl, total;
+    size_t off_p, off_lah, off_lal, off_lb, total;
 };
 
 void fwd_plan(int64_t rows, int64_t n, int64_t m, int r, FwdPlan* p) {
@@ -751,8 +703,7 @@ void fwd_plan(int64_t rows, int64_t n, int64_t m, int r, FwdPlan* p) {
     p->off_p = off; off += align_up((size_t)rows * p->r_pad * 4, 256);
     p->off_lah = off; off += align_up((size_t)m * p->r_pad * 2, 256);
     p->off_lal = off; off += align_up((size_t)m * p->r_pad * 2, 256);
-    p->off_lbh = off; off += align_up((size_t)p->r_pad * n * 2, 256);
-    p->off_lbl = off; off += align_up((size_t)p->r_pad * n * 2, 256);
+    p->off_lb = off; off += 2 * align_up((size_t)p->r_pad * n * 2, 256);
     p->total = r > 0 ? off : 0;
 }
 
@@ -789,17 +740,38 @@ int launch_dma(aser_ctx* ctx, const FwdArgs& g) {
 }
 
 template <int RB, bool SPLIT>
-int launch_down(aser_ctx* ctx, const int8_t* xq, const float* xs, int64_t rows, int64_t n, const uint16_t* lbh,
-                const uint16_t* lbl, uint16_t* p_hi, uint16_t* p_lo, int64_t ldp) {
+int launch_down(aser_ctx* ctx, const DownArgs& g) {
     static bool done[16] = {false};
-    constexpr int lds = 2 * (128 * 64 + 2 * (32 * RB * 128));   // two buffers of (codes, L_B hi, L_B lo)
-    auto kern = cf_down_kernel<RB, SPLIT>;
+    constexpr int NW = RB <= 2 ? 16 : 8, lds = NW * RB * 16 * 64 * 4;
+    auto kern = rank_down_kernel<RB, SPLIT, NW>;
     ASER_TRY(set_lds_once(ctx, kern, lds, done));
-    hipLaunchKernelGGL(kern, dim3((unsigned)ceil_div64(rows, 128)), dim3(kDownThreads), lds, ctx->stream, xq, xs, rows, n, lbh, lbl, p_hi, p_lo, ldp);
-    return aser_check_launch(ctx, "compensated_forward_down");
+    hipLaunchKernelGGL(kern, dim3((unsigned)ceil_div64(g.rows, 32)), dim3(64 * NW), lds, ctx->stream, g);
+    return aser_check_launch(ctx, "rank_down");
+}
+
+template <bool SPLIT>
+int rank_down(aser_ctx* ctx, const DownArgs& g, const float* L_A, int64_t m, const float* L_B, int r, uint16_t* la_hi, uint16_t* la_lo, uint4* lb) {
+    const int64_t lb_blocks = ceil_div64(g.n, 256) * (g.r_pad / 8), la_blocks = ceil_div64(m * g.r_pad, 256 * 4);
+    hipLaunchKernelGGL(split_factors_kernel<SPLIT>, dim3((unsigned)(lb_blocks + (la_blocks < 2048 ? la_blocks : 2048))), dim3(256), 0, ctx->stream,
+                       L_A, L_B, m, g.n, r, g.r_pad, la_hi, la_lo, lb, lb_blocks);
+    ASER_TRY(aser_check_launch(ctx, "split_factors"));
+    switch (g.r_pad / 32) {
+        case 1: return launch_down<1, SPLIT>(ctx, g);
+        case 2: return launch_down<2, SPLIT>(ctx, g);
+        case 3: return launch_down<3, SPLIT>(ctx, g);
+        default: return launch_down<4, SPLIT>(ctx, g);
+    }
 }
 
 }  // namespace
+
+int aser_rank_down(aser_ctx* ctx, const int8_t* xq, int64_t ldq, const float* xs, int64_t rows, int64_t n, const float* L_B, int r,
+                   bool split, uint16_t* p_hi, uint16_t* p_lo, const float* L_A, int64_t m, uint16_t* la_hi, uint16_t* la_lo, void* lb) {
+    DownArgs g{};
+    g.xq = xq; g.ldq = ldq; g.xs = xs; g.rows = rows; g.n = n; g.lb = (const uint4*)lb; g.r_pad = (r + 31) / 32 * 32;
+    g.p_hi = p_hi; g.p_lo = p_lo;
+    return split ? rank_down<true>(ctx, g, L_A, m, L_B, r, la_hi, la_lo, (uint4*)lb) : rank_down<false>(ctx, g, L_A, m, L_B, r, la_hi, la_lo, (uint4*)lb);
+}
 
 extern "C" size_t aser_forward_workspace_bytes(int64_t rows, int64_t n, int64_t m, int32_t r) {
     if (rows <= 0 || n <= 0 || m <= 0 || r < 0) return 0;
@@ -846,24 +818,8 @@ extern "C" int aser_compensated_forward(aser_ctx* ctx, const int8_t* x_codes, co
         uint16_t* p_lo = p_hi + (size_t)rows * pl.r_pad;
         uint16_t* lah = (uint16_t*)(ws + pl.off_lah);
         uint16_t* lal = (uint16_t*)(ws + pl.off_lal);
-        uint16_t* lbh = (uint16_t*)(ws + pl.off_lbh);
-        uint16_t* lbl = (uint16_t*)(ws + pl.off_lbl);
         const int rp = pl.r_pad;
-        // the factors as bf16 planes: L_A (m x r) padded to r_pad columns, L_B (r x n) padded to r_pad rows
-        {
-            const int64_t total = (m + n) * rp, blocks = ceil_div64(total, 256);
-            hipLaunchKernelGGL(split_factors_kernel, dim3((unsigned)(blocks < 2048 ? blocks : 2048)), dim3(256), 0, ctx->stream,
-                               L_A, L_B, m, n, (int64_t)r, (int64_t)rp, lah, lal, lbh, lbl);
-            ASER_TRY(aser_check_launch(ctx, "split_factors"));
-        }
-#define ASER_DOWN(RB)                                                                                   \
-    (split ? launch_down<RB, true>(ctx, x_codes, x_scales, rows, n, lbh, lbl, p_hi, p_lo, rp)           \
-           : launch_down<RB, false>(ctx, x_codes, x_scales, rows, n, lbh, lbl, p_hi, p_lo, rp))
-        if (rp == 32) ASER_TRY(ASER_DOWN(1));
-        else if (rp == 64) ASER_TRY(ASER_DOWN(2));
-        else if (rp == 96) ASER_TRY(ASER_DOWN(3));
-        else ASER_TRY(ASER_DOWN(4));
-#undef ASER_DOWN
+        ASER_TRY(aser_rank_down(ctx, x_codes, n, x_scales, rows, n, L_B, r, split, p_hi, p_lo, L_A, m, lah, lal, ws + pl.off_lb));
         g.p_hi = p_hi; g.p_lo = p_lo; g.la_hi = lah; g.la_lo = lal; g.r_pad = rp;
     }
     if (rows >= kDmaTM && m >= kDmaTN) {                 // the 256 x 256 tiles without a register stage

@@ -113,3 +113,33 @@ def test_mfma_rate_probe_runs():
         ctx.check(st)
         say("MFMA loop with operand traffic, kind %d: %.0f T op/s" % (kind + 2, rate))
         assert 0.1 * peak < rate <= 1.05 * alone[1]
+
+
+@pytest.mark.parametrize("rows,n,m,r,split,offset", [
+    (2049, 32, 200, 1, True, 0), (2049, 96, 300, 33, False, 1), (2080, 4128, 256, 64, True, 0), (2081, 4096, 257, 65, False, 0),
+    (2111, 1056, 128, 97, True, 1), (2112, 224, 512, 128, False, 0)])
+def test_first_product_of_the_rank_branch_for_many_tokens(rows, n, m, r, split, offset):
+    """Token counts around blocks of 32, channels short of and beyond what sixteen wavefronts take at a time, every number of column
+    blocks, and an L_B that does not start on 16 bytes, against the same product in fp64 on rounded factors."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(rows + n)
+    xq = torch.randint(-127, 128, (rows, n), generator=g, device=DEV, dtype=torch.int8)
+    xs = torch.rand(rows, generator=g, device=DEV) * 0.1
+    wq = torch.randint(-7, 8, (m, n), generator=g, device=DEV, dtype=torch.int8)
+    ws = torch.rand(m, generator=g, device=DEV) * 0.01
+    la = torch.randn((m, r), generator=g, device=DEV)
+    store = torch.randn(r * n + offset, generator=g, device=DEV)
+    lb = store[offset:].view(r, n)
+    ctx = new_ctx()
+    ctx.ensure_workspace(aser.aser_forward_workspace_bytes(rows, n, m, r))
+    Y = torch.empty((rows, m), device=DEV)
+    ctx.check(aser.aser_compensated_forward(ctx, xq, xs, wq, aser.ASER_CODES_INT8, ws, la, lb, r, split, Y))
+    torch.cuda.synchronize()
+    x = (xq.double() * xs.double()[:, None]).cpu()
+    rnd = (lambda t: t.cpu().double()) if split else (lambda t: t.cpu().float().bfloat16().double())
+    P = rnd((x @ rnd(lb).T).float())
+    ref = x @ (wq.double() * ws.double()[:, None]).cpu().T + P @ rnd(la).T
+    # split: 2^-17 per factor and product; plain: P is rounded to 2^-9 from fp32 sums that differ from the reference's, so single values fall on the
+    # other side (2^-8 of one of r terms)
+    tol = 2e-5 if split else 1e-3
+    assert float(torch.linalg.norm(Y.cpu().double() - ref) / torch.linalg.norm(ref)) <= tol
