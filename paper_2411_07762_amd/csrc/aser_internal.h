@@ -230,7 +230,7 @@ int aser_gemm_small_f32(aser_ctx* ctx, float* A, int64_t lda, const float* B, in
 
 // P = s_t x_q L_B^T (rows x r_pad, r_pad = r rounded up to 32) and L_A (m x r_pad) as bf16 planes (forward.hip), r <= 128.  split: hi and
 // lo of P, L_A and L_B; otherwise all three rounded to bf16 and the lo planes left alone.  Codes in rows of ldq bytes, 16-byte aligned, a multiple of
-// 32 of them finite.  lb: scratch, 4 r_pad bytes per channel rounded up to 32, 16-byte aligned.
+// 32 of them finite.  xs null: s_t = 1.  lb: scratch, 4 r_pad bytes per channel rounded up to 32, 16-byte aligned.
 int aser_rank_down(aser_ctx* ctx, const int8_t* xq, int64_t ldq, const float* xs, int64_t rows, int64_t n, const float* L_B, int r,
                    bool split, uint16_t* p_hi, uint16_t* p_lo, const float* L_A, int64_t m, uint16_t* la_hi, uint16_t* la_lo, void* lb);
 // The compensated layer for a few tokens (forward_few.hip); arguments as aser_compensated_forward has checked them.

@@ -6,16 +6,20 @@
 // reconstruction for the other methods), in this library's tokens x channels orientation.
 //
 // Both outputs are contractions over the channel dimension, which is the contiguous one of every operand (X rows,
-// W rows, code rows), and that is how the bf16 MFMA wants its operands.  The factors that are not bf16 already
-// become pairs of bf16 planes, x = hi + lo (about 2^-17 relative): W and W~ (one pass that also
-// dequantizes and adds L_A L_B), fp32 activations.  bf16 activations and activation codes (at most 127 in magnitude)
-// are exact as they are, so a product of either with W or W~ is two plane products instead of the three of a general
-// fp32 product.  ONE kernel then forms both outputs of a tile: it accumulates Y = X W^T over the plane
-// pairs, takes ||Y||^2 from the accumulators, multiplies row t by -1 / s_t, goes on accumulating the codes times W~^T on top, and
-// takes ||s_t (...)||^2: neither output is ever stored.  Without activation quantization M^-1 goes into W~ and the
-// factor is -1.
-// Bound: bf16 MFMA; 2048 tokens of the 4096 x 4096 layer are 2.7e11 operations in four plane products.
+// W rows, code rows), and that is how the MFMA wants its operands.  The factors that are not bf16 already become pairs of bf16
+// planes, x = hi + lo (about 2^-17 relative): W, fp32 activations.  bf16 activations are exact as they are, so Y = X W^T is two plane
+// products instead of the three of a general fp32 product.  The second output needs no planes of W~: the codes of both sides multiply
+// exactly on the int8 MFMA, at twice the rate, and the rank-r branch is r / 16 further bf16 steps per tile (P = x_q L_B^T and L_A as
+// planes, three products).  ONE kernel forms both outputs of a tile: the integer sums, then Y on accumulators of its own, ||Y||^2 from
+// these, which are then multiplied by -1 / s_t per row and receive c_o times the integer sums and L_A P, and ||s_t (...)||^2:
+// neither output is ever stored.
+// Without activation quantization (and with r > 128, or where the planes do not fit the workspace) the second output is a product of planes
+// as well, of the activations or codes with those of W~ (divided by M when there are no codes), accumulated on top of the first.
+// Bound: the MFMA rates; 2048 tokens of the 4096 x 4096 layer are 1.4e11 operations in two bf16 plane products and 0.7e11 in int8: 219 us
+// (339 with four plane products), plus 30 for the planes of W (76 with those of W~) and 25 for P; the whole call 426 -> 289.
 #include <math.h>
+
+#include <type_traits>
 
 #include "aser_internal.h"
 
@@ -24,6 +28,8 @@ namespace {
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
+typedef int i32x16_t __attribute__((ext_vector_type(16)));
+typedef int i32x4_t __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 
@@ -144,6 +150,69 @@ __global__ __launch_bounds__(256) void weight_planes_kernel(const float* __restr
     }
 }
 
+// Planes of W, np columns with zeros from n on, and the codes as int8 rows of nc bytes, likewise (q null: they are used where they are).
+// Eight columns per thread; bound by HBM.
+__global__ __launch_bounds__(256) void weight_split_kernel(const float* __restrict__ W, int64_t m, int64_t n, int64_t ldw, int64_t np,
+                                                           const uint8_t* __restrict__ codes, int layout, int w_vec, int c_vec,
+                                                           uint16_t* __restrict__ w_hi, uint16_t* __restrict__ w_lo, int8_t* __restrict__ q, int64_t nc) {
+    const int64_t per_row = nc / 8, total = m * per_row, pitch = (layout == ASER_CODES_INT8) ? n : n / 2;
+    for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < total; t += (int64_t)gridDim.x * 256) {
+        const int64_t o = t / per_row, c = (t % per_row) * 8;
+        if (c < np) {
+            float w[8];
+            if (w_vec && c + 8 <= n) {
+                const f32x4_t x = __builtin_nontemporal_load((const f32x4_t*)(W + o * ldw + c)), y = __builtin_nontemporal_load((const f32x4_t*)(W + o * ldw + c + 4));
+#pragma unroll
+                for (int e = 0; e < 4; ++e) { w[e] = x[e]; w[4 + e] = y[e]; }
+            } else {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) w[e] = c + e < n ? W[o * ldw + c + e] : 0.f;
+            }
+            uint4 hi, lo;
+            split8(w, hi, lo);
+            *(uint4*)(w_hi + o * np + c) = hi;
+            *(uint4*)(w_lo + o * np + c) = lo;
+        }
+        if (!q) continue;
+        uint32_t b[2] = {0u, 0u};
+        const uint8_t* src = codes + o * pitch;
+        if (layout == ASER_CODES_INT8) {
+            if (c_vec && c + 8 <= n) {
+                const uint2 x = *(const uint2*)(src + c);
+                b[0] = x.x; b[1] = x.y;
+            } else {
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    if (c + e < n) b[e >> 2] |= (uint32_t)src[c + e] << (8 * (e & 3));
+            }
+        } else {                                                    // two's-complement nibbles, even column in the low one
+            uint32_t x = 0u;
+            if (c_vec && c + 8 <= n) x = *(const uint32_t*)(src + c / 2);
+            else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (c + 2 * e < n) x |= (uint32_t)src[c / 2 + e] << (8 * e);      // n is even
+            }
+#pragma unroll
+            for (int e = 0; e < 8; ++e) b[e >> 2] |= ((uint32_t)((int)(x << (28 - 4 * e)) >> 28) & 0xFFu) << (8 * (e & 3));
+        }
+        *(uint2*)(q + o * nc + c) = make_uint2(b[0], b[1]);
+    }
+}
+
+// Activation codes in rows of nc bytes, zeros from n on.
+__global__ __launch_bounds__(256) void code_rows_kernel(const int8_t* __restrict__ src, int64_t rows, int64_t n, int8_t* __restrict__ dst, int64_t nc) {
+    const int64_t total = rows * (nc / 8);
+    for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < total; t += (int64_t)gridDim.x * 256) {
+        const int64_t row = t / (nc / 8), c = (t % (nc / 8)) * 8;
+        uint32_t b[2] = {0u, 0u};
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            if (c + e < n) b[e >> 2] |= (uint32_t)(uint8_t)src[row * n + c + e] << (8 * (e & 3));
+        *(uint2*)(dst + row * nc + c) = make_uint2(b[0], b[1]);
+    }
+}
+
 // Activations as bf16 planes of np columns (zeros from n on): KIND 0 bf16 X copied, 1 fp32 X as hi and lo, 2 int8 codes.
 template <int KIND>
 __global__ __launch_bounds__(256) void act_planes_kernel(const void* __restrict__ X, int64_t rows, int64_t n, int64_t ldx, int64_t np,
@@ -170,10 +239,12 @@ __global__ __launch_bounds__(256) void act_planes_kernel(const void* __restrict_
 
 struct EvalArgs {
     const char* a[6]; int64_t pa[6];          // activation planes: address and row pitch in bytes
-    const char* b[6];                         // weight planes, row pitch 2 np
-    int segs1, segs;                          // plane products of Y, and of both outputs
-    int64_t np, rows, m;
+    const char* b[6]; int64_t pb[6];          // weight planes, likewise
+    int segs1, segs;                          // plane products up to Y (CODED: the first is of the codes), and of both outputs
+    int64_t np, nc, rows, m;                  // channels of a plane row (a multiple of 32), of a code row (of 64)
     const float* xs;                          // per-token scales, or null (1)
+    const float* ws;                          // CODED: scales of the outputs, and the rank-r branch as planes of r_pad columns
+    const uint16_t *p_hi, *p_lo, *la_hi, *la_lo; int r_pad;
     double* out;                              // [0] += ||Y||^2, [1] += ||difference||^2
 };
 
@@ -184,8 +255,9 @@ __device__ __forceinline__ int eval_off(int r, int c) { return r * 64 + ((c ^ ((
 // ring of four stages, the LDS-direct loads in inline assembly, the XOR swizzle and the XCD-aware numbering of the tiles are those of
 // the inference kernel's 256 x 256 tiles; operand fragments of the next 16 channels are read under the MFMAs of the
 // current ones.  Rows past the end repeat the last one and are left out of the sums.
-template <int TI, int TJ>
-__global__ __launch_bounds__(256) void eval_kernel(EvalArgs g, int tiles_n, int64_t tiles_total) {
+// CODED: the first product is of int8 codes, 64 channels per step, on integer accumulators.
+template <int TI, int TJ, bool CODED>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2))) void eval_kernel(EvalArgs g, int tiles_n, int64_t tiles_total) {
     extern __shared__ __align__(16) char smem[];
     __shared__ float sx[64 * TI], live[64 * TI];          // per row: its scale, 1; 0 past the last row
     constexpr int A_BYTES = 64 * TI * 64, STAGE = A_BYTES + 64 * TJ * 64, NL = TI + TJ;
@@ -204,7 +276,7 @@ __global__ __launch_bounds__(256) void eval_kernel(EvalArgs g, int tiles_n, int6
 
     // ---- fetch roles: instruction t of this wave is tile rows 16 (NT wave + t) + lane / 4, chunk slot lane % 4
     const int chunk = 16 * ((lane & 3) ^ ((lane >> 4) & 3));
-    int arow[TI];
+    int arow[TI], brow[TJ];
     uint32_t aoff[TI], boff[TJ];
 #pragma unroll
     for (int t = 0; t < TI; ++t) {
@@ -214,19 +286,22 @@ __global__ __launch_bounds__(256) void eval_kernel(EvalArgs g, int tiles_n, int6
 #pragma unroll
     for (int t = 0; t < TJ; ++t) {
         const int row = 16 * (TJ * wave + t) + (lane >> 2);
-        boff[t] = (uint32_t)((O0 + row < g.m ? row : (int)(g.m - 1 - O0)) * 2 * (int)g.np + chunk);
+        brow[t] = O0 + row < g.m ? row : (int)(g.m - 1 - O0);
     }
-    const int64_t segsteps = g.np / 32, nsteps = segsteps * g.segs, steps1 = segsteps * g.segs1;
+    const int64_t segsteps = g.np / 32, steps0 = CODED ? g.nc / 64 : 0;
+    const int64_t nsteps = steps0 + segsteps * (g.segs - (CODED ? 1 : 0)), steps1 = CODED ? nsteps : segsteps * g.segs1;
     const uint32_t ring = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
     int iseg = 0;
     int64_t ikk = 0;                                      // plane product and step inside it of the stage to be fetched
     const char *abase = nullptr, *bbase = nullptr;
     auto seg_start = [&]() {
-        const int64_t pa = g.pa[iseg];
+        const int64_t pa = g.pa[iseg], pb = g.pb[iseg];
         abase = g.a[iseg] + T0 * pa;
-        bbase = g.b[iseg] + O0 * 2 * g.np;
+        bbase = g.b[iseg] + O0 * pb;
 #pragma unroll
         for (int t = 0; t < TI; ++t) aoff[t] = (uint32_t)(arow[t] * (int)pa + chunk);
+#pragma unroll
+        for (int t = 0; t < TJ; ++t) boff[t] = (uint32_t)(brow[t] * (int)pb + chunk);
     };
     auto issue_one = [&](int64_t step, int q) {           // q: 0 .. TI - 1 activations, TI .. NL - 1 weights
         const uint32_t dst = ring + (uint32_t)(step & 3) * STAGE + (q < TI ? (TI * wave + q) * 1024 : A_BYTES + (TJ * wave + q - TI) * 1024);
@@ -237,7 +312,7 @@ __global__ __launch_bounds__(256) void eval_kernel(EvalArgs g, int tiles_n, int6
     auto stage_done = [&]() {                             // all loads of a stage are issued: on to the next one
         abase += 64;
         bbase += 64;
-        if (++ikk == segsteps) {
+        if (++ikk == (CODED && iseg == 0 ? steps0 : segsteps)) {
             ikk = 0;
             if (++iseg < g.segs) seg_start();
         }
@@ -258,6 +333,15 @@ __global__ __launch_bounds__(256) void eval_kernel(EvalArgs g, int tiles_n, int6
         for (int j = 0; j < TJ; ++j)
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+    i32x16_t iacc[CODED ? TI : 1][CODED ? TJ : 1];
+    if constexpr (CODED) {
+#pragma unroll
+        for (int i = 0; i < TI; ++i)
+#pragma unroll
+            for (int j = 0; j < TJ; ++j)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) iacc[i][j][e] = 0;
+    }
 
     seg_start();
     for (int64_t s = 0; s < 3 && s < nsteps; ++s) {
@@ -294,29 +378,32 @@ __global__ __launch_bounds__(256) void eval_kernel(EvalArgs g, int tiles_n, int6
         for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
         return sum;
     };
-    for (int64_t s = 0; s < nsteps; ++s) {
+    auto scale_rows = [&]() {                             // Y has its norm: rows times -1 / s_t
+#pragma unroll
+        for (int i = 0; i < TI; ++i)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const float sc = sx[wm0 + 32 * i + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3)];
+                const float f = sc >= 1.17549435e-38f ? -1.f / sc : 0.f;      // no reciprocal of a denormal scale (or past the last row)
+#pragma unroll
+                for (int j = 0; j < TJ; ++j) acc[i][j][e] *= f;
+            }
+    };
+    auto step = [&](int64_t s, auto codes_tag) {
+        constexpr bool CODES = decltype(codes_tag)::value;
         const char* st = smem + (int)(s & 3) * STAGE;
         const char* sn = smem + (int)((s + 1) & 3) * STAGE;
         const bool more = s + 1 < nsteps, fetch = s + 3 < nsteps;
-        if (s == steps1) {
-            const double y2 = norm2(live);
-            if (lane == 0) atomicAdd(g.out, y2);
-#pragma unroll
-            for (int i = 0; i < TI; ++i)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const float sc = sx[wm0 + 32 * i + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3)];
-                    const float f = sc >= 1.17549435e-38f ? -1.f / sc : 0.f;      // no reciprocal of a denormal scale (or past the last row)
-#pragma unroll
-                    for (int j = 0; j < TJ; ++j) acc[i][j][e] *= f;
-                }
-        }
-        // slice 0 (16 channels): the operands of slice 1 are read under its MFMAs
+        auto multiply = [&](int i, int j, const bf16x8_t& a, const bf16x8_t& b) {
+            if constexpr (CODES) iacc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(__builtin_bit_cast(i32x4_t, a), __builtin_bit_cast(i32x4_t, b), iacc[i][j], 0, 0, 0);
+            else acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc[i][j], 0, 0, 0);
+        };
+        // slice 0 (32 bytes of every row): the operands of slice 1 are read under its MFMAs
 #pragma unroll
         for (int i = 0; i < TI; ++i)
 #pragma unroll
             for (int j = 0; j < TJ; ++j) {
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0[i], b0[j], acc[i][j], 0, 0, 0);
+                multiply(i, j, a0[i], b0[j]);
                 const int q = i * TJ + j;
                 if (q < TI) a1[q < TI ? q : 0] = read(st, 1, offa[q < TI ? q : 0]);
 #pragma unroll
@@ -329,7 +416,7 @@ __global__ __launch_bounds__(256) void eval_kernel(EvalArgs g, int tiles_n, int6
         for (int i = 0; i < TI; ++i)
 #pragma unroll
             for (int j = 0; j < TJ; ++j) {
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1[i], b1[j], acc[i][j], 0, 0, 0);
+                multiply(i, j, a1[i], b1[j]);
                 const int q = i * TJ + j;
                 if (q == 0 && more) {
                     if (s + 2 < nsteps) __builtin_amdgcn_s_waitcnt(W1);
@@ -351,16 +438,62 @@ __global__ __launch_bounds__(256) void eval_kernel(EvalArgs g, int tiles_n, int6
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
+    };
+    if constexpr (CODED) {
+        for (int64_t s = 0; s < steps0; ++s) step(s, std::true_type{});
+        for (int64_t s = steps0; s < nsteps; ++s) step(s, std::false_type{});
+        const double y2 = norm2(live);
+        if (lane == 0) atomicAdd(g.out, y2);
+        scale_rows();
+#pragma unroll
+        for (int j = 0; j < TJ; ++j) {
+            const int64_t col = O0 + wn0 + 32 * j + (lane & 31);
+            const float c = g.ws[col < g.m ? col : g.m - 1];
+#pragma unroll
+            for (int i = 0; i < TI; ++i)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) acc[i][j][e] = fmaf((float)iacc[i][j][e], c, acc[i][j][e]);
+        }
+        for (int kk = 0; kk < g.r_pad; kk += 16) {        // L_A P, 16 columns of either at a time
+            const int kq = kk + 8 * (lane >> 5);
+            bf16x8_t ph[TI], pl[TI];
+#pragma unroll
+            for (int i = 0; i < TI; ++i) {
+                const int64_t row = T0 + wm0 + 32 * i + (lane & 31), at = (row < g.rows ? row : g.rows - 1) * g.r_pad + kq;
+                ph[i] = *(const bf16x8_t*)(g.p_hi + at);
+                pl[i] = *(const bf16x8_t*)(g.p_lo + at);
+            }
+#pragma unroll
+            for (int j = 0; j < TJ; ++j) {
+                const int64_t col = O0 + wn0 + 32 * j + (lane & 31), at = (col < g.m ? col : g.m - 1) * g.r_pad + kq;
+                const bf16x8_t lh = *(const bf16x8_t*)(g.la_hi + at), ll = *(const bf16x8_t*)(g.la_lo + at);
+#pragma unroll
+                for (int i = 0; i < TI; ++i) {
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pl[i], lh, acc[i][j], 0, 0, 0);
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ph[i], ll, acc[i][j], 0, 0, 0);
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ph[i], lh, acc[i][j], 0, 0, 0);
+                }
+            }
+        }
+    } else {
+        for (int64_t s = 0; s < nsteps; ++s) {
+            if (s == steps1) {
+                const double y2 = norm2(live);
+                if (lane == 0) atomicAdd(g.out, y2);
+                scale_rows();
+            }
+            step(s, std::false_type{});
+        }
     }
     const double e2 = norm2(sx);
     if (lane == 0) atomicAdd(g.out + 1, e2);
 }
 
-template <int TI, int TJ>
+template <int TI, int TJ, bool CODED>
 int launch_eval(aser_ctx* ctx, const EvalArgs& g) {
     static bool done[16] = {false};
     constexpr int lds = 4 * 64 * (64 * TI + 64 * TJ);
-    auto kern = eval_kernel<TI, TJ>;
+    auto kern = eval_kernel<TI, TJ, CODED>;
     if (ctx->device >= 0 && ctx->device < 16 && !done[ctx->device]) {
         ASER_HIP(ctx, hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
         done[ctx->device] = true;
@@ -368,6 +501,14 @@ int launch_eval(aser_ctx* ctx, const EvalArgs& g) {
     const int64_t tn = ceil_div64(g.m, 64 * TJ), total = tn * ceil_div64(g.rows, 64 * TI);
     hipLaunchKernelGGL(kern, dim3((unsigned)(8 * ceil_div64(total, 8))), dim3(256), lds, ctx->stream, g, (int)tn, total);
     return aser_check_launch(ctx, "layer_output_error");
+}
+
+// The largest tile with which the launch still fills the device
+template <bool CODED>
+int pick_eval(aser_ctx* ctx, const EvalArgs& g) {
+    if (ceil_div64(g.rows, 128) * ceil_div64(g.m, 256) >= 200) return launch_eval<2, 4, CODED>(ctx, g);
+    if (ceil_div64(g.rows, 128) * ceil_div64(g.m, 128) >= 200) return launch_eval<2, 2, CODED>(ctx, g);
+    return launch_eval<1, 1, CODED>(ctx, g);
 }
 
 // The workspace is what the operands, one output and L_A take in fp32 (two m x n, two rows x n, a rows x m and an r x m array), the
@@ -395,6 +536,37 @@ void eval_plan(int64_t m, int64_t n, int64_t rows, int r, EvalPlan* p) {
         int64_t& larger = 8 * p->m_blk >= 6 * p->rows_blk && p->m_blk > 1 ? p->m_blk : (p->rows_blk > 1 ? p->rows_blk : p->m_blk);
         larger = (larger + 1) / 2;
     }
+}
+
+// Where the operands of the form on codes lie, in the room of the planes; total: what they take.
+struct CodedPlan {
+    int64_t np, nc;
+    int r_pad;
+    bool x_direct, xc_direct, wc_direct;
+    size_t w_hi, w_lo, wc, x_hi, x_lo, xc, p_hi, p_lo, la_hi, la_lo, lb, total;
+};
+
+void coded_plan(int64_t m, int64_t n, int64_t rows, int r, bool bf16, bool x_direct, bool wc_direct, CodedPlan* p) {
+    p->np = (n + 31) / 32 * 32;
+    p->nc = (n + 63) / 64 * 64;
+    p->r_pad = (r + 31) / 32 * 32;
+    p->x_direct = x_direct;
+    p->xc_direct = p->nc == n;
+    p->wc_direct = wc_direct && p->nc == n;
+    size_t off = 0;
+    auto take = [&](size_t bytes) { const size_t at = off; off += align_up(bytes, 256); return at; };
+    p->w_hi = take((size_t)m * p->np * 2);
+    p->w_lo = take((size_t)m * p->np * 2);
+    p->wc = take(p->wc_direct ? 0 : (size_t)m * p->nc);
+    p->x_hi = take(x_direct ? 0 : (size_t)rows * p->np * 2);
+    p->x_lo = take(x_direct || bf16 ? 0 : (size_t)rows * p->np * 2);
+    p->xc = take(p->xc_direct ? 0 : (size_t)rows * p->nc);
+    p->p_hi = take((size_t)rows * p->r_pad * 2);
+    p->p_lo = take((size_t)rows * p->r_pad * 2);
+    p->la_hi = take((size_t)m * p->r_pad * 2);
+    p->la_lo = take((size_t)m * p->r_pad * 2);
+    p->lb = take((size_t)p->np * p->r_pad * 4);
+    p->total = off;
 }
 
 }  // namespace
@@ -445,7 +617,46 @@ extern "C" int aser_layer_output_error(aser_ctx* ctx, const float* W, int64_t m,
 
     ASER_TRY(aser_fill_bytes(ctx, scal, 256));
     if (act_bits != 0) ASER_TRY(aser_quantize_act_rtn(ctx, X, x_dtype, rows, n, ldx, mdiag, act_bits, acodes, ascales));
-    for (int64_t t0 = 0; t0 < rows; t0 += pl.rows_blk) {
+    CodedPlan cp;
+    coded_plan(m, n, rows, (int)r, bf16, direct, layout == ASER_CODES_INT8 && ((uintptr_t)codes & 15) == 0, &cp);
+    const bool coded = act_bits != 0 && r <= 128 && cp.total <= pl.planes;
+    if (coded) {
+        auto grid = [](int64_t items) { return dim3((unsigned)(ceil_div64(items, 256) < 4096 ? ceil_div64(items, 256) : 4096)); };
+        uint16_t *xh = (uint16_t*)(ws + cp.x_hi), *xl = (uint16_t*)(ws + cp.x_lo);
+        if (!direct) {
+            if (bf16) hipLaunchKernelGGL(act_planes_kernel<0>, grid(rows * (np / 8)), dim3(256), 0, ctx->stream, X, rows, n, ldx, np, xh, xl);
+            else hipLaunchKernelGGL(act_planes_kernel<1>, grid(rows * (np / 8)), dim3(256), 0, ctx->stream, X, rows, n, ldx, np, xh, xl);
+            ASER_TRY(aser_check_launch(ctx, "act_planes"));
+        }
+        const int8_t* xc = acodes;
+        if (!cp.xc_direct) {
+            xc = (const int8_t*)(ws + cp.xc);
+            hipLaunchKernelGGL(code_rows_kernel, grid(rows * (cp.nc / 8)), dim3(256), 0, ctx->stream, (const int8_t*)acodes, rows, n, (int8_t*)(ws + cp.xc), cp.nc);
+            ASER_TRY(aser_check_launch(ctx, "code_rows"));
+        }
+        const int8_t* wc = cp.wc_direct ? (const int8_t*)codes : (const int8_t*)(ws + cp.wc);
+        hipLaunchKernelGGL(weight_split_kernel, grid(m * (cp.nc / 8)), dim3(256), 0, ctx->stream, W, m, n, ldw, np, (const uint8_t*)codes, (int)layout, w_vec, c_vec,
+                           (uint16_t*)(ws + cp.w_hi), (uint16_t*)(ws + cp.w_lo), cp.wc_direct ? (int8_t*)nullptr : (int8_t*)(ws + cp.wc), cp.nc);
+        ASER_TRY(aser_check_launch(ctx, "weight_split"));
+        EvalArgs g{};
+        g.np = np; g.nc = cp.nc; g.rows = rows; g.m = m; g.out = scal; g.xs = ascales; g.ws = scales;
+        auto add = [&](const void* a, int64_t pa, const void* b, int64_t pb) {
+            g.a[g.segs] = (const char*)a; g.pa[g.segs] = pa; g.b[g.segs] = (const char*)b; g.pb[g.segs] = pb; ++g.segs;
+        };
+        const void* xa = direct ? X : (const void*)xh;
+        const int64_t xpitch = direct ? ldx * 2 : np * 2;
+        add(xc, cp.nc, wc, cp.nc);
+        add(xa, xpitch, ws + cp.w_hi, np * 2);
+        add(xa, xpitch, ws + cp.w_lo, np * 2);
+        if (!bf16) add(xl, np * 2, ws + cp.w_hi, np * 2);
+        if (r > 0) {
+            uint16_t *ph = (uint16_t*)(ws + cp.p_hi), *plo = (uint16_t*)(ws + cp.p_lo), *lah = (uint16_t*)(ws + cp.la_hi), *lal = (uint16_t*)(ws + cp.la_lo);
+            ASER_TRY(aser_rank_down(ctx, xc, cp.nc, nullptr, rows, n, L_B, (int)r, true, ph, plo, L_A, m, lah, lal, ws + cp.lb));
+            g.p_hi = ph; g.p_lo = plo; g.la_hi = lah; g.la_lo = lal; g.r_pad = cp.r_pad;
+        }
+        ASER_TRY(pick_eval<true>(ctx, g));
+    }
+    for (int64_t t0 = 0; t0 < rows && !coded; t0 += pl.rows_blk) {
         const int64_t tr = rows - t0 < pl.rows_blk ? rows - t0 : pl.rows_blk;
         const void* Xt = (const char*)X + (size_t)t0 * ldx * xsz;
         const int64_t groups = tr * (np / 8);
@@ -470,7 +681,7 @@ extern "C" int aser_layer_output_error(aser_ctx* ctx, const float* W, int64_t m,
             }
             EvalArgs g{};
             g.np = np; g.rows = tr; g.m = om; g.out = scal;
-            auto add = [&](const void* a, int64_t pa, const void* b) { g.a[g.segs] = (const char*)a; g.pa[g.segs] = pa; g.b[g.segs] = (const char*)b; ++g.segs; };
+            auto add = [&](const void* a, int64_t pa, const void* b) { g.a[g.segs] = (const char*)a; g.pa[g.segs] = pa; g.b[g.segs] = (const char*)b; g.pb[g.segs] = np * 2; ++g.segs; };
             const void* xa = direct ? Xt : (const void*)x_hi;
             const int64_t xpitch = direct ? ldx * 2 : np * 2;
             add(xa, xpitch, w_hi);
@@ -486,10 +697,7 @@ extern "C" int aser_layer_output_error(aser_ctx* ctx, const float* W, int64_t m,
                 add(c_q, np * 2, v_lo);
                 g.xs = ascales + t0;
             }
-            // The largest tile with which the launch still fills the device
-            if (ceil_div64(tr, 128) * ceil_div64(om, 256) >= 200) ASER_TRY((launch_eval<2, 4>(ctx, g)));
-            else if (ceil_div64(tr, 128) * ceil_div64(om, 128) >= 200) ASER_TRY((launch_eval<2, 2>(ctx, g)));
-            else ASER_TRY((launch_eval<1, 1>(ctx, g)));
+            ASER_TRY(pick_eval<false>(ctx, g));
         }
     }
     double h[2] = {0.0, 0.0};

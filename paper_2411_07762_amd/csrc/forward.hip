@@ -612,7 +612,7 @@ __global__ __launch_bounds__(64 * NW) void rank_down_kernel(DownArgs g) {
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t T0 = (int64_t)blockIdx.x * 32;
     const int steps = (int)((g.n + 31) / 32);
-    if (tid < 32) sx[tid] = T0 + tid < g.rows ? g.xs[T0 + tid] : 0.f;
+    if (tid < 32) sx[tid] = T0 + tid < g.rows ? (g.xs ? g.xs[T0 + tid] : 1.f) : 0.f;
     const char* const ap = (const char*)g.xq + (T0 + li < g.rows ? T0 + li : g.rows - 1) * g.ldq + 16 * h;      // past the end: the last token again, not stored
     f32x16_t acc[RB];
 #pragma unroll

@@ -166,3 +166,37 @@ def test_non_finite_activations_are_refused(value, act_bits, x_dtype):
     st, _, _ = aser.aser_layer_output_error(ctx, W, X.to(torch.bfloat16) if x_dtype == "bf16" else X, None, codes, aser.ASER_CODES_INT8, scales, None, None,
                                             0, act_bits)
     assert st == aser.ASER_ERR_INVALID_ARG and "non-finite" in ctx.last_error()
+
+
+@pytest.mark.parametrize("m,n,rows,r,bits,x_dtype,act_bits", [
+    (70, 96, 33, 0, 8, "bf16", 8), (130, 334, 257, 1, 4, "bf16", 6), (257, 1000, 65, 33, 8, "f32", 8), (64, 64, 1, 64, 4, "bf16", 4),
+    (1700, 224, 1800, 97, 4, "bf16", 8), (300, 4128, 129, 128, 8, "bf16", 8), (200, 301, 90, 129, 8, "f32", 8), (5, 3, 7, 2, 8, "bf16", 8)])
+def test_second_output_from_codes(m, n, rows, r, bits, x_dtype, act_bits):
+    """Channels short of a step of 32 and of 64, code rows used in place and copied, every number of blocks of the rank-r branch, one
+    token, every tile size, and the calls that keep the product of planes (r = 129; planes that do not fit), against fp64."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(m * n + r)
+    W = torch.randn((m, n), generator=g, device=DEV) * 0.05
+    X = torch.randn((rows, n), generator=g, device=DEV)
+    X = X.to(torch.bfloat16) if x_dtype == "bf16" else X
+    md = torch.ones(n, device=DEV)
+    md[: n // 3] = 1.5
+    qmax = 2 ** (bits - 1) - 1
+    q = torch.randint(-qmax, qmax + 1, (m, n), generator=g, device=DEV, dtype=torch.int8)
+    packed = bits == 4 and n % 2 == 0
+    codes = ((q[:, 0::2] & 15) | (q[:, 1::2] << 4)).view(torch.uint8).contiguous() if packed else q
+    scales = (0.5 + torch.rand(m, generator=g, device=DEV)) * 0.1 / qmax
+    L_A = torch.randn((m, max(r, 1)), generator=g, device=DEV) * 0.1
+    L_B = torch.randn((max(r, 1), n), generator=g, device=DEV) * 0.05
+    ctx = new_ctx()
+    ctx.ensure_workspace(aser.aser_output_error_workspace_bytes(m, n, rows, r))
+    st, err, ref = aser.aser_layer_output_error(ctx, W, X, md, codes, aser.ASER_CODES_INT4_PACKED if packed else aser.ASER_CODES_INT8, scales,
+                                                L_A if r else None, L_B if r else None, r, act_bits)
+    ctx.check(st)
+    xq, xs = orc.quantize_act_rtn(X.float().cpu().numpy(), md.cpu().numpy(), act_bits)
+    x = torch.from_numpy(xq.astype(np.float64) * xs.astype(np.float64)[:, None])
+    Wt = (q.double() * scales.double()[:, None]).cpu() + ((L_A.double() @ L_B.double()).cpu() if r else 0.0)
+    Y = X.double().cpu() @ W.double().cpu().T
+    want, ynorm = float(torch.linalg.norm(Y - x @ Wt.T)), float(torch.linalg.norm(Y))
+    assert abs(ref - ynorm) <= 1e-5 * ynorm              # 2^-17 per product
+    assert abs(err - want) <= 1e-5 * (want + ynorm)
