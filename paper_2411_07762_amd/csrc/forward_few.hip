@@ -10,8 +10,8 @@
 // in LDS by integer atomics, so the result does not depend on their order.  The rank-r branch is a kernel in front
 // (few_down_kernel: P summed over up to 2048 channels per workgroup) and r / 4 further steps per output tile in the epilogue, or, with many
 // outputs, P in workgroups of the same launch as the codes (neither needs the other) and those steps in a second, short launch;
-// all on the fp32 MFMA instruction, operands straight from global memory.  In the mode that rounds the factors
-// to bf16 the same three roundings are made (L_B, P, L_A) as in the prefill kernels.
+// all on MFMA instructions, operands straight from global memory.  In the mode that rounds the factors
+// to bf16 the same three roundings are made (L_B, P, L_A) as in the prefill kernels; the other one is exact in every product with L_B and keeps fp32 behind it.
 #include "aser_internal.h"
 
 namespace {
@@ -37,55 +37,95 @@ struct FewArgs {
     float* Y; int64_t ldy;
 };
 
-// part[chunk][t][k] = sum over 2048 channels of xq[t][i] L_B[k][i] (without s_t), k up to rp (r rounded up to 16; zeros
-// behind r).  A workgroup takes 16 rows of L_B and 16 tokens, a wavefront 2048 / NW channels of them, in fp32 sums of 256 channels
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+typedef float f2v __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ uint32_t upper_halves(float a, float b) { return __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u); }
+__device__ __forceinline__ float below_upper_half(float x) { return x - __uint_as_float(__float_as_uint(x) & 0xFFFF0000u); }
+__device__ __forceinline__ bf16x8_t operand(const uint32_t (&p)[4]) { return __builtin_bit_cast(bf16x8_t, make_uint4(p[0], p[1], p[2], p[3])); }
+
+// The products of eight channels of L_B (b) and of the codes (x) added to acc, v_mfma_f32_16x16x32_bf16.  Codes are bf16 values.  The mode that rounds the factors
+// takes b to the nearest bf16; otherwise b is the sum of three bf16 values, each the upper half of what the ones before it leave of its 24 bits, so
+// the products are exact either way.  (Of an infinity nothing is left.)
+__device__ __forceinline__ f4v down_step(bool split, float4 b0, float4 b1, uint2 x, f4v acc) {
+    const float b[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
+    uint32_t c[4], hi[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const uint32_t w = q < 2 ? x.x : x.y;
+        const int s = 16 * (q & 1);
+        c[q] = upper_halves((float)(int)(int8_t)(w >> s), (float)(int)(int8_t)(w >> (s + 8)));
+    }
+    const bf16x8_t codes = operand(c);
+    if (!split) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const f2v v = {b[2 * q], b[2 * q + 1]};
+            hi[q] = __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
+        }
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(operand(hi), codes, acc, 0, 0, 0);
+    }
+    uint32_t mid[4], lo[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        float m[2], l[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            m[u] = __builtin_isinf(b[2 * q + u]) ? 0.f : below_upper_half(b[2 * q + u]);
+            l[u] = below_upper_half(m[u]);
+        }
+        hi[q] = upper_halves(b[2 * q], b[2 * q + 1]);
+        mid[q] = upper_halves(m[0], m[1]);
+        lo[q] = upper_halves(l[0], l[1]);
+    }
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(operand(lo), codes, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(operand(mid), codes, acc, 0, 0, 0);
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(operand(hi), codes, acc, 0, 0, 0);
+}
+
+// part[chunk][t][k] = sum over 2048 channels of xq[t][i] L_B[k][i] (without s_t), k up to rp (r rounded up to 16; what stands
+// behind r is not read).  A workgroup takes 16 rows of L_B and 16 tokens, a wavefront 2048 / NW channels of them, in fp32 sums of 256 channels
 // each, so that P does not depend on NW; lane (l % 16, g = l / 16)
-// feeds channels 16 s + 4 g + e of its row and of its token to the e-th of four v_mfma_f32_16x16x4_f32 (codes and products
-// exact, fp32 sums).  All loads of a round are in flight at once: they are unconditional (addresses clamped into the
-// operands, the values dropped afterwards), because a load behind a branch is waited for where the branches meet.
+// feeds channels 32 s + 8 g .. + 7 of its row and of its token.  All loads of a round are in flight at once: they are unconditional (addresses clamped into the
+// operands), because a load behind a branch is waited for where the branches meet.
+// What bounds it: latency, of the launch, of two rounds of loads and of the chain of sums.  One K = 4 fp32 instruction per four channels, each value
+// converted and masked by itself, was 3200 cycles per wavefront (us for the whole call; 4096 x 4096 int4, r = 64, 16 tokens: 16.6 -> 14.8; split
+// factors, 8192 x 8192, 16 tokens: 27.1 -> 25.5, 3.3e-7 -> 2.3e-7 off the fp64 result; 4096 x 11008 int8, 19 tokens: 29.6 -> 28.1; one token: no faster, no slower).
 template <int NW>
 __device__ __forceinline__ void few_down(const FewArgs& g, int task, float (*red)[16][17]) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int li = lane & 15, lg = lane >> 4;
     const int kt = g.rp / 16, chunk = task % g.chunks, ky = (task / g.chunks) % kt, tz = task / (g.chunks * kt);
     const int k = ky * 16 + li, t = tz * 16 + li;
-    const bool kok = k < g.r, tok = t < g.rows;
-    const float* bp = g.L_B + (int64_t)(kok ? k : 0) * g.n;
-    const int8_t* xp = g.xq + (int64_t)(tok ? t : 0) * g.n;
-    // NS * 16 channels at a time: with 256 the registers of the eight-wavefront kernels would leave room for one workgroup per compute unit
-    constexpr int NS = 8;
+    const float* bp = g.L_B + (int64_t)(k < g.r ? k : 0) * g.n + 8 * lg;
+    const int8_t* xp = g.xq + (int64_t)(t < g.rows ? t : 0) * g.n + 8 * lg;
+    constexpr int NS = 4;                                 // steps of 32 channels in flight; eight are up to 0.8 us slower
 #pragma unroll 1
     for (int w = wave * (kDownSums / NW); w < (wave + 1) * (kDownSums / NW); ++w) {
         f4v acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll 1
-        for (int h = 0; h < kDownSum; h += 16 * NS) {
-            const int64_t c0 = (int64_t)chunk * kDownChunk + w * kDownSum + h + 4 * lg;
-            if (c0 - 4 * lg >= g.n) break;
-            float4 b[NS];
-            uint32_t x[NS];
-            if (g.vec_b) {
+        for (int h = 0; h < kDownSum; h += 32 * NS) {
+            const int64_t c0 = (int64_t)chunk * kDownChunk + w * kDownSum + h;
+            if (c0 >= g.n) break;
+            float4 b[NS][2];
+            uint2 x[NS];
 #pragma unroll
-                for (int s = 0; s < NS; ++s) b[s] = *(const float4*)(bp + ((c0 + 16 * s < g.n) ? c0 + 16 * s : 0));   // n % 32 == 0: four channels are whole or absent
-            } else {
-#pragma unroll
-                for (int s = 0; s < NS; ++s) {
-                    const float* q = bp + ((c0 + 16 * s < g.n) ? c0 + 16 * s : 0);
-                    b[s] = make_float4(q[0], q[1], q[2], q[3]);
+            for (int s = 0; s < NS; ++s) {                // n % 32 == 0: a step is whole or absent
+                const int64_t c = c0 + 32 * s < g.n ? c0 + 32 * s : 0;
+                if (g.vec_b) {
+                    b[s][0] = *(const float4*)(bp + c);
+                    b[s][1] = *(const float4*)(bp + c + 4);
+                } else {
+                    const float* q = bp + c;
+                    b[s][0] = make_float4(q[0], q[1], q[2], q[3]);
+                    b[s][1] = make_float4(q[4], q[5], q[6], q[7]);
                 }
+                x[s] = *(const uint2*)(xp + c);
             }
 #pragma unroll
-            for (int s = 0; s < NS; ++s) x[s] = *(const uint32_t*)(xp + ((c0 + 16 * s < g.n) ? c0 + 16 * s : 0));
-#pragma unroll
-            for (int s = 0; s < NS; ++s) {
-                const bool in = c0 + 16 * s < g.n;
-                const uint32_t xs = (in && tok) ? x[s] : 0u;
-                const float bb[4] = {b[s].x, b[s].y, b[s].z, b[s].w};
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const float v = (in && kok) ? bb[e] : 0.f;
-                    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(g.split ? v : round_bf16(v), (float)((int)(xs << (24 - 8 * e)) >> 24), acc, 0, 0, 0);
-                }
-            }
+            for (int s = 0; s < NS; ++s)
+                if (c0 + 32 * s < g.n) acc = down_step(g.split, b[s][0], b[s][1], x[s], acc);
         }
 #pragma unroll
         for (int e = 0; e < 4; ++e) red[w][li][4 * lg + e] = acc[e];     // (token li, row 4 lg + e)

@@ -143,3 +143,58 @@ def test_first_product_of_the_rank_branch_for_many_tokens(rows, n, m, r, split, 
     # other side (2^-8 of one of r terms)
     tol = 2e-5 if split else 1e-3
     assert float(torch.linalg.norm(Y.cpu().double() - ref) / torch.linalg.norm(ref)) <= tol
+
+
+@pytest.mark.parametrize("rows,n,m,w4", [
+    (1, 32, 16, True), (16, 96, 33, False), (17, 1056, 100, True), (1, 2080, 4100, False), (33, 3104, 4100, True), (32, 5152, 300, False),
+    (3, 4128, 8205, True), (16, 8224, 8205, False), (2, 672, 16500, True), (65, 1568, 500, False), (130, 1120, 700, True)])
+def test_integer_sums_of_a_few_tokens(rows, n, m, w4):
+    """Contractions that end inside a round of the code stream, inside a step and before the last wavefront's share, tokens and
+    outputs that end inside a tile: without factors Y is an exact integer, rounded once, times two scales (four roundings of 2^-24)."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(rows * 7 + n)
+    xq = torch.randint(-127, 128, (rows, n), generator=g, device=DEV, dtype=torch.int8)
+    xs = torch.rand(rows, generator=g, device=DEV) * 0.1
+    q = torch.randint(-7, 8, (m, n), generator=g, device=DEV, dtype=torch.int8)
+    codes = ((q[:, 0::2] & 15) | (q[:, 1::2] << 4)).view(torch.uint8).contiguous() if w4 else q
+    ws = torch.rand(m, generator=g, device=DEV) * 0.01
+    ctx = new_ctx()
+    ctx.ensure_workspace(aser.aser_forward_workspace_bytes(rows, n, m, 0))
+    Y = torch.full((rows + 1, m), 7.0, device=DEV)
+    ctx.check(aser.aser_compensated_forward(ctx, xq, xs, codes, aser.ASER_CODES_INT4_PACKED if w4 else aser.ASER_CODES_INT8, ws, None, None, 0, True, Y[:rows]))
+    torch.cuda.synchronize()
+    ref = (xq.cpu().double() @ q.cpu().double().T) * xs.cpu().double()[:, None] * ws.cpu().double()
+    assert bool(((Y[:rows].cpu().double() - ref).abs() <= 5 * 2.0 ** -24 * ref.abs()).all())
+    assert bool((Y[rows] == 7.0).all())
+
+
+@pytest.mark.parametrize("rows,n,m,r,offset", [(1, 32, 40, 1, 0), (16, 96, 33, 16, 1), (17, 224, 100, 17, 0), (2, 288, 64, 33, 2), (5, 2080, 8205, 64, 0), (33, 2336, 300, 100, 3),
+                                               (16, 4128, 8205, 128, 0), (130, 6176, 48, 7, 0)])
+@pytest.mark.parametrize("split", [False, True])
+def test_rank_branch_of_a_few_tokens(rows, n, m, r, offset, split):
+    """Contractions that end inside a round, a sum of 256 and a workgroup's 2048 channels, ranks around the tiles of 16 and the steps of 32, an L_B that does not
+    start on 16 bytes; P in front and beside the codes.  Split: a sum takes eight steps and meets at most 8 + 4 others, 2^-24 each and of the
+    largest partial one: 2^-20.  Rounded: P from fp32 sums that differ from the reference's, as for many tokens above.  An infinite factor stays one."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(rows + n + r)
+    xq = torch.randint(1, 128, (rows, n), generator=g, device=DEV, dtype=torch.int8) * (1 - 2 * (torch.arange(n, device=DEV) % 2)).to(torch.int8)
+    xs = 0.01 + torch.rand(rows, generator=g, device=DEV) * 0.1
+    wq = torch.randint(-7, 8, (m, n), generator=g, device=DEV, dtype=torch.int8)
+    ws = torch.rand(m, generator=g, device=DEV) * 0.01
+    la = torch.randn((m, r), generator=g, device=DEV)
+    lb = torch.randn(r * n + offset, generator=g, device=DEV)[offset:].view(r, n)
+    ctx = new_ctx()
+    ctx.ensure_workspace(aser.aser_forward_workspace_bytes(rows, n, m, r))
+
+    def call():
+        Y = torch.empty((rows, m), device=DEV)
+        ctx.check(aser.aser_compensated_forward(ctx, xq, xs, wq, aser.ASER_CODES_INT8, ws, la, lb, r, split, Y))
+        torch.cuda.synchronize()
+        return Y.cpu().double()
+
+    x = (xq.double() * xs.double()[:, None]).cpu()
+    rnd = (lambda t: t.cpu().double()) if split else (lambda t: t.cpu().float().bfloat16().double())
+    ref = x @ (wq.double() * ws.double()[:, None]).cpu().T + rnd((x @ rnd(lb).T).float()) @ rnd(la).T
+    assert float(torch.linalg.norm(call() - ref) / torch.linalg.norm(ref)) <= (2.0 ** -20 if split else 1e-3)
+    lb[r - 1, n - 2] = float("inf")                       # the codes of even channels are positive
+    assert bool((call() == torch.where(la[:, r - 1].cpu() > 0, np.inf, -np.inf)).all())
