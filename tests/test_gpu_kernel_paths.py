@@ -498,3 +498,29 @@ def test_ritz_pairs_at_the_distance_where_the_fallback_takes_over(b, need, dista
     assert off <= (2.0 ** -23 + 2.0 * 2.0 ** -52 / distance if apart else 1e-4)
     assert np.max(np.abs(lam.cpu().numpy()[:need] / pair - 1.0)) <= (2.0 ** -23 if apart else 1e-4)
     assert np.max(np.abs(M.astype(np.float64) @ got - got * pair)) <= (2.0 ** -22 if apart else 1e-4) * pair[0]
+
+
+@pytest.mark.parametrize("b", [2, 3, 16, 17, 18, 49, 97, 127, 128])
+@pytest.mark.parametrize("scale", [1e-7, 1.0, 1e9])
+def test_ritz_pairs_of_dense_matrices(b, scale):
+    """All eigenpairs at the sides around the slots of 16 rows that the tridiagonalisation drops one after the other.  Every one of b - 2 reflections
+    moves the matrix by a small multiple of 2^-24 of its norm, in directions of its own: 4 sqrt(b) 2^-24 of the largest eigenvalue
+    for the eigenvalues and the residuals, 8 sqrt(b) 2^-24 for the products of vectors that went through b - 2 reflectors."""
+    rng = np.random.default_rng([96, b])
+    A = rng.standard_normal((b, 2 * b + 3))
+    M = (A @ A.T * scale).astype(np.float32)
+    sym = 0.5 * (M.astype(np.float64) + M.T)
+    want = np.linalg.eigvalsh(sym)[::-1]
+    lib, ctx = aser.load_library(), new_ctx()
+    Md = torch.from_numpy(M).to(DEV)
+    lam, V, refl, tri = (torch.full(shape, 7.0, dtype=torch.float32, device=DEV) for shape in ((b,), (b, b), (b, 128), (384,)))
+    flag = torch.ones(1, dtype=torch.int32, device=DEV)
+    p = lambda t: ctypes.c_void_p(t.data_ptr())
+    ctx.check(lib["_Z16aser_tridiag_eigP8aser_ctxPKfiPfS3_S3_S3_Pii"](ctx.handle, p(Md), b, p(lam), p(V), p(refl), p(tri), p(flag), b))
+    torch.cuda.synchronize()
+    got, v = lam.double().cpu().numpy(), V.double().cpu().numpy()
+    eps = 2.0 ** -24 * np.sqrt(b)
+    assert int(flag.item()) == 0
+    assert np.max(np.abs(got - want)) <= 4 * eps * want[0]
+    assert np.max(np.abs(sym @ v - v * want)) <= 4 * eps * want[0]
+    assert np.max(np.abs(v.T @ v - np.eye(b))) <= 8 * eps
