@@ -853,80 +853,202 @@ __device__ __forceinline__ double invit_start_value(int64_t t) {
 }
 
 // Eigenvectors of the symmetric tridiagonal matrix (d, e) for the r largest eigenvalues lam[0 .. r),
-// as rows of X (r x k).  One workgroup (small problems).  Three rounds of: thread c solves (T - lam_c I) y = x_c,
-// then the vectors are orthonormalised in order (classical Gram-Schmidt, twice).  scr: r x 3 k doubles.
-// LOCAL: everything stands in LDS, (2 + 4 r) k doubles with a word of padding per vector, and X receives the result; the solves are chains of
-// dependent steps on one thread each and the orthonormalisation short passes between barriers, so what bounds both is the latency of
-// what they read (k = 256, r = 8: 345 us from memory, 250 from LDS).
-constexpr int kInvitLds = 150 * 1024;
-__host__ __device__ static inline size_t invit_lds_bytes(int64_t k, int r) { return (size_t)(2 * k + (int64_t)r * 4 * (k + 1)) * 8; }
-template <bool LOCAL>
-__global__ __launch_bounds__(256) void tridiag_invit_kernel(int64_t k, int r, const double* __restrict__ dg,
-                                                            const double* __restrict__ eg, const double* __restrict__ lam,
-                                                            double* __restrict__ Xg, double* __restrict__ scrg) {
-    __shared__ double dots[256];                      // r <= 256
-    __shared__ double red[4];
-    extern __shared__ __align__(16) double mem[];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int64_t ld = LOCAL ? k + 1 : k;
-    const double *d = dg, *e = eg;
-    double *X = Xg, *scr = scrg;
-    if constexpr (LOCAL) {
-        double *dl = mem, *el = mem + k;
-        for (int64_t i = tid; i < k; i += 256) {
-            dl[i] = dg[i];
-            el[i] = i + 1 < k ? eg[i] : 0.0;
+// as rows of X (r x k), k <= kInvitMost.  Three rounds of: (T - lam_c I) y = x_c for every c, then the vectors are orthonormalised in
+// order, in two sweeps after the last solves and in one after the others, which only keep the vectors apart.
+//
+// The solves: a workgroup per vector, everything in LDS, the recurrences on its first lane.  What bounds them is the number of instructions, one every six
+// cycles or so: the matrix is padded to a multiple of 16 rows that nothing couples to the others, so that no row asks where the matrix ends,
+// a row's entries are read and written in pairs, sixteen rows ahead, and the triangular factors of the first round are kept (scr: r x 3 k doubles), which saves
+// the later ones the elimination with row interchanges.  A multiplier is at most 1 in magnitude, so the top bit of its exponent is free: set where
+// the rows were interchanged.  A zero pivot becomes `tiny`.
+// All rounds together, before -> now (one workgroup for everything, a vector per thread, and classical Gram-Schmidt with two barriers per vector and pass):
+// k = 256, r = 8: 250 -> 108 us; 512, 64: 6740 -> 572; whole reconstructions: 700 x 900, r = 128: 37.9 -> 4.5 ms, 512 x 512, r = 64: 8.6 -> 2.3.  A round of
+// solves is 28, 56 and 107 us at k = 256, 512 and 1000 (78, 157 and 304 with bounds tests and selects on every row), a sweep of r = 64 rows 101 us at 512.
+constexpr int kInvitMost = 1024, kInvitPad = 16;
+constexpr uint64_t kSwapped = 1ull << 62;
+__host__ __device__ static inline int invit_rows(int k) { return (k + kInvitPad - 1) / kInvitPad * kInvitPad; }
+__host__ __device__ static inline int invit_lds_bytes(int k) { return (invit_rows(k) + 2 * kInvitPad) * 7 * (int)sizeof(double); }
+__global__ __launch_bounds__(64) void invit_solve_lds_kernel(int k, const double* __restrict__ dg, const double* __restrict__ eg, const double* __restrict__ lam,
+                                                             int round, double* __restrict__ X, double* __restrict__ scr) {
+    extern __shared__ __align__(16) double2 mem2[];
+    constexpr int C = kInvitPad / 2;                      // rows per buffer
+    const int lane = threadIdx.x, c = blockIdx.x, rows = invit_rows(k), room = rows + 2 * kInvitPad;
+    double2* const de = mem2;                             // d - lam, e
+    double2* const up = de + room;                        // reciprocal pivot, super-diagonal of the triangular factor
+    double2* const mu = up + room;                        // multiplier, second super-diagonal
+    double* const x = (double*)(mu + room);
+    double *Xc = X + (int64_t)c * k, *kept = scr + (int64_t)c * 3 * k;
+    const double shift = lam[c], tiny = fmax(tridiag_norm(k, dg, eg) * 2.3e-16, 1e-300);
+    for (int i = lane; i < room; i += 64) {
+        de[i] = i < k ? make_double2(dg[i] - shift, i + 1 < k ? eg[i] : 0.0) : make_double2(1.0, 0.0);
+        x[i] = i >= k ? 0.0 : round == 0 ? invit_start_value((int64_t)c * k + i) : Xc[i];
+        if (round != 0) {
+            const double m = i < k ? kept[2 * k + i] : 0.0;
+            up[i] = i < k ? make_double2(kept[i], kept[k + i]) : make_double2(1.0, 0.0);
+            mu[i] = make_double2(m, (__builtin_bit_cast(uint64_t, m) & kSwapped) && i + 2 < k ? eg[i + 1] : 0.0);
         }
-        d = dl;
-        e = el;
-        X = mem + 2 * k;
-        scr = X + (int64_t)r * ld;
-        __syncthreads();
     }
-    const double tiny = fmax(tridiag_norm(k, d, e) * 2.3e-16, 1e-300);
-    for (int64_t t = tid; t < (int64_t)r * k; t += 256) X[t / k * ld + t % k] = invit_start_value(t);
     __syncthreads();
-    for (int round = 0; round < 3; ++round) {
-        if (tid < r) {
-            const int c = tid;
-            double* dd = scr + (int64_t)c * 3 * ld;
-            invit_solve_one(k, d, e, lam[c], tiny, X + (int64_t)c * ld, dd, dd + ld, dd + 2 * ld);
-        }
-        __syncthreads();
-        for (int c = 0; c < r; ++c) {
-            double* x = X + (int64_t)c * ld;
-            for (int pass = 0; pass < 2; ++pass) {
-                for (int j = wave; j < c; j += 4) {
-                    const double* y = X + (int64_t)j * ld;
-                    double s = 0.0;
-                    for (int64_t i = lane; i < k; i += 64) s += y[i] * x[i];
-                    s = wave_sum(s);
-                    if (lane == 0) dots[j] = s;
+    if (lane == 0) {
+        if (round == 0) {
+            double a = de[0].x, b = de[0].y, sub = b, xi = x[0];       // current row: diagonal, super-diagonal; sub-diagonal below it; right-hand side
+            double2 r[2][C];
+            double t[2][C];
+            auto load = [&](int buf, int i0) {
+#pragma unroll
+                for (int u = 0; u < C; ++u) { r[buf][u] = de[i0 + u + 1]; t[buf][u] = x[i0 + u + 1]; }
+            };
+            auto eliminate = [&](int buf, int i0) {
+#pragma unroll
+                for (int u = 0; u < C; ++u) {
+                    const double dn = r[buf][u].x, en = r[buf][u].y, xn = t[buf][u];
+                    const bool keep = fabs(a) >= fabs(sub);
+                    if (keep && fabs(a) < tiny) a = tiny;
+                    const double q = rcp_f64(keep ? a : sub), mult = (keep ? sub : a) * q;
+                    const double top = keep ? b : dn, top2 = keep ? 0.0 : en, xt = keep ? xi : xn;
+                    up[i0 + u] = make_double2(q, top);
+                    mu[i0 + u] = make_double2(__builtin_bit_cast(double, __builtin_bit_cast(uint64_t, mult) | (keep ? 0 : kSwapped)), top2);
+                    x[i0 + u] = xt;
+                    xi = (keep ? xn : xi) - mult * xt;
+                    a = (keep ? dn : b) - mult * top;
+                    b = (keep ? en : 0.0) - mult * top2;
+                    sub = en;
                 }
-                __syncthreads();
-                for (int64_t i = tid; i < k; i += 256) {
-                    double v = x[i];
-                    for (int j = 0; j < c; ++j) v -= dots[j] * X[(int64_t)j * ld + i];
-                    x[i] = v;
-                }
-                __syncthreads();
+            };
+            load(0, 0);
+#pragma unroll 1
+            for (int i0 = 0; i0 < rows; i0 += 2 * C) {
+                load(1, i0 + C);
+                eliminate(0, i0);
+                load(0, i0 + 2 * C);
+                eliminate(1, i0 + C);
             }
-            double s = 0.0;
-            for (int64_t i = tid; i < k; i += 256) s += x[i] * x[i];
-            s = wave_sum(s);
-            if (lane == 0) red[wave] = s;
-            __syncthreads();
-            const double nrm = sqrt(red[0] + red[1] + red[2] + red[3]);
-            const double inv = nrm > 0.0 ? 1.0 / nrm : 0.0;
-            for (int64_t i = tid; i < k; i += 256) x[i] *= inv;
-            __syncthreads();
+        } else {
+            double xi = x[0], m[2][C], t[2][C];
+            auto load = [&](int buf, int i0) {
+#pragma unroll
+                for (int u = 0; u < C; ++u) { m[buf][u] = mu[i0 + u].x; t[buf][u] = x[i0 + u + 1]; }
+            };
+            auto forward = [&](int buf, int i0) {
+#pragma unroll
+                for (int u = 0; u < C; ++u) {
+                    const uint64_t bits = __builtin_bit_cast(uint64_t, m[buf][u]);
+                    const bool keep = !(bits & kSwapped);
+                    const double xn = t[buf][u], xt = keep ? xi : xn;
+                    x[i0 + u] = xt;
+                    xi = (keep ? xn : xi) - __builtin_bit_cast(double, bits & ~kSwapped) * xt;
+                }
+            };
+            load(0, 0);
+#pragma unroll 1
+            for (int i0 = 0; i0 < rows; i0 += 2 * C) {
+                load(1, i0 + C);
+                forward(0, i0);
+                load(0, i0 + 2 * C);
+                forward(1, i0 + C);
+            }
+        }
+        double x1 = 0.0, x2 = 0.0;                        // x_{i+1}, x_{i+2}
+        double2 f[2][C];
+        double w[2][C], t[2][C];
+        auto load = [&](int buf, int i0) {                // rows i0 + C - 1 down to i0
+#pragma unroll
+            for (int u = 0; u < C; ++u) { f[buf][u] = up[i0 + u]; w[buf][u] = mu[i0 + u].y; t[buf][u] = x[i0 + u]; }
+        };
+        auto backward = [&](int buf, int i0) {
+#pragma unroll
+            for (int u = C - 1; u >= 0; --u) {
+                const double v = (t[buf][u] - w[buf][u] * x2 - f[buf][u].y * x1) * f[buf][u].x;
+                x2 = x1;
+                x1 = v;
+                x[i0 + u] = v;
+            }
+        };
+        load(0, rows - C);
+#pragma unroll 1
+        for (int i0 = rows - C; i0 > 0; i0 -= 2 * C) {
+            load(1, i0 - C);
+            backward(0, i0);
+            load(0, i0 >= 2 * C ? i0 - 2 * C : 0);
+            backward(1, i0 - C);
         }
     }
-    if constexpr (LOCAL)
-        for (int64_t t = tid; t < (int64_t)r * k; t += 256) Xg[t] = X[t / k * ld + t % k];
+    __syncthreads();
+    double mx = 0.0;
+    for (int i = lane; i < k; i += 64) mx = fmax(mx, fabs(x[i]));
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, 64));
+    const double sc = mx > 0.0 ? 1.0 / mx : 1.0;
+    for (int i = lane; i < k; i += 64) {
+        Xc[i] = x[i] * sc;
+        if (round == 0) { kept[i] = up[i].x; kept[k + i] = up[i].y; kept[2 * k + i] = mu[i].x; }
+    }
 }
 
-// The same computation for large problems, one launch per step, because the orthonormalisation is r^2 k work that
+// The rows of X (r x k, k <= 64 PER) orthonormalised in order by modified Gram-Schmidt, `sweeps` times.  One workgroup; four rows at a time
+// become a panel in LDS, a wavefront each, then every wavefront takes its share of the rows behind it through the panel.
+template <int PER>
+__global__ __launch_bounds__(1024) void invit_orthonormalize_kernel(int k, int r, int sweeps, double* __restrict__ X) {
+    constexpr int P = 4, W = 16;
+    __shared__ double pan[P][64 * PER];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    auto load = [&](int j, double (&v)[PER]) {
+#pragma unroll
+        for (int u = 0; u < PER; ++u) v[u] = lane + 64 * u < k ? X[(int64_t)j * k + lane + 64 * u] : 0.0;
+    };
+    auto store = [&](int j, const double (&v)[PER]) {
+#pragma unroll
+        for (int u = 0; u < PER; ++u)
+            if (lane + 64 * u < k) X[(int64_t)j * k + lane + 64 * u] = v[u];
+    };
+    auto project = [&](int i, double (&v)[PER]) {          // v -= (v, panel i) panel i
+        double p[PER], s = 0.0;
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            p[u] = pan[i][lane + 64 * u];
+            s = fma(v[u], p[u], s);
+        }
+        s = wave_sum(s);
+#pragma unroll
+        for (int u = 0; u < PER; ++u) v[u] = fma(-s, p[u], v[u]);
+    };
+    for (int sweep = 0; sweep < sweeps; ++sweep)
+        for (int p0 = 0; p0 < r; p0 += P) {
+            const int width = r - p0 < P ? r - p0 : P;
+            double v[PER];
+            if (wave < width) load(p0 + wave, v);
+            for (int i = 0; i < width; ++i) {
+                if (wave == i) {
+                    double s = 0.0;
+#pragma unroll
+                    for (int u = 0; u < PER; ++u) s = fma(v[u], v[u], s);
+                    const double nrm = sqrt(wave_sum(s)), inv = nrm > 0.0 ? 1.0 / nrm : 0.0;
+#pragma unroll
+                    for (int u = 0; u < PER; ++u) {
+                        v[u] *= inv;
+                        pan[i][lane + 64 * u] = v[u];
+                    }
+                    store(p0 + i, v);
+                }
+                lds_barrier();
+                if (wave > i && wave < width) project(i, v);
+            }
+            for (int j = p0 + P + wave; j < r; j += W) {
+                load(j, v);
+                for (int i = 0; i < P; ++i) project(i, v);
+                store(j, v);
+            }
+            __syncthreads();                              // the next panel's rows have been written, this one has been read
+        }
+}
+
+template <int PER>
+int orthonormalize(aser_ctx* ctx, int64_t k, int r, int sweeps, double* X) {
+    hipLaunchKernelGGL(invit_orthonormalize_kernel<PER>, dim3(1), dim3(1024), 0, ctx->stream, (int)k, r, sweeps, X);
+    return aser_check_launch(ctx, "invit_orthonormalize");
+}
+
+// The same computation for larger problems, one launch per step, because the orthonormalisation is r^2 k work that
 // one workgroup takes most of a second for at k = 4096, r = 200: the start vectors, the r solves (one thread each),
 // and per vector c and pass the dots against the vectors before it (one workgroup per earlier vector), the
 // update (workgroups over the k entries) and, after the second pass, the normalisation (one workgroup).
@@ -1193,9 +1315,17 @@ int aser_exact_reconstruct(aser_ctx* ctx, const float* T, int64_t m, int64_t n, 
     ASER_TRY(tridiagonalize(ctx, B, k, vec, vstore, taustore));
     double* sig64 = vec[7];
     ASER_TRY(tridiag_eigenvalues(ctx, k, vec[4], vec[5], sig64, lam));
-    if (pl.big) {
-        const double* dd = vec[4];
-        const double* ee = vec[5];
+    const double* dd = vec[4];
+    const double* ee = vec[5];
+    if (k <= kInvitMost) {
+        for (int round = 0; round < 3; ++round) {
+            hipLaunchKernelGGL(invit_solve_lds_kernel, dim3((unsigned)r), dim3(64), (unsigned)invit_lds_bytes((int)k), ctx->stream, (int)k, dd, ee, (const double*)lam,
+                               round, X, scr);
+            ASER_TRY(aser_check_launch(ctx, "invit_solve"));
+            const int sweeps = round == 2 ? 2 : 1;
+            ASER_TRY(k <= 256 ? orthonormalize<4>(ctx, k, r, sweeps, X) : k <= 512 ? orthonormalize<8>(ctx, k, r, sweeps, X) : orthonormalize<16>(ctx, k, r, sweeps, X));
+        }
+    } else {
         double* dots = (double*)(ws + pl.off_dots);
         const int64_t total = (int64_t)r * k;
         hipLaunchKernelGGL(invit_start_kernel, dim3((unsigned)(ceil_div64(total, 256) < 1024 ? ceil_div64(total, 256) : 1024)), dim3(256),
@@ -1213,17 +1343,6 @@ int aser_exact_reconstruct(aser_ctx* ctx, const float* T, int64_t m, int64_t n, 
             }
             ASER_TRY(aser_check_launch(ctx, "tridiag_invit (multi-launch)"));
         }
-    } else {
-        const size_t local = invit_lds_bytes(k, r);
-        if (local <= kInvitLds) {
-            ASER_HIP(ctx, hipFuncSetAttribute((const void*)tridiag_invit_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize, kInvitLds));
-            hipLaunchKernelGGL(tridiag_invit_kernel<true>, dim3(1), dim3(256), local, ctx->stream, k, r, (const double*)vec[4], (const double*)vec[5],
-                               (const double*)lam, X, scr);
-        } else {
-            hipLaunchKernelGGL(tridiag_invit_kernel<false>, dim3(1), dim3(256), 0, ctx->stream, k, r, (const double*)vec[4], (const double*)vec[5],
-                               (const double*)lam, X, scr);
-        }
-        ASER_TRY(aser_check_launch(ctx, "tridiag_invit"));
     }
     if (k <= 256)
         hipLaunchKernelGGL(backtransform_wave_kernel<4>, dim3((unsigned)r), dim3(64), 0, ctx->stream, k, (const double*)vstore, (const double*)taustore, X);

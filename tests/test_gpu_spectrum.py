@@ -172,3 +172,24 @@ def test_rank_of_a_non_finite_spectrum_is_refused(k, value):
         ctx.check(aser.aser_singular_values(ctx, T, S, sig))
         st, _, _ = aser.aser_select_rank(ctx, sig, 0.5)
         assert st == aser.ASER_ERR_INVALID_ARG and "positive sum" in ctx.last_error()
+
+
+@pytest.mark.parametrize("m,n,r", [(1, 5, 1), (2, 3, 2), (9, 30, 3), (10, 11, 10), (255, 257, 8), (258, 300, 5)])
+def test_factors_of_the_dense_solver(m, n, r):
+    """Sides around the eight rows that the solves of inverse iteration read ahead, none to read ahead at all, and around the 256 rows of the last
+    kernel of the tridiagonalisation, against LAPACK."""
+    rng = np.random.default_rng([11, m, n])
+    u = np.linalg.qr(rng.standard_normal((m, m)))[0]
+    v = np.linalg.qr(rng.standard_normal((n, m)))[0]
+    T = ((u * np.linspace(2.0, 1.0, m)) @ v.T).astype(np.float32)
+    uu, sg, vt = np.linalg.svd(T.astype(np.float64), full_matrices=False)
+    ctx = new_ctx()
+    ctx.ensure_workspace(aser.aser_workspace_bytes(m, n, r))
+    L_A, L_B, sigma = (torch.empty(shape, dtype=torch.float32, device=DEV) for shape in ((m, r), (r, n), (r,)))
+    st, err, _ = aser.aser_error_reconstruct(ctx, torch.from_numpy(T).to(DEV), torch.eye(n, device=DEV), r, L_A, L_B, sigma)
+    ctx.check(st)
+    got, want = L_A.double().cpu().numpy() @ L_B.double().cpu().numpy(), (uu[:, :r] * sg[:r]) @ vt[:r]
+    # neighbouring singular values are 1 / m apart, which the products' rounding (2^-24) is divided by
+    gap = 1.0 / max(m - 1, 1)
+    assert np.max(np.abs(sigma.double().cpu().numpy() - sg[:r])) <= 2.0 ** -22 * sg[0]
+    assert np.linalg.norm(got - want) <= 2.0 ** -22 * (1.0 + 1.0 / gap) * np.linalg.norm(want)
