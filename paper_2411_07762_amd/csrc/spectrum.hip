@@ -1127,38 +1127,47 @@ __global__ __launch_bounds__(256) void backtransform_kernel(int64_t k, const dou
 }
 
 // The same for k <= 64 PER: one wavefront per vector with the vector in registers and the next four reflectors on their way, sums by
-// lane shifts (k = 256: 194 us with a workgroup per vector and two barriers per reflector, 144 with one reflector ahead and sums by
-// lane exchanges through LDS, 63 like this).
+// lane shifts (k = 256: 194 us with a workgroup per vector and two barriers per reflector).  The loads stand behind no branch, what lies past the row's end
+// is dropped at its use: with a test around every load the compiler waits for all of them where the branches meet, and nothing is on
+// its way (k = 256: 63 -> 59 us, 512: 240 -> 134, 1000: 551 -> 348).
 template <int PER>
 __global__ __launch_bounds__(64) void backtransform_wave_kernel(int64_t k, const double* __restrict__ vstore,
                                                                 const double* __restrict__ taustore, double* __restrict__ X) {
     constexpr int kAhead = 4;
+    if (k < 3) return;                                               // no reflectors
     const int lane = threadIdx.x;
     double* x = X + (int64_t)blockIdx.x * k;
+    uint32_t col[PER];
     double xv[PER], v[kAhead][PER], tau[kAhead];
 #pragma unroll
-    for (int u = 0; u < PER; ++u) xv[u] = lane + 64 * u < k ? x[lane + 64 * u] : 0.0;
+    for (int u = 0; u < PER; ++u) {
+        col[u] = lane + 64 * u < k ? lane + 64 * u : 0;
+        xv[u] = x[col[u]];
+        if (lane + 64 * u >= k) xv[u] = 0.0;
+    }
     auto load = [&](int64_t j, double (&t)[PER], double& tt) {       // entries up to j are zero in the store
         if (j < 0) j = 0;                                            // not used
+        const double* const row = vstore + j * k;
 #pragma unroll
-        for (int u = 0; u < PER; ++u) t[u] = lane + 64 * u < k ? vstore[j * k + lane + 64 * u] : 0.0;
+        for (int u = 0; u < PER; ++u) t[u] = row[col[u]];
         tt = taustore[j];
     };
-    if (k >= 3) {
 #pragma unroll
-        for (int q = 0; q < kAhead; ++q) load(k - 3 - q, v[q], tau[q]);
-    }
+    for (int q = 0; q < kAhead; ++q) load(k - 3 - q, v[q], tau[q]);
     for (int64_t j = k - 3; j >= 0; j -= kAhead) {
 #pragma unroll
         for (int q = 0; q < kAhead; ++q) {
             if (j - q < 0) break;
-            double s = 0.0;
+            double s[4] = {0.0, 0.0, 0.0, 0.0}, y[PER];
 #pragma unroll
-            for (int u = 0; u < PER; ++u) s += v[q][u] * xv[u];
-            s = wave_sum(s) * tau[q];
-#pragma unroll
-            for (int u = 0; u < PER; ++u) xv[u] -= s * v[q][u];
+            for (int u = 0; u < PER; ++u) {
+                y[u] = lane + 64 * u < k ? v[q][u] : 0.0;
+                s[u & 3] = fma(y[u], xv[u], s[u & 3]);
+            }
+            const double f = wave_sum((s[0] + s[1]) + (s[2] + s[3])) * tau[q];
             load(j - q - kAhead, v[q], tau[q]);
+#pragma unroll
+            for (int u = 0; u < PER; ++u) xv[u] = fma(-f, y[u], xv[u]);
         }
     }
 #pragma unroll
@@ -1346,6 +1355,8 @@ int aser_exact_reconstruct(aser_ctx* ctx, const float* T, int64_t m, int64_t n, 
     }
     if (k <= 256)
         hipLaunchKernelGGL(backtransform_wave_kernel<4>, dim3((unsigned)r), dim3(64), 0, ctx->stream, k, (const double*)vstore, (const double*)taustore, X);
+    else if (k <= 512)
+        hipLaunchKernelGGL(backtransform_wave_kernel<8>, dim3((unsigned)r), dim3(64), 0, ctx->stream, k, (const double*)vstore, (const double*)taustore, X);
     else if (k <= 1024)
         hipLaunchKernelGGL(backtransform_wave_kernel<16>, dim3((unsigned)r), dim3(64), 0, ctx->stream, k, (const double*)vstore, (const double*)taustore, X);
     else
