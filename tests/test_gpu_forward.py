@@ -198,3 +198,24 @@ def test_rank_branch_of_a_few_tokens(rows, n, m, r, offset, split):
     assert float(torch.linalg.norm(call() - ref) / torch.linalg.norm(ref)) <= (2.0 ** -20 if split else 1e-3)
     lb[r - 1, n - 2] = float("inf")                       # the codes of even channels are positive
     assert bool((call() == torch.where(la[:, r - 1].cpu() > 0, np.inf, -np.inf)).all())
+
+
+@pytest.mark.parametrize("n", [8, 504, 2056, 4096, 4097, 4104, 6152, 11008, 16392])
+@pytest.mark.parametrize("dt", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("scaled,offset", [(True, 0), (True, 1), (False, 0)])
+def test_activation_quantizer_at_the_ends_of_a_token(n, dt, scaled, offset):
+    """Tokens that end inside a thread's groups, in the last one's start and in no group of eight, with M that starts on 16 bytes or not, bit for bit."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(n)
+    X = (torch.randn((5, n), generator=g, device=DEV) * 3.0).to(dt)
+    X[3] = 0.0
+    X[4, n - 1] = -500.0                                  # the largest value is the token's last
+    md = torch.ones(n + 1, device=DEV)
+    md[offset::7] = 1.0 + 30.0 * torch.rand(md[offset::7].shape, generator=g, device=DEV)
+    md = md[offset:offset + n] if scaled else None
+    q, s = torch.full((6, n), 99, dtype=torch.int8, device=DEV), torch.empty(5, device=DEV)
+    ctx = new_ctx()
+    ctx.check(aser.aser_quantize_act_rtn(ctx, X, md, 8, q[:5], s))
+    torch.cuda.synchronize()
+    ref_q, ref_s = orc.quantize_act_rtn(X.float().cpu().numpy(), md.cpu().numpy() if scaled else np.ones(n, np.float32), 8)
+    assert np.array_equal(q[:5].cpu().numpy(), ref_q) and np.array_equal(s.cpu().numpy(), ref_s.reshape(-1).astype(np.float32)) and bool((q[5] == 99).all())
