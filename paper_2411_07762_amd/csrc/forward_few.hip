@@ -363,7 +363,8 @@ template <bool W4, int OT, int TG, int NW>
 int launch_few(aser_ctx* ctx, FewArgs g) {
     g.tiles = (int)ceil_div64(g.m, 16 * OT);
     const int64_t work = g.tiles * ceil_div64(g.rows, 16 * TG);
-    // P beside the codes: where the output tiles are small workgroups, one or two per compute unit, and long enough to hide P.  Measured (us, P in front
+    // P beside the codes: where the output tiles are small workgroups, one or two per compute unit, and long enough to hide P.  Measured with P on the fp32 MFMA
+    // instruction, which made it up to 2 us longer in front and 1 us longer beside the codes (us, P in front
     // -> beside; channels, outputs, one token / 16 tokens, r = 64, int4): 2048, 8224: 13.5 -> 12.4 / 18.1 -> 17.0; 4096, 10240: 17.6 -> 14.9 / 23.8 -> 19.9; 4096,
     // 14336: 18.3 -> 15.7 / 24.2 -> 20.3; 14336, 8224: 32.1 -> 29.3 / 46.4 -> 40.0.  Not at 1024, 14336: 10.9 -> 11.7 / 13.5 -> 13.8, nor with eight wavefronts per
     // tile (8192, 8192: 17.8 -> 19.2 / 27.0 -> 28.4; 4096, 4096: 12.0 -> 13.8 / 16.5 -> 19.1) or 64 outputs (8192, 16384: 25.5 -> 24.9 / 33.9 -> 34.1).
