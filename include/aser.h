@@ -222,7 +222,7 @@ int aser_whiten(aser_ctx* ctx, const float* G, int64_t ldg, int64_t n, const flo
  * Its products carry about 2^-16 relative error (2^-24 in the EXACT mode), so a whitened error below
  * about 1e-3 of ||T S||_F is resolved to fewer than four digits there; such residuals were only met on
  * layers of a few hundred channels, which the dense solver takes.
- * ASER_ERR_NO_CONVERGE: a pivot of a block Gram matrix was not positive.
+ * ASER_ERR_NO_CONVERGE: a pivot of a block Gram matrix was not positive, or the dense solver met values that are not finite.
  * Reports (as ASER_ERR_NOT_SPD / ASER_ERR_INVALID_ARG) what an asynchronous aser_whiten or an
  * aser_smooth_outliers on this context has left pending.  Needs workspace. */
 int aser_error_reconstruct(aser_ctx* ctx, const float* T, int64_t m, int64_t n, int64_t ldt,

@@ -35,6 +35,8 @@ extern "C" int aser_create(aser_ctx** out, int device, void* hip_stream) {
     c->rec_exact = false;
     c->rec_iters = 0;
     c->share = 1;
+    c->gate_attempts = 1 << 20;
+    c->exchange_broken = false;
     c->err[0] = 0;
     *out = c;
     return ASER_OK;

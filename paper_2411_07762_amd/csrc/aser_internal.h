@@ -29,6 +29,8 @@ struct aser_ctx {
     bool rec_exact;      // the dense solver ran (no orthogonalisation flag to look at)
     int32_t rec_iters;
     int share;           // layers in flight on the device next to this context's (1: alone); see aser_split_k_parts
+    int gate_attempts;   // of the wait that tridiag_resident.hip begins with; < 0: the chain of launches alone
+    bool exchange_broken;
     char err[256];
 };
 
@@ -98,6 +100,9 @@ static inline bool aser_use_exact_solver(int precision, int64_t m, int64_t n, in
     if (r > kAserMaxIterRank) return true;
     return precision != ASER_PRECISION_FAST && m * n <= ((int64_t)1 << 20) && !(o && (o->max_iter > 0 || o->block > 0));
 }
+
+// For the tests of what happens when a wait inside tridiag_resident.hip runs out of attempts.
+void aser_set_exchange(aser_ctx* ctx, int gate_attempts, bool broken);
 
 // Makes ctx's device current (first compute call) and checks a launch.
 int aser_prepare_device(aser_ctx* ctx);

@@ -128,6 +128,7 @@ struct TridiagStep {
     const double* tau_cur; double* tau_next;
     int* counter;                         // workgroups that have finished (0 between launches)
     double *vstore, *taustore;            // reflectors kept for a back-transformation, or null
+    const uint64_t* broken;               // not null and the word not zero: what the tail kernel is given may not be used
 };
 
 // The start of the chain: d_0 and the first reflector from row 0 of B (or the whole of a matrix of one or two rows).
@@ -316,6 +317,10 @@ __global__ __launch_bounds__(64 * kTailWaves) void tridiag_tail_kernel(TridiagSt
         taus[kTailRows], red[2 * T], entry[2], corner, tau_s;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t k = a.k;
+    if (a.broken && *a.broken != 0) {
+        for (int64_t i = tid; i < k; i += 64 * kTailWaves) a.d[i] = a.e[i] = __builtin_nan("");
+        return;
+    }
     const int first = kTailRows - (int)(k - a.c0);        // 0 .. kTailRows - 2; row i here is row i + base of the matrix
     const int64_t base = a.c0 - first;
     const double* const Bo = a.B + base * k + base;       // entries from `first` on only
@@ -478,7 +483,7 @@ __global__ __launch_bounds__(64 * kTailWaves) void tridiag_tail_kernel(TridiagSt
 // when k is larger).  More points per eigenvalue mean fewer rounds but more chains: one wavefront per SIMD hides nothing, a
 // second chain in it costs a third more and shares the terms, and at k = 4096 sixteen lanes of two points are one wavefront per SIMD
 // (2570 us with quotients and one point per lane in 15 rounds, 1110 now).  Where the chip is empty anyway a wavefront of 64 points takes an eigenvalue, alone in its workgroup (k = 256: 103 -> 40 us).
-// sigma[k - 1 - i] = sqrt(max(lambda_i, 0)).
+// sigma[k - 1 - i] = sqrt(max(lambda_i, 0)).  Where an entry of d or e is not finite every sigma is 0, which has no rank, and every eigenvalue NaN.
 constexpr int kSturmLds = 4096;
 
 template <int L, int P, int THREADS>
@@ -489,12 +494,14 @@ __global__ __launch_bounds__(THREADS) void tridiag_eigenvalues_kernel(int64_t k,
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t i = (int64_t)blockIdx.x * (THREADS / L) + tid / L;
     const int sub = tid % L;
-    // Gershgorin interval
+    // Gershgorin interval; none where an entry is not finite
     double lo = 1e300, hi = -1e300;
+    int odd = 0;
     for (int64_t l = tid; l < k; l += THREADS) {
         const double dl = d[l], el = (l + 1 < k) ? fabs(e[l]) : 0.0, ep = (l > 0) ? fabs(e[l - 1]) : 0.0;
         lo = fmin(lo, dl - el - ep);
         hi = fmax(hi, dl + el + ep);
+        odd |= !__builtin_isfinite(dl + el + ep);
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
@@ -502,7 +509,13 @@ __global__ __launch_bounds__(THREADS) void tridiag_eigenvalues_kernel(int64_t k,
         hi = fmax(hi, __shfl_xor(hi, o, 64));
     }
     if (lane == 0) { red[0][wave] = lo; red[1][wave] = hi; }
-    __syncthreads();
+    if (__syncthreads_or(odd)) {
+        if (sub == 0 && i < k) {
+            sigma[k - 1 - i] = 0.0;
+            if (lam_desc) lam_desc[k - 1 - i] = __builtin_nan("");
+        }
+        return;
+    }
 #pragma unroll
     for (int g = 0; g < THREADS / 64; ++g) {
         lo = fmin(lo, red[0][g]);
@@ -531,11 +544,10 @@ __global__ __launch_bounds__(THREADS) void tridiag_eigenvalues_kernel(int64_t k,
             }
             for (int t = 0; t < padded; t += kSturmTerms) sturm_terms(c, de + t, x);
         }
-        // the count grows with x: the points with cnt <= i are the first p of the group.  (A NaN in d or e reaches the last term and would count
-        // by its sign; counted as nothing, sigma is 0.)
+        // the count grows with x: the points with cnt <= i are the first p of the group
         int mine = 0;
 #pragma unroll
-        for (int u = 0; u < P; ++u) mine += (c[u].p != c[u].p || (int64_t)c[u].count <= i) ? 1 : 0;
+        for (int u = 0; u < P; ++u) mine += (int64_t)c[u].count <= i ? 1 : 0;
         int p = 0;
 #pragma unroll
         for (int u = 0; u < P; ++u) {
@@ -689,15 +701,19 @@ int tridiagonalize(aser_ctx* ctx, double* B, int64_t k, double* const* vec, doub
         // the columns up to the last 256 on the chip, once six rows that the chain has left behind (and that hold no pair) are there for the
         // exchange.  A column costs 2.8 us there against 7.7 (and more) for a launch; kResidentLeast: less than that is not worth two launches
         const int64_t gone = s < kFirst ? 0 : 2 * kSlots;
-        if (!tried && k - a.c0 <= kAserResidentMost && k - a.c0 >= kResidentLeast && pending <= 1 && a.c0 >= gone + 6 && ctx->share == 1) {
+        if (!tried && k - a.c0 <= kAserResidentMost && k - a.c0 >= kResidentLeast && pending <= 1 && a.c0 >= gone + 6 && ctx->share == 1 && ctx->gate_attempts >= 0) {
             tried = true;
             const AserTridiagResident r{k, a.c0, B, a.vn, pending ? a.v[0] : nullptr, pending ? a.w[0] : nullptr, a.tau_cur,
-                                        vec[0], vec[1], vec[2], a.tau_next, a.d, a.e, vstore, taustore, (uint64_t*)(B + gone * k)};
-            if (aser_tridiag_resident(ctx, r)) {
+                                        vec[0], vec[1], vec[2], a.tau_next, a.d, a.e, vstore, taustore, (uint64_t*)(B + gone * k),
+                                        ctx->gate_attempts, ctx->exchange_broken};
+            bool done = false;
+            ASER_TRY(aser_tridiag_resident(ctx, r, &done));
+            if (done) {
                 s = k - kTailRows - 1;
                 a.c0 = s + 1;
                 a.vn = vec[0]; a.v[0] = vec[1]; a.w[0] = vec[2];
                 a.tau_cur = r.tau_out;
+                a.broken = aser_tridiag_broken(r);
                 pending = 1;
             }
         }
@@ -1210,7 +1226,7 @@ __global__ __launch_bounds__(256) void exact_factors_kernel(int phase, int left,
         return;
     }
     if (t == 0) {
-        double tail = 0.0;
+        double tail = lam[0] != lam[0] ? lam[0] : 0.0;     // NaN: all of them are
         for (int64_t i = k - 1; i >= r; --i) tail += lam[i] > 0.0 ? lam[i] : 0.0;    // smallest first
         *err2 = tail;
     }

@@ -21,8 +21,14 @@
 // readers ask again until the pattern is gone.  Three buffers rotate; an owner of rows that are left restores the pattern in the buffer
 // of step j - 1 once it has read all of step j (whose entries their owners wrote after they had read step j - 1), and everybody who
 // could read that buffer again, in step j + 2, has first to see the owner's entry of step j + 1, which is written behind it.
-// All workgroups have to run at the same time, which the cooperative launch guarantees; a reader gives up after two million
-// attempts all the same, and then every result is NaN.
+//
+// All workgroups have to run at the same time.  The cooperative launch only sees to it that they would fit an empty device: work of other
+// streams or processes keeps the last ones out until it leaves a compute unit to them.  So the workgroups count themselves in before
+// anything is written, and whoever has waited a second or so for the rest calls it off (one word decides, so all agree); the kernel of one
+// workgroup behind this one (rescue) then does these columns, in seconds instead of milliseconds, with nothing to wait for.  Past that gate an entry is
+// as late as its owner's pass.  A reader that gives up on one all the same, after two million attempts, marks the computation broken, and then
+// the last kernel of the chain makes all of d and e NaN, which no caller takes for a spectrum.
+// The gate and the second launch: whole spectra of k = 326: 968 -> 976 us, 700 and more within what runs differ.
 //
 // What bounds it: the exchange, 2.0 us at 1024 columns left and 4.2 at 4096 (every workgroup reads 16 bytes per column past its L2), then
 // the pass, 768 fp64 operations per thread at 4096 columns.  A column costs 2.8 us while at most 1024 are left, 5 on average at
@@ -48,7 +54,8 @@ __host__ __device__ constexpr int row_of(int s, int w) { return 4 * kGroups * (s
 __host__ __device__ constexpr int reg_slot(int s) { return s < 16 - kRegSlots ? 0 : s - (16 - kRegSlots); }
 constexpr int kSide = kGroups * kSlots;                   // 4096
 constexpr int kTail = kAserTridiagTail;
-constexpr int kMaxTries = 1 << 21;
+constexpr int kMaxTries = 1 << 21;                        // a launch argument instead makes 114 registers spill, not 22
+constexpr uint64_t kOff = 1ull << 63;                     // in the word of arrivals: called off
 constexpr uint64_t kEmpty = 0x7ff8a5e25eed0001ull;        // fp32 inputs widened leave the low 29 bits of a NaN's payload zero
 static_assert(!in_lds(8, 0) && !in_lds(7, 0) && kRegSlots == 10, "the dynamic LDS holds slots below 8 only");
 static_assert(kSide == kThreads * kCols && kSide == kAserResidentMost && kTail % 4 == 0, "rows and columns");
@@ -121,19 +128,44 @@ __device__ __forceinline__ double entry_of_p(double alpha, double s, double x) {
 __device__ __forceinline__ double entry_of_w(double tau, double kk, double p, double v) { return fma(-kk, v, tau * p); }
 __device__ __forceinline__ double entry_of_u(double vj, double wj, double x, double w, double v) { return fma(-wj, v, fma(-vj, w, x)); }
 
-__global__ void resident_clear_kernel(uint64_t* ring, int64_t words) {
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < words; i += (int64_t)gridDim.x * 256) ring[i] = kEmpty;
+// The ring, and behind it the word of arrivals and the mark of a broken computation.
+__device__ __forceinline__ uint64_t* arrivals(const AserTridiagResident& a) { return a.ring + 6 * (a.k - a.c0 + 3); }
+__global__ void resident_clear_kernel(AserTridiagResident a) {
+    const int64_t words = 6 * (a.k - a.c0 + 3);
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < words + 2; i += (int64_t)gridDim.x * 256) a.ring[i] = i < words ? kEmpty : 0;
+}
+
+// Counts this workgroup in and waits for the others: true in all of them, or false in all of them.  (No attempts at all: false.)
+__device__ __forceinline__ bool all_here(const AserTridiagResident& a) {
+    uint64_t* const word = arrivals(a);
+    if (a.gate_attempts == 0) __hip_atomic_fetch_or(word, kOff, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    uint64_t seen = __hip_atomic_fetch_add(word, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1;
+    for (int tries = 0; seen < kGroups; ++tries) {        // with the mark it is not less
+        if (tries < a.gate_attempts) {
+            __builtin_amdgcn_s_sleep(1);
+            seen = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        } else if (__hip_atomic_compare_exchange_strong(word, &seen, seen | kOff, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
+            return false;                                 // otherwise `seen` is new: it changes no more than once per workgroup
+        }
+    }
+    return (seen & kOff) == 0;
 }
 
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void tridiag_resident_kernel(AserTridiagResident a) {
     extern __shared__ double low[];                       // [kLdsChunks][kThreads], when the matrix has such rows
     __shared__ double part[kWaves][kSlots], n2part[kWaves], dotpart[kWaves], rowv[kSlots], rowp[kSlots], colj[kSlots], near[6];
-    __shared__ int failed;
+    __shared__ int failed, here;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), w = blockIdx.x;
     const int64_t k = a.k, base = k - kSide;              // row i here is row i + base of the matrix
     const int first = (int)(a.c0 - base);
     const int ring0 = first & ~3, turn_words = 2 * (kSide - ring0);
     double* const Bo = a.B + base * k + base;             // only rows and columns from `first` on are looked at
+    if (tid == 0) {
+        failed = a.broken;
+        here = all_here(a);
+    }
+    lds_barrier();
+    if (!here) return;
     double m[kRegSlots][kCols], u[kCols], v[kCols], wv[kCols];
 #pragma unroll
     for (int s = 0; s < kSlots; ++s) {
@@ -164,7 +196,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
         rowv[lane] = (in && a.vp) ? a.vp[base + row] : 0.0;
         rowp[lane] = (in && a.vp) ? a.wp[base + row] : 0.0;
     }
-    if (tid == 0) failed = 0;
     double tau = 1.0, kk = 0.0;                           // w in a row is tau rowp - kk rowv
     double x0 = lane_value(a.vn[a.c0], 0);                // u in row j
     const double tau_in = lane_value(*a.tau, 0);
@@ -353,7 +384,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
                       steps(std::integral_constant<int, 6>{}) && steps(std::integral_constant<int, 7>{});
     if (finished) return;
     if (!done) {                                          // gave up
-        for (int64_t i = tid; i < k; i += kThreads) a.d[i] = a.e[i] = __builtin_nan("");
+        if (tid == 0) __hip_atomic_store(aser_tridiag_broken(a), (uint64_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return;
     }
     // ---- the last 256 rows, with the reflector that is due and the pair that has not been applied, go back to memory
@@ -379,36 +410,119 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     }
 }
 
+// The same columns in one workgroup, where the gate was called off; otherwise it leaves at once.  B in memory, the vectors of a step in LDS; a wavefront
+// takes a row at a time.  Bound by what one compute unit reads and writes: whole spectra of k = 326, 700, 1030, 2049, 4096
+// in 2.3, 27, 107, 850 and 6700 ms.
+constexpr int kRescueThreads = 1024;
+__global__ __launch_bounds__(kRescueThreads) void tridiag_rescue_kernel(AserTridiagResident a) {
+    extern __shared__ double vecs[];                      // entry i: row and column c0 + i
+    __shared__ double red[2][kRescueThreads / 64];
+    if ((*arrivals(a) & kOff) == 0) return;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, rest = (int)(a.k - a.c0);
+    double *const u = vecs, *const v = u + rest, *const w = v + rest, *const p = w + rest;      // the reflector, the pair B lacks, B u
+    double* const Bo = a.B + a.c0 * a.k + a.c0;
+    for (int i = tid; i < rest; i += kRescueThreads) {
+        u[i] = a.vn[a.c0 + i];
+        v[i] = a.vp ? a.vp[a.c0 + i] : 0.0;
+        w[i] = a.vp ? a.wp[a.c0 + i] : 0.0;
+    }
+    double tau = *a.tau;
+    auto sum = [&](double x, double* r) {                 // over the workgroup
+        x = wave_sum(x);
+        if (lane == 0) r[wave] = x;
+        __syncthreads();
+        double s = 0.0;
+        for (int g = 0; g < kRescueThreads / 64; ++g) s += r[g];
+        return s;
+    };
+    __syncthreads();
+    for (int j = 0; j < rest - kTail; ++j) {
+        for (int i = j + wave; i < rest; i += kRescueThreads / 64) {
+            double* const row = Bo + (int64_t)i * a.k;
+            const double vi = v[i], wi = w[i];
+            double s = 0.0;
+            for (int l = j + lane; l < rest; l += 64) {
+                const double x = row[l] - (vi * w[l] + wi * v[l]);
+                row[l] = x;
+                s = fma(x, u[l], s);
+            }
+            s = wave_sum(s);
+            if (lane == 0) p[i] = s;
+        }
+        __syncthreads();
+        double dot = 0.0;
+        for (int i = j + tid; i < rest; i += kRescueThreads) dot = fma(u[i], p[i], dot);
+        const double kk = 0.5 * tau * tau * sum(dot, red[0]), vj = u[j], wj = tau * p[j] - kk * vj, x0 = Bo[(int64_t)j * a.k + j + 1] - (vj * (tau * p[j + 1] - kk * u[j + 1]) + wj * u[j + 1]);
+        __syncthreads();                                  // u and p of rows j and j + 1 have been read
+        double n2 = 0.0;
+        for (int i = j + tid; i < rest; i += kRescueThreads) {
+            const double ui = u[i], wi = tau * p[i] - kk * ui, x = Bo[(int64_t)j * a.k + i] - (vj * wi + wj * ui);
+            v[i] = ui;
+            w[i] = wi;
+            if (i == j) a.d[a.c0 + j] = x;
+            u[i] = i == j ? 0.0 : x;
+            n2 += i == j ? 0.0 : x * x;
+        }
+        n2 = sum(n2, red[1]);
+        const double alpha = x0 > 0.0 ? -sqrt(n2) : sqrt(n2), v0 = x0 - alpha, vn2 = n2 - x0 * x0 + v0 * v0;
+        tau = vn2 > 0.0 ? 2.0 / vn2 : 0.0;
+        if (tid == 0) {
+            u[j + 1] = v0;
+            a.e[a.c0 + j] = alpha;
+            if (a.vstore) a.taustore[a.c0 + j] = tau;
+        }
+        __syncthreads();
+        if (a.vstore)
+            for (int i = j + 1 + tid; i < rest; i += kRescueThreads) a.vstore[(a.c0 + j) * a.k + a.c0 + i] = u[i];
+    }
+    for (int i = rest - kTail + tid; i < rest; i += kRescueThreads) {
+        a.vn_out[a.c0 + i] = u[i];
+        a.vp_out[a.c0 + i] = v[i];
+        a.wp_out[a.c0 + i] = w[i];
+    }
+    if (tid == 0) *a.tau_out = tau;
+}
+
 }  // namespace
 
-bool aser_tridiag_resident(aser_ctx* ctx, const AserTridiagResident& a) {
+void aser_set_exchange(aser_ctx* ctx, int gate_attempts, bool broken) {
+    ctx->gate_attempts = gate_attempts;
+    ctx->exchange_broken = broken;
+}
+
+int aser_tridiag_resident(aser_ctx* ctx, const AserTridiagResident& a, bool* done) {
+    *done = false;
     const int64_t rest = a.k - a.c0;
-    if (rest <= kTail || rest > kSide) return false;
+    if (rest <= kTail || rest > kSide) return ASER_OK;
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     if (ctx->stream && (hipStreamIsCapturing(ctx->stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone)) {
         (void)hipGetLastError();
-        return false;
+        return ASER_OK;
     }
     int cus = 0, coop = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device) != hipSuccess ||
         hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, ctx->device) != hipSuccess || cus < kGroups || !coop) {
         (void)hipGetLastError();
-        return false;
+        return ASER_OK;
     }
     const int first = (int)(kSide - rest);
     constexpr int most_lds = kLdsChunks * kThreads * (int)sizeof(double);
     const size_t lds = first < kGroups * 8 ? (size_t)most_lds : 0;
-    if (hipFuncSetAttribute((const void*)tridiag_resident_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, most_lds) != hipSuccess) {
+    constexpr int row_bytes = 4 * (int)sizeof(double);
+    if (hipFuncSetAttribute((const void*)tridiag_resident_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, most_lds) != hipSuccess ||
+        hipFuncSetAttribute((const void*)tridiag_rescue_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, row_bytes * kSide) != hipSuccess) {
         (void)hipGetLastError();
-        return false;
+        return ASER_OK;
     }
-    hipLaunchKernelGGL(resident_clear_kernel, dim3(96), dim3(256), 0, ctx->stream, a.ring, 6 * (rest + 3));
+    hipLaunchKernelGGL(resident_clear_kernel, dim3(96), dim3(256), 0, ctx->stream, a);
     AserTridiagResident args = a;
     void* params[] = {&args};
     if (hipGetLastError() != hipSuccess ||
         hipLaunchCooperativeKernel((const void*)tridiag_resident_kernel, dim3(kGroups), dim3(kThreads), params, (unsigned)lds, ctx->stream) != hipSuccess) {
         (void)hipGetLastError();
-        return false;
+        return ASER_OK;
     }
-    return true;
+    hipLaunchKernelGGL(tridiag_rescue_kernel, dim3(1), dim3(kRescueThreads), (size_t)row_bytes * rest, ctx->stream, a);
+    *done = true;
+    return aser_check_launch(ctx, "tridiag_rescue");
 }

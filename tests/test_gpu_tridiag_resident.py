@@ -1,6 +1,8 @@
 """The tridiagonalisation that keeps the matrix on the chip, through the singular values of T alone (S = NULL: T T^T is then formed in fp64
 from fp32 entries): matrix sides around its limits (the last 256 rows, chunks of 512 columns, groups of 1024 rows, 4096 rows), odd
 ones, and beyond them, where the chain of launches runs first."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -71,3 +73,95 @@ def test_captured_calls_take_the_chain_of_launches():
         graph.replay()
         torch.cuda.synchronize()
         assert np.abs(sig.cpu().numpy() - eager).max() <= 1e-11 * eager[0]
+
+
+def exchange(ctx, gate_attempts, broken=False):
+    """The waits of the resident kernel as after `gate_attempts` attempts at its gate, or with an entry that never came."""
+    aser.load_library()["_Z17aser_set_exchangeP8aser_ctxib"](ctx.handle, ctypes.c_int(gate_attempts), ctypes.c_bool(broken))
+    return ctx
+
+
+@pytest.mark.parametrize("k", [326, 517, 700, 1031, 2054])
+def test_columns_where_the_workgroups_do_not_all_get_in(k):
+    """The gate called off by every workgroup: the kernel of one workgroup does the columns instead, to the same bound."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(k)
+    T = torch.randn((k, k + 9), generator=g, device=DEV) * torch.logspace(0, -2, k + 9, device=DEV)
+    got = spectrum(exchange(new_ctx(), 0), T) ** 2
+    Td = T.double().cpu()
+    ref = torch.linalg.eigvalsh(Td @ Td.T).flip(0).numpy()
+    assert np.abs(got - ref).max() <= 4 * k * 2.2e-16 * ref[0]
+
+
+def reconstruct(ctx, T, r):
+    m, n = T.shape
+    ctx.ensure_workspace(aser.aser_workspace_bytes(m, n, r))
+    L_A, L_B, sigma = (torch.empty(shape, device=DEV) for shape in ((m, r), (r, n), (r,)))
+    st, err, _ = aser.aser_error_reconstruct(ctx, T, torch.eye(n, device=DEV), r, L_A, L_B, sigma)
+    return st, err, L_A.double() @ L_B.double()
+
+
+@pytest.mark.parametrize("m,n", [(700, 750), (620, 400)])
+def test_factors_where_the_workgroups_do_not_all_get_in(m, n):
+    """The reflectors that the dense solver carries its vectors back through: the product of the factors is the best approximation whichever
+    kernel has made them (neighbouring singular values 1e-3 apart: 2^-24 of the products over that)."""
+    rng = np.random.default_rng(m)
+    k = min(m, n)
+    u, v = np.linalg.qr(rng.standard_normal((m, k)))[0], np.linalg.qr(rng.standard_normal((n, k)))[0]
+    s = np.linspace(2.0, 1.0, k)
+    T = torch.from_numpy(((u * s) @ v.T).astype(np.float32)).to(DEV)
+    uu, sg, vt = np.linalg.svd(T.double().cpu().numpy(), full_matrices=False)
+    want = (uu[:, :20] * sg[:20]) @ vt[:20]
+    for ctx in (new_ctx(), exchange(new_ctx(), 0)):
+        st, err, got = reconstruct(ctx, T, 20)
+        ctx.check(st)
+        assert abs(err - np.sqrt((sg[20:] ** 2).sum())) <= 1e-6 * err
+        assert np.linalg.norm(got.cpu().numpy() - want) <= 2.0 ** -22 * 1e3 * np.linalg.norm(want)
+
+
+@pytest.mark.parametrize("k", [400, 1500])
+def test_a_broken_exchange_is_no_spectrum(k):
+    """What the kernels in front have left finite must not come out as one: no singular value, a rank that is refused, factors with an error."""
+    T = torch.randn((k, k), device=DEV)
+    ctx = exchange(new_ctx(), 1 << 20, broken=True)
+    assert np.all(spectrum(ctx, T) == 0.0)
+    st, _, _ = aser.aser_select_rank(ctx, torch.zeros(k, dtype=torch.float64, device=DEV), 0.5)
+    assert st == aser.ASER_ERR_INVALID_ARG
+    if k * k <= 1 << 20:
+        st, _, _ = reconstruct(ctx, T, 8)
+        assert st == aser.ASER_ERR_NO_CONVERGE
+    exchange(ctx, 1 << 20)
+    assert spectrum(ctx, T)[0] > 0.0
+
+
+def test_spectra_beside_work_of_other_streams():
+    """Three contexts on streams of their own and products on a fourth: whoever gets in when, the results are those of a call alone."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(3)
+    Ts = [torch.randn((k, k), generator=g, device=DEV) for k in (700, 900, 1300)]
+    alone = [spectrum(new_ctx(), T) for T in Ts]
+    streams = [torch.cuda.Stream() for _ in range(4)]
+    ctxs = [aser.Context(0, s.cuda_stream) for s in streams[:3]]
+    sig = [torch.zeros(T.shape[0], dtype=torch.float64, device=DEV) for T in Ts]
+    for c, T in zip(ctxs, Ts):
+        c.ensure_workspace(aser.aser_spectrum_workspace_bytes(T.shape[0], T.shape[0], False))
+    A = torch.randn((4096, 4096), device=DEV)
+    torch.cuda.synchronize()
+    for _ in range(2):
+        with torch.cuda.stream(streams[3]):
+            for _ in range(10):
+                B = A @ A
+        for c, T, s in zip(ctxs, Ts, sig):
+            c.check(aser.aser_singular_values(c, T, None, s))
+    torch.cuda.synchronize()
+    for s, ref in zip(sig, alone):
+        assert np.abs(s.cpu().numpy() - ref).max() <= 1e-11 * ref[0]
+
+
+@pytest.mark.parametrize("k", [40, 300, 700])
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+def test_factors_of_a_matrix_that_is_not_finite(k, value):
+    T = torch.randn((k, k), device=DEV)
+    T[k // 2, k // 3] = value
+    st, _, _ = reconstruct(new_ctx(), T, 8)
+    assert st == aser.ASER_ERR_NO_CONVERGE
