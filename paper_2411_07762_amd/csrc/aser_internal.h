@@ -233,11 +233,12 @@ int aser_gemm_small_f32(aser_ctx* ctx, float* A, int64_t lda, const float* B, in
                         float* C, int64_t ldc, int64_t rows, int k, int c, int64_t clear_rows = 0, bool transposed = false, float* A2 = nullptr,
                         float* C2 = nullptr);
 
-// P = s_t x_q L_B^T (rows x r_pad, r_pad = r rounded up to 32) and L_A (m x r_pad) as bf16 planes (forward.hip), r <= 128.  split: hi and
-// lo of P, L_A and L_B; otherwise all three rounded to bf16 and the lo planes left alone.  Codes in rows of ldq bytes, 16-byte aligned, a multiple of
-// 32 of them finite.  xs null: s_t = 1.  lb: scratch, 4 r_pad bytes per channel rounded up to 32, 16-byte aligned.
+// P = s_t x_q L_B^T (rows x r_pad, r_pad = r rounded up to 32) and L_A (m x r_pad) as bf16 planes (forward.hip), r <= 128.  `parts` planes each of P, L_A
+// and L_B, 1 to 3, a plane what is left of the value behind the ones before it, rounded to bf16: 9, 17 or all 24 of its bits.  Codes in rows of ldq
+// bytes, 16-byte aligned, a multiple of 32 of them finite.  xs null: s_t = 1.  lb: scratch, 2 parts r_pad bytes per channel rounded up to 32, 16-byte aligned.
+struct AserRankPlanes { uint16_t *p[3], *la[3]; void* lb; };
 int aser_rank_down(aser_ctx* ctx, const int8_t* xq, int64_t ldq, const float* xs, int64_t rows, int64_t n, const float* L_B, int r,
-                   bool split, uint16_t* p_hi, uint16_t* p_lo, const float* L_A, int64_t m, uint16_t* la_hi, uint16_t* la_lo, void* lb);
+                   int parts, const float* L_A, int64_t m, const AserRankPlanes& out);
 // The compensated layer for a few tokens (forward_few.hip); arguments as aser_compensated_forward has checked them.
 // scratch: ceil(n / 2048) * rows * (r rounded up to 16) floats when r > 0, 16-byte aligned.
 int aser_forward_few(aser_ctx* ctx, const int8_t* xq, const float* xs, int rows, int64_t n, const void* wq, bool w4, const float* ws,

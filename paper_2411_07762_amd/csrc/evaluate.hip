@@ -9,14 +9,15 @@
 // W rows, code rows), and that is how the MFMA wants its operands.  The factors that are not bf16 already become pairs of bf16
 // planes, x = hi + lo (about 2^-17 relative): W, fp32 activations.  bf16 activations are exact as they are, so Y = X W^T is two plane
 // products instead of the three of a general fp32 product.  The second output needs no planes of W~: the codes of both sides multiply
-// exactly on the int8 MFMA, at twice the rate, and the rank-r branch is r / 16 further bf16 steps per tile (P = x_q L_B^T and L_A as
-// planes, three products).  ONE kernel forms both outputs of a tile: the integer sums, then Y on accumulators of its own, ||Y||^2 from
+// exactly on the int8 MFMA, at twice the rate, and the rank-r branch is r / 16 further bf16 steps per tile: L_B, P = x_q L_B^T and L_A as
+// three planes each, which hold all of their 24 bits, and six products (with two planes and three products, 297 us instead of 300, the result was up to 30 times
+// as far from fp64 where factors cancel, and 2 to 5 times elsewhere).  ONE kernel forms both outputs of a tile: the integer sums, then Y on accumulators of its own, ||Y||^2 from
 // these, which are then multiplied by -1 / s_t per row and receive c_o times the integer sums and L_A P, and ||s_t (...)||^2:
 // neither output is ever stored.
 // Without activation quantization (and with r > 128, or where the planes do not fit the workspace) the second output is a product of planes
 // as well, of the activations or codes with those of W~ (divided by M when there are no codes), accumulated on top of the first.
 // Bound: the MFMA rates; 2048 tokens of the 4096 x 4096 layer are 1.4e11 operations in two bf16 plane products and 0.7e11 in int8: 219 us
-// (339 with four plane products), plus 30 for the planes of W (76 with those of W~) and 25 for P; the whole call 426 -> 289.
+// (339 with four plane products), plus 30 for the planes of W (76 with those of W~) and 25 to 30 for P; the whole call 415 -> 300.
 #include <math.h>
 
 #include <type_traits>
@@ -244,7 +245,7 @@ struct EvalArgs {
     int64_t np, nc, rows, m;                  // channels of a plane row (a multiple of 32), of a code row (of 64)
     const float* xs;                          // per-token scales, or null (1)
     const float* ws;                          // CODED: scales of the outputs, and the rank-r branch as planes of r_pad columns
-    const uint16_t *p_hi, *p_lo, *la_hi, *la_lo; int r_pad;
+    AserRankPlanes rank; int r_pad;
     double* out;                              // [0] += ||Y||^2, [1] += ||difference||^2
 };
 
@@ -456,23 +457,25 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2))) voi
         }
         for (int kk = 0; kk < g.r_pad; kk += 16) {        // L_A P, 16 columns of either at a time
             const int kq = kk + 8 * (lane >> 5);
-            bf16x8_t ph[TI], pl[TI];
+            bf16x8_t pv[TI][3];
 #pragma unroll
             for (int i = 0; i < TI; ++i) {
                 const int64_t row = T0 + wm0 + 32 * i + (lane & 31), at = (row < g.rows ? row : g.rows - 1) * g.r_pad + kq;
-                ph[i] = *(const bf16x8_t*)(g.p_hi + at);
-                pl[i] = *(const bf16x8_t*)(g.p_lo + at);
+#pragma unroll
+                for (int p = 0; p < 3; ++p) pv[i][p] = *(const bf16x8_t*)(g.rank.p[p] + at);
             }
 #pragma unroll
             for (int j = 0; j < TJ; ++j) {
                 const int64_t col = O0 + wn0 + 32 * j + (lane & 31), at = (col < g.m ? col : g.m - 1) * g.r_pad + kq;
-                const bf16x8_t lh = *(const bf16x8_t*)(g.la_hi + at), ll = *(const bf16x8_t*)(g.la_lo + at);
+                bf16x8_t lv[3];
 #pragma unroll
-                for (int i = 0; i < TI; ++i) {
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pl[i], lh, acc[i][j], 0, 0, 0);
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ph[i], ll, acc[i][j], 0, 0, 0);
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ph[i], lh, acc[i][j], 0, 0, 0);
-                }
+                for (int p = 0; p < 3; ++p) lv[p] = *(const bf16x8_t*)(g.rank.la[p] + at);
+#pragma unroll
+                for (int both = 2; both >= 0; --both)        // products down to 2^-16 of the largest, small ones first; the rest is 2^-24
+#pragma unroll
+                    for (int p = 0; p <= both; ++p)
+#pragma unroll
+                        for (int i = 0; i < TI; ++i) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pv[i][p], lv[both - p], acc[i][j], 0, 0, 0);
             }
         }
     } else {
@@ -543,7 +546,7 @@ struct CodedPlan {
     int64_t np, nc;
     int r_pad;
     bool x_direct, xc_direct, wc_direct;
-    size_t w_hi, w_lo, wc, x_hi, x_lo, xc, p_hi, p_lo, la_hi, la_lo, lb, total;
+    size_t w_hi, w_lo, wc, x_hi, x_lo, xc, p[3], la[3], lb, total;
 };
 
 void coded_plan(int64_t m, int64_t n, int64_t rows, int r, bool bf16, bool x_direct, bool wc_direct, CodedPlan* p) {
@@ -561,11 +564,9 @@ void coded_plan(int64_t m, int64_t n, int64_t rows, int r, bool bf16, bool x_dir
     p->x_hi = take(x_direct ? 0 : (size_t)rows * p->np * 2);
     p->x_lo = take(x_direct || bf16 ? 0 : (size_t)rows * p->np * 2);
     p->xc = take(p->xc_direct ? 0 : (size_t)rows * p->nc);
-    p->p_hi = take((size_t)rows * p->r_pad * 2);
-    p->p_lo = take((size_t)rows * p->r_pad * 2);
-    p->la_hi = take((size_t)m * p->r_pad * 2);
-    p->la_lo = take((size_t)m * p->r_pad * 2);
-    p->lb = take((size_t)p->np * p->r_pad * 4);
+    for (size_t& at : p->p) at = take((size_t)rows * p->r_pad * 2);
+    for (size_t& at : p->la) at = take((size_t)m * p->r_pad * 2);
+    p->lb = take((size_t)p->np * p->r_pad * 6);
     p->total = off;
 }
 
@@ -650,9 +651,13 @@ extern "C" int aser_layer_output_error(aser_ctx* ctx, const float* W, int64_t m,
         add(xa, xpitch, ws + cp.w_lo, np * 2);
         if (!bf16) add(xl, np * 2, ws + cp.w_hi, np * 2);
         if (r > 0) {
-            uint16_t *ph = (uint16_t*)(ws + cp.p_hi), *plo = (uint16_t*)(ws + cp.p_lo), *lah = (uint16_t*)(ws + cp.la_hi), *lal = (uint16_t*)(ws + cp.la_lo);
-            ASER_TRY(aser_rank_down(ctx, xc, cp.nc, nullptr, rows, n, L_B, (int)r, true, ph, plo, L_A, m, lah, lal, ws + cp.lb));
-            g.p_hi = ph; g.p_lo = plo; g.la_hi = lah; g.la_lo = lal; g.r_pad = cp.r_pad;
+            for (int i = 0; i < 3; ++i) {
+                g.rank.p[i] = (uint16_t*)(ws + cp.p[i]);
+                g.rank.la[i] = (uint16_t*)(ws + cp.la[i]);
+            }
+            g.rank.lb = ws + cp.lb;
+            g.r_pad = cp.r_pad;
+            ASER_TRY(aser_rank_down(ctx, xc, cp.nc, nullptr, rows, n, L_B, (int)r, 3, L_A, m, g.rank));
         }
         ASER_TRY(pick_eval<true>(ctx, g));
     }

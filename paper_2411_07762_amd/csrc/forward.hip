@@ -537,9 +537,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     }
 }
 
-// Both factors as bf16 planes: hi = bf16(x), with SPLIT also lo = bf16(x - hi).  L_A (m x r) as [m][r_pad] with zeros behind r; L_B (r x n) in the
+// Both factors as NP bf16 planes, each what the ones before it leave of the value, rounded.  L_A (m x r) as [m][r_pad] with zeros behind r; L_B (r x n) in the
 // order in which rank_down_kernel feeds it to the MFMA: [32 channels][plane][32 rows][8-channel slice][lane][8 channels], lane 32 h + i holding
-// channels 16 h + 8 slice .. + 7 of row i, zeros past r and n.
+// channels 16 h + 8 slice .. + 7 of row i, zeros past r and n; three planes: one block of 32 rows after the other.
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t bf16_pair(float a, float b) {         // rounded to nearest even
@@ -547,10 +547,9 @@ __device__ __forceinline__ uint32_t bf16_pair(float a, float b) {         // rou
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
 }
 
-template <bool SPLIT>
+template <int NP>
 __global__ __launch_bounds__(256) void split_factors_kernel(const float* __restrict__ L_A, const float* __restrict__ L_B, int64_t m,
-                                                            int64_t n, int r, int r_pad, uint16_t* __restrict__ la_hi,
-                                                            uint16_t* __restrict__ la_lo, uint4* __restrict__ lb, int64_t lb_blocks) {
+                                                            int64_t n, int r, int r_pad, AserRankPlanes out, int64_t lb_blocks) {
     if ((int64_t)blockIdx.x < lb_blocks) {                   // eight rows, 256 channels
         const int64_t k = ((int64_t)blockIdx.x % ((n + 255) / 256)) * 256 + 8 * (threadIdx.x & 31);
         const int row = (int)((int64_t)blockIdx.x / ((n + 255) / 256)) * 8 + (threadIdx.x >> 5);
@@ -564,31 +563,40 @@ __global__ __launch_bounds__(256) void split_factors_kernel(const float* __restr
 #pragma unroll
             for (int e = 0; e < 8; ++e) f[e] = k + e < n ? src[k + e] : 0.f;
         }
-        uint32_t hi[4], lo[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const float f0 = row < r ? f[2 * q] : 0.f, f1 = row < r ? f[2 * q + 1] : 0.f;
-            hi[q] = bf16_pair(f0, f1);
-            lo[q] = bf16_pair(f0 - __uint_as_float(hi[q] << 16), f1 - __uint_as_float(hi[q] & 0xFFFF0000u));
-        }
         const int c8 = (int)(k & 31) >> 3, h = c8 >> 1, sl = c8 & 1, blocks = r_pad / 32;
-        const int64_t at = ((k / 32 * (SPLIT ? 2 : 1) * blocks + row / 32) * 2 + sl) * 64 + 32 * h + (row & 31);
-        lb[at] = make_uint4(hi[0], hi[1], hi[2], hi[3]);
-        if (SPLIT) lb[at + blocks * 128] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+        const int together = NP == 3 ? 1 : blocks;           // blocks of rows that a workgroup takes
+        const int64_t step = NP == 3 ? row / 32 * ((n + 31) / 32) + k / 32 : k / 32;
+        uint4* lb = (uint4*)out.lb + ((step * NP * together + (NP == 3 ? 0 : row / 32)) * 2 + sl) * 64 + 32 * h + (row & 31);
+#pragma unroll
+        for (int p = 0; p < NP; ++p, lb += together * 128) {
+            uint32_t pair[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                float &f0 = f[2 * q], &f1 = f[2 * q + 1];
+                pair[q] = row < r ? bf16_pair(f0, f1) : 0u;
+                f0 -= __uint_as_float(pair[q] << 16);
+                f1 -= __uint_as_float(pair[q] & 0xFFFF0000u);
+            }
+            *lb = make_uint4(pair[0], pair[1], pair[2], pair[3]);
+        }
         return;
     }
     const int64_t total = m * r_pad;
     for (int64_t t = ((int64_t)blockIdx.x - lb_blocks) * 256 + threadIdx.x; t < total; t += ((int64_t)gridDim.x - lb_blocks) * 256) {
         const int64_t i = t / r_pad;
         const int j = (int)(t % r_pad);
-        const float x = j < r ? L_A[i * r + j] : 0.f;
-        const uint32_t hi = bf16_rne(x);
-        la_hi[t] = (uint16_t)hi;
-        if (SPLIT) la_lo[t] = (uint16_t)bf16_rne(x - __uint_as_float(hi << 16));
+        float x = j < r ? L_A[i * r + j] : 0.f;
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            const uint32_t part = bf16_rne(x);
+            out.la[p][t] = (uint16_t)part;
+            x -= __uint_as_float(part << 16);
+        }
     }
 }
 
-// P[t][k] = s_t sum_i xq[t][i] L_B[k][i] as bf16 planes, for 32 tokens per workgroup and all r_pad columns (RB blocks of 32).  NW
+// P[t][k] = s_t sum_i xq[t][i] L_B[k][i] as bf16 planes, for 32 tokens per workgroup and all r_pad columns (RB blocks of 32; of three planes the
+// registers hold one block, and the samples that they are made of are small, so the others are workgroups of their own).  NW
 // wavefronts share the contraction, and all operands come straight from memory into MFMA registers: a lane's 16 channels of its token
 // (the codes become bf16 there, exactly, |q| <= 128), and the planes of L_B in the order split_factors_kernel left them, a kilobyte per load.
 // kAhead steps of loads are in flight, nothing waits for another wavefront, and the NW sums meet in LDS once, in a fixed order.
@@ -600,14 +608,14 @@ __global__ __launch_bounds__(256) void split_factors_kernel(const float* __restr
 struct DownArgs {
     const int8_t* xq; int64_t ldq; const float* xs; int64_t rows;   // codes: rows of ldq bytes, 16-byte aligned, finite from channel n to the next multiple of 32
     int64_t n; const uint4* lb; int r_pad;
-    uint16_t* p_hi; uint16_t* p_lo;
+    uint16_t* p[3];
 };
 
-template <int RB, bool SPLIT, int NW>
+template <int RB, int NP, int NW>
 __global__ __launch_bounds__(64 * NW) void rank_down_kernel(DownArgs g) {
     extern __shared__ __align__(16) float part[];
     __shared__ float sx[32];
-    constexpr int NP = SPLIT ? 2 : 1, kAhead = 2;
+    constexpr int kAhead = 2;
     const int tid = threadIdx.x, lane = tid & 63, li = lane & 31, h = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t T0 = (int64_t)blockIdx.x * 32;
@@ -620,7 +628,7 @@ __global__ __launch_bounds__(64 * NW) void rank_down_kernel(DownArgs g) {
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[j][e] = 0.f;
     uint4 ar[kAhead], br[kAhead][NP][RB][2];
-    const uint4* const bl = g.lb + lane;
+    const uint4* const bl = g.lb + lane + (int64_t)blockIdx.y * steps * (NP * RB * 128);
     auto load = [&](int s, int buf) {                        // steps past the end read the last one and are not used
         const int sc = s < steps ? s : steps - 1;
         ar[buf] = *(const uint4*)(ap + 32 * sc);
@@ -684,10 +692,14 @@ __global__ __launch_bounds__(64 * NW) void rank_down_kernel(DownArgs g) {
         const int o = tid + 64 * NW * u, e = (o >> 6) & 15, j = o >> 10;
         const int64_t row = T0 + 8 * (e >> 2) + 4 * h + (e & 3);
         if (row < g.rows) {
-            const int64_t at = row * g.r_pad + 32 * j + li;
-            const uint32_t hi = bf16_rne(v[u]);
-            g.p_hi[at] = (uint16_t)hi;
-            if (SPLIT) g.p_lo[at] = (uint16_t)bf16_rne(v[u] - __uint_as_float(hi << 16));
+            const int64_t at = row * g.r_pad + 32 * (int)(blockIdx.y * RB + j) + li;
+            float x = v[u];
+#pragma unroll
+            for (int p = 0; p < NP; ++p) {
+                const uint32_t part = bf16_rne(x);
+                g.p[p][at] = (uint16_t)part;
+                x -= __uint_as_float(part << 16);
+            }
         }
     }
 }
@@ -739,38 +751,43 @@ int launch_dma(aser_ctx* ctx, const FwdArgs& g) {
     return aser_check_launch(ctx, "compensated_forward");
 }
 
-template <int RB, bool SPLIT>
+template <int RB, int NP>
 int launch_down(aser_ctx* ctx, const DownArgs& g) {
     static bool done[16] = {false};
     constexpr int NW = RB <= 2 ? 16 : 8, lds = NW * RB * 16 * 64 * 4;
-    auto kern = rank_down_kernel<RB, SPLIT, NW>;
+    auto kern = rank_down_kernel<RB, NP, NW>;
     ASER_TRY(set_lds_once(ctx, kern, lds, done));
-    hipLaunchKernelGGL(kern, dim3((unsigned)ceil_div64(g.rows, 32)), dim3(64 * NW), lds, ctx->stream, g);
+    hipLaunchKernelGGL(kern, dim3((unsigned)ceil_div64(g.rows, 32), (unsigned)(g.r_pad / (32 * RB))), dim3(64 * NW), lds, ctx->stream, g);
     return aser_check_launch(ctx, "rank_down");
 }
 
-template <bool SPLIT>
-int rank_down(aser_ctx* ctx, const DownArgs& g, const float* L_A, int64_t m, const float* L_B, int r, uint16_t* la_hi, uint16_t* la_lo, uint4* lb) {
+template <int NP>
+int rank_down(aser_ctx* ctx, const DownArgs& g, const float* L_A, int64_t m, const float* L_B, int r, const AserRankPlanes& out) {
     const int64_t lb_blocks = ceil_div64(g.n, 256) * (g.r_pad / 8), la_blocks = ceil_div64(m * g.r_pad, 256 * 4);
-    hipLaunchKernelGGL(split_factors_kernel<SPLIT>, dim3((unsigned)(lb_blocks + (la_blocks < 2048 ? la_blocks : 2048))), dim3(256), 0, ctx->stream,
-                       L_A, L_B, m, g.n, r, g.r_pad, la_hi, la_lo, lb, lb_blocks);
+    hipLaunchKernelGGL(split_factors_kernel<NP>, dim3((unsigned)(lb_blocks + (la_blocks < 2048 ? la_blocks : 2048))), dim3(256), 0, ctx->stream,
+                       L_A, L_B, m, g.n, r, g.r_pad, out, lb_blocks);
     ASER_TRY(aser_check_launch(ctx, "split_factors"));
-    switch (g.r_pad / 32) {
-        case 1: return launch_down<1, SPLIT>(ctx, g);
-        case 2: return launch_down<2, SPLIT>(ctx, g);
-        case 3: return launch_down<3, SPLIT>(ctx, g);
-        default: return launch_down<4, SPLIT>(ctx, g);
+    if constexpr (NP == 3) return launch_down<1, NP>(ctx, g);
+    else switch (g.r_pad / 32) {
+        case 1: return launch_down<1, NP>(ctx, g);
+        case 2: return launch_down<2, NP>(ctx, g);
+        case 3: return launch_down<3, NP>(ctx, g);
+        default: return launch_down<4, NP>(ctx, g);
     }
 }
 
 }  // namespace
 
 int aser_rank_down(aser_ctx* ctx, const int8_t* xq, int64_t ldq, const float* xs, int64_t rows, int64_t n, const float* L_B, int r,
-                   bool split, uint16_t* p_hi, uint16_t* p_lo, const float* L_A, int64_t m, uint16_t* la_hi, uint16_t* la_lo, void* lb) {
+                   int parts, const float* L_A, int64_t m, const AserRankPlanes& out) {
     DownArgs g{};
-    g.xq = xq; g.ldq = ldq; g.xs = xs; g.rows = rows; g.n = n; g.lb = (const uint4*)lb; g.r_pad = (r + 31) / 32 * 32;
-    g.p_hi = p_hi; g.p_lo = p_lo;
-    return split ? rank_down<true>(ctx, g, L_A, m, L_B, r, la_hi, la_lo, (uint4*)lb) : rank_down<false>(ctx, g, L_A, m, L_B, r, la_hi, la_lo, (uint4*)lb);
+    g.xq = xq; g.ldq = ldq; g.xs = xs; g.rows = rows; g.n = n; g.lb = (const uint4*)out.lb; g.r_pad = (r + 31) / 32 * 32;
+    for (int i = 0; i < parts; ++i) g.p[i] = out.p[i];
+    switch (parts) {
+        case 1: return rank_down<1>(ctx, g, L_A, m, L_B, r, out);
+        case 2: return rank_down<2>(ctx, g, L_A, m, L_B, r, out);
+        default: return rank_down<3>(ctx, g, L_A, m, L_B, r, out);
+    }
 }
 
 extern "C" size_t aser_forward_workspace_bytes(int64_t rows, int64_t n, int64_t m, int32_t r) {
@@ -819,7 +836,8 @@ extern "C" int aser_compensated_forward(aser_ctx* ctx, const int8_t* x_codes, co
         uint16_t* lah = (uint16_t*)(ws + pl.off_lah);
         uint16_t* lal = (uint16_t*)(ws + pl.off_lal);
         const int rp = pl.r_pad;
-        ASER_TRY(aser_rank_down(ctx, x_codes, n, x_scales, rows, n, L_B, r, split, p_hi, p_lo, L_A, m, lah, lal, ws + pl.off_lb));
+        const AserRankPlanes planes{{p_hi, p_lo, nullptr}, {lah, lal, nullptr}, ws + pl.off_lb};
+        ASER_TRY(aser_rank_down(ctx, x_codes, n, x_scales, rows, n, L_B, r, split ? 2 : 1, L_A, m, planes));
         g.p_hi = p_hi; g.p_lo = p_lo; g.la_hi = lah; g.la_lo = lal; g.r_pad = rp;
     }
     if (rows >= kDmaTM && m >= kDmaTN) {                 // the 256 x 256 tiles without a register stage

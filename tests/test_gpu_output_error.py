@@ -200,3 +200,36 @@ def test_second_output_from_codes(m, n, rows, r, bits, x_dtype, act_bits):
     want, ynorm = float(torch.linalg.norm(Y - x @ Wt.T)), float(torch.linalg.norm(Y))
     assert abs(ref - ynorm) <= 1e-5 * ynorm              # 2^-17 per product
     assert abs(err - want) <= 1e-5 * (want + ynorm)
+
+
+@pytest.mark.parametrize("m,n,rows,r", [(1024, 1024, 500, 64), (300, 4128, 129, 128), (1700, 224, 1800, 33), (96, 512, 64, 16)])
+def test_second_output_of_factors_that_cancel(m, n, rows, r):
+    """L_A L_B is 1e-4 of its terms, and these are 100 sqrt(r) times the output.  The factors, P and their products keep 24 bits, so an output is off by
+    2^-24 of the terms in P and again in L_A P, and by 2^-17 of itself in the planes of W, all with random signs: of the norm over rows m
+    outputs that is the same over sqrt(rows m), four standard deviations below, and the square of it."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(m + n)
+    W = torch.randn((m, n), generator=g, device=DEV) * 0.05
+    X = torch.randn((rows, n), generator=g, device=DEV).to(torch.bfloat16)
+    q = torch.randint(-127, 128, (m, n), generator=g, device=DEV, dtype=torch.int8)
+    scales = (0.5 + torch.rand(m, generator=g, device=DEV)) * 0.1 / 127
+    L_A = torch.randn((m, r), generator=g, device=DEV) * 100.0
+    L_B = torch.randn((r, n), generator=g, device=DEV) * 0.05
+    h = r // 2
+    L_A[:, h:2 * h] = -L_A[:, :h]
+    L_B[h:2 * h] = L_B[:h] + 1e-6 * torch.randn((h, n), generator=g, device=DEV)
+    if r % 2:
+        L_A[:, r - 1] *= 1e-4
+    ctx = new_ctx()
+    ctx.ensure_workspace(aser.aser_output_error_workspace_bytes(m, n, rows, r))
+    st, err, ref = aser.aser_layer_output_error(ctx, W, X, None, q, aser.ASER_CODES_INT8, scales, L_A, L_B, r, 8)
+    ctx.check(st)
+    xq, xs = orc.quantize_act_rtn(X.float().cpu().numpy(), np.ones(n, np.float32), 8)
+    x = torch.from_numpy(xq.astype(np.float64) * xs.astype(np.float64)[:, None])
+    Y = X.double().cpu() @ W.double().cpu().T
+    D = Y - x @ (q.double() * scales.double()[:, None]).cpu().T - (x @ L_B.double().cpu().T) @ L_A.double().cpu().T
+    want = float(torch.linalg.norm(D))
+    each = 2 * 2.0 ** -24 * 100 * np.sqrt(r) + 2.0 ** -17
+    bound = 4 * each / np.sqrt(rows * m) + each ** 2
+    say("output error of factors that cancel %s: %.2e of %.2e" % ((m, n, rows, r), abs(err - want) / want, bound))
+    assert abs(err - want) <= bound * want
