@@ -61,6 +61,10 @@ __device__ __forceinline__ float wave_sum(float v) {
 // been formed from u.  Every thread forms v, w and u in its own rows and columns, and the wavefronts' sums in a third copy: the
 // helpers below keep the copies the same to the last bit.
 //
+// A u and |u|^2 are of the size of the squared matrix, so its largest entry is brought to [2^54, 2^55) first: nothing in the loop then reaches 2^127, and a
+// column counts down to 2^-106 of the largest entry, whatever the scale of the input.  A power of two, taken out of d and e again: no result
+// that was in range before is another.
+//
 // What bounds it: latency, one wavefront per SIMD; a step is 1.2 us.  b = 128: 230 -> 147 us (before: the mat-vec with the normalised reflector behind the
 // square root and two divisions, the update in a pass of its own, two barriers).
 __device__ __forceinline__ int cyc(int i) { return (i & 15) * 8 + (i >> 4); }
@@ -74,6 +78,7 @@ __global__ __launch_bounds__(256) void tridiag_kernel(const float* __restrict__ 
     // Everything the loop produces stays in LDS until the end: a global store inside the loop
     // would have to drain before each barrier.
     extern __shared__ __align__(16) float sm[];
+    __shared__ float largest[4];
     float (*sums)[kB] = (float (*)[kB])sm;              // [2][kB] A u (cyclic order), double-buffered
     float (*cols)[kB] = (float (*)[kB])(sm + 2 * kB);   // [2][kB] column k + 1 (cyclic order)
     float* td = sm + 4 * kB;
@@ -95,6 +100,14 @@ __global__ __launch_bounds__(256) void tridiag_kernel(const float* __restrict__ 
             const float lo = Mb[rc * b + qc], up = Mb[qc * b + rc];
             a[s][c] = (r < b && q < b) ? 0.5f * (lo + up) : 0.f;
         }
+    float most = 0.f;
+#pragma unroll
+    for (int s = 0; s < 8; ++s)
+#pragma unroll
+        for (int c = 0; c < 8; ++c) most = fmaxf(most, fabsf(a[s][c]));
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) most = fmaxf(most, __shfl_xor(most, o, 64));
+    if (lane == 0) largest[tid >> 6] = most;
     if (tid == 0) *cluster_flag = 0;
     if (tid < kB) { td[tid] = 0.f; te[tid] = 0.f; tt[tid] = 0.f; }
     if (tj == 0) {
@@ -102,6 +115,11 @@ __global__ __launch_bounds__(256) void tridiag_kernel(const float* __restrict__ 
         *(float4*)(cols[1] + 8 * ti + 4) = make_float4(a[4][0], a[5][0], a[6][0], a[7][0]);
     }
     __syncthreads();
+    const int up = 55 - __builtin_amdgcn_frexp_expf(fmaxf(fmaxf(largest[0], largest[1]), fmaxf(largest[2], largest[3])));
+#pragma unroll
+    for (int s = 0; s < 8; ++s)
+#pragma unroll
+        for (int c = 0; c < 8; ++c) a[s][c] = __builtin_amdgcn_ldexpf(a[s][c], up);
     auto eight = [](const float* at, float (&x)[8]) {
         const float4 p = *(const float4*)at, q = *(const float4*)(at + 4);
         x[0] = p.x; x[1] = p.y; x[2] = p.z; x[3] = p.w; x[4] = q.x; x[5] = q.y; x[6] = q.z; x[7] = q.w;
@@ -112,7 +130,12 @@ __global__ __launch_bounds__(256) void tridiag_kernel(const float* __restrict__ 
     float ur[8], uc[8], vr[8], vc[8], wr[8], wc[8];     // u, v, w in this thread's rows and columns; u is 0 up to row k
     eight(cols[1] + 8 * ti, ur);
     eight(cols[1] + 8 * tj, uc);
-    float u0 = i0 > 0 ? cols[1][lane] : 0.f, u1 = cols[1][lane + 64];      // u at the positions lane and lane + 64
+    float u0 = i0 > 0 ? __builtin_amdgcn_ldexpf(cols[1][lane], up) : 0.f, u1 = __builtin_amdgcn_ldexpf(cols[1][lane + 64], up);      // u at the positions lane and lane + 64
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+        ur[s] = __builtin_amdgcn_ldexpf(ur[s], up);
+        uc[s] = __builtin_amdgcn_ldexpf(uc[s], up);
+    }
     if (ti == 0) ur[0] = 0.f;
     if (tj == 0) uc[0] = 0.f;
 #pragma unroll
@@ -211,7 +234,7 @@ __global__ __launch_bounds__(256) void tridiag_kernel(const float* __restrict__ 
     }
     __syncthreads();
     for (int t = tid; t < (b - 2) * kB; t += 256) refl[t] = rs[t];
-    for (int t = tid; t < 3 * kB; t += 256) tri[t] = td[t];
+    for (int t = tid; t < 3 * kB; t += 256) tri[t] = t < 2 * kB ? __builtin_amdgcn_ldexpf(td[t], -up) : td[t];
 }
 
 __device__ __forceinline__ double wave_max_d(double v) {

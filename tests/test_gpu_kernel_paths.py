@@ -524,3 +524,27 @@ def test_ritz_pairs_of_dense_matrices(b, scale):
     assert np.max(np.abs(got - want)) <= 4 * eps * want[0]
     assert np.max(np.abs(sym @ v - v * want)) <= 4 * eps * want[0]
     assert np.max(np.abs(v.T @ v - np.eye(b))) <= 8 * eps
+
+
+@pytest.mark.parametrize("diagonal,coupling", [(3e21, 3e17), (1e30, 1e26), (1.0, 1e-4), (1e-22, 1e-26), (1e-30, 1e-34)])
+def test_ritz_pairs_of_nearly_diagonal_matrices_at_any_scale(diagonal, coupling):
+    """Entries whose products with a column do not fit fp32, or vanish in it, although entries and eigenvalues do.  Tolerances as above."""
+    b = 96
+    rng = np.random.default_rng(96)
+    A = rng.standard_normal((b, b))
+    M = (diagonal * np.eye(b) + coupling * (A + A.T)).astype(np.float32)
+    sym = 0.5 * (M.astype(np.float64) + M.T)
+    want = np.linalg.eigvalsh(sym)[::-1]
+    lib, ctx = aser.load_library(), new_ctx()
+    Md = torch.from_numpy(M).to(DEV)
+    lam, V, refl, tri = (torch.full(shape, 7.0, dtype=torch.float32, device=DEV) for shape in ((b,), (b, b), (b, 128), (384,)))
+    flag = torch.ones(1, dtype=torch.int32, device=DEV)
+    p = lambda t: ctypes.c_void_p(t.data_ptr())
+    ctx.check(lib["_Z16aser_tridiag_eigP8aser_ctxPKfiPfS3_S3_S3_Pii"](ctx.handle, p(Md), b, p(lam), p(V), p(refl), p(tri), p(flag), b))
+    torch.cuda.synchronize()
+    got, v = lam.double().cpu().numpy(), V.double().cpu().numpy()
+    eps = 2.0 ** -24 * np.sqrt(b)
+    assert int(flag.item()) == 0
+    assert np.max(np.abs(got - want)) <= 4 * eps * want[0]
+    assert np.max(np.abs(sym @ v - v * want)) <= 4 * eps * want[0]
+    assert np.max(np.abs(v.T @ v - np.eye(b))) <= 8 * eps
