@@ -46,8 +46,10 @@ __device__ __forceinline__ bf16x8_t operand(const uint32_t (&p)[4]) { return __b
 
 // The products of eight channels of L_B (b) and of the codes (x) added to acc, v_mfma_f32_16x16x32_bf16.  Codes are bf16 values.  The mode that rounds the factors
 // takes b to the nearest bf16; otherwise b is the sum of three bf16 values, each the upper half of what the ones before it leave of its 24 bits, so
-// the products are exact either way.  (Of an infinity nothing is left.)
-__device__ __forceinline__ f4v down_step(bool split, float4 b0, float4 b1, uint2 x, f4v acc) {
+// the products are exact either way.  (Of an infinity nothing is left.)  The second is multiplied by 2^7 and the third by 2^15, to the size of the first at
+// most, and summed apart: as they are, the bits of a b below 1e-34 would fall under the smallest bf16 value.
+struct DownSums { f4v hi = {0.f, 0.f, 0.f, 0.f}, mid = hi, lo = hi; };
+__device__ __forceinline__ void down_step(bool split, float4 b0, float4 b1, uint2 x, DownSums& acc) {
     const float b[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
     uint32_t c[4], hi[4];
 #pragma unroll
@@ -60,7 +62,8 @@ __device__ __forceinline__ f4v down_step(bool split, float4 b0, float4 b1, uint2
     if (!split) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) hi[q] = nearest_pair(b[2 * q], b[2 * q + 1]);
-        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(operand(hi), codes, acc, 0, 0, 0);
+        acc.hi = __builtin_amdgcn_mfma_f32_16x16x32_bf16(operand(hi), codes, acc.hi, 0, 0, 0);
+        return;
     }
     uint32_t mid[4], lo[4];
 #pragma unroll
@@ -68,16 +71,16 @@ __device__ __forceinline__ f4v down_step(bool split, float4 b0, float4 b1, uint2
         float m[2], l[2];
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
-            m[u] = __builtin_isinf(b[2 * q + u]) ? 0.f : below_upper_half(b[2 * q + u]);
-            l[u] = below_upper_half(m[u]);
+            m[u] = __builtin_isinf(b[2 * q + u]) ? 0.f : below_upper_half(b[2 * q + u]) * 0x1p7f;
+            l[u] = below_upper_half(m[u]) * 0x1p8f;
         }
         hi[q] = upper_halves(b[2 * q], b[2 * q + 1]);
         mid[q] = upper_halves(m[0], m[1]);
         lo[q] = upper_halves(l[0], l[1]);
     }
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(operand(lo), codes, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(operand(mid), codes, acc, 0, 0, 0);
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(operand(hi), codes, acc, 0, 0, 0);
+    acc.lo = __builtin_amdgcn_mfma_f32_16x16x32_bf16(operand(lo), codes, acc.lo, 0, 0, 0);
+    acc.mid = __builtin_amdgcn_mfma_f32_16x16x32_bf16(operand(mid), codes, acc.mid, 0, 0, 0);
+    acc.hi = __builtin_amdgcn_mfma_f32_16x16x32_bf16(operand(hi), codes, acc.hi, 0, 0, 0);
 }
 
 // part[chunk][t][k] = sum over 2048 channels of xq[t][i] L_B[k][i] (without s_t), k up to rp (r rounded up to 16; what stands
@@ -87,7 +90,7 @@ __device__ __forceinline__ f4v down_step(bool split, float4 b0, float4 b1, uint2
 // operands), because a load behind a branch is waited for where the branches meet.
 // What bounds it: latency, of the launch, of two rounds of loads and of the chain of sums.  One K = 4 fp32 instruction per four channels, each value
 // converted and masked by itself, was 3200 cycles per wavefront (us for the whole call; 4096 x 4096 int4, r = 64, 16 tokens: 16.6 -> 14.8; split
-// factors, 8192 x 8192, 16 tokens: 27.1 -> 25.5, 3.3e-7 -> 2.3e-7 off the fp64 result; 4096 x 11008 int8, 19 tokens: 29.6 -> 28.1; one token: no faster, no slower).
+// factors, 8192 x 8192, 16 tokens: 27.1 -> 25.6, 3.3e-7 -> 1.8e-7 off the fp64 result; 4096 x 11008 int8, 19 tokens: 29.6 -> 28.1; one token: no faster, no slower).
 template <int NW>
 __device__ __forceinline__ void few_down(const FewArgs& g, int task, float (*red)[16][17]) {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -99,7 +102,7 @@ __device__ __forceinline__ void few_down(const FewArgs& g, int task, float (*red
     constexpr int NS = 4;                                 // steps of 32 channels in flight; eight are up to 0.8 us slower
 #pragma unroll 1
     for (int w = wave * (kDownSums / NW); w < (wave + 1) * (kDownSums / NW); ++w) {
-        f4v acc = {0.f, 0.f, 0.f, 0.f};
+        DownSums acc;
 #pragma unroll 1
         for (int h = 0; h < kDownSum; h += 32 * NS) {
             const int64_t c0 = (int64_t)chunk * kDownChunk + w * kDownSum + h;
@@ -121,10 +124,10 @@ __device__ __forceinline__ void few_down(const FewArgs& g, int task, float (*red
             }
 #pragma unroll
             for (int s = 0; s < NS; ++s)
-                if (c0 + 32 * s < g.n) acc = down_step(g.split, b[s][0], b[s][1], x[s], acc);
+                if (c0 + 32 * s < g.n) down_step(g.split, b[s][0], b[s][1], x[s], acc);
         }
 #pragma unroll
-        for (int e = 0; e < 4; ++e) red[w][li][4 * lg + e] = acc[e];     // (token li, row 4 lg + e)
+        for (int e = 0; e < 4; ++e) red[w][li][4 * lg + e] = fmaf(acc.lo[e], 0x1p-15f, fmaf(acc.mid[e], 0x1p-7f, acc.hi[e]));     // (token li, row 4 lg + e)
     }
     __syncthreads();
     if (tid < 256) {

@@ -219,3 +219,25 @@ def test_activation_quantizer_at_the_ends_of_a_token(n, dt, scaled, offset):
     torch.cuda.synchronize()
     ref_q, ref_s = orc.quantize_act_rtn(X.float().cpu().numpy(), md.cpu().numpy() if scaled else np.ones(n, np.float32), 8)
     assert np.array_equal(q[:5].cpu().numpy(), ref_q) and np.array_equal(s.cpu().numpy(), ref_s.reshape(-1).astype(np.float32)) and bool((q[5] == 99).all())
+
+
+@pytest.mark.parametrize("rows,n,m", [(1, 4096, 300), (16, 2080, 8205), (33, 1056, 500)])
+@pytest.mark.parametrize("scale", [1e-36, 1e-30, 1e30])
+def test_rank_branch_of_a_few_tokens_keeps_its_bits_at_any_scale(rows, n, m, scale):
+    """Factors of an uneven size, whose three parts would leave the range of bf16 at one end or the other: the bound of the split factors above."""
+    r = 40
+    g = torch.Generator(device=DEV)
+    g.manual_seed(rows + n)
+    xq = torch.randint(-127, 128, (rows, n), generator=g, device=DEV, dtype=torch.int8)
+    xs = 0.01 + torch.rand(rows, generator=g, device=DEV) * 0.1
+    wq = torch.zeros((m, n), device=DEV, dtype=torch.int8)
+    ws = torch.ones(m, device=DEV)
+    la = torch.randn((m, r), generator=g, device=DEV) / scale
+    lb = torch.randn((r, n), generator=g, device=DEV) * scale
+    ctx = new_ctx()
+    ctx.ensure_workspace(aser.aser_forward_workspace_bytes(rows, n, m, r))
+    Y = torch.empty((rows, m), device=DEV)
+    ctx.check(aser.aser_compensated_forward(ctx, xq, xs, wq, aser.ASER_CODES_INT8, ws, la, lb, r, True, Y))
+    torch.cuda.synchronize()
+    ref = ((xq.double() * xs.double()[:, None]).cpu() @ lb.double().cpu().T) @ la.double().cpu().T
+    assert float(torch.linalg.norm(Y.double().cpu() - ref) / torch.linalg.norm(ref)) <= 2.0 ** -20
