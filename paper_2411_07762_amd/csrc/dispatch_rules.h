@@ -2,24 +2,32 @@
 #pragma once
 #include <stdint.h>
 
-// True where the kernels for a few tokens (forward_few.hip) are faster than the tiles of the prefill kernels.
-// Up to 64 tokens they are.  Up to one workgroup per two compute units of their widest tile (128 tokens x 64 outputs) too, but for
+// True where the kernels for a few tokens (forward_few.hip) are faster than the tiles of the prefill kernels, or, with split factors, as long as they are not
+// much slower: P keeps all bits of the factors there (2e-7 of the rank-r branch instead of 5e-6).
+// Up to 64 tokens they are faster.  Up to one workgroup per two compute units of their widest tile (128 tokens x 64 outputs) too, but for
 // many tokens with a wide rank-r branch: its first product reads L_B once per 16 tokens.  Up to one workgroup per compute unit they
-// re-use less per load than the 256 x 256 tiles, so there the contraction has to be long against the fixed part and against the
-// rank-r branch, less so where the prefill kernels split the factors into two planes.  At most 2048 tokens, so that the partial sums
-// fit the workspace (see aser_compensated_forward).
-// Measured (us, prefill kernels -> few tokens; channels, outputs, tokens; int4).  r = 0: 4096, 4096, 300: 49 -> 32; 4096, 1024, 2048:
-// 45 -> 35; 1024, 4096, 512: 20.3 -> 19.5; 512, 3072, 512: 15.8 -> 17.3 (prefill); 256, 4096, 384: 20.9 -> 15.2; 4096, 14336, 256: 47 -> 68 (prefill).
-// r = 64, plain: 4096, 4096, 512: 86 -> 73; 2048, 8192, 256: 55 -> 52; 1024, 1024, 2048: 40 -> 48 and 4096, 1024, 2048: 86 -> 94 (prefill);
-// split: 1024, 4096, 512: 48 -> 45; 4096, 1024, 2048: 101 -> 93; 512, 768, 1536: 38 -> 44 (prefill).  r = 128, plain: 8192, 256, 2048: 168 -> 166;
-// 8192, 512, 2048: 168 -> 184 (prefill); split: 1024, 8192, 256: 68 -> 61; 4096, 1024, 2048: 136 -> 149 (prefill).
+// re-use less per load than the 256 x 256 tiles, so there the contraction has to be long against the fixed part and, the more so the larger
+// the rank, against the rank-r branch.  At most 2048 tokens, so that the partial sums fit the workspace (see aser_compensated_forward).
+// Measured (us, prefill kernels -> few tokens; channels, outputs, tokens; int4).  r = 0: 4096, 4096, 300: 49 -> 33; 4096, 1024, 2048:
+// 44 -> 35; 1024, 4096, 512: 19.7 -> 18.9; 512, 3072, 512: 15.5 -> 17.3 (prefill); 256, 4096, 384: 20.6 -> 15.2; 4096, 14336, 256: 47 -> 68 (prefill).
+// Plain, r = 64: 4096, 4096, 384: 72 -> 66; 8192, 4096, 512: 109 -> 97; 11008, 1024, 1536: 140 -> 152 and 2048, 8192, 256: 44 -> 48 (prefill);
+// 4096, 512, 2048: 65 -> 58.
+// r = 128: 4096, 14336, 128: 90 -> 91; 8192, 4096, 512: 123 -> 138 (prefill); 8192, 1024, 1024: 122 -> 112; 8192, 512, 1536: 123 -> 133 (prefill);
+// 4096, 256, 2048: 75 -> 76; 8192, 256, 2048: 121 -> 136 (prefill).  r = 16: 2048, 4096, 512: 40 -> 46 (prefill), 2048, 14336, 65: 42 -> 35, 4096, 1024, 2048: 61 -> 64 (prefill).
+// Split, the furthest on the wrong side: r = 64: 4096, 1024, 2048: 75 -> 85; r = 128: 4096, 1024, 1536: 94 -> 120; r = 16: 1024, 1024, 2048: 32 -> 40.
+// Over 540 plain calls (65 to 2048 tokens, 512 to 11008 channels, 256 to 14336 outputs, r 16 to 128) the rule loses at
+// most 3 %, but 12 to 16 % at 65 tokens of 1024 channels and 6 % at 384 tokens of 2048.
 static inline bool aser_forward_few_pays(int64_t rows, int64_t n, int64_t m, int r, bool split) {
-    const int64_t tiles = ((rows + 127) / 128) * ((m + 63) / 64), rank_work = (int64_t)((r + 15) / 16 * 16) * rows;
+    const int64_t tiles = ((rows + 127) / 128) * ((m + 63) / 64), rank = (r + 15) / 16 * 16, rank_work = rank * rows;
     if (rows > 2048 || tiles > 256) return false;
     if (rows <= 64) return true;
-    if (tiles <= 128) return split || tiles <= 64 || rank_work <= 128 * 1536;
+    if (tiles <= 128) {
+        if (split || rank_work <= 128 * 1280) return true;
+        return tiles <= 64 ? rank_work <= 128 * 1536 || n <= 6144 : rank_work <= 128 * 1536 && n <= 1024;
+    }
     if (r == 0) return n >= 1024 || (rows > 256 && rows < 1024 && ((rows - 1) & 255) < 128);   // or the last 256 tokens' tile would be half empty
-    return split ? n >= 1024 && rank_work <= 64 * n && rank_work <= 128 * 1536 : n >= 2048 && rank_work <= 9 * n;
+    if (split) return n >= 1024 && rank_work <= 64 * n && rank_work <= 128 * 1536;
+    return rows <= 96 ? n >= 2048 : n >= (rows <= 512 ? 3072 : 5120) && rank * rank_work <= 512 * n;    // so few leave a quarter of the prefill kernels' tiles of 128 and more empty
 }
 
 // True where f rounds of an arg-max in one workgroup select the outlier channels faster than the comparison of all pairs of

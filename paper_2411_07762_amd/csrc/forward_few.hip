@@ -366,15 +366,15 @@ template <bool W4, int OT, int TG, int NW>
 int launch_few(aser_ctx* ctx, FewArgs g) {
     g.tiles = (int)ceil_div64(g.m, 16 * OT);
     const int64_t work = g.tiles * ceil_div64(g.rows, 16 * TG);
-    // P beside the codes: where the output tiles are small workgroups, one or two per compute unit, and long enough to hide P.  Measured with P on the fp32 MFMA
-    // instruction, which made it up to 2 us longer in front and 1 us longer beside the codes (us, P in front
-    // -> beside; channels, outputs, one token / 16 tokens, r = 64, int4): 2048, 8224: 13.5 -> 12.4 / 18.1 -> 17.0; 4096, 10240: 17.6 -> 14.9 / 23.8 -> 19.9; 4096,
-    // 14336: 18.3 -> 15.7 / 24.2 -> 20.3; 14336, 8224: 32.1 -> 29.3 / 46.4 -> 40.0.  Not at 1024, 14336: 10.9 -> 11.7 / 13.5 -> 13.8, nor with eight wavefronts per
-    // tile (8192, 8192: 17.8 -> 19.2 / 27.0 -> 28.4; 4096, 4096: 12.0 -> 13.8 / 16.5 -> 19.1) or 64 outputs (8192, 16384: 25.5 -> 24.9 / 33.9 -> 34.1).
-    // int8, 4096, 14336: 23.5 -> 20.3 / 30.9 -> 25.2; r = 1: 21.7 -> 17.9 / 26.2 -> 23.3; with weights that rotate through 0.7 GB (r = 64): int4 20.9 -> 18.6 /
-    // 27.5 -> 22.5, int8 25.8 -> 21.8 / 33.6 -> 27.5.  Over 504 such calls (r 1 to 128) at worst 37.7 -> 38.5 (int4, 11008, 16384, r = 128, one token, rotating).
+    // P beside the codes: where the output tiles are small workgroups, one or two per compute unit, and long enough to hide P.  Measured (us, P in front
+    // -> beside; channels, outputs, one token / 16 tokens, r = 64, int4): 1536, 14336: 12.9 -> 11.0 / 14.8 -> 13.7; 2048, 8224: 13.6 -> 12.1 / 16.2 -> 14.9; 4096, 10240:
+    // 17.0 -> 14.8 / 21.3 -> 19.0; 4096, 14336: 17.0 -> 14.7 / 21.5 -> 19.1; 14336, 8224: 31.3 -> 28.1 / 43.7 -> 38.8; int8, 4096, 14336: 22.4 -> 19.0 / 28.1 -> 24.4;
+    // r = 1: 12.6 -> 11.4 / 16.7 -> 15.4.  Either way at 1024 channels (14336 outputs: 11.0 -> 9.8 / 12.7 -> 13.6, split factors 11.4 -> 11.5 / 14.0 -> 13.3) and not at 512
+    // (split factors 10.5 -> 11.0 / 11.4 -> 12.4).  From 1536 channels on beside was the faster one in 160 such calls (r 1 to 128).  Not with eight wavefronts
+    // per tile or 64 outputs: with P on the fp32 MFMA instruction, up to 2 us longer in front and 1 us beside, 8192, 8192: 17.8 -> 19.2 / 27.0 -> 28.4; 4096, 4096:
+    // 12.0 -> 13.8 / 16.5 -> 19.1; 8192, 16384: 25.5 -> 24.9 / 33.9 -> 34.1.
     if constexpr (TG == 1 && NW == 4 && OT == 2) {
-        if (g.r > 0 && g.n >= 2048) {
+        if (g.r > 0 && g.n >= 1536) {
             hipLaunchKernelGGL((few_main_kernel<W4, OT, TG, NW, true>), dim3((unsigned)(g.down + work)), dim3(64 * NW), 0, ctx->stream, g);
             ASER_TRY(aser_check_launch(ctx, "compensated_forward_few"));
             hipLaunchKernelGGL(few_rank_kernel, dim3((unsigned)ceil_div64(g.m, 64), (unsigned)ceil_div64(g.rows, 16)), dim3(256), 0, ctx->stream, g);

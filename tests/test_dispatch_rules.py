@@ -24,20 +24,27 @@ def rule(tmp_path_factory):
 
 # tokens, channels, outputs, rank, split factors; us of the prefill kernels, us of the kernels for a few tokens (int4 codes)
 FORWARD = [
-    (1, 4096, 4096, 64, 0, 83.2, 13.9), (16, 1024, 14336, 64, 0, 36.5, 14.6), (64, 1024, 14336, 64, 0, 39.9, 27.0), (2048, 256, 768, 0, 0, 13.6, 15.9),
-    (512, 512, 3072, 0, 0, 15.8, 17.3), (384, 256, 4096, 0, 0, 20.9, 15.2), (300, 4096, 4096, 0, 0, 49.0, 32.2), (2048, 4096, 1024, 0, 0, 45.3, 35.1),
-    (512, 1024, 4096, 0, 0, 20.3, 19.5), (128, 512, 14336, 16, 0, 29.4, 38.8), (2048, 1024, 1024, 16, 0, 36.5, 43.0), (2048, 4096, 1024, 16, 0, 79.8, 70.4),
-    (2048, 1024, 512, 64, 0, 39.2, 32.0), (2048, 1024, 1024, 64, 0, 39.7, 48.4), (1024, 1024, 2048, 64, 0, 40.3, 44.8), (512, 1024, 4096, 64, 0, 40.5, 45.0),
-    (256, 1024, 8192, 64, 0, 40.4, 43.9), (256, 2048, 8192, 64, 0, 55.3, 52.2), (2048, 4096, 1024, 64, 0, 85.8, 94.2), (512, 4096, 4096, 64, 0, 86.4, 72.6),
-    (256, 4096, 8192, 64, 0, 86.0, 72.1), (2048, 1024, 1024, 64, 1, 46.8, 48.5), (512, 1024, 4096, 64, 1, 47.5, 44.8), (2048, 4096, 1024, 64, 1, 100.6, 93.4),
-    (1536, 512, 768, 64, 1, 37.8, 43.6), (256, 1024, 8192, 128, 1, 68.1, 61.2), (2048, 4096, 1024, 128, 1, 135.8, 148.6), (2048, 4096, 256, 128, 1, 137.1, 91.8),
-    (2048, 8192, 512, 128, 0, 168.3, 183.8), (2048, 8192, 256, 128, 0, 168.1, 165.6), (768, 4096, 2048, 128, 0, 102.1, 113.7), (128, 4096, 14336, 128, 0, 115.5, 98.4),
+    (1, 4096, 4096, 64, 0, 62.7, 11.9), (16, 1024, 14336, 64, 0, 29.6, 12.5), (64, 1024, 14336, 64, 0, 33.0, 24.2), (2048, 256, 768, 0, 0, 13.4, 15.7),
+    (512, 512, 3072, 0, 0, 15.5, 17.3), (384, 256, 4096, 0, 0, 20.6, 15.2), (300, 4096, 4096, 0, 0, 48.7, 32.6), (2048, 4096, 1024, 0, 0, 44.3, 34.6),
+    (512, 1024, 4096, 0, 0, 19.7, 18.9), (128, 512, 14336, 16, 0, 25.4, 35.6), (2048, 1024, 1024, 16, 0, 29.9, 39.5), (2048, 4096, 1024, 16, 0, 61.2, 63.6),
+    (2048, 1024, 512, 64, 0, 32.7, 28.0), (2048, 1024, 1024, 64, 0, 33.7, 43.8), (1024, 1024, 2048, 64, 0, 33.5, 40.9), (512, 1024, 4096, 64, 0, 33.7, 40.8),
+    (256, 1024, 8192, 64, 0, 34.0, 40.8), (256, 2048, 8192, 64, 0, 44.1, 47.7), (2048, 4096, 1024, 64, 0, 66.4, 82.9), (512, 4096, 4096, 64, 0, 67.0, 66.1),
+    (256, 4096, 8192, 64, 0, 67.2, 66.5), (2048, 1024, 1024, 64, 1, 39.0, 44.2), (512, 1024, 4096, 64, 1, 39.9, 41.1), (2048, 4096, 1024, 64, 1, 75.4, 84.6),
+    (1536, 512, 768, 64, 1, 34.2, 39.6), (256, 1024, 8192, 128, 1, 53.5, 58.6), (2048, 4096, 1024, 128, 1, 94.4, 131.4),
+    (2048, 4096, 256, 128, 1, 93.9, 76.5), (2048, 8192, 512, 128, 0, 121.2, 153.0), (2048, 8192, 256, 128, 0, 121.1, 135.5),
+    (768, 4096, 2048, 128, 0, 76.9, 101.9), (128, 4096, 14336, 128, 0, 90.0, 90.6), (384, 4096, 4096, 64, 0, 71.9, 66.2),
+    (512, 8192, 4096, 64, 0, 108.8, 97.3), (1536, 11008, 1024, 64, 0, 139.9, 151.9), (2048, 4096, 512, 64, 0, 64.7, 57.5),
+    (512, 8192, 4096, 128, 0, 123.3, 137.6), (1024, 8192, 1024, 128, 0, 121.5, 112.0), (1536, 8192, 512, 128, 0, 122.9, 132.6),
+    (1536, 512, 512, 128, 0, 33.6, 32.7), (2048, 11008, 256, 128, 0, 155.5, 190.8), (2048, 4096, 256, 128, 0, 74.7, 75.8),
+    (512, 2048, 4096, 16, 0, 39.5, 45.7), (65, 2048, 14336, 16, 0, 41.6, 34.9), (65, 2048, 14336, 128, 0, 54.2, 47.2), (128, 2048, 14336, 16, 0, 42.9, 46.5),
+    (1536, 4096, 1024, 128, 1, 94.0, 120.2), (2048, 1024, 1024, 16, 1, 32.2, 39.9),
 ]
 
 
 def test_kernels_for_a_few_tokens_are_taken_where_they_are_faster(rule):
     got = rule("forward", 'printf("%d", (int)aser_forward_few_pays(a[0], a[1], a[2], (int)a[3], a[4] != 0));', [q[:5] for q in FORWARD])
-    wrong = [q for q, (few,) in zip(FORWARD, got) if (q[5] > 1.03 * q[6] and not few) or (q[6] > 1.03 * q[5] and few)]
+    # with split factors the kernels for a few tokens are 25 times as exact (csrc/forward_few.hip), and kept up to 30 % behind the others
+    wrong = [q for q, (few,) in zip(FORWARD, got) if (q[5] > 1.03 * q[6] and not few) or (q[6] > (1.3 if q[4] else 1.03) * q[5] and few)]
     assert not wrong
 
 
