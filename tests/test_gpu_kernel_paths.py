@@ -145,7 +145,8 @@ def known_matrix(m, n, sg, seed):
 
 @pytest.mark.parametrize("k", [1040, 1500, 2300, 3100, 4100])
 def test_eigenvalues_of_wide_full_matrices(k):
-    """Deferred updates of two and four pairs, and above 4096 the Sturm counts in pieces, on full matrices.  The bar is the rounding
+    """The matrix on the chip from all its sides on, and above 4096 the Sturm counts in pieces, on full matrices (the chain of launches with
+    its deferred updates: test_gpu_tridiag_resident.py).  The bar is the rounding
     of the matrix to fp32 (Weyl: at most its Frobenius norm) and the backward error of the fp64 chain as below."""
     sg = np.sort(np.random.default_rng(k).uniform(0.5, 2.0, k))[::-1]
     A = known_matrix(k, k, sg, k).astype(np.float32)
@@ -159,7 +160,7 @@ def test_eigenvalues_of_wide_full_matrices(k):
 
 @pytest.mark.parametrize("m,n", [(1300, 1200), (2100, 2300), (1100, 3000)])
 def test_dense_solver_keeps_its_reflectors_over_deferred_updates(m, n):
-    """A rank above the subspace iteration's, S = I: T is a known matrix with a gap behind the r-th singular value, so the product of
+    """A rank above the subspace iteration's, S = I (the reflectors of the launches: test_gpu_tridiag_resident.py): T is a known matrix with a gap behind the r-th singular value, so the product of
     the factors is its truncation.  The bars of the other reconstruction tests (error 1e-4, product 1e-3)."""
     r = 130
     rng = np.random.default_rng([m, n])
