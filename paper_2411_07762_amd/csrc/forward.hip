@@ -28,6 +28,7 @@
 #include <type_traits>
 
 #include "aser_internal.h"
+#include "bf16_pair.h"
 #include "dispatch_rules.h"
 
 namespace {
@@ -40,9 +41,6 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 
 constexpr int kFwdTM = 128, kFwdTN = 256, kFwdBK = 64;
 
-__device__ __forceinline__ uint32_t bf16_hi_pair(float a, float b) {       // truncation-free: callers pass bf16-exact values or accept RNE below
-    return (__float_as_uint(a) >> 16) | (__float_as_uint(b) & 0xFFFF0000u);
-}
 __device__ __forceinline__ uint32_t bf16_rne(float x) {
     const uint32_t u = __float_as_uint(x);
     return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
@@ -540,13 +538,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 // Both factors as NP bf16 planes, each what the ones before it leave of the value, rounded.  L_A (m x r) as [m][r_pad] with zeros behind r; L_B (r x n) in the
 // order in which rank_down_kernel feeds it to the MFMA: [32 channels][plane][32 rows][8-channel slice][lane][8 channels], lane 32 h + i holding
 // channels 16 h + 8 slice .. + 7 of row i, zeros past r and n; three planes: one block of 32 rows after the other.
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-typedef float f32x2_t __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ uint32_t bf16_pair(float a, float b) {         // rounded to nearest even
-    const f32x2_t v = {a, b};
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
-}
-
 template <int NP>
 __global__ __launch_bounds__(256) void split_factors_kernel(const float* __restrict__ L_A, const float* __restrict__ L_B, int64_t m,
                                                             int64_t n, int r, int r_pad, AserRankPlanes out, int64_t lb_blocks) {
@@ -650,7 +641,7 @@ __global__ __launch_bounds__(64 * NW) void rank_down_kernel(DownArgs g) {
             for (int q = 0; q < 4; ++q) {                    // a byte is converted by one instruction, and the upper halves of two floats are a pair
                 const uint32_t w = w2[q >> 1];
                 const int b0 = 16 * (q & 1);
-                pk[q] = __builtin_amdgcn_perm(__float_as_uint((float)(int)(int8_t)(w >> (b0 + 8))), __float_as_uint((float)(int)(int8_t)(w >> b0)), 0x07060302u);
+                pk[q] = upper_halves((float)(int)(int8_t)(w >> b0), (float)(int)(int8_t)(w >> (b0 + 8)));
             }
             const bf16x8_t a = __builtin_bit_cast(bf16x8_t, make_uint4(pk[0], pk[1], pk[2], pk[3]));
 #pragma unroll

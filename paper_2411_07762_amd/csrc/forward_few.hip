@@ -13,6 +13,7 @@
 // all on MFMA instructions, operands straight from global memory.  In the mode that rounds the factors
 // to bf16 the same three roundings are made (L_B, P, L_A) as in the prefill kernels; the other one is exact in every product with L_B and keeps fp32 behind it.
 #include "aser_internal.h"
+#include "bf16_pair.h"
 
 namespace {
 
@@ -33,14 +34,7 @@ struct FewArgs {
 };
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-typedef float f2v __attribute__((ext_vector_type(2)));
 
-__device__ __forceinline__ uint32_t nearest_pair(float a, float b) {
-    const f2v v = {a, b};
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
-}
-__device__ __forceinline__ uint32_t upper_halves(float a, float b) { return __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u); }
 __device__ __forceinline__ float below_upper_half(float x) { return x - __uint_as_float(__float_as_uint(x) & 0xFFFF0000u); }
 __device__ __forceinline__ bf16x8_t operand(const uint32_t (&p)[4]) { return __builtin_bit_cast(bf16x8_t, make_uint4(p[0], p[1], p[2], p[3])); }
 
@@ -61,7 +55,7 @@ __device__ __forceinline__ void down_step(bool split, float4 b0, float4 b1, uint
     const bf16x8_t codes = operand(c);
     if (!split) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) hi[q] = nearest_pair(b[2 * q], b[2 * q + 1]);
+        for (int q = 0; q < 4; ++q) hi[q] = bf16_pair(b[2 * q], b[2 * q + 1]);
         acc.hi = __builtin_amdgcn_mfma_f32_16x16x32_bf16(operand(hi), codes, acc.hi, 0, 0, 0);
         return;
     }
@@ -196,8 +190,8 @@ __device__ __forceinline__ f4v few_rank(const FewArgs& g, f4v y, int64_t O, int 
                 uint32_t ab[4], pb[4];
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    ab[q] = nearest_pair(a[2 * q], a[2 * q + 1]);
-                    pb[q] = nearest_pair(p[2 * q], p[2 * q + 1]);
+                    ab[q] = bf16_pair(a[2 * q], a[2 * q + 1]);
+                    pb[q] = bf16_pair(p[2 * q], p[2 * q + 1]);
                 }
                 y = __builtin_amdgcn_mfma_f32_16x16x32_bf16(operand(ab), operand(pb), y, 0, 0, 0);
             }

@@ -2,10 +2,9 @@
 // the products of a K step, the epilogues, and the two bodies that put them together.
 #pragma once
 #include "aser_internal.h"
+#include "bf16_pair.h"
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-typedef float f32x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
 namespace {
@@ -21,12 +20,6 @@ template <> struct InTraits<GEMM_IN_F32X6> { static constexpr int BK = 32, NP = 
 // the transposing stores (8 consecutive rows per lane) and the MFMA operand reads (32
 // consecutive rows per half wave) hit distinct bank groups.
 __device__ __forceinline__ int swz(int mn) { return (mn ^ ((mn >> 3) & 7)) ^ (((mn >> 6) & 1) << 3); }
-
-__device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
-    f32x2_t v = {a, b};
-    bf16x2_t h = __builtin_convertvector(v, bf16x2_t);
-    return __builtin_bit_cast(uint32_t, h);
-}
 
 // Eight 16-byte rows of one operand block in flight between global memory and LDS.
 struct Staged {
@@ -152,14 +145,14 @@ struct Fetch {
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const float a = x[4 * (2 * q) + c], b = x[4 * (2 * q + 1) + c];
-                    const uint32_t h = pack_bf16x2(a, b);
+                    const uint32_t h = bf16_pair(a, b);
                     const float ah = __uint_as_float(h << 16), bh = __uint_as_float(h & 0xFFFF0000u);
                     hi[q] = h;
                     const float ar = a - ah, br = b - bh;           // exact: the remainder has at most 16 significant bits
-                    lo[q] = pack_bf16x2(ar, br);
+                    lo[q] = bf16_pair(ar, br);
                     if (IN == GEMM_IN_F32X6) {
                         const float am = __uint_as_float(lo[q] << 16), bm = __uint_as_float(lo[q] & 0xFFFF0000u);
-                        lo2[q] = pack_bf16x2(ar - am, br - bm);     // third term: x = hi + mid + lo to 24 bits
+                        lo2[q] = bf16_pair(ar - am, br - bm);     // third term: x = hi + mid + lo to 24 bits
                     }
                 }
                 const int pos = kb * BMN + swz(cg * 4 + c);
@@ -522,7 +515,7 @@ struct FetchRows {
                 float u = x[4 * (2 * q) + c], v = x[4 * (2 * q + 1) + c];
 #pragma unroll
                 for (int n = 0; n < NP; ++n) {            // the next term is what the ones before it leave (exact differences)
-                    t[n][q] = pack_bf16x2(u, v);
+                    t[n][q] = bf16_pair(u, v);
                     u -= __uint_as_float(t[n][q] << 16);
                     v -= __uint_as_float(t[n][q] & 0xFFFF0000u);
                 }
