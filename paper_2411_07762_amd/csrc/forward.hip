@@ -537,8 +537,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 
 // Both factors as NP bf16 planes, each what the ones before it leave of the value, rounded.  L_A (m x r) as [m][r_pad] with zeros behind r; L_B (r x n) in the
 // order in which rank_down_kernel feeds it to the MFMA: [32 channels][plane][32 rows][8-channel slice][lane][8 channels], lane 32 h + i holding
-// channels 16 h + 8 slice .. + 7 of row i, zeros past r and n; three planes: one block of 32 rows after the other.
-template <int NP>
+// channels 16 h + 8 slice .. + 7 of row i, zeros past r and n; three planes: one block of 32 rows after the other.  PLAIN: as planes [r_pad][n] (n % 32 == 0).
+template <int NP, bool PLAIN>
 __global__ __launch_bounds__(256) void split_factors_kernel(const float* __restrict__ L_A, const float* __restrict__ L_B, int64_t m,
                                                             int64_t n, int r, int r_pad, AserRankPlanes out, int64_t lb_blocks) {
     if ((int64_t)blockIdx.x < lb_blocks) {                   // eight rows, 256 channels
@@ -557,9 +557,9 @@ __global__ __launch_bounds__(256) void split_factors_kernel(const float* __restr
         const int c8 = (int)(k & 31) >> 3, h = c8 >> 1, sl = c8 & 1, blocks = r_pad / 32;
         const int together = NP == 3 ? 1 : blocks;           // blocks of rows that a workgroup takes
         const int64_t step = NP == 3 ? row / 32 * ((n + 31) / 32) + k / 32 : k / 32;
-        uint4* lb = (uint4*)out.lb + ((step * NP * together + (NP == 3 ? 0 : row / 32)) * 2 + sl) * 64 + 32 * h + (row & 31);
+        uint4* lb = (uint4*)out.lb + (PLAIN ? (row * n + k) / 8 : ((step * NP * together + (NP == 3 ? 0 : row / 32)) * 2 + sl) * 64 + 32 * h + (row & 31));
 #pragma unroll
-        for (int p = 0; p < NP; ++p, lb += together * 128) {
+        for (int p = 0; p < NP; ++p, lb += PLAIN ? r_pad * n / 8 : (int64_t)together * 128) {
             uint32_t pair[4];
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
@@ -592,8 +592,8 @@ __global__ __launch_bounds__(256) void split_factors_kernel(const float* __restr
 // (the codes become bf16 there, exactly, |q| <= 128), and the planes of L_B in the order split_factors_kernel left them, a kilobyte per load.
 // kAhead steps of loads are in flight, nothing waits for another wavefront, and the NW sums meet in LDS once, in a fixed order.
 // What bounds it: instructions (a step of 32 channels is 24 conversions, 2 RB NP MFMAs and as much again for loads and addresses),
-// hence four wavefronts per SIMD where the sums fit the LDS (r <= 64), which are 15 us at 8192 tokens of 4096 channels, r = 64, against 18
-// with two; 36 with 128 tokens per workgroup (64 compute units) and both operands staged through LDS.  32768 tokens: 55 -> 49 us.  Reading L_B
+// hence four wavefronts per SIMD where the sums fit the LDS (r <= 64), which are 14 us (17 between the quantizer and the product of the codes) at 8192 tokens of 4096
+// channels, r = 64; 32 with 128 tokens per workgroup (64 compute units) and both operands staged through LDS.  Reading L_B
 // itself costs more than the launch it saves: 50 us with a lane's 64 bytes of a row each, 29 in whole lines (a row is 16 KB, so the rows of
 // a load share a channel of the L2).
 struct DownArgs {
@@ -695,6 +695,182 @@ __global__ __launch_bounds__(64 * NW) void rank_down_kernel(DownArgs g) {
     }
 }
 
+// The same for many tokens, 128 per workgroup, with both operands staged through LDS; L_B in planes [r_pad][n].  Beyond two rounds of workgroups
+// of the kernel above what counts is what goes through the L2: there all of L_B once per 32 tokens, and a token's line of codes in pieces
+// of 32 bytes; here L_B once per 128 tokens and 64 bytes of a token side by side.
+// Per step 64 channels: the code tile as in the main kernel (no reordering), the L_B tiles as 16-byte chunks of 8 bf16 with an XOR swizzle.  A step is a
+// chain of waits (tile stores, barrier, fragment reads, conversion, MFMA), so the workgroup has eight wavefronts, two per SIMD: wavefront w takes
+// tokens 32 (w % 4) .. + 32 and the 16-channel slices 2 (w / 4), 2 (w / 4) + 1 of every step; the two halves of the sum meet in LDS at the end.  The loads
+// of step s + 3 are issued in step s (three register stages, the step loop unrolled by three so that they are
+// named at compile time), the LDS tiles are double buffered, one barrier per step.
+// Whole calls of 4096 channels (us, 32 tokens per workgroup -> 128): 256 outputs, r = 64, 16385 tokens 86 -> 81, 17000: 94 -> 84, 32768: 109 -> 88; r = 128, split, 32768:
+// 182 -> 148; 4096 outputs, r = 64, 32768: 634 -> 617.  At 16384 tokens, two whole rounds, the other one is as fast or faster.
+constexpr int kDownThreads = 512, kDownRows = 16384;
+
+template <int RB, bool SPLIT>
+__global__ __launch_bounds__(kDownThreads) void rank_down_staged_kernel(DownArgs g) {
+    const int64_t rows = g.rows, n = g.n;
+    const uint16_t *const lb_hi = (const uint16_t*)g.lb, *const lb_lo = lb_hi + (int64_t)g.r_pad * n;
+    extern __shared__ __align__(16) char smem[];
+    constexpr int RP = 32 * RB;                              // r_pad
+    constexpr int A_BYTES = 128 * 64, B_BYTES = RP * 128;    // 64 bf16 per row
+    constexpr int BUF = A_BYTES + 2 * B_BYTES;
+    constexpr int BCHUNKS = RP * 8;                          // 16-byte chunks of a B plane per step
+    constexpr int BCH = (BCHUNKS + kDownThreads - 1) / kDownThreads;
+    constexpr int kAhead = 3;
+    static_assert(2 * BUF >= 4 * RB * 16 * 64 * 4 + 128 * 4, "the partial sums of wavefronts 4 .. 7 and the token scales must fit the tile buffers");
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tb = wave & 3, sh = wave >> 2;
+    const int64_t T0 = (int64_t)blockIdx.x * 128;
+    // staging role: 16-byte chunk tid % 4 of code row tid / 4
+    const int srow = tid >> 2, sc = tid & 3;
+    const bool srow_ok = T0 + srow < rows;
+    const char* ap = (const char*)g.xq + (srow_ok ? T0 + srow : 0) * g.ldq + 16 * sc;
+    const uint32_t amask = srow_ok ? 0xFFFFFFFFu : 0u;       // rows past the end read row 0 and drop it
+    f32x16_t acc[RB];
+#pragma unroll
+    for (int j = 0; j < RB; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[j][e] = 0.f;
+    uint4 ar[kAhead], bh[kAhead][BCH], bl[kAhead][BCH];
+    // STEADY: all 64 channels of the step exist; the loads are unconditional (clamped addresses, the value
+    // dropped afterwards), so that the loop body is straight-line code and the compiler's counting of the
+    // loads in flight stays exact
+    auto fetch = [&](auto utag, int64_t s, auto steady_tag) {
+        constexpr int U = decltype(utag)::value;
+        constexpr bool STEADY = decltype(steady_tag)::value;
+        const int64_t k0 = s * 64;
+        if (STEADY) {
+            const uint4 v = *(const uint4*)(ap + k0);
+            ar[U] = make_uint4(v.x & amask, v.y & amask, v.z & amask, v.w & amask);
+        } else {
+            ar[U] = make_uint4(0u, 0u, 0u, 0u);
+            if (srow_ok && k0 + 16 * sc < n) ar[U] = *(const uint4*)(ap + k0);      // n % 32 == 0: a chunk of 16 is whole or absent
+        }
+#pragma unroll
+        for (int u = 0; u < BCH; ++u) {
+            const int q = tid + kDownThreads * u, c = q & 7;
+            const int row = (q >> 3) < RP ? (q >> 3) : RP - 1;
+            const int64_t k = k0 + 8 * c;
+            if (STEADY) {
+                bh[U][u] = *(const uint4*)(lb_hi + (int64_t)row * n + k);
+                if (SPLIT) bl[U][u] = *(const uint4*)(lb_lo + (int64_t)row * n + k);
+            } else {
+                bh[U][u] = make_uint4(0u, 0u, 0u, 0u);
+                bl[U][u] = make_uint4(0u, 0u, 0u, 0u);
+                if (k < n) {
+                    bh[U][u] = *(const uint4*)(lb_hi + (int64_t)row * n + k);
+                    if (SPLIT) bl[U][u] = *(const uint4*)(lb_lo + (int64_t)row * n + k);
+                }
+            }
+        }
+    };
+    const int64_t steps = (n + 63) / 64;
+    const int64_t full_steps = n / 64;
+    fetch(std::integral_constant<int, 0>{}, 0, std::false_type{});
+    if (steps > 1) fetch(std::integral_constant<int, 1>{}, 1, std::false_type{});
+    if (steps > 2) fetch(std::integral_constant<int, 2>{}, 2, std::false_type{});
+    auto step = [&](auto utag, int64_t s, auto steady_tag) {
+        constexpr int U = decltype(utag)::value;
+        constexpr bool STEADY = decltype(steady_tag)::value;
+        // buffer s % 2 was last read in step s - 2; every wavefront has left that step's reads behind it when
+        // the first one passes the barrier of step s - 1
+        char* sA = smem + (int)(s & 1) * BUF;
+        char* sBh = sA + A_BYTES;
+        char* sBl = sBh + B_BYTES;
+        *(uint4*)(sA + chunk_off(srow, sc)) = ar[U];
+#pragma unroll
+        for (int u = 0; u < BCH; ++u) {
+            const int q = tid + kDownThreads * u, row = q >> 3, c = q & 7;
+            const int off = row * 128 + ((c ^ ((row >> 1) & 7)) << 4);
+            if (q < BCHUNKS) {
+                *(uint4*)(sBh + off) = bh[U][u];
+                if (SPLIT) *(uint4*)(sBl + off) = bl[U][u];
+            }
+        }
+        if (STEADY) fetch(utag, s + kAhead, std::true_type{});
+        else if (s + kAhead < steps) fetch(utag, s + kAhead, std::false_type{});
+        __syncthreads();
+        const int arow = tb * 32 + (lane & 31);
+#pragma unroll
+        for (int ss = 0; ss < 2; ++ss) {                     // 16 channels per slice; this lane's 8: bytes [16 sl + 8 g, +8) of its row
+            const int sl = 2 * sh + ss;
+            const int g8 = lane >> 5;
+            const uint2 raw = *(const uint2*)(sA + chunk_off(arow, sl) + 8 * g8);
+            const uint32_t w2[2] = {raw.x, raw.y};
+            uint32_t pk[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const uint32_t w = w2[q >> 1];
+                const int b0 = 16 * (q & 1);
+                pk[q] = upper_halves((float)(int)(int8_t)(w >> b0), (float)(int)(int8_t)(w >> (b0 + 8)));
+            }
+            const bf16x8_t a = __builtin_bit_cast(bf16x8_t, make_uint4(pk[0], pk[1], pk[2], pk[3]));
+            const int c = 2 * sl + g8;
+#pragma unroll
+            for (int j = 0; j < RB; ++j) {
+                const int brow = 32 * j + (lane & 31);
+                const int off = brow * 128 + ((c ^ ((brow >> 1) & 7)) << 4);
+                const bf16x8_t bhv = *(const bf16x8_t*)(sBh + off);
+                if (SPLIT) {
+                    const bf16x8_t blv = *(const bf16x8_t*)(sBl + off);
+                    acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, blv, acc[j], 0, 0, 0);
+                }
+                acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, bhv, acc[j], 0, 0, 0);
+            }
+        }
+    };
+    int64_t s = 0;
+    // Twelve steps per trip first: the compiler lets all loads in flight land at a loop's head, and that wait
+    // should come once in twelve steps, not once in three.  The steps fetched, up to s + 14, are whole.
+    for (; s + 5 * kAhead <= full_steps; s += 4 * kAhead) {
+#pragma unroll
+        for (int rep = 0; rep < 4; ++rep) {
+            step(std::integral_constant<int, 0>{}, s + 3 * rep, std::true_type{});
+            step(std::integral_constant<int, 1>{}, s + 3 * rep + 1, std::true_type{});
+            step(std::integral_constant<int, 2>{}, s + 3 * rep + 2, std::true_type{});
+        }
+    }
+    for (; s + 2 * kAhead <= full_steps; s += kAhead) {     // the steps these three fetch, up to s + 5, are whole
+        step(std::integral_constant<int, 0>{}, s, std::true_type{});
+        step(std::integral_constant<int, 1>{}, s + 1, std::true_type{});
+        step(std::integral_constant<int, 2>{}, s + 2, std::true_type{});
+    }
+    for (; s < steps; s += kAhead) {
+        step(std::integral_constant<int, 0>{}, s, std::false_type{});
+        if (s + 1 < steps) step(std::integral_constant<int, 1>{}, s + 1, std::false_type{});
+        if (s + 2 < steps) step(std::integral_constant<int, 2>{}, s + 2, std::false_type{});
+    }
+    // the sums over slices 2, 3 (wavefronts 4 .. 7) join those over slices 0, 1 of the same tokens; the tile's
+    // token scales go through LDS as well (one load per token instead of one per accumulator register)
+    __syncthreads();
+    float* part = (float*)smem;
+    float* xsl = part + 4 * RB * 16 * 64;
+    if (tid < 128) xsl[tid] = (T0 + tid < rows) ? (g.xs ? g.xs[T0 + tid] : 1.f) : 0.f;
+    if (sh == 1) {
+#pragma unroll
+        for (int j = 0; j < RB; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) part[((tb * RB + j) * 16 + e) * 64 + lane] = acc[j][e];
+    }
+    __syncthreads();
+    if (sh == 1) return;
+#pragma unroll
+    for (int j = 0; j < RB; ++j) {
+        const int col = 32 * j + (lane & 31);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            const int64_t row = T0 + tb * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
+            if (row < rows) {
+                const float pv = (acc[j][e] + part[((tb * RB + j) * 16 + e) * 64 + lane]) * xsl[row - T0];
+                const uint32_t h = bf16_rne(pv);
+                g.p[0][row * RP + col] = (uint16_t)h;
+                if (SPLIT) g.p[1][row * RP + col] = (uint16_t)bf16_rne(pv - __uint_as_float(h << 16));
+            }
+        }
+    }
+}
+
 struct FwdPlan {
     int r_pad;
     size_t off_p, off_lah, off_lal, off_lb, total;
@@ -752,12 +928,34 @@ int launch_down(aser_ctx* ctx, const DownArgs& g) {
     return aser_check_launch(ctx, "rank_down");
 }
 
+template <int RB, bool SPLIT>
+int launch_down_staged(aser_ctx* ctx, const DownArgs& g) {
+    static bool done[16] = {false};
+    constexpr int lds = 2 * (128 * 64 + 2 * (32 * RB * 128));   // two buffers of (codes, L_B hi, L_B lo)
+    auto kern = rank_down_staged_kernel<RB, SPLIT>;
+    ASER_TRY(set_lds_once(ctx, kern, lds, done));
+    hipLaunchKernelGGL(kern, dim3((unsigned)ceil_div64(g.rows, 128)), dim3(kDownThreads), lds, ctx->stream, g);
+    return aser_check_launch(ctx, "rank_down_staged");
+}
+
 template <int NP>
 int rank_down(aser_ctx* ctx, const DownArgs& g, const float* L_A, int64_t m, const float* L_B, int r, const AserRankPlanes& out) {
     const int64_t lb_blocks = ceil_div64(g.n, 256) * (g.r_pad / 8), la_blocks = ceil_div64(m * g.r_pad, 256 * 4);
-    hipLaunchKernelGGL(split_factors_kernel<NP>, dim3((unsigned)(lb_blocks + (la_blocks < 2048 ? la_blocks : 2048))), dim3(256), 0, ctx->stream,
+    const bool staged = NP < 3 && g.rows > kDownRows && g.n % 32 == 0;
+    auto split = split_factors_kernel<NP, false>;
+    if constexpr (NP < 3)
+        if (staged) split = split_factors_kernel<NP, true>;
+    hipLaunchKernelGGL(split, dim3((unsigned)(lb_blocks + (la_blocks < 2048 ? la_blocks : 2048))), dim3(256), 0, ctx->stream,
                        L_A, L_B, m, g.n, r, g.r_pad, out, lb_blocks);
     ASER_TRY(aser_check_launch(ctx, "split_factors"));
+    if constexpr (NP < 3) {
+        if (staged) switch (g.r_pad / 32) {
+            case 1: return launch_down_staged<1, NP == 2>(ctx, g);
+            case 2: return launch_down_staged<2, NP == 2>(ctx, g);
+            case 3: return launch_down_staged<3, NP == 2>(ctx, g);
+            default: return launch_down_staged<4, NP == 2>(ctx, g);
+        }
+    }
     if constexpr (NP == 3) return launch_down<1, NP>(ctx, g);
     else switch (g.r_pad / 32) {
         case 1: return launch_down<1, NP>(ctx, g);
