@@ -842,7 +842,7 @@ extern "C" int aser_quantize_act_rtn(aser_ctx* ctx, const void* X, int x_dtype, 
         else if (groups <= 512 * 3) ASER_ACT_LAUNCH(B, 3, 512, W);\
         else if (groups <= 512 * 4) ASER_ACT_LAUNCH(B, 4, 512, W);\
         else if (groups <= 1024 * 3) ASER_ACT_LAUNCH(B, 3, 1024, W);\
-        else ASER_ACT_LAUNCH(B, 4, 1024, W);                      \
+        else ASER_ACT_LAUNCH(B, 4, 1024, false);                  \
     } while (0)
     const int esz = (x_dtype == ASER_DTYPE_BF16) ? 2 : 4;
     const bool wave_ok = n <= 4096 && (n & 15) == 0 && ((uintptr_t)X & 15) == 0 && ((ldx * esz) & 15) == 0 &&
@@ -859,7 +859,8 @@ extern "C" int aser_quantize_act_rtn(aser_ctx* ctx, const void* X, int x_dtype, 
             hipLaunchKernelGGL(act_rtn_wave_kernel<false>, wgrid, dim3(256), 0, ctx->stream, X, rows, n, ldx, mdiag, qmax, codes, scales, tpw);
         return aser_check_launch(ctx, "act_rtn");
     }
-    // up to 1024 channels a token is at most two loads per thread (8192 x 512: 7.1 us, 7.4 with WHOLE); fp32 rows gain nothing (8192 x 4096: 35.4 -> 35.1)
+    // up to 1024 channels a token is at most two loads per thread (8192 x 512: 7.1 us, 7.4 with WHOLE); above 24576 WHOLE takes 66 registers, two more than
+    // two workgroups of 1024 threads per compute unit have (8192 x 28672 with M: 169 us, 230 with WHOLE); fp32 rows gain nothing (8192 x 4096: 35.4 -> 35.1)
     const bool whole = (n & 7) == 0 && ((uintptr_t)X & 15) == 0 && ((ldx * esz) & 15) == 0 && (!mdiag || ((uintptr_t)mdiag & 15) == 0);
     if (x_dtype != ASER_DTYPE_BF16) ASER_ACT_PICK(false, false);
     else if (whole) ASER_ACT_PICK(true, true);
