@@ -234,7 +234,7 @@ __global__ __launch_bounds__(256) void act_planes_kernel(const void* __restrict_
 
 struct EvalArgs {
     const char* a[6]; int64_t pa[6];          // activation planes: address and row pitch in bytes
-    const char* b[6]; int64_t pb[6];          // weight planes, likewise
+    const char* b[6]; int64_t pb[6];          // weight planes, likewise (pb: CODED, otherwise 2 np)
     int segs1, segs;                          // plane products up to Y (CODED: the first is of the codes), and of both outputs
     int64_t np, nc, rows, m;                  // channels of a plane row (a multiple of 32), of a code row (of 64)
     const float* xs;                          // per-token scales, or null (1)
@@ -251,8 +251,10 @@ __device__ __forceinline__ int eval_off(int r, int c) { return r * 64 + ((c ^ ((
 // the inference kernel's 256 x 256 tiles; operand fragments of the next 16 channels are read under the MFMAs of the
 // current ones.  Rows past the end repeat the last one and are left out of the sums.
 // CODED: the first product is of int8 codes, 64 channels per step, on integer accumulators.
+// No more than two wavefronts per SIMD are asked for where two sets of accumulators fill the registers; for 64 x 64 tiles that bound would keep three of five workgroups
+// off a compute unit (500 tokens of 6144 x 6144: 454 -> 552 us).
 template <int TI, int TJ, bool CODED>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2))) void eval_kernel(EvalArgs g, int tiles_n, int64_t tiles_total) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, CODED && TI * TJ > 1 ? 2 : 8))) void eval_kernel(EvalArgs g, int tiles_n, int64_t tiles_total) {
     extern __shared__ __align__(16) char smem[];
     __shared__ float sx[64 * TI], live[64 * TI];          // per row: its scale, 1; 0 past the last row
     constexpr int A_BYTES = 64 * TI * 64, STAGE = A_BYTES + 64 * TJ * 64, NL = TI + TJ;
@@ -271,7 +273,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2))) voi
 
     // ---- fetch roles: instruction t of this wave is tile rows 16 (NT wave + t) + lane / 4, chunk slot lane % 4
     const int chunk = 16 * ((lane & 3) ^ ((lane >> 4) & 3));
-    int arow[TI], brow[TJ];
+    int arow[TI], brow[CODED ? TJ : 1];
     uint32_t aoff[TI], boff[TJ];
 #pragma unroll
     for (int t = 0; t < TI; ++t) {
@@ -281,7 +283,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2))) voi
 #pragma unroll
     for (int t = 0; t < TJ; ++t) {
         const int row = 16 * (TJ * wave + t) + (lane >> 2);
-        brow[t] = O0 + row < g.m ? row : (int)(g.m - 1 - O0);
+        const int at = O0 + row < g.m ? row : (int)(g.m - 1 - O0);
+        if constexpr (CODED) brow[t] = at;
+        else boff[t] = (uint32_t)(at * 2 * (int)g.np + chunk);       // every plane of weights has the same rows
     }
     const int64_t segsteps = g.np / 32, steps0 = CODED ? g.nc / 64 : 0;
     const int64_t nsteps = steps0 + segsteps * (g.segs - (CODED ? 1 : 0)), steps1 = CODED ? nsteps : segsteps * g.segs1;
@@ -290,13 +294,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2))) voi
     int64_t ikk = 0;                                      // plane product and step inside it of the stage to be fetched
     const char *abase = nullptr, *bbase = nullptr;
     auto seg_start = [&]() {
-        const int64_t pa = g.pa[iseg], pb = g.pb[iseg];
+        const int64_t pa = g.pa[iseg], pb = CODED ? g.pb[iseg] : 2 * g.np;
         abase = g.a[iseg] + T0 * pa;
         bbase = g.b[iseg] + O0 * pb;
 #pragma unroll
         for (int t = 0; t < TI; ++t) aoff[t] = (uint32_t)(arow[t] * (int)pa + chunk);
+        if constexpr (CODED) {
 #pragma unroll
-        for (int t = 0; t < TJ; ++t) boff[t] = (uint32_t)(brow[t] * (int)pb + chunk);
+            for (int t = 0; t < TJ; ++t) boff[t] = (uint32_t)(brow[t] * (int)pb + chunk);
+        }
     };
     auto issue_one = [&](int64_t step, int q) {           // q: 0 .. TI - 1 activations, TI .. NL - 1 weights
         const uint32_t dst = ring + (uint32_t)(step & 3) * STAGE + (q < TI ? (TI * wave + q) * 1024 : A_BYTES + (TJ * wave + q - TI) * 1024);
@@ -680,7 +686,7 @@ extern "C" int aser_layer_output_error(aser_ctx* ctx, const float* W, int64_t m,
             }
             EvalArgs g{};
             g.np = np; g.rows = tr; g.m = om; g.out = scal;
-            auto add = [&](const void* a, int64_t pa, const void* b) { g.a[g.segs] = (const char*)a; g.pa[g.segs] = pa; g.b[g.segs] = (const char*)b; g.pb[g.segs] = np * 2; ++g.segs; };
+            auto add = [&](const void* a, int64_t pa, const void* b) { g.a[g.segs] = (const char*)a; g.pa[g.segs] = pa; g.b[g.segs] = (const char*)b; ++g.segs; };
             const void* xa = direct ? Xt : (const void*)x_hi;
             const int64_t xpitch = direct ? ldx * 2 : np * 2;
             add(xa, xpitch, w_hi);
