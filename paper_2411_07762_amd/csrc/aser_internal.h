@@ -235,7 +235,8 @@ int aser_gemm_small_f32(aser_ctx* ctx, float* A, int64_t lda, const float* B, in
 
 // P = s_t x_q L_B^T (rows x r_pad, r_pad = r rounded up to 32) and L_A (m x r_pad) as bf16 planes (forward.hip), r <= 128.  `parts` planes each of P, L_A
 // and L_B, 1 to 3, a plane what is left of the value behind the ones before it, rounded to bf16: 9, 17 or all 24 of its bits.  Codes in rows of ldq
-// bytes, 16-byte aligned, a multiple of 32 of them finite.  xs null: s_t = 1.  lb: scratch, 2 parts r_pad bytes per channel rounded up to 32, 16-byte aligned.
+// bytes, 16-byte aligned, a multiple of 32 of them finite.  xs null: s_t = 1.  parts = 3: the planes of the factors are there (split_factors,
+// rank_planes.h), L_A and L_B are not looked at.  lb: scratch, 2 parts r_pad bytes per channel rounded up to 32, 16-byte aligned.
 struct AserRankPlanes { uint16_t *p[3], *la[3]; void* lb; };
 int aser_rank_down(aser_ctx* ctx, const int8_t* xq, int64_t ldq, const float* xs, int64_t rows, int64_t n, const float* L_B, int r,
                    int parts, const float* L_A, int64_t m, const AserRankPlanes& out);

@@ -11,3 +11,7 @@ __device__ __forceinline__ uint32_t bf16_pair(float a, float b) {            // 
 }
 // Their upper halves: truncated, exact for values that are bf16 already.
 __device__ __forceinline__ uint32_t upper_halves(float a, float b) { return __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u); }
+__device__ __forceinline__ uint32_t bf16_rne(float x) {
+    const uint32_t u = __float_as_uint(x);
+    return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
+}

@@ -24,6 +24,7 @@
 
 #include "aser_internal.h"
 #include "bf16_pair.h"
+#include "rank_planes.h"
 
 namespace {
 
@@ -145,13 +146,69 @@ __global__ __launch_bounds__(256) void weight_planes_kernel(const float* __restr
     }
 }
 
-// Planes of W, np columns with zeros from n on, and the codes as int8 rows of nc bytes, likewise (q null: they are used where they are).
-// Eight columns per thread; bound by HBM.
-__global__ __launch_bounds__(256) void weight_split_kernel(const float* __restrict__ W, int64_t m, int64_t n, int64_t ldw, int64_t np,
-                                                           const uint8_t* __restrict__ codes, int layout, int w_vec, int c_vec,
-                                                           uint16_t* __restrict__ w_hi, uint16_t* __restrict__ w_lo, int8_t* __restrict__ q, int64_t nc) {
-    const int64_t per_row = nc / 8, total = m * per_row, pitch = (layout == ASER_CODES_INT8) ? n : n / 2;
-    for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < total; t += (int64_t)gridDim.x * 256) {
+// What the product on codes reads, in one launch: workgroups [0, bx) the activations as bf16 planes of np columns (KIND as below, 3: they are used where
+// they are) and their codes in rows of nc bytes, [bx, bx + bw) the planes of W and the weights' codes in such rows, the rest the factors
+// (split_factors).  Zeros from channel n on; codes that are used where they are have no destination.  Eight columns per thread.  Bound by HBM, or, for a
+// small layer, by the launch (a launch each: 512 x 1000, 17 tokens, r = 64: 95 us for the whole call, 62 now).
+struct PrepArgs {
+    const void* X; int64_t rows, ldx; uint16_t *x_hi, *x_lo; const int8_t* x_codes; int8_t* x_rows;
+    const float* W; int64_t m, ldw; const uint8_t* w_codes; int layout, w_vec, c_vec; uint16_t *w_hi, *w_lo; int8_t* w_rows;
+    const float *L_A, *L_B; int r, r_pad; AserRankPlanes rank;
+    int64_t n, np, nc;
+    int bx, bw;
+};
+
+template <int KIND>
+__device__ __forceinline__ void act_plane8(const void* __restrict__ X, int64_t row, int64_t c, int64_t n, int64_t ldx, int64_t np, uint16_t* __restrict__ hi,
+                                           uint16_t* __restrict__ lo) {
+    float v[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {                         // past the end the last one again: a load behind a test is waited for at once
+        const int64_t at = row * ldx + (c + e < n ? c + e : n - 1);
+        if (KIND == 0) v[e] = __uint_as_float((uint32_t)((const uint16_t*)X)[at] << 16);
+        if (KIND == 1) v[e] = ((const float*)X)[at];
+        if (KIND == 2) v[e] = (float)((const int8_t*)X)[at];
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = c + e < n ? v[e] : 0.f;
+    uint4 h, l;
+    split8(v, h, l);
+    *(uint4*)(hi + row * np + c) = h;
+    if (KIND == 1) *(uint4*)(lo + row * np + c) = l;
+}
+
+template <int KIND>
+__global__ __launch_bounds__(256) void eval_prep_kernel(PrepArgs a) {
+    const int64_t n = a.n, np = a.np, nc = a.nc, per_row = nc / 8;
+    if ((int)blockIdx.x < a.bx) {
+        const int64_t total = a.rows * per_row;
+        for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < total; t += (int64_t)a.bx * 256) {
+            const int64_t row = t / per_row, c = (t % per_row) * 8;
+            if constexpr (KIND != 3)
+                if (c < np) act_plane8<KIND>(a.X, row, c, n, a.ldx, np, a.x_hi, a.x_lo);
+            if (!a.x_rows) continue;
+            uint32_t b[2] = {0u, 0u};
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                if (c + e < n) b[e >> 2] |= (uint32_t)(uint8_t)a.x_codes[row * n + c + e] << (8 * (e & 3));
+            *(uint2*)(a.x_rows + row * nc + c) = make_uint2(b[0], b[1]);
+        }
+        return;
+    }
+    if ((int)blockIdx.x >= a.bx + a.bw) {
+        split_factors<3, false>((int64_t)blockIdx.x - a.bx - a.bw, (int64_t)gridDim.x - a.bx - a.bw, a.L_A, a.L_B, a.m, n, a.r, a.r_pad, a.rank);
+        return;
+    }
+    const int64_t block = (int64_t)blockIdx.x - a.bx, blocks = a.bw;
+    const float* const W = a.W;
+    const uint8_t* const codes = a.w_codes;
+    const int64_t m = a.m, ldw = a.ldw;
+    const int layout = a.layout;
+    uint16_t *const w_hi = a.w_hi, *const w_lo = a.w_lo;
+    int8_t* const q = a.w_rows;
+    const bool w_vec = a.w_vec, c_vec = a.c_vec;
+    const int64_t total = m * per_row, pitch = (layout == ASER_CODES_INT8) ? n : n / 2;
+    for (int64_t t = block * 256 + threadIdx.x; t < total; t += blocks * 256) {
         const int64_t o = t / per_row, c = (t % per_row) * 8;
         if (c < np) {
             float w[8];
@@ -195,41 +252,13 @@ __global__ __launch_bounds__(256) void weight_split_kernel(const float* __restri
     }
 }
 
-// Activation codes in rows of nc bytes, zeros from n on.
-__global__ __launch_bounds__(256) void code_rows_kernel(const int8_t* __restrict__ src, int64_t rows, int64_t n, int8_t* __restrict__ dst, int64_t nc) {
-    const int64_t total = rows * (nc / 8);
-    for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < total; t += (int64_t)gridDim.x * 256) {
-        const int64_t row = t / (nc / 8), c = (t % (nc / 8)) * 8;
-        uint32_t b[2] = {0u, 0u};
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-            if (c + e < n) b[e >> 2] |= (uint32_t)(uint8_t)src[row * n + c + e] << (8 * (e & 3));
-        *(uint2*)(dst + row * nc + c) = make_uint2(b[0], b[1]);
-    }
-}
-
 // Activations as bf16 planes of np columns (zeros from n on): KIND 0 bf16 X copied, 1 fp32 X as hi and lo, 2 int8 codes.
 template <int KIND>
 __global__ __launch_bounds__(256) void act_planes_kernel(const void* __restrict__ X, int64_t rows, int64_t n, int64_t ldx, int64_t np,
                                                          uint16_t* __restrict__ hi, uint16_t* __restrict__ lo) {
     const int64_t total = rows * (np / 8);
-    for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < total; t += (int64_t)gridDim.x * 256) {
-        const int64_t row = t / (np / 8), c = (t % (np / 8)) * 8;
-        float v[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            v[e] = 0.f;
-            if (c + e < n) {
-                if (KIND == 0) v[e] = __uint_as_float((uint32_t)((const uint16_t*)X)[row * ldx + c + e] << 16);
-                if (KIND == 1) v[e] = ((const float*)X)[row * ldx + c + e];
-                if (KIND == 2) v[e] = (float)((const int8_t*)X)[row * ldx + c + e];
-            }
-        }
-        uint4 h, l;
-        split8(v, h, l);
-        *(uint4*)(hi + row * np + c) = h;
-        if (KIND == 1) *(uint4*)(lo + row * np + c) = l;
-    }
+    for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < total; t += (int64_t)gridDim.x * 256)
+        act_plane8<KIND>(X, t / (np / 8), (t % (np / 8)) * 8, n, ldx, np, hi, lo);
 }
 
 struct EvalArgs {
@@ -622,23 +651,30 @@ extern "C" int aser_layer_output_error(aser_ctx* ctx, const float* W, int64_t m,
     coded_plan(m, n, rows, (int)r, bf16, direct, layout == ASER_CODES_INT8 && ((uintptr_t)codes & 15) == 0, &cp);
     const bool coded = act_bits != 0 && r <= 128 && cp.total <= pl.planes;
     if (coded) {
-        auto grid = [](int64_t items) { return dim3((unsigned)(ceil_div64(items, 256) < 4096 ? ceil_div64(items, 256) : 4096)); };
+        auto blocks = [](int64_t items) { return (int)(ceil_div64(items, 256) < 4096 ? ceil_div64(items, 256) : 4096); };
         uint16_t *xh = (uint16_t*)(ws + cp.x_hi), *xl = (uint16_t*)(ws + cp.x_lo);
-        if (!direct) {
-            if (bf16) hipLaunchKernelGGL(act_planes_kernel<0>, grid(rows * (np / 8)), dim3(256), 0, ctx->stream, X, rows, n, ldx, np, xh, xl);
-            else hipLaunchKernelGGL(act_planes_kernel<1>, grid(rows * (np / 8)), dim3(256), 0, ctx->stream, X, rows, n, ldx, np, xh, xl);
-            ASER_TRY(aser_check_launch(ctx, "act_planes"));
-        }
-        const int8_t* xc = acodes;
-        if (!cp.xc_direct) {
-            xc = (const int8_t*)(ws + cp.xc);
-            hipLaunchKernelGGL(code_rows_kernel, grid(rows * (cp.nc / 8)), dim3(256), 0, ctx->stream, (const int8_t*)acodes, rows, n, (int8_t*)(ws + cp.xc), cp.nc);
-            ASER_TRY(aser_check_launch(ctx, "code_rows"));
-        }
+        const int8_t* xc = cp.xc_direct ? acodes : (const int8_t*)(ws + cp.xc);
         const int8_t* wc = cp.wc_direct ? (const int8_t*)codes : (const int8_t*)(ws + cp.wc);
-        hipLaunchKernelGGL(weight_split_kernel, grid(m * (cp.nc / 8)), dim3(256), 0, ctx->stream, W, m, n, ldw, np, (const uint8_t*)codes, (int)layout, w_vec, c_vec,
-                           (uint16_t*)(ws + cp.w_hi), (uint16_t*)(ws + cp.w_lo), cp.wc_direct ? (int8_t*)nullptr : (int8_t*)(ws + cp.wc), cp.nc);
-        ASER_TRY(aser_check_launch(ctx, "weight_split"));
+        PrepArgs a{};
+        a.X = X; a.rows = rows; a.ldx = ldx; a.x_hi = xh; a.x_lo = xl; a.x_codes = acodes; a.x_rows = cp.xc_direct ? nullptr : (int8_t*)(ws + cp.xc);
+        a.W = W; a.m = m; a.ldw = ldw; a.w_codes = (const uint8_t*)codes; a.layout = (int)layout; a.w_vec = w_vec; a.c_vec = c_vec;
+        a.w_hi = (uint16_t*)(ws + cp.w_hi); a.w_lo = (uint16_t*)(ws + cp.w_lo); a.w_rows = cp.wc_direct ? nullptr : (int8_t*)(ws + cp.wc);
+        a.n = n; a.np = np; a.nc = cp.nc;
+        a.bx = direct && cp.xc_direct ? 0 : blocks(rows * (cp.nc / 8));
+        a.bw = blocks(m * (cp.nc / 8));
+        int64_t total = (int64_t)a.bx + a.bw;
+        if (r > 0) {
+            for (int i = 0; i < 3; ++i) {
+                a.rank.p[i] = (uint16_t*)(ws + cp.p[i]);
+                a.rank.la[i] = (uint16_t*)(ws + cp.la[i]);
+            }
+            a.rank.lb = ws + cp.lb;
+            a.L_A = L_A; a.L_B = L_B; a.r = (int)r; a.r_pad = cp.r_pad;
+            total += split_factors_blocks(m, n, cp.r_pad);
+        }
+        auto prep = direct ? eval_prep_kernel<3> : (bf16 ? eval_prep_kernel<0> : eval_prep_kernel<1>);
+        hipLaunchKernelGGL(prep, dim3((unsigned)total), dim3(256), 0, ctx->stream, a);
+        ASER_TRY(aser_check_launch(ctx, "eval_prep"));
         EvalArgs g{};
         g.np = np; g.nc = cp.nc; g.rows = rows; g.m = m; g.out = scal; g.xs = ascales; g.ws = scales;
         auto add = [&](const void* a, int64_t pa, const void* b, int64_t pb) {
@@ -651,13 +687,9 @@ extern "C" int aser_layer_output_error(aser_ctx* ctx, const float* W, int64_t m,
         add(xa, xpitch, ws + cp.w_lo, np * 2);
         if (!bf16) add(xl, np * 2, ws + cp.w_hi, np * 2);
         if (r > 0) {
-            for (int i = 0; i < 3; ++i) {
-                g.rank.p[i] = (uint16_t*)(ws + cp.p[i]);
-                g.rank.la[i] = (uint16_t*)(ws + cp.la[i]);
-            }
-            g.rank.lb = ws + cp.lb;
+            g.rank = a.rank;
             g.r_pad = cp.r_pad;
-            ASER_TRY(aser_rank_down(ctx, xc, cp.nc, nullptr, rows, n, L_B, (int)r, 3, L_A, m, g.rank));
+            ASER_TRY(aser_rank_down(ctx, xc, cp.nc, nullptr, rows, n, nullptr, (int)r, 3, nullptr, m, a.rank));
         }
         ASER_TRY(pick_eval<true>(ctx, g));
     }

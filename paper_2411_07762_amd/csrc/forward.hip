@@ -30,6 +30,7 @@
 #include "aser_internal.h"
 #include "bf16_pair.h"
 #include "dispatch_rules.h"
+#include "rank_planes.h"
 
 namespace {
 
@@ -40,11 +41,6 @@ typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 
 constexpr int kFwdTM = 128, kFwdTN = 256, kFwdBK = 64;
-
-__device__ __forceinline__ uint32_t bf16_rne(float x) {
-    const uint32_t u = __float_as_uint(x);
-    return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
-}
 
 // byte offset of 16-byte chunk c (0..3) of row r inside a [rows][64 bytes] LDS tile
 __device__ __forceinline__ int chunk_off(int r, int c) { return r * 64 + ((c ^ ((r >> 2) & 3)) << 4); }
@@ -535,55 +531,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     }
 }
 
-// Both factors as NP bf16 planes, each what the ones before it leave of the value, rounded.  L_A (m x r) as [m][r_pad] with zeros behind r; L_B (r x n) in the
-// order in which rank_down_kernel feeds it to the MFMA: [32 channels][plane][32 rows][8-channel slice][lane][8 channels], lane 32 h + i holding
-// channels 16 h + 8 slice .. + 7 of row i, zeros past r and n; three planes: one block of 32 rows after the other.  PLAIN: as planes [r_pad][n] (n % 32 == 0).
 template <int NP, bool PLAIN>
 __global__ __launch_bounds__(256) void split_factors_kernel(const float* __restrict__ L_A, const float* __restrict__ L_B, int64_t m,
-                                                            int64_t n, int r, int r_pad, AserRankPlanes out, int64_t lb_blocks) {
-    if ((int64_t)blockIdx.x < lb_blocks) {                   // eight rows, 256 channels
-        const int64_t k = ((int64_t)blockIdx.x % ((n + 255) / 256)) * 256 + 8 * (threadIdx.x & 31);
-        const int row = (int)((int64_t)blockIdx.x / ((n + 255) / 256)) * 8 + (threadIdx.x >> 5);
-        if (k >= (n + 31) / 32 * 32) return;
-        float f[8];
-        const float* src = L_B + (int64_t)(row < r ? row : 0) * n;
-        if (((uintptr_t)src & 15) == 0 && k + 8 <= n) {
-            const float4 x = *(const float4*)(src + k), y = *(const float4*)(src + k + 4);
-            f[0] = x.x; f[1] = x.y; f[2] = x.z; f[3] = x.w; f[4] = y.x; f[5] = y.y; f[6] = y.z; f[7] = y.w;
-        } else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) f[e] = k + e < n ? src[k + e] : 0.f;
-        }
-        const int c8 = (int)(k & 31) >> 3, h = c8 >> 1, sl = c8 & 1, blocks = r_pad / 32;
-        const int together = NP == 3 ? 1 : blocks;           // blocks of rows that a workgroup takes
-        const int64_t step = NP == 3 ? row / 32 * ((n + 31) / 32) + k / 32 : k / 32;
-        uint4* lb = (uint4*)out.lb + (PLAIN ? (row * n + k) / 8 : ((step * NP * together + (NP == 3 ? 0 : row / 32)) * 2 + sl) * 64 + 32 * h + (row & 31));
-#pragma unroll
-        for (int p = 0; p < NP; ++p, lb += PLAIN ? r_pad * n / 8 : (int64_t)together * 128) {
-            uint32_t pair[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                float &f0 = f[2 * q], &f1 = f[2 * q + 1];
-                pair[q] = row < r ? bf16_pair(f0, f1) : 0u;
-                f0 -= __uint_as_float(pair[q] << 16);
-                f1 -= __uint_as_float(pair[q] & 0xFFFF0000u);
-            }
-            *lb = make_uint4(pair[0], pair[1], pair[2], pair[3]);
-        }
-        return;
-    }
-    const int64_t total = m * r_pad;
-    for (int64_t t = ((int64_t)blockIdx.x - lb_blocks) * 256 + threadIdx.x; t < total; t += ((int64_t)gridDim.x - lb_blocks) * 256) {
-        const int64_t i = t / r_pad;
-        const int j = (int)(t % r_pad);
-        float x = j < r ? L_A[i * r + j] : 0.f;
-#pragma unroll
-        for (int p = 0; p < NP; ++p) {
-            const uint32_t part = bf16_rne(x);
-            out.la[p][t] = (uint16_t)part;
-            x -= __uint_as_float(part << 16);
-        }
-    }
+                                                            int64_t n, int r, int r_pad, AserRankPlanes out) {
+    split_factors<NP, PLAIN>(blockIdx.x, gridDim.x, L_A, L_B, m, n, r, r_pad, out);
 }
 
 // P[t][k] = s_t sum_i xq[t][i] L_B[k][i] as bf16 planes, for 32 tokens per workgroup and all r_pad columns (RB blocks of 32; of three planes the
@@ -940,14 +891,12 @@ int launch_down_staged(aser_ctx* ctx, const DownArgs& g) {
 
 template <int NP>
 int rank_down(aser_ctx* ctx, const DownArgs& g, const float* L_A, int64_t m, const float* L_B, int r, const AserRankPlanes& out) {
-    const int64_t lb_blocks = ceil_div64(g.n, 256) * (g.r_pad / 8), la_blocks = ceil_div64(m * g.r_pad, 256 * 4);
     const bool staged = NP < 3 && g.rows > kDownRows && g.n % 32 == 0;
-    auto split = split_factors_kernel<NP, false>;
-    if constexpr (NP < 3)
-        if (staged) split = split_factors_kernel<NP, true>;
-    hipLaunchKernelGGL(split, dim3((unsigned)(lb_blocks + (la_blocks < 2048 ? la_blocks : 2048))), dim3(256), 0, ctx->stream,
-                       L_A, L_B, m, g.n, r, g.r_pad, out, lb_blocks);
-    ASER_TRY(aser_check_launch(ctx, "split_factors"));
+    if constexpr (NP < 3) {
+        auto split = staged ? split_factors_kernel<NP, true> : split_factors_kernel<NP, false>;
+        hipLaunchKernelGGL(split, dim3((unsigned)split_factors_blocks(m, g.n, g.r_pad)), dim3(256), 0, ctx->stream, L_A, L_B, m, g.n, r, g.r_pad, out);
+        ASER_TRY(aser_check_launch(ctx, "split_factors"));
+    }
     if constexpr (NP < 3) {
         if (staged) switch (g.r_pad / 32) {
             case 1: return launch_down_staged<1, NP == 2>(ctx, g);
