@@ -30,6 +30,19 @@ static inline bool aser_forward_few_pays(int64_t rows, int64_t n, int64_t m, int
     return rows <= 96 ? n >= 2048 : n >= (rows <= 512 ? 3072 : 5120) && rank * rank_work <= 512 * n;    // so few leave a quarter of the prefill kernels' tiles of 128 and more empty
 }
 
+// First product of the prefill kernels' rank-r branch, r_pad columns: true where 128 tokens per workgroup with both operands through LDS are faster than 32
+// tokens with L_B read straight (forward.hip).  Beyond two rounds of 32 x 256 tokens always; in the second round (a few workgroups of it run
+// beside the first) where the contraction is so short that a workgroup's start and end count: there are a quarter as many of them.
+// Measured (us of the call, 32 tokens -> 128; channels, outputs, tokens): r = 40: 256, 107, 16384: 26.1 -> 24.2; 512, 107, 16384: 31.8 -> 28.3; 768, 1024, 9000: 42.5
+// -> 41.5; split, 512, 107, 16384: 38.5 -> 33.6; not 288, 107, 8193: 24.9 -> 25.8, nor 896, 1024, 8193: 40.1 -> 41.4.  Up to 32 columns, split, 512, 107, 12000:
+// 29.6 -> 27.8, plain never (768, 1024, 14000: 41.7 -> 42.6); up to 128, split, 256, 107, 16384: 42.7 -> 38.6, plain 31.7 -> 29.8,
+// 768, 1024, 9000: 50.0 -> 50.7; 96 never (768, 1024, 9000, split: 54.0 -> 56.5).
+// The rule loses at most 3 % (split, up to 32 columns: 288, 1024, 9000: 35.1 -> 36.2).
+static inline bool aser_down_staged(int64_t rows, int64_t n, int r_pad, bool split) {
+    if (rows <= 8448 || rows > 16384) return rows > 16384;
+    return r_pad != 96 && n <= (split || r_pad == 64 ? 768 : (r_pad == 128 ? 320 : 0));
+}
+
 // True where f rounds of an arg-max in one workgroup select the outlier channels faster than the comparison of all pairs of
 // channels: a round costs 1.6 to 3.3 us, the pairs n^2 / 5.4e6 us and one more launch, so the line is a constant plus n^2 (the rounds
 // take 1024 threads instead of 512 above 16384 channels).

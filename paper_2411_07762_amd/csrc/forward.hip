@@ -646,8 +646,8 @@ __global__ __launch_bounds__(64 * NW) void rank_down_kernel(DownArgs g) {
     }
 }
 
-// The same for many tokens, 128 per workgroup, with both operands staged through LDS; L_B in planes [r_pad][n].  Beyond two rounds of workgroups
-// of the kernel above what counts is what goes through the L2: there all of L_B once per 32 tokens, and a token's line of codes in pieces
+// The same for many tokens, 128 per workgroup, with both operands staged through LDS; L_B in planes [r_pad][n] (see aser_down_staged).  Beyond two
+// rounds of workgroups of the kernel above what counts is what goes through the L2: there all of L_B once per 32 tokens, and a token's line of codes in pieces
 // of 32 bytes; here L_B once per 128 tokens and 64 bytes of a token side by side.
 // Per step 64 channels: the code tile as in the main kernel (no reordering), the L_B tiles as 16-byte chunks of 8 bf16 with an XOR swizzle.  A step is a
 // chain of waits (tile stores, barrier, fragment reads, conversion, MFMA), so the workgroup has eight wavefronts, two per SIMD: wavefront w takes
@@ -655,8 +655,8 @@ __global__ __launch_bounds__(64 * NW) void rank_down_kernel(DownArgs g) {
 // of step s + 3 are issued in step s (three register stages, the step loop unrolled by three so that they are
 // named at compile time), the LDS tiles are double buffered, one barrier per step.
 // Whole calls of 4096 channels (us, 32 tokens per workgroup -> 128): 256 outputs, r = 64, 16385 tokens 86 -> 81, 17000: 94 -> 84, 32768: 109 -> 88; r = 128, split, 32768:
-// 182 -> 148; 4096 outputs, r = 64, 32768: 634 -> 617.  At 16384 tokens, two whole rounds, the other one is as fast or faster.
-constexpr int kDownThreads = 512, kDownRows = 16384;
+// 182 -> 148; 4096 outputs, r = 64, 32768: 634 -> 617.  At 16384 tokens, two whole rounds, the other one is as fast or faster from 1024 channels.
+constexpr int kDownThreads = 512;
 
 template <int RB, bool SPLIT>
 __global__ __launch_bounds__(kDownThreads) void rank_down_staged_kernel(DownArgs g) {
@@ -891,7 +891,7 @@ int launch_down_staged(aser_ctx* ctx, const DownArgs& g) {
 
 template <int NP>
 int rank_down(aser_ctx* ctx, const DownArgs& g, const float* L_A, int64_t m, const float* L_B, int r, const AserRankPlanes& out) {
-    const bool staged = NP < 3 && g.rows > kDownRows && g.n % 32 == 0;
+    const bool staged = NP < 3 && g.n % 32 == 0 && aser_down_staged(g.rows, g.n, g.r_pad, NP == 2);
     if constexpr (NP < 3) {
         auto split = staged ? split_factors_kernel<NP, true> : split_factors_kernel<NP, false>;
         hipLaunchKernelGGL(split, dim3((unsigned)split_factors_blocks(m, g.n, g.r_pad)), dim3(256), 0, ctx->stream, L_A, L_B, m, g.n, r, g.r_pad, out);

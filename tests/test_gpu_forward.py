@@ -119,7 +119,8 @@ def test_mfma_rate_probe_runs():
     (2049, 32, 200, 1, True, 0), (2049, 96, 300, 33, False, 1), (2080, 4128, 256, 64, True, 0), (2081, 4096, 257, 65, False, 0),
     (2111, 1056, 128, 97, True, 1), (2112, 224, 512, 128, False, 0),
     # 128 tokens per workgroup: tokens around blocks of 128, steps of 64 channels in threes and twelves, whole and halves
-    (16385, 32, 256, 33, True, 0), (16511, 96, 256, 64, False, 1), (16512, 416, 260, 128, True, 0), (16513, 1184, 256, 1, False, 0), (16640, 2080, 300, 96, True, 1)])
+    (16385, 32, 256, 33, True, 0), (16511, 96, 256, 64, False, 1), (16512, 416, 260, 128, True, 0), (16513, 1184, 256, 1, False, 0), (16640, 2080, 300, 96, True, 1),
+    (8449, 768, 260, 64, False, 0), (8577, 32, 128, 40, True, 1), (9000, 288, 300, 16, True, 0), (12417, 480, 107, 128, True, 1), (16384, 320, 130, 97, False, 0)])
 def test_first_product_of_the_rank_branch_for_many_tokens(rows, n, m, r, split, offset):
     """Token counts around blocks of 32, channels short of and beyond what sixteen wavefronts take at a time, every number of column
     blocks, and an L_B that does not start on 16 bytes, against the same product in fp64 on rounded factors."""
