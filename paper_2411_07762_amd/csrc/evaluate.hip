@@ -10,14 +10,14 @@
 // planes, x = hi + lo (about 2^-17 relative): W, fp32 activations.  bf16 activations are exact as they are, so Y = X W^T is two plane
 // products instead of the three of a general fp32 product.  The second output needs no planes of W~: the codes of both sides multiply
 // exactly on the int8 MFMA, at twice the rate, and the rank-r branch is r / 16 further bf16 steps per tile: L_B, P = x_q L_B^T and L_A as
-// three planes each, which hold all of their 24 bits, and six products (with two planes and three products, 297 us instead of 300, the result was up to 30 times
+// three planes each, which hold all of their 24 bits, and six products (with two planes and three products the call took 3 us less, and the result was up to 30 times
 // as far from fp64 where factors cancel, and 2 to 5 times elsewhere).  ONE kernel forms both outputs of a tile: the integer sums, then Y on accumulators of its own, ||Y||^2 from
 // these, which are then multiplied by -1 / s_t per row and receive c_o times the integer sums and L_A P, and ||s_t (...)||^2:
 // neither output is ever stored.
 // Without activation quantization (and with r > 128, or where the planes do not fit the workspace) the second output is a product of planes
 // as well, of the activations or codes with those of W~ (divided by M when there are no codes), accumulated on top of the first.
 // Bound: the MFMA rates; 2048 tokens of the 4096 x 4096 layer are 1.4e11 operations in two bf16 plane products and 0.7e11 in int8: 219 us
-// (339 with four plane products), plus 30 for the planes of W (76 with those of W~) and 25 to 30 for P; the whole call 415 -> 300.
+// (339 with four plane products; traced now 230), plus 31 for the planes of W and the factors (76 with those of W~) and 17 for P; the whole call 422 -> 289.
 #include <math.h>
 
 #include <type_traits>

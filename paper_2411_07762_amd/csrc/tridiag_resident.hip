@@ -32,7 +32,10 @@
 //
 // What bounds it: the exchange, 2.0 us at 1024 columns left and 4.2 at 4096 (every workgroup reads 16 bytes per column past its L2), then
 // the pass, 768 fp64 operations per thread at 4096 columns.  A column costs 2.8 us while at most 1024 are left, 5 on average at
-// k = 4096.  Whole spectra: k = 700: 5.2 -> 2.1 ms, 1030: 9.2 -> 3.4, 2049: 24.0 -> 7.7, 4096: 82 -> 24.9.
+// k = 4096.  Whole spectra: k = 700: 5.2 -> 1.9 ms, 1030: 9.2 -> 3.1, 2049: 24.0 -> 7.1, 4096: 82 -> 23.8.
+// Callers that overlap wait for each other here, and are still served sooner.  One spectrum on each of 1, 2, 4, 8 streams, ms, a launch per column -> this: k = 700: 5.3, 5.5,
+// 6.2, 11.9 -> 2.0, 2.4, 4.6, 9.0; 1000: 8.8, 9.3, 11, 22 -> 2.9, 4.7, 8.6, 17; 2048: 23, 27, 54, 73 -> 7.0, 13, 25, 51.  One-token decode on
+// a stream beside spectra of k = 700: median 27 -> 30 us, of k = 4096: 17 -> 2.4 ms (longest 44 -> 22).
 #include <math.h>
 
 #include <type_traits>
