@@ -174,9 +174,10 @@ def test_rank_of_a_non_finite_spectrum_is_refused(k, value):
         assert st == aser.ASER_ERR_INVALID_ARG and "positive sum" in ctx.last_error()
 
 
-@pytest.mark.parametrize("m,n,r", [(1, 5, 1), (2, 3, 2), (9, 30, 3), (10, 11, 10), (255, 257, 8), (258, 300, 5)])
+@pytest.mark.parametrize("m,n,r", [(1, 5, 1), (2, 3, 2), (9, 30, 3), (10, 11, 10), (255, 257, 8), (258, 300, 5),
+                                   (1, 1, 1), (3, 40, 1), (4, 4, 4), (7, 50, 5), (8, 8, 8), (8, 64, 3), (9, 9, 9)])
 def test_factors_of_the_dense_solver(m, n, r):
-    """Sides around the eight rows that the solves of inverse iteration read ahead, none to read ahead at all, and around the 256 rows of the last
+    """Sides up to and beyond the eight rows of which one wavefront does the inverse iteration in one launch, and around the 256 rows of the last
     kernel of the tridiagonalisation, against LAPACK."""
     rng = np.random.default_rng([11, m, n])
     u = np.linalg.qr(rng.standard_normal((m, m)))[0]
@@ -193,3 +194,22 @@ def test_factors_of_the_dense_solver(m, n, r):
     gap = 1.0 / max(m - 1, 1)
     assert np.max(np.abs(sigma.double().cpu().numpy() - sg[:r])) <= 2.0 ** -22 * sg[0]
     assert np.linalg.norm(got - want) <= 2.0 ** -22 * (1.0 + 1.0 / gap) * np.linalg.norm(want)
+
+
+@pytest.mark.parametrize("m,n,r", [(2, 2, 2), (5, 5, 3), (8, 12, 8), (8, 8, 1)])
+def test_factors_of_a_few_equal_singular_values(m, n, r):
+    """All singular values 1 (the start vectors alone make the basis), and all but the first 0: factors with orthogonal columns of the right norms."""
+    for diag in (np.ones(m), np.eye(m)[0] * 3.0):
+        T = np.zeros((m, n), dtype=np.float32)
+        T[:, :m] = np.diag(diag)
+        ctx = new_ctx()
+        ctx.ensure_workspace(aser.aser_workspace_bytes(m, n, r))
+        L_A, L_B, sigma = (torch.empty(shape, dtype=torch.float32, device=DEV) for shape in ((m, r), (r, n), (r,)))
+        st, _, _ = aser.aser_error_reconstruct(ctx, torch.from_numpy(T).to(DEV), torch.eye(n, device=DEV), r, L_A, L_B, sigma)
+        ctx.check(st)
+        want = np.sort(diag)[::-1][:r]
+        # sigma is the root of an eigenvalue that is known to k ulp of the largest (fp64): 2^-24 of it where it is zero; entries are rounded to fp32
+        assert np.max(np.abs(sigma.double().cpu().numpy() - want)) <= 2.0 ** -22 * diag.max()
+        low = L_A.double().cpu().numpy() @ L_B.double().cpu().numpy()
+        got = np.linalg.svd(low, compute_uv=False)[:r]
+        assert np.max(np.abs(got - want)) <= r * 2.0 ** -21 * diag.max()
